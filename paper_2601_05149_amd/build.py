@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmulo.so")
-SOURCES = ["mulo_api.hip", "decide.hip", "elementwise.hip", "gemm.hip", "attention.hip"]
+SOURCES = ["mulo_api.hip", "decide.hip", "elementwise.hip", "gemm.hip", "attention.hip", "forward_f32.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
 

@@ -13,7 +13,6 @@
 // B operand of the second product.  The K rows are fetched in a permuted order
 // (bits 2 and 3 of the row index swapped) so that a lane's accumulators cover 8
 // consecutive keys, which is what lets V^T be read with 16-byte LDS loads.
-// float32 path (small configuration): one workgroup per query row.
 #include <hip/hip_bf16.h>
 
 #include "mulo_internal.h"
@@ -330,52 +329,6 @@ __global__ __launch_bounds__(NTH, NTH <= 256 ? 2 : 1) void k_attn_bf16(const Att
     }
 }
 
-// float32: one workgroup per (query j, head, sequence); scores live in LDS.
-__global__ __launch_bounds__(256) void k_attn_f32(const float* __restrict__ q, const float* __restrict__ kc,
-                                                  const float* __restrict__ vc, float* __restrict__ out, int L,
-                                                  int P, int nh, int dh, int max_seq, int max_batch, int layer) {
-    extern __shared__ float sc[];   // [dh] query, then [P + j + 1] scores
-    __shared__ float red[4];
-    const int j = blockIdx.x, hd = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
-    const int n = P + j + 1;
-    float* qs = sc;
-    float* s = sc + dh;
-    const int64_t hb = ((int64_t)layer * max_batch + b) * nh + hd;
-    const float* kb = kc + hb * max_seq * dh;
-    const float* vb = vc + hb * dh * max_seq;
-    for (int c = tid; c < dh; c += 256) qs[c] = q[(((int64_t)b * nh + hd) * L + j) * dh + c];
-    __syncthreads();
-    const float scale = 1.0f / sqrtf((float)dh);
-    float mx = -__builtin_huge_valf();
-    for (int t = tid; t < n; t += 256) {
-        float acc = 0.f;
-        for (int c = 0; c < dh; ++c) acc += qs[c] * kb[(int64_t)t * dh + c];
-        acc *= scale;
-        s[t] = acc;
-        mx = fmaxf(mx, acc);
-    }
-    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    if ((tid & 63) == 0) red[tid >> 6] = mx;
-    __syncthreads();
-    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    __syncthreads();
-    float sum = 0.f;
-    for (int t = tid; t < n; t += 256) {
-        const float e = expf(s[t] - mx);
-        s[t] = e;
-        sum += e;
-    }
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-    if ((tid & 63) == 0) red[tid >> 6] = sum;
-    __syncthreads();
-    sum = (red[0] + red[1]) + (red[2] + red[3]);
-    for (int c = tid; c < dh; c += 256) {
-        float acc = 0.f;
-        for (int t = 0; t < n; ++t) acc += s[t] * vb[(int64_t)c * max_seq + t];
-        out[((int64_t)b * L + j) * (nh * dh) + hd * dh + c] = acc / sum;
-    }
-}
-
 // out[b, hd, :] = sum_s o_s 2^(m_s - M) / sum_s l_s 2^(m_s - M), M = max_s m_s (maxima are in exponent units)
 template <int DH>
 __global__ __launch_bounds__(DH) void k_attn_combine(const AttnArgs a) {
@@ -465,15 +418,6 @@ void launch_attention_scattered_bf16(const void* q, const void* k_cache, const v
     }
     if (head_dim == 128) run_attn_cfg<128, 128, BKV_SMALL, 256>(a, st);
     else run_attn_cfg<64, 128, BKV_SMALL, 256>(a, st);
-}
-
-void launch_attention_f32(const float* q, const float* k_cache, const float* v_cache, float* out,
-                          float* scratch, int B, int L, int P, int n_heads, int head_dim, int max_seq,
-                          int max_batch, int layer, hipStream_t st) {
-    (void)scratch;
-    const size_t lds = (size_t)(head_dim + P + L) * sizeof(float);
-    hipLaunchKernelGGL(k_attn_f32, dim3(L, n_heads, B), dim3(256), lds, st, q, k_cache, v_cache, out, L, P,
-                       n_heads, head_dim, max_seq, max_batch, layer);
 }
 
 }  // namespace mulo

@@ -1,7 +1,5 @@
-// Row-wise pieces of the target forward (Alg. 1 Step 3): embedding lookup,
-// RMSNorm, and -- for the float32 configuration only -- rotary + cache append and
-// the SwiGLU product as separate kernels (the bf16 path fuses those into GEMM
-// epilogues).  All are HBM-bound streams over [M, d] activations.
+// Row-wise pieces of the target forward (Alg. 1 Step 3): embedding lookup and
+// RMSNorm, HBM-bound streams over [M, d] activations.
 #include <hip/hip_bf16.h>
 
 #include "mulo_internal.h"
@@ -77,41 +75,6 @@ __global__ __launch_bounds__(TPB) void k_rmsnorm(const float* __restrict__ x, co
     }
 }
 
-// float32 path: rotary on adjacent pairs of q and k, q -> [B, nh, L, dh],
-// k -> cache [.., S, dh], v -> cache transposed [.., dh, S]
-__global__ __launch_bounds__(TPB) void k_rope_append_f32(const float* __restrict__ qkv, float* __restrict__ q_out,
-                                                         float* __restrict__ kc, float* __restrict__ vc,
-                                                         int d, RopeArgs ra) {
-    const int64_t m = blockIdx.x;
-    const int b = m / ra.L, j = m % ra.L, pos = ra.P + j, dh = ra.head_dim, half = dh / 2;
-    const float* row = qkv + m * 3 * d;
-    for (int pr = threadIdx.x; pr < d / 2; pr += TPB) {
-        const int hd = (2 * pr) / dh, c = (2 * pr) % dh, mm = c / 2;
-        const float cs = ra.cos[(int64_t)pos * half + mm], sn = ra.sin[(int64_t)pos * half + mm];
-        const float q0 = row[2 * pr], q1 = row[2 * pr + 1];
-        const float k0 = row[d + 2 * pr], k1 = row[d + 2 * pr + 1];
-        const int64_t qo = (((int64_t)b * ra.n_heads + hd) * ra.L + j) * dh + c;
-        q_out[qo] = q0 * cs - q1 * sn;
-        q_out[qo + 1] = q0 * sn + q1 * cs;
-        const int64_t hb = ((int64_t)ra.layer * ra.max_batch + b) * ra.n_heads + hd;
-        const int64_t ko = (hb * ra.max_seq + pos) * dh + c;
-        kc[ko] = k0 * cs - k1 * sn;
-        kc[ko + 1] = k0 * sn + k1 * cs;
-        const int64_t vo = (hb * dh + c) * ra.max_seq + pos;
-        vc[vo] = row[2 * d + 2 * pr];
-        vc[vo + ra.max_seq] = row[2 * d + 2 * pr + 1];
-    }
-}
-
-// h = silu(gate) * up from gu = [gate | up] rows of 2f floats
-__global__ __launch_bounds__(TPB) void k_swiglu_f32(const float* __restrict__ gu, float* __restrict__ h, int f) {
-    const int64_t m = blockIdx.x;
-    for (int c = threadIdx.x; c < f; c += TPB) {
-        const float g = gu[m * 2 * f + c], u = gu[m * 2 * f + f + c];
-        h[m * f + c] = g / (1.0f + expf(-g)) * u;
-    }
-}
-
 }  // namespace
 
 void launch_embed(const void* embed, int dtype, const int32_t* tok, const void* in_embeds, float* x,
@@ -136,15 +99,6 @@ void launch_rmsnorm(const float* x, const void* gain, int dtype, void* out, int 
                     hipStream_t s) {
     if (dtype == 1) rmsnorm_dispatch(x, (const __hip_bfloat16*)gain, (__hip_bfloat16*)out, M, d, eps, frag ? 1 : 0, s);
     else rmsnorm_dispatch(x, (const float*)gain, (float*)out, M, d, eps, 0, s);
-}
-
-void launch_rope_append_f32(const float* qkv, float* q_out, float* k_cache, float* v_cache, int M, int d,
-                            const RopeArgs& ra, hipStream_t s) {
-    hipLaunchKernelGGL(k_rope_append_f32, dim3(M), dim3(TPB), 0, s, qkv, q_out, k_cache, v_cache, d, ra);
-}
-
-void launch_swiglu_f32(const float* gu, float* h, int M, int f, hipStream_t s) {
-    hipLaunchKernelGGL(k_swiglu_f32, dim3(M), dim3(TPB), 0, s, gu, h, f);
 }
 
 }  // namespace mulo

@@ -14,7 +14,6 @@
 //   gate|up   -> silu(gate) * up, gate and up columns interleaved inside a tile so
 //                that one lane owns both accumulators of a feed-forward column
 //   lm-head   -> float32 logits
-// float32 path (small configuration): a plain register-tiled kernel.
 #include <hip/hip_bf16.h>
 
 #include <utility>
@@ -1069,47 +1068,6 @@ bool dispatch(const GemmArgs& g, hipStream_t st) {
     return true;
 }
 
-// ---------------------------------------------------------------- float32
-// C[M, N] (ld = ldc) (+)= A[M, K] W[N, K]^T, 64x64 tile, 4x4 per lane.
-__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ A, const float* __restrict__ W,
-                                                  float* __restrict__ C, int M, int N, int K, int ldc,
-                                                  int accumulate) {
-    constexpr int T = 64, KB = 16;
-    __shared__ float sa[KB][T + 1], sb[KB][T + 1];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += KB) {
-        for (int e = tid; e < T * KB; e += 256) {
-            const int r = e / KB, c = e % KB;
-            sa[c][r] = (m0 + r < M && k0 + c < K) ? A[(int64_t)(m0 + r) * K + k0 + c] : 0.f;
-            sb[c][r] = (n0 + r < N && k0 + c < K) ? W[(int64_t)(n0 + r) * K + k0 + c] : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int c = 0; c < KB; ++c) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { a[i] = sa[c][ty * 4 + i]; b[i] = sb[c][tx * 4 + i]; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * b[j];
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int m = m0 + ty * 4 + i, n = n0 + tx * 4 + j;
-            if (m < M && n < N) {
-                float* p = C + (int64_t)m * ldc + n;
-                *p = accumulate ? *p + acc[i][j] : acc[i][j];
-            }
-        }
-}
-
 }  // namespace
 
 void launch_gemm_qkv_bf16(const void* xh, const void* wq, const void* wk, const void* wv, void* q_out,
@@ -1169,12 +1127,6 @@ void launch_pack_weights(const void* src, void* dst, int layers, int rows, int K
     const int64_t pieces = (int64_t)layers * ((rows + 15) / 16) * (K / 32) * 64;
     hipLaunchKernelGGL(k_pack_weights, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st, (const bf16*)src, (bf16*)dst,
                        layers, rows, K);
-}
-
-void launch_gemm_f32(const float* a, const float* w, float* c, int M, int N, int K, int ldc, int accumulate,
-                     hipStream_t st) {
-    hipLaunchKernelGGL(k_gemm_f32, dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, st, a, w, c, M, N, K,
-                       ldc, accumulate);
 }
 
 }  // namespace mulo

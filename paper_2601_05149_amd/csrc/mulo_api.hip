@@ -48,7 +48,6 @@ struct mulo_ctx {
     void* qbuf;      // [maxB, nh, maxL, dh]
     void* att;       // [maxM, d]
     void* hmid;      // [maxM, f]
-    float* tmp;      // float32 path only: [maxM, max(3d, 2f)]
     float* logits;   // [maxM, V]   (mulo_verify_step)
     float* q_lo;     // [maxM, V]
     float* rowmax;   // [maxM]
@@ -77,7 +76,7 @@ namespace {
 
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
-constexpr int N_BUF = 19;
+constexpr int N_BUF = 18;
 struct Layout {
     size_t off[N_BUF];
     size_t total;
@@ -106,8 +105,7 @@ Layout plan(const mulo_model_cfg& c) {
     const size_t M = (size_t)c.max_batch * c.max_block, d = c.d_model, f = c.d_ffn, V = c.vocab;
     const size_t M16 = (M + 15) / 16 * 16;   // the operands of the projections hold whole groups of 16 tokens (fragment order)
     const size_t e = c.dtype == MULO_BF16 ? 2 : 4;
-    const size_t tmpw = c.dtype == MULO_F32 ? (3 * d > 2 * f ? 3 * d : 2 * f) : 0;
-    const size_t sizes[N_BUF] = {M * d * 4, M16 * d * e, M * d * e, M16 * d * e, M16 * f * e, M * tmpw * 4,
+    const size_t sizes[N_BUF] = {M * d * 4, M16 * d * e, M * d * e, M16 * d * e, M16 * f * e,
                               M * V * 4, M * V * 4, M * 4, M * 4, M * 4, M * 4, (size_t)c.max_block * 4,
                               c.dtype == MULO_BF16 ? attention_scratch_bytes(c.max_batch, c.n_heads, c.head_dim) : 0,
                               M * 4, M, c.dtype == MULO_BF16 ? M * ((V + 127) / 128) * 8 : 0,
@@ -211,8 +209,8 @@ bool enqueue_forward(mulo_ctx* c, mulo_kv* kv, int B, int L, int P, const int32_
         const char* wd = (wfrag ? c->pk_down : (const char*)c->w.w_down) + (size_t)l * d * f * e;
         const char* g_attn = (const char*)c->w.attn_norm + (size_t)l * d * e;
         const char* g_ffn = (const char*)c->w.ffn_norm + (size_t)l * d * e;
-        { PROF(MULO_PROF_NORM_EMBED); launch_rmsnorm(c->x, g_attn, dt, c->xh, M, d, m.rms_eps, frag, st); }
         if (dt == MULO_BF16) {
+            { PROF(MULO_PROF_NORM_EMBED); launch_rmsnorm(c->x, g_attn, dt, c->xh, M, d, m.rms_eps, frag, st); }
             { PROF(MULO_PROF_GEMM_QKV); launch_gemm_qkv_bf16(c->xh, wq, wk, wv, c->qbuf, kv->k, kv->v, M, d, ra, sm, st); }
             { PROF(MULO_PROF_ATTENTION);
               if (sc) launch_attention_scattered_bf16(c->qbuf, kv->k, kv->v, c->att, c->attn_part, B, sc->pos_tab, L, sc->hide,
@@ -224,29 +222,22 @@ bool enqueue_forward(mulo_ctx* c, mulo_kv* kv, int B, int L, int P, const int32_
             { PROF(MULO_PROF_GEMM_GATE_UP); launch_gemm_swiglu_bf16(c->xh, wg, wu, c->hmid, M, f, d, sm, st); }
             { PROF(MULO_PROF_GEMM_DOWN); launch_gemm_resid_bf16(c->hmid, wd, c->x, M, d, f, sm, st); }
         } else {
-            const float* xh = (const float*)c->xh;
             { PROF(MULO_PROF_GEMM_QKV);
-              launch_gemm_f32(xh, (const float*)wq, c->tmp, M, d, d, 3 * d, 0, st);
-              launch_gemm_f32(xh, (const float*)wk, c->tmp + d, M, d, d, 3 * d, 0, st);
-              launch_gemm_f32(xh, (const float*)wv, c->tmp + 2 * d, M, d, d, 3 * d, 0, st); }
-            { PROF(MULO_PROF_OTHER);
-              launch_rope_append_f32(c->tmp, (float*)c->qbuf, (float*)kv->k, (float*)kv->v, M, d, ra, st); }
+              launch_qkv_f32(c->x, (const float*)g_attn, m.rms_eps, (const float*)wq, (const float*)wk, (const float*)wv,
+                             (float*)c->qbuf, (float*)kv->k, (float*)kv->v, M, d, ra, st); }
             { PROF(MULO_PROF_ATTENTION);
-              launch_attention_f32((const float*)c->qbuf, (const float*)kv->k, (const float*)kv->v, (float*)c->att,
-                                   nullptr, B, L, P, m.n_heads, m.head_dim, m.max_seq, m.max_batch, l, st); }
-            { PROF(MULO_PROF_GEMM_OUT); launch_gemm_f32((const float*)c->att, (const float*)wo, c->x, M, d, d, d, 1, st); }
-            { PROF(MULO_PROF_NORM_EMBED); launch_rmsnorm(c->x, g_ffn, dt, c->xh, M, d, m.rms_eps, frag, st); }
+              launch_attention_f32((const float*)c->qbuf, (const float*)kv->k, (const float*)kv->v, (float*)c->att, B, L, P,
+                                   m.n_heads, m.head_dim, m.max_seq, m.max_batch, l, st); }
+            { PROF(MULO_PROF_GEMM_OUT); launch_resid_f32((const float*)c->att, (const float*)wo, c->x, M, d, d, st); }
             { PROF(MULO_PROF_GEMM_GATE_UP);
-              launch_gemm_f32(xh, (const float*)wg, c->tmp, M, f, d, 2 * f, 0, st);
-              launch_gemm_f32(xh, (const float*)wu, c->tmp + f, M, f, d, 2 * f, 0, st); }
-            { PROF(MULO_PROF_OTHER); launch_swiglu_f32(c->tmp, (float*)c->hmid, M, f, st); }
-            { PROF(MULO_PROF_GEMM_DOWN); launch_gemm_f32((const float*)c->hmid, (const float*)wd, c->x, M, d, f, d, 1, st); }
+              launch_swiglu_f32(c->x, (const float*)g_ffn, m.rms_eps, (const float*)wg, (const float*)wu, (float*)c->hmid, M, f, d, st); }
+            { PROF(MULO_PROF_GEMM_DOWN); launch_resid_f32((const float*)c->hmid, (const float*)wd, c->x, M, d, f, st); }
         }
     }
     { PROF(MULO_PROF_NORM_EMBED); launch_rmsnorm(c->x, c->w.final_norm, dt, c->xh, M, d, m.rms_eps, frag, st); }
     PROF(MULO_PROF_GEMM_LM_HEAD);
     if (dt == MULO_BF16) return launch_gemm_logits_bf16(c->xh, wfrag ? (const void*)c->pk_lm : c->w.lm_head, logits, want_parts ? c->row_parts : nullptr, M, V, d, sm, st);
-    launch_gemm_f32((const float*)c->xh, (const float*)c->w.lm_head, logits, M, V, d, V, 0, st);
+    launch_logits_f32((const float*)c->xh, (const float*)c->w.lm_head, logits, M, V, d, st);
     return false;
 }
 
@@ -388,23 +379,22 @@ mulo_status mulo_create(const mulo_model_cfg* cfg, const mulo_weights* w, void* 
     c->qbuf = b + l.off[2];
     c->att = b + l.off[3];
     c->hmid = b + l.off[4];
-    c->tmp = (float*)(b + l.off[5]);
-    c->logits = (float*)(b + l.off[6]);
-    c->q_lo = (float*)(b + l.off[7]);
-    c->rowmax = (float*)(b + l.off[8]);
-    c->rowinv = (float*)(b + l.off[9]);
-    c->inputs = (int32_t*)(b + l.off[10]);
-    c->tokens_hi = (int32_t*)(b + l.off[11]);
-    c->q_row = (int32_t*)(b + l.off[12]);
-    c->attn_part = (float*)(b + l.off[13]);
-    c->isl_pos = (int32_t*)(b + l.off[14]);
-    c->isl_hide = (uint8_t*)(b + l.off[15]);
-    c->row_parts = c->esz == 2 ? (float*)(b + l.off[16]) : nullptr;
+    c->logits = (float*)(b + l.off[5]);
+    c->q_lo = (float*)(b + l.off[6]);
+    c->rowmax = (float*)(b + l.off[7]);
+    c->rowinv = (float*)(b + l.off[8]);
+    c->inputs = (int32_t*)(b + l.off[9]);
+    c->tokens_hi = (int32_t*)(b + l.off[10]);
+    c->q_row = (int32_t*)(b + l.off[11]);
+    c->attn_part = (float*)(b + l.off[12]);
+    c->isl_pos = (int32_t*)(b + l.off[13]);
+    c->isl_hide = (uint8_t*)(b + l.off[14]);
+    c->row_parts = c->esz == 2 ? (float*)(b + l.off[15]) : nullptr;
     c->pk_wq = c->pk_wk = c->pk_wv = c->pk_wo = c->pk_gate = c->pk_up = c->pk_down = c->pk_lm = nullptr;
-    c->ksums = cfg->stream_copy ? (float*)(b + l.off[18]) : nullptr;
+    c->ksums = cfg->stream_copy ? (float*)(b + l.off[17]) : nullptr;
     if (cfg->stream_copy) {   // bf16 (checked): the second copy of the weights, made once on the context's stream
         const int nl = cfg->n_layers, d = cfg->d_model, f = cfg->d_ffn;
-        char* p = b + l.off[17];
+        char* p = b + l.off[16];
         auto take = [&](const void* src, int layers, int rows, int K) {
             const char* at = p;
             launch_pack_weights(src, p, layers, rows, K, c->st);

@@ -158,14 +158,15 @@ void launch_attention_scattered_bf16(const void* q, const void* k_cache, const v
                                      int P0, int Lblk, int n_heads, int head_dim, int max_seq, int max_batch,
                                      int layer, bool frag_out, hipStream_t st);
 
-// float32 path (small configurations): plain tiled GEMM + separate elementwise kernels
-void launch_gemm_f32(const float* a, const float* w, float* c, int M, int N, int K, int ldc,
-                     int accumulate, hipStream_t st);
-void launch_rope_append_f32(const float* qkv, float* q_out, float* k_cache, float* v_cache, int M,
-                            int d, const RopeArgs& ra, hipStream_t st);
-void launch_swiglu_f32(const float* gu, float* h, int M, int f, hipStream_t st);
-void launch_attention_f32(const float* q, const float* k_cache, const float* v_cache, float* out,
-                          float* scratch, int B, int L, int P, int n_heads, int head_dim,
-                          int max_seq, int max_batch, int layer, hipStream_t st);
+// float32 path (forward_f32.hip): x is the residual stream, its RMSNorm with `gain` is part of the projection; rotary and
+// cache append, the SwiGLU product and the residual add are the projections' epilogues
+void launch_qkv_f32(const float* x, const float* gain, float eps, const float* wq, const float* wk, const float* wv,
+                    float* q_out, float* k_cache, float* v_cache, int M, int d, const RopeArgs& ra, hipStream_t st);
+void launch_swiglu_f32(const float* x, const float* gain, float eps, const float* wg, const float* wu, float* h, int M,
+                       int f, int d, hipStream_t st);
+void launch_resid_f32(const float* a, const float* w, float* x, int M, int N, int K, hipStream_t st);
+void launch_logits_f32(const float* xh, const float* w, float* logits, int M, int V, int d, hipStream_t st);
+void launch_attention_f32(const float* q, const float* k_cache, const float* v_cache, float* out, int B, int L, int P,
+                          int n_heads, int head_dim, int max_seq, int max_batch, int layer, hipStream_t st);
 
 }  // namespace mulo

@@ -68,6 +68,33 @@ def test_forward_tiny_f32():
     assert np.abs(seq - blk[:, :24]).max() < 1e-4
 
 
+@pytest.mark.parametrize("nh,dh,f,V,B,L,P", [
+    (3, 4, 30, 20, 1, 1, 0),          # nothing a multiple of 16, rows of 30 floats not 16-byte aligned, one token
+    (2, 18, 44, 68, 2, 17, 3),        # a head of 18: 16 + 2; two query tiles, the second one query deep
+    (2, 64, 176, 128, 3, 33, 31),     # whole blocks of the head, keys ending on a tile edge
+    (2, 128, 90, 64, 1, 16, 49),      # the widest head of the tiled attention
+    (1, 136, 64, 64, 2, 5, 7),        # wider: one workgroup per query
+    (2, 16, 1030, 1028, 2, 1024, 0),  # more outputs than the split launches take: the 64 x 64 tiles, ragged columns, K of 1030
+])
+def test_forward_f32_shapes(nh, dh, f, V, B, L, P):
+    """The float32 projections and attention at the edges of their tiles.  Bar: 1e-4 as for the tiny configuration
+    (sums of at most 1030 float32 products of order 1: 1030 * 2^-24 = 6e-5)."""
+    m = dict(n_layers=2, d_model=nh * dh, n_heads=nh, head_dim=dh, d_ffn=f, vocab=V, dtype="f32", rms_eps=1e-5)
+    w = G.make_weights(m, seed=3, std=0.1)
+    S = P + L + 3
+    ctx, cos, sin = make_ctx(m, w, B, S, max(L, P, 1))
+    kv = mulo.alloc_kv(ctx, DEV)
+    kv[1].fill_(float("nan"))         # cache columns nobody has written must not reach the result
+    dec = OD.DecoderOracle(m, w, cos, sin, B, S, round_bf16=False)
+    if P:
+        prefix = G.uniform_tokens((B, P), V, 0, tag=0)
+        assert np.abs(gpu_forward(ctx, kv, prefix, 0) - dec.forward(prefix, 0).numpy()).max() <= 1e-4
+    block = G.uniform_tokens((B, L), V, 0, tag=1)
+    err = np.abs(gpu_forward(ctx, kv, block, P) - dec.forward(block, P).numpy()).max()
+    say("  f32 %s: max|err| %.3g" % ((nh, dh, f, V, B, L, P), err))
+    assert err <= 1e-4
+
+
 def test_forward_small_bf16_chained_blocks():
     c = WC.get("cfg2")
     m, B, L, Pn = c["model"], c["B"], c["L"], c["prefix"]
