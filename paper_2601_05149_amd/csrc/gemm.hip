@@ -7,9 +7,8 @@
 // the weight rows are fetched with bits 2-3 of the row index swapped, so a lane
 // ends up owning one token and runs of 8 consecutive output columns: every
 // epilogue reads and writes 16-byte pieces.  Fused epilogues:
-//   Q|K    -> rotary on the adjacent pairs of a run (float4 table reads) + q buffer / K cache rows
-//   V      -> operands in order instead: a lane owns 8 consecutive tokens of one
-//             column = 16 contiguous bytes of the transposed V cache
+//   Q|K|V  -> rotary on the adjacent pairs of a run (float4 table reads) + q buffer / K cache rows; V: the 32 lanes of
+//             a half are 32 consecutive tokens = 64 contiguous bytes of a row of the transposed V cache
 //   out, down -> residual add into the float32 stream
 //   gate|up   -> silu(gate) * up, gate and up columns interleaved inside a tile so
 //                that one lane owns both accumulators of a feed-forward column
@@ -29,8 +28,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __hip_bfloat16 bf16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-enum { EPI_QK = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3, EPI_V = 4,
-       EPI_QKV = 5 };   // q | k | v in one launch: the weight-streaming kernel, and tiled launches of a few hundred tokens
+enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
 
 struct GemmArgs {
     const bf16* A;        // [M, K]
@@ -74,7 +72,7 @@ __device__ __forceinline__ float silu(float g) { return g * __builtin_amdgcn_rcp
 template <int EPI, int BN, int TN>
 __device__ __forceinline__ int b_row_src(const GemmArgs& g, int n0, int tile_n, int nl, int& which) {
     int r;
-    if constexpr (EPI == EPI_QK || EPI == EPI_QKV) {
+    if constexpr (EPI == EPI_QKV) {
         const int seg = n0 / g.d;
         which = seg;
         r = n0 - seg * g.d + nl;
@@ -93,12 +91,6 @@ __device__ __forceinline__ int b_row_src(const GemmArgs& g, int n0, int tile_n, 
     }
     return r;
 }
-template <int EPI, int BN, int TN>
-__device__ __forceinline__ const bf16* b_row(const GemmArgs& g, int n0, int tile_n, int nl) {
-    int which;
-    const int r = b_row_src<EPI, BN, TN>(g, n0, tile_n, nl, which);
-    return (which == 0 ? g.W0 : which == 1 ? g.W1 : g.W2) + (int64_t)r * g.K;
-}
 
 // Whole-tile launches address their operands through buffer descriptors: the descriptor (matrix base and size)
 // and a byte offset of the tile row and K-step live in scalar registers, a lane adds one fixed 32-bit offset
@@ -112,8 +104,8 @@ __device__ __forceinline__ u32x4 bload(rsrc_t r, uint32_t lane_off, uint32_t bas
 }
 // rows of the weight matrices of each fused problem
 template <int EPI>
-__device__ __forceinline__ int64_t weight_rows(const GemmArgs& g) {
-    return (EPI == EPI_QK || EPI == EPI_QKV) ? g.d : EPI == EPI_SWIGLU ? g.N / 2 : g.N;
+__host__ __device__ __forceinline__ int64_t weight_rows(const GemmArgs& g) {
+    return EPI == EPI_QKV ? g.d : EPI == EPI_SWIGLU ? g.N / 2 : g.N;
 }
 
 // Which tile row feeds MFMA row rho: bits 2 and 3 exchanged.  With it, accumulator r of a lane
@@ -125,10 +117,8 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8s;
 
 // Fused epilogues.  acc[i][j] is the 32x32 block (i, j) of the wavefront's TM x TN tile whose corner
-// is (m0 + wm TM, n0 + wn TN).  All projections but V run with the MFMA operands exchanged, so a
-// lane owns ONE token row (m = ... + l32) and, per block, the column runs [16 g + 8 lh, +8), g = 0, 1
-// (accumulators 8 g .. 8 g + 7).  The V projection keeps the operands in order: a lane owns one
-// output column and runs of 8 consecutive tokens, which are contiguous in the transposed V cache.
+// is (m0 + wm TM, n0 + wn TN).  The MFMA operands are exchanged, so a lane owns ONE token row
+// (m = ... + l32) and, per block, the column runs [16 g + 8 lh, +8), g = 0, 1 (accumulators 8 g .. 8 g + 7).
 // Where token row m of a projection lives: b, jj index the q buffer [B, nh, L, dh]; bc is its cache sequence and pos
 // its cache row (< 0: an unused slot of a scattered launch, nothing of it is written).
 struct TokPlace { int b, jj, bc, pos; };
@@ -229,102 +219,75 @@ __device__ __forceinline__ void epilogue(const GemmArgs& g, f32x16 (&acc)[MB][NB
                 float v[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[e] = acc[i][j][g2 * 8 + e];
-                if constexpr (EPI == EPI_V) {
-                    const int n = n0 + wn * TN + j * 32 + l32;                       // output column (head, cc)
-                    const int mb = m0 + wm * TM + i * 32 + g2 * 16 + lh * 8;         // first of 8 tokens
-                    if (n < g.N && mb < g.M) {
-                        const int dh = g.ra.head_dim, hd = n / dh, cc = n % dh;
-                        if (!g.ra.pos_tab && ((g.ra.P | g.ra.L) & 7) == 0) {          // aligned run inside one sequence
-                            const int b = mb / g.ra.L, jj = mb % g.ra.L;
-                            const int64_t hb = ((int64_t)g.ra.layer * g.ra.max_batch + b) * g.ra.n_heads + hd;
-                            bf16* dst = g.vc + (hb * dh + cc) * g.ra.max_seq + g.ra.P + jj;
+                const int m = m0 + wm * TM + i * 32 + l32;                       // token row of this lane
+                const int cl = j * 32 + g2 * 16 + lh * 8;                        // column run inside the wave tile
+                if (m < g.M) {
+                    if constexpr (EPI == EPI_RESID || EPI == EPI_LOGITS) {
+                        const int n = n0 + wn * TN + cl;
+                        float* dst = g.Cf + (int64_t)m * g.N + n;
+                        if (n + 8 <= g.N) {
+                            f32x4 lo = {v[0], v[1], v[2], v[3]}, hi = {v[4], v[5], v[6], v[7]};
+                            if constexpr (EPI == EPI_RESID) {
+                                lo += *reinterpret_cast<const f32x4*>(dst);
+                                hi += *reinterpret_cast<const f32x4*>(dst + 4);
+                            }
+                            *reinterpret_cast<f32x4*>(dst) = lo;
+                            *reinterpret_cast<f32x4*>(dst + 4) = hi;
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < 8; ++e)
+                                if (n + e < g.N) dst[e] = EPI == EPI_RESID ? dst[e] + v[e] : v[e];
+                        }
+                    } else if constexpr (EPI == EPI_SWIGLU) {
+                        const int f = g.N / 2;
+                        const int n = tile_n * (BN / 2) + wn * (TN / 2) + cl;
+                        bf16* dst = g.Cb + (int64_t)m * f + n;
+                        float h[8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) h[e] = silu(v[e]) * acc[i][j + NB / 2][g2 * 8 + e];
+                        if (n + 8 <= f) {
                             bf16x8s o;
 #pragma unroll
-                            for (int e = 0; e < 8; ++e) o[e] = (__bf16)v[e];
+                            for (int e = 0; e < 8; ++e) o[e] = (__bf16)h[e];
                             *reinterpret_cast<bf16x8s*>(dst) = o;
                         } else {
 #pragma unroll
-                            for (int e = 0; e < 8; ++e) {
-                                const int m = mb + e;
-                                if (m < g.M) {
-                                    const TokPlace pl = place(g.ra, m);
-                                    const int64_t hb2 = ((int64_t)g.ra.layer * g.ra.max_batch + pl.bc) * g.ra.n_heads + hd;
-                                    if (pl.pos >= 0) g.vc[(hb2 * dh + cc) * g.ra.max_seq + pl.pos] = __float2bfloat16(v[e]);
-                                }
-                            }
+                            for (int e = 0; e < 8; ++e)
+                                if (n + e < f) dst[e] = __float2bfloat16(h[e]);
                         }
-                    }
-                } else {
-                    const int m = m0 + wm * TM + i * 32 + l32;                       // token row of this lane
-                    const int cl = j * 32 + g2 * 16 + lh * 8;                        // column run inside the wave tile
-                    if (m < g.M) {
-                        if constexpr (EPI == EPI_RESID || EPI == EPI_LOGITS) {
-                            const int n = n0 + wn * TN + cl;
-                            float* dst = g.Cf + (int64_t)m * g.N + n;
-                            if (n + 8 <= g.N) {
-                                f32x4 lo = {v[0], v[1], v[2], v[3]}, hi = {v[4], v[5], v[6], v[7]};
-                                if constexpr (EPI == EPI_RESID) {
-                                    lo += *reinterpret_cast<const f32x4*>(dst);
-                                    hi += *reinterpret_cast<const f32x4*>(dst + 4);
-                                }
-                                *reinterpret_cast<f32x4*>(dst) = lo;
-                                *reinterpret_cast<f32x4*>(dst + 4) = hi;
-                            } else {
+                    } else {  // EPI_QKV: rotary on the 4 adjacent pairs of the run, q -> [B, nh, L, dh], k -> cache row
+                        const int n = n0 + wn * TN + cl, seg = n / g.d, c = n - seg * g.d;
+                        const int dh = g.ra.head_dim, hd = c / dh, cc = c % dh;
+                        const TokPlace pl = place(g.ra, m);
+                        if (seg == 2) {
+                            // a lane holds 8 consecutive channels of ONE token, the 32 lanes of a half are 32
+                            // consecutive tokens = 64 contiguous bytes of a row of the transposed cache per store
+                            // (4096 x 12288 x 4096: 345 us in one launch, 350 with a V projection of its own whose lanes
+                            // hold 8 consecutive tokens; 2560 tokens: 224 against 276)
+                            if (pl.pos >= 0) {
+                                const int64_t hb = ((int64_t)g.ra.layer * g.ra.max_batch + pl.bc) * g.ra.n_heads + hd;
 #pragma unroll
                                 for (int e = 0; e < 8; ++e)
-                                    if (n + e < g.N) dst[e] = EPI == EPI_RESID ? dst[e] + v[e] : v[e];
+                                    g.vc[(hb * dh + cc + e) * g.ra.max_seq + pl.pos] = __float2bfloat16(v[e]);
                             }
-                        } else if constexpr (EPI == EPI_SWIGLU) {
-                            const int f = g.N / 2;
-                            const int n = tile_n * (BN / 2) + wn * (TN / 2) + cl;
-                            bf16* dst = g.Cb + (int64_t)m * f + n;
-                            float h[8];
+                        } else if (pl.pos >= 0) {
+                            const int pos = pl.pos;
+                            const f32x4 cs = *reinterpret_cast<const f32x4*>(g.ra.cos + (int64_t)pos * (dh / 2) + (cc >> 1));
+                            const f32x4 sn = *reinterpret_cast<const f32x4*>(g.ra.sin + (int64_t)pos * (dh / 2) + (cc >> 1));
+                            bf16x8s o;
 #pragma unroll
-                            for (int e = 0; e < 8; ++e) h[e] = silu(v[e]) * acc[i][j + NB / 2][g2 * 8 + e];
-                            if (n + 8 <= f) {
-                                bf16x8s o;
-#pragma unroll
-                                for (int e = 0; e < 8; ++e) o[e] = (__bf16)h[e];
-                                *reinterpret_cast<bf16x8s*>(dst) = o;
+                            for (int pr = 0; pr < 4; ++pr) {
+                                o[2 * pr] = (__bf16)(v[2 * pr] * cs[pr] - v[2 * pr + 1] * sn[pr]);
+                                o[2 * pr + 1] = (__bf16)(v[2 * pr] * sn[pr] + v[2 * pr + 1] * cs[pr]);
+                            }
+                            bf16* dst;
+                            if (seg == 0) {
+                                dst = g.Cb + (((int64_t)pl.b * g.ra.n_heads + hd) * g.ra.L + pl.jj) * dh + cc;
                             } else {
-#pragma unroll
-                                for (int e = 0; e < 8; ++e)
-                                    if (n + e < f) dst[e] = __float2bfloat16(h[e]);
+                                const int64_t hb = ((int64_t)g.ra.layer * g.ra.max_batch + pl.bc) * g.ra.n_heads + hd;
+                                dst = g.kc + (hb * g.ra.max_seq + pos) * dh + cc;
                             }
-                        } else {  // EPI_QK: rotary on the 4 adjacent pairs of the run, q -> [B, nh, L, dh], k -> cache row
-                            const int n = n0 + wn * TN + cl, seg = n / g.d, c = n - seg * g.d;
-                            const int dh = g.ra.head_dim, hd = c / dh, cc = c % dh;
-                            const TokPlace pl = place(g.ra, m);
-                            if (EPI == EPI_QKV && seg == 2) {
-                                // V with the operands exchanged: a lane holds 8 consecutive channels of ONE token, the
-                                // 32 lanes of a half are 32 consecutive tokens = 64 contiguous bytes of a row of the
-                                // transposed cache per store (fine for a few hundred tokens; the large launches keep the
-                                // V projection of its own, whose lanes hold 8 consecutive tokens)
-                                if (pl.pos >= 0) {
-                                    const int64_t hb = ((int64_t)g.ra.layer * g.ra.max_batch + pl.bc) * g.ra.n_heads + hd;
-#pragma unroll
-                                    for (int e = 0; e < 8; ++e)
-                                        g.vc[(hb * dh + cc + e) * g.ra.max_seq + pl.pos] = __float2bfloat16(v[e]);
-                                }
-                            } else if (pl.pos >= 0) {
-                                const int pos = pl.pos;
-                                const f32x4 cs = *reinterpret_cast<const f32x4*>(g.ra.cos + (int64_t)pos * (dh / 2) + (cc >> 1));
-                                const f32x4 sn = *reinterpret_cast<const f32x4*>(g.ra.sin + (int64_t)pos * (dh / 2) + (cc >> 1));
-                                bf16x8s o;
-#pragma unroll
-                                for (int pr = 0; pr < 4; ++pr) {
-                                    o[2 * pr] = (__bf16)(v[2 * pr] * cs[pr] - v[2 * pr + 1] * sn[pr]);
-                                    o[2 * pr + 1] = (__bf16)(v[2 * pr] * sn[pr] + v[2 * pr + 1] * cs[pr]);
-                                }
-                                bf16* dst;
-                                if (seg == 0) {
-                                    dst = g.Cb + (((int64_t)pl.b * g.ra.n_heads + hd) * g.ra.L + pl.jj) * dh + cc;
-                                } else {
-                                    const int64_t hb = ((int64_t)g.ra.layer * g.ra.max_batch + pl.bc) * g.ra.n_heads + hd;
-                                    dst = g.kc + (hb * g.ra.max_seq + pos) * dh + cc;
-                                }
-                                *reinterpret_cast<bf16x8s*>(dst) = o;
-                            }
+                            *reinterpret_cast<bf16x8s*>(dst) = o;
                         }
                     }
                 }
@@ -333,19 +296,15 @@ __device__ __forceinline__ void epilogue(const GemmArgs& g, f32x16 (&acc)[MB][NB
     });
 }
 
-template <bool SWAP>
+// D[n][m]: MFMA rows = weight rows (output columns), lanes = tokens
 __device__ __forceinline__ f32x16 mma(const bf16x8& a, const bf16x8& b, const f32x16& c) {
-    if constexpr (SWAP)   // D[n][m]: MFMA rows = weight rows (output columns), lanes = tokens
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, c, 0, 0, 0);
-    else                  // D[m][n]: MFMA rows = tokens, lanes = output columns (V projection)
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, c, 0, 0, 0);
 }
 
 // ---- BM x BN x 64 tiles, double-buffered LDS, one barrier per K-tile ---------------------------
-template <int BM, int BN, int WGM, int WGN, int EPI, int BKT = 64, bool FULL = false>
-__global__ __launch_bounds__(WGM* WGN * 64, (WGM * WGN >= 8 || BM * BN >= 65536) ? 1 : 2) void k_gemm_bf16(const GemmArgs g) {
-    constexpr int BK = BKT, LDS_STRIDE = BKT + 8, CPR = BKT / 8;   // 16-byte chunks per tile row
-    constexpr bool SWAP = EPI != EPI_V;
+template <int BM, int BN, int WGM, int WGN, int EPI>
+__global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_bf16(const GemmArgs g) {
+    constexpr int BK = 64, LDS_STRIDE = BK + 8, CPR = BK / 8;   // 16-byte chunks per tile row
     constexpr int NT = WGM * WGN * 64;
     constexpr int TM = BM / WGM, TN = BN / WGN, MB = TM / 32, NB = TN / 32;
     constexpr int LA = BM * CPR / NT, LB = BN * CPR / NT;  // 16-byte chunks per lane per stage
@@ -358,7 +317,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, (WGM * WGN >= 8 || BM * BN >= 65536)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WGN, wn = wave % WGN, l32 = lane & 31, lh = lane >> 5;
-    const int fra = SWAP ? l32 : kperm(l32), frb = SWAP ? kperm(l32) : l32;   // fragment rows (MFMA-row operand permuted)
+    const int fra = l32, frb = kperm(l32);   // fragment rows (MFMA-row operand permuted)
     // Persistent workgroups.  Workgroup b runs on XCD b % 8 (round-robin dispatch), and each XCD has
     // its own L2, so the tile sequence is cut into one contiguous chunk per XCD and the sequence
     // itself walks groups of GW column tiles row by row: the workgroups of one XCD then work, at any
@@ -371,20 +330,17 @@ __global__ __launch_bounds__(WGM* WGN * 64, (WGM * WGN >= 8 || BM * BN >= 65536)
     const int chunk_len = total_tiles - chunk_base < chunk ? total_tiles - chunk_base : chunk;   // may be <= 0
     int tile = blockIdx.x / nxcd, tile_n = 0, m0 = 0, n0 = 0;
     const int kc8 = (tid % CPR) * 8, trow = tid / CPR;
-    // Operand addresses.  General case: one pointer per staged chunk.  FULL (M and N multiples of the
-    // tile, the launcher checks): the rows a lane fetches are a fixed stride apart, so a lane keeps
-    // ONE 32-bit offset (its row and chunk inside a pass) and everything else is scalar: buffer loads
-    // through a descriptor of the whole matrix, with the pass's row and the K-step as scalar offset.
-    // No 64-bit lane addresses to keep or to advance (about 25 vector registers fewer).
+    // Operand addresses: the rows a lane fetches are a fixed stride apart, so a lane keeps ONE 32-bit offset (its row and
+    // chunk inside a pass) and everything else is scalar: buffer loads through a descriptor of the whole matrix, with
+    // the pass's row and the K-step as scalar offset.  No 64-bit lane addresses to keep or to advance.  N is a multiple
+    // of the tile (choose_tile); token rows past M read as zeros through the descriptor and are not stored.
     constexpr int RP = NT / CPR;   // tile rows per pass
-    const bf16* pa[FULL ? 1 : LA];
-    const bf16* pb[FULL ? 1 : LB];
-    uint32_t sa[FULL ? LA : 1];   // byte offset of pass i's first row in its matrix
-    uint32_t sb[FULL ? LB : 1];
+    uint32_t sa[LA];   // byte offset of pass i's first row in its matrix
+    uint32_t sb[LB];
     const uint32_t voff = (uint32_t)(trow * g.K + kc8) * 2u;
     const rsrc_t rA = make_rsrc(g.A, (int64_t)g.M * g.K * 2);
     rsrc_t rW[2] = {make_rsrc(g.W0, weight_rows<EPI>(g) * g.K * 2),
-                    make_rsrc(EPI == EPI_QK || EPI == EPI_QKV || EPI == EPI_SWIGLU ? g.W1 : g.W0, weight_rows<EPI>(g) * g.K * 2)};
+                    make_rsrc(EPI == EPI_QKV || EPI == EPI_SWIGLU ? g.W1 : g.W0, weight_rows<EPI>(g) * g.K * 2)};
     // which descriptor pass i of the weight tile reads: gate | up alternate inside a tile (compile-time), q | k is per tile
     auto wsel = [&](int i) -> rsrc_t { return rW[EPI == EPI_SWIGLU ? ((i * RP) % TN >= TN / 2 ? 1 : 0) : 0]; };
     auto setup = [&](int local) {   // operand rows of the chunk's tile `local` (fixed over its K loop)
@@ -393,43 +349,25 @@ __global__ __launch_bounds__(WGM* WGN * 64, (WGM * WGN >= 8 || BM * BN >= 65536)
         tile_n = g.tile_n0 + grp * GW + rem % gw;
         m0 = (rem / gw) * BM;
         n0 = tile_n * BN;
-        if constexpr (FULL) {
 #pragma unroll
-            for (int i = 0; i < LA; ++i) sa[i] = (uint32_t)((m0 + i * RP) * g.K) * 2u;
+        for (int i = 0; i < LA; ++i) sa[i] = (uint32_t)((m0 + i * RP) * g.K) * 2u;
 #pragma unroll
-            for (int i = 0; i < LB; ++i) {
-                int which;
-                sb[i] = (uint32_t)(b_row_src<EPI, BN, TN>(g, n0, tile_n, i * RP, which) * g.K) * 2u;
-                if constexpr (EPI == EPI_QK || EPI == EPI_QKV) {
-                    if (i == 0) rW[0] = make_rsrc(which == 0 ? g.W0 : which == 1 ? g.W1 : g.W2, weight_rows<EPI>(g) * g.K * 2);
-                }
+        for (int i = 0; i < LB; ++i) {
+            int which;
+            sb[i] = (uint32_t)(b_row_src<EPI, BN, TN>(g, n0, tile_n, i * RP, which) * g.K) * 2u;
+            if constexpr (EPI == EPI_QKV) {
+                if (i == 0) rW[0] = make_rsrc(which == 0 ? g.W0 : which == 1 ? g.W1 : g.W2, weight_rows<EPI>(g) * g.K * 2);
             }
-        } else {
-#pragma unroll
-            for (int i = 0; i < LA; ++i) {
-                int r = m0 + trow + i * RP;
-                r = r < g.M ? r : g.M - 1;
-                pa[i] = g.A + (int64_t)r * g.K + kc8;
-            }
-#pragma unroll
-            for (int i = 0; i < LB; ++i) pb[i] = b_row<EPI, BN, TN>(g, n0, tile_n, trow + i * RP) + kc8;
         }
     };
 
     f32x16 acc[MB][NB];
     u32x4 ra[LA], rb[LB];
     auto gload = [&](int kt) {
-        if constexpr (FULL) {
 #pragma unroll
-            for (int i = 0; i < LA; ++i) ra[i] = bload(rA, voff, sa[i] + kt * (BK * 2));
+        for (int i = 0; i < LA; ++i) ra[i] = bload(rA, voff, sa[i] + kt * (BK * 2));
 #pragma unroll
-            for (int i = 0; i < LB; ++i) rb[i] = bload(wsel(i), voff, sb[i] + kt * (BK * 2));
-        } else {
-#pragma unroll
-            for (int i = 0; i < LA; ++i) ra[i] = *reinterpret_cast<const u32x4*>(pa[i] + kt * BK);
-#pragma unroll
-            for (int i = 0; i < LB; ++i) rb[i] = *reinterpret_cast<const u32x4*>(pb[i] + kt * BK);
-        }
+        for (int i = 0; i < LB; ++i) rb[i] = bload(wsel(i), voff, sb[i] + kt * (BK * 2));
     };
     const int nk = g.K / BK;
     auto sstore = [&](int buf) {
@@ -445,11 +383,10 @@ __global__ __launch_bounds__(WGM* WGN * 64, (WGM * WGN >= 8 || BM * BN >= 65536)
     // Fragments of one k-slice, double-buffered in registers.  Inside every 64 consecutive k the index is dealt so
     // that lane half lh owns k in [32 lh, 32 lh + 32) and MFMA slice kk takes its kk-th 8 (both operands alike, so
     // the products are unchanged): the same deal, hence the same summation order, as in the kernels that fetch an
-    // operand straight from memory, where it makes a lane's bytes contiguous.  A 128-deep K-step is two such runs of
-    // 64 one after the other, so the depth of a step does not show in the sums either.
+    // operand straight from memory, where it makes a lane's bytes contiguous.
     bf16x8 af[2][MB], bfr[2][NB];
     auto lfrag = [&](const bf16* a, const bf16* b, int kk, int slot) {
-        const int ko = (kk >> 2) * 64 + (kk & 3) * 8;
+        const int ko = kk * 8;
 #pragma unroll
         for (int i = 0; i < MB; ++i)
             af[slot][i] = *reinterpret_cast<const bf16x8*>(a + i * 32 * LDS_STRIDE + ko);
@@ -474,12 +411,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, (WGM * WGN >= 8 || BM * BN >= 65536)
     constexpr int KS = BK / 16;                      // k-slices (one MFMA deep) per K-step
     constexpr int NMS = MB * NB, NF = MB + NB;       // MFMAs and fragment reads per k-slice
     constexpr int NL = LA + LB;                      // staging registers per lane
-    static_assert(KS == 4 || KS == 8, "K-steps are one or two runs of 64");
     auto mm = [&](int slot) {
 #pragma unroll
         for (int i = 0; i < MB; ++i)
 #pragma unroll
-            for (int j = 0; j < NB; ++j) acc[i][j] = mma<SWAP>(af[slot][i], bfr[slot][j], acc[i][j]);
+            for (int j = 0; j < NB; ++j) acc[i][j] = mma(af[slot][i], bfr[slot][j], acc[i][j]);
     };
     // One K-step, rotated by one k-slice: the step's first fragments are requested right after the barrier and
     // the MFMAs of the PREVIOUS step's last slice (fragments already in registers, slot 1) run while they are on
@@ -523,13 +459,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, (WGM * WGN >= 8 || BM * BN >= 65536)
                 constexpr int i = decltype(ic)::value;
                 if constexpr (i < LA) {
                     *reinterpret_cast<u32x4*>(na + i * RP * LDS_STRIDE) = ra[i];
-                    if constexpr (FULL) ra[i] = bload(rA, voff, sa[i] + (kt + 2) * (BK * 2));
-                    else ra[i] = *reinterpret_cast<const u32x4*>(pa[i] + (kt + 2) * BK);
+                    ra[i] = bload(rA, voff, sa[i] + (kt + 2) * (BK * 2));
                 } else {
                     constexpr int j = i - LA;
                     *reinterpret_cast<u32x4*>(nb + j * RP * LDS_STRIDE) = rb[j];
-                    if constexpr (FULL) rb[j] = bload(wsel(j), voff, sb[j] + (kt + 2) * (BK * 2));
-                    else rb[j] = *reinterpret_cast<const u32x4*>(pb[j] + (kt + 2) * BK);
+                    rb[j] = bload(wsel(j), voff, sb[j] + (kt + 2) * (BK * 2));
                 }
             };
             // The NL write + load pairs are dealt evenly over the first SPAN MFMAs of the iteration; the rest run
@@ -576,6 +510,213 @@ __global__ __launch_bounds__(WGM* WGN * 64, (WGM * WGN >= 8 || BM * BN >= 65536)
     }
 }
 
+// ---- BM x BN x 64 tiles over an LDS ring of NS stages, filled by direct loads (global memory -> LDS) ------------
+// For launches whose 256 x 256 tiles do not fill the chip.  What bounds them is the operand traffic into a CU: with the
+// matrix instructions taken out the loads alone take the kernel's time (576 x 4096 x 4096 on 128 x 128 tiles: 36.5 of
+// 37.4 us, the tokens alone 14, the weights alone 26; with the loads taken out 30).  So: no staging registers and no
+// ds_write (a wavefront's load puts 1 KB, 8 rows of 64, straight into the ring), NS - 1 stages in flight while one is
+// multiplied, and the tile is chosen per launch so that all CUs fetch (choose_tile).  One barrier per stage: it is
+// passed when the stage has landed for every wavefront (each waits for its own loads, younger stages stay in flight)
+// and every wavefront has read the stage before, whose slot the next loads fill.
+// The direct load writes lane l's 16 bytes at 16 l, so a row cannot be padded against bank conflicts; instead chunk c
+// of row r sits at chunk position c ^ ((r / 2) % 8): 16 consecutive lanes of a fragment read, 16 rows 128 bytes apart,
+// then touch every bank once (no conflicts counted; with c ^ (r % 8) half of the LDS cycles were conflicts).
+// The k deal, hence every sum, is that of k_gemm_bf16 below, whatever the tile.
+// us per launch, before (128 x 128 tiles, staged through registers) -> here, cold weights: 186 tokens: 4096 x 4096
+// 36 -> 21, 4096 x 11008 83 -> 54, q|k|v 84 -> 40, gate|up 67 -> 58; 1024 tokens of width 1024: out 15 -> 6.6, down
+// 27 -> 12, q|k|v 27 -> 14; 1980 tokens of width 4096: out 73 -> 65, down 174 -> 152.
+// PAIRED (5 stages): loads go out for two K-steps at a time, every other step, both halves of a 256-byte row segment one
+// behind the other, where a row's next 128 bytes otherwise follow a whole step later: 128 x 128 tiles over K = 11008, 576
+// tokens 94 -> 87 us, 1024 tokens 111 -> 99; the smaller tiles, which keep fewer bytes in flight, lose by it.
+template <int BM, int BN, int WGM, int WGN, int NS, int EPI, bool PAIRED>
+__global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g) {
+    constexpr int NW = WGM * WGN, TM = BM / WGM, TN = BN / WGN, MB = TM / 32, NB = TN / 32;
+    constexpr int RB = 128;                                             // bytes of a tile row
+    constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW, LPS = LA + LB;    // loads of a wavefront per stage
+    constexpr int STAGE = (BM + BN) * RB;
+    static_assert(BM % (8 * NW) == 0 && BN % (8 * NW) == 0, "whole loads per wavefront");
+    static_assert(EPI != EPI_SWIGLU || (NB % 2 == 0 && (TN / 2) % (8 * NW) == 0), "a load never straddles gate and up");
+    static_assert((NS - 2) * LPS < 64 && NS >= 3, "the wait counts loads in 6 bits");
+    static_assert(!PAIRED || NS == 5, "two pairs and the step between them");
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // NS stages of [BM + BN][RB]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WGN, wn = wave % WGN, l32 = lane & 31, lh = lane >> 5;
+    // one tile per workgroup; tiles to XCDs as in k_gemm_bf16 (the grid is a multiple of 8)
+    constexpr int GW = 8;
+    const int tiles_m = (g.M + BM - 1) / BM, total = tiles_m * g.tiles_n, chunk = (total + 7) / 8;
+    const int loc = blockIdx.x >> 3, t = (blockIdx.x & 7) * chunk + loc;
+    if (loc >= chunk || t >= total) return;                             // uniform over the workgroup, before any barrier
+    const int grp = t / (tiles_m * GW), rem = t - grp * tiles_m * GW;
+    const int gw = g.tiles_n - grp * GW < GW ? g.tiles_n - grp * GW : GW;
+    const int tile_n = grp * GW + rem % gw, m0 = (rem / gw) * BM, n0 = tile_n * BN;
+
+    // Operand addresses: a descriptor at the tile's first row, a lane offset per load (its row, clamped to the matrix, and
+    // the chunk that belongs at its position), the K-step as scalar offset.
+    const int lrow = lane >> 3, lch = lane & 7;
+    auto row_key = [](int r) { return (r >> 1) & 7; };
+    uint32_t va[LA], vb[LB];
+    const rsrc_t rA = make_rsrc(g.A + (int64_t)m0 * g.K, 0x7fffffff);
+    rsrc_t rW[2];
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+        const int r = (i * NW + wave) * 8 + lrow, rc = m0 + r < g.M ? r : g.M - 1 - m0;
+        va[i] = (uint32_t)(rc * g.K + (lch ^ row_key(r)) * 8) * 2u;
+    }
+    {
+        int which;
+        const int base = b_row_src<EPI, BN, TN>(g, n0, tile_n, 0, which);
+        const bf16* w0 = which == 0 ? g.W0 : which == 1 ? g.W1 : g.W2;
+        rW[0] = make_rsrc(w0 + (int64_t)base * g.K, 0x7fffffff);
+        rW[1] = make_rsrc((EPI == EPI_SWIGLU ? g.W1 : w0) + (int64_t)base * g.K, 0x7fffffff);
+#pragma unroll
+        for (int i = 0; i < LB; ++i) {
+            const int r = (i * NW + wave) * 8 + lrow;
+            const int rs = b_row_src<EPI, BN, TN>(g, n0, tile_n, r, which) - base;
+            vb[i] = (uint32_t)(rs * g.K + (lch ^ row_key(r)) * 8) * 2u;
+        }
+    }
+    typedef __attribute__((address_space(3))) void lds_void;
+    auto load = [&](auto ic, int kt, int slot) {   // load i of this wavefront for K-step kt
+        constexpr int i = decltype(ic)::value;
+        unsigned char* st = smem + slot * STAGE;
+        if constexpr (i < LA) {
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, (lds_void*)(st + (i * NW + wave) * 1024), 16, (int)va[i], kt * RB, 0, 0);
+        } else {
+            constexpr int j = i - LA;
+            constexpr int w = EPI == EPI_SWIGLU ? ((j * NW * 8) % TN >= TN / 2 ? 1 : 0) : 0;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rW[w], (lds_void*)(st + BM * RB + (j * NW + wave) * 1024), 16, (int)vb[j], kt * RB, 0, 0);
+        }
+    };
+    const int nk = g.K / 64;
+    f32x16 acc[MB][NB];
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    int ka[4], kb[4];   // this lane's fragment of slice kk in row block 0: chunk 4 lh + kk
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        const int c = lh * 4 + kk;
+        ka[kk] = (wm * TM + l32) * RB + (c ^ row_key(l32)) * 16;
+        kb[kk] = BM * RB + (wn * TN + kperm(l32)) * RB + (c ^ row_key(kperm(l32))) * 16;
+    }
+    bf16x8 af[2][MB], bfr[2][NB];
+    auto lfrag = [&](const unsigned char* st, int kk, int slot) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i) af[slot][i] = *reinterpret_cast<const bf16x8*>(st + ka[kk] + i * 32 * RB);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) bfr[slot][j] = *reinterpret_cast<const bf16x8*>(st + kb[kk] + j * 32 * RB);
+    };
+    auto mm = [&](int slot) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) acc[i][j] = mma(af[slot][i], bfr[slot][j], acc[i][j]);
+    };
+    // One K-step, rotated by one slice as in k_gemm_bf16: the MFMAs of the step before's last slice run while the first
+    // fragments are on their way.  more: load step kt + NS - 1 into the slot of step kt - 1 (PAIRED: steps kt + 3 and
+    // kt + 4 into the slots of kt - 2 and kt - 1; a step past the end is the last one again, into a slot nobody reads);
+    // first: nothing is pending.
+    auto step = [&](int slot, int kt, auto more, auto first) {
+        const unsigned char* st = smem + slot * STAGE;
+        static_for<4>([&](auto kc) {
+            constexpr int kk = decltype(kc)::value;
+            lfrag(st, kk, kk & 1);
+            if constexpr (decltype(more)::value) {
+                constexpr int lo = kk * LPS / 4, hi = (kk + 1) * LPS / 4;
+                static_for<hi - lo>([&](auto ic) {
+                    constexpr std::integral_constant<int, lo + decltype(ic)::value> i;
+                    if constexpr (PAIRED) load(i, kt + 3, slot >= 2 ? slot - 2 : slot + 3);
+                    load(i, PAIRED && kt + 4 >= nk ? nk - 1 : kt + NS - 1, slot == 0 ? NS - 1 : slot - 1);
+                });
+            }
+            if constexpr (!(kk == 0 && decltype(first)::value)) mm((kk + 1) & 1);
+        });
+        // per slice: its fragment reads first (left alone, the scheduler puts the pending MFMAs in front of them), then
+        // the MFMAs of the slice before with the loads in between
+        if constexpr (!decltype(first)::value) static_for<4>([&](auto kc) {
+            constexpr int kk = decltype(kc)::value, per = PAIRED ? 2 : 1;
+            constexpr int nl = decltype(more)::value ? ((kk + 1) * LPS / 4 - kk * LPS / 4) * per : 0, nm = MB * NB;
+            __builtin_amdgcn_sched_group_barrier(0x100, MB + NB, 0);
+            static_for<nm>([&](auto mc) {
+                constexpr int m = decltype(mc)::value, n = (m + 1) * nl / nm - m * nl / nm;
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if constexpr (n > 0) __builtin_amdgcn_sched_group_barrier(0x010, n, 0);
+            });
+        });
+    };
+    // wait until this wavefront's share of the next stage has landed (at most `younger` loads in flight; < 0: it has
+    // already) and its fragment reads are done, then meet the others
+    auto sync = [&](auto younger) {
+        constexpr int n = decltype(younger)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (n >= 0) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(n) : "memory");
+        else asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    constexpr std::true_type yes;
+    constexpr std::false_type no;
+    constexpr std::integral_constant<int, 0> none_in_flight;
+    int kt = 0, slot = 0;
+    auto next = [&]() { ++kt; slot = slot + 1 == NS ? 0 : slot + 1; };
+    if constexpr (PAIRED) {
+        static_for<LPS>([&](auto ic) { load(ic, 0, 0); load(ic, 1, 1); });   // K >= 128: both steps exist
+        if (nk > 2) static_for<LPS>([&](auto ic) { load(ic, 2, 2); load(ic, nk > 3 ? 3 : 2, 3); });
+        constexpr std::integral_constant<int, 2 * LPS> next_pair;
+        constexpr std::integral_constant<int, -1> landed;                    // an odd step landed with the one before
+        if (nk > 2) sync(next_pair);
+        else sync(none_in_flight);
+        step(slot, kt, no, yes);
+        next();
+        while (kt + 3 < nk) {                                                // no branch inside: the accumulators would be copied
+            sync(landed);
+            step(slot, kt, yes, no);
+            next();
+            sync(next_pair);
+            step(slot, kt, no, no);
+            next();
+        }
+        sync(landed);                                                        // the last one to three steps
+        step(slot, kt, no, no);
+        next();
+        if (kt < nk) {
+            sync(none_in_flight);
+            step(slot, kt, no, no);
+            next();
+            if (kt < nk) {
+                sync(landed);
+                step(slot, kt, no, no);
+            }
+        }
+    } else {
+        static_for<NS - 1>([&](auto sc) {
+            constexpr int s = decltype(sc)::value;
+            if (s < nk) static_for<LPS>([&](auto ic) { load(ic, s, s); });
+        });
+        if (nk >= NS) {
+            sync(std::integral_constant<int, (NS - 2) * LPS>{});
+            step(slot, kt, yes, yes);
+            for (next(); kt + NS - 1 < nk; next()) {
+                sync(std::integral_constant<int, (NS - 2) * LPS>{});
+                step(slot, kt, yes, no);
+            }
+            static_for<NS - 1>([&](auto ic) {   // the last NS - 1 stages: nothing more to load
+                sync(std::integral_constant<int, (NS - 2 - decltype(ic)::value) * LPS>{});
+                step(slot, kt, no, no);
+                next();
+            });
+        } else {                                // a short K: everything is in flight already
+            sync(none_in_flight);
+            step(slot, kt, no, yes);
+            for (next(); kt < nk; next()) step(slot, kt, no, no);
+        }
+    }
+    mm(1);
+    epilogue<EPI, BN, TM, TN, MB, NB>(g, acc, m0, n0, tile_n, wm, wn, l32, lh);
+}
+
 
 static int cu_count() {
     static int n = 0;
@@ -588,19 +729,29 @@ static int cu_count() {
     return n;
 }
 
-template <int BM, int BN, int WGM, int WGN, int EPI, int BKT = 64, bool FULL = false>
-void run_gemm(GemmArgs g, int tile_n0, int tiles_n, int blocks_per_cu, hipStream_t st) {
-    auto kern = k_gemm_bf16<BM, BN, WGM, WGN, EPI, BKT, FULL>;
-    const size_t lds = (size_t)2 * (BM + BN) * (BKT + 8) * sizeof(bf16);
+template <int BM, int BN, int WGM, int WGN, int EPI>
+void run_gemm(GemmArgs g, int tile_n0, int tiles_n, hipStream_t st) {
+    auto kern = k_gemm_bf16<BM, BN, WGM, WGN, EPI>;
+    const size_t lds = (size_t)2 * (BM + BN) * (64 + 8) * sizeof(bf16);
     static int attr_state = 0;  // each instantiation is configured once per process
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds, &attr_state)) return;
-    const int tiles_m = (g.M + BM - 1) / BM, total = tiles_m * tiles_n;
-    const int resident = cu_count() * blocks_per_cu;
+    const int tiles_m = (g.M + BM - 1) / BM, total = tiles_m * tiles_n, resident = cu_count();
     g.tiles_n = tiles_n;
     g.tile_n0 = tile_n0;
     hipLaunchKernelGGL(kern, dim3(total < resident ? total : resident), dim3(WGM * WGN * 64), lds, st, g);
 }
 
+template <int BM, int BN, int WGM, int WGN, int NS, int EPI, bool PAIRED = false>
+void run_ring(GemmArgs g, hipStream_t st) {
+    auto kern = k_gemm_ring<BM, BN, WGM, WGN, NS, EPI, PAIRED>;
+    const size_t lds = (size_t)NS * (BM + BN) * 128;
+    static int attr_state = 0;
+    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds, &attr_state)) return;
+    g.tiles_n = (g.N + BN - 1) / BN;
+    g.tile_n0 = 0;
+    const int64_t total = (int64_t)((g.M + BM - 1) / BM) * g.tiles_n;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(WGM * WGN * 64), lds, st, g);
+}
 
 // Epilogue of the weight-streaming kernels on two adjacent output columns n, n + 1 of token m (v1: the up sums of
 // gate|up).  The same five fused epilogues as the tiled kernels; a bf16 operand of a following projection is written
@@ -622,7 +773,7 @@ __device__ __forceinline__ void stream_epilogue(const GemmArgs& g, int m, int n,
         const TokPlace pl = place(g.ra, m);
         if (pl.pos < 0) return;   // an unused slot of a scattered launch
         const int dh = g.ra.head_dim, pos = pl.pos;
-        if (EPI == EPI_QK || (EPI == EPI_QKV && n < 2 * g.d)) {
+        if (n < 2 * g.d) {
             const int seg = n / g.d, c = n - seg * g.d;
             const int hd = c / dh, cc = c % dh;
             const float cs = g.ra.cos[(int64_t)pos * (dh / 2) + (cc >> 1)], sn = g.ra.sin[(int64_t)pos * (dh / 2) + (cc >> 1)];
@@ -636,12 +787,12 @@ __device__ __forceinline__ void stream_epilogue(const GemmArgs& g, int m, int n,
             dst[0] = __float2bfloat16(v0[0] * cs - v0[1] * sn);
             dst[1] = __float2bfloat16(v0[0] * sn + v0[1] * cs);
         } else {   // V: transposed cache
-            const int nv = EPI == EPI_QKV ? n - 2 * g.d : n, nlim = EPI == EPI_QKV ? g.d : g.N;
+            const int nv = n - 2 * g.d;
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 const int hd = (nv + e) / dh, cc = (nv + e) % dh;
                 const int64_t hb = ((int64_t)g.ra.layer * g.ra.max_batch + pl.bc) * g.ra.n_heads + hd;
-                if (nv + e < nlim) g.vc[(hb * dh + cc) * g.ra.max_seq + pos] = __float2bfloat16(v0[e]);
+                if (nv + e < g.d) g.vc[(hb * dh + cc) * g.ra.max_seq + pos] = __float2bfloat16(v0[e]);
             }
         }
     }
@@ -689,7 +840,7 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
     if constexpr (WFRAG) {
         int blk = blockIdx.x;   // 16-row block inside its matrix
         const bf16* base = g.W0;
-        if constexpr (EPI == EPI_QK || EPI == EPI_QKV) {
+        if constexpr (EPI == EPI_QKV) {
             const int seg = n_blk / g.d;
             base = seg == 0 ? g.W0 : seg == 1 ? g.W1 : g.W2;
             blk -= seg * (g.d / 16);
@@ -698,7 +849,7 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
         if constexpr (EPI == EPI_SWIGLU) w[1] = g.W1 + (int64_t)blk * steps * 512 + lane * 8;
     } else {
         int r = n_blk + lrow;
-        if constexpr (EPI == EPI_QK || EPI == EPI_QKV) {
+        if constexpr (EPI == EPI_QKV) {
             const int seg = n_blk / g.d;                       // a block never straddles q | k | v (d % 16 == 0)
             w[0] = (seg == 0 ? g.W0 : seg == 1 ? g.W1 : g.W2) + (int64_t)(r - seg * g.d) * g.K;
         } else if constexpr (EPI == EPI_SWIGLU) {
@@ -943,7 +1094,7 @@ __global__ __launch_bounds__(256) void k_stream_finish(const GemmArgs g, int nco
 
 template <int EPI>
 void run_gemv_shared(GemmArgs g, hipStream_t st) {
-    const int ncols = g.N, seg_rows = (EPI == EPI_QKV || EPI == EPI_QK) ? g.d : EPI == EPI_SWIGLU ? g.N / 2 : g.N;
+    const int ncols = g.N, seg_rows = EPI == EPI_QKV ? g.d : EPI == EPI_SWIGLU ? g.N / 2 : g.N;
     const int ncg = (ncols + 127) / 128;
     g.ksplit = stream_ksplit(ncols, g.K);
     const dim3 grid(ncg * g.ksplit);
@@ -1014,58 +1165,93 @@ __global__ __launch_bounds__(256) void k_pack_weights(const bf16* __restrict__ s
     *reinterpret_cast<u32x4*>(dst + p * 8) = v;
 }
 
-// returns whether the launch ran on the kernels whose wavefront tile is 128 columns wide (whole tiles)
-enum { CLS_STREAM, CLS_BIG, CLS_MID, CLS_SMALL };
-template <int EPI>
-int classify(const GemmArgs& g) {
-    if (g.stream) return CLS_STREAM;   // a handful of tokens: stream the weights (A is in fragment order)
-    // large problems: 256x256 tiles, 8 wavefronts (4x2, 64x128 each, two per SIMD); small: 128x128, 4 wavefronts
-    // (whole tiles only: their operand rows are addressed from scalar bases; a q|k|v tile must not straddle two weights)
-    const bool whole_n = g.N % 256 == 0 && ((EPI == EPI_QK || EPI == EPI_QKV) ? g.d % 256 == 0 : true) &&
-                         (int64_t)g.K * 256 * 2 < (1ll << 31) && (int64_t)g.M * g.K * 2 < (1ll << 31) &&
-                         (int64_t)((EPI == EPI_QK || EPI == EPI_QKV) ? g.d : EPI == EPI_SWIGLU ? g.N / 2 : g.N) * g.K * 2 < (1ll << 31);
-    const bool big = whole_n && g.M >= 1024 && g.M % 256 == 0 &&
-                     (int64_t)(g.M / 256) * (g.N / 256) * 4 >= 3 * (int64_t)cu_count();   // enough 256x256 tiles to fill the chip
-    if (big) return CLS_BIG;
-    // a few hundred tokens (any count: rows past M read as zeros through the descriptor and are not stored): the
-    // pipelined kernel on 128x256 tiles where their rounds are at least 80 % full (gate|up at 576 tokens: 430 tiles,
-    // +10 %; the lm-head's 320 tiles would leave the second round three quarters empty and lose 14 %)
-    const int64_t mid_tiles = (int64_t)((g.M + 127) / 128) * (g.N / 256), cus64 = cu_count();
-    const bool mid = whole_n && g.M >= 256 && mid_tiles * 5 >= ((mid_tiles + cus64 - 1) / cus64) * cus64 * 4;
-    return mid ? CLS_MID : CLS_SMALL;
+// ---- which tile a launch runs on ----
+// Every tile adds the same products in the same order, so the choice is about time alone.  Time of a launch of T tiles on
+// S = (workgroups per CU) x CUs places: c0 + e per round + (K / 64) x (tf per full round; a last round of r tiles between
+// t0, where few CUs fetch, and tf: t0 + (tf - t0) r / S).  The constants (us) are the least-squares fit over 18 token
+// counts from 72 to 4096 and the ten projection shapes of the two bf16 configurations (widths 1024 and 4096), cold
+// weights: rms error 9 to 13 %; over that grid the tile it picks takes 2 % longer than the best of each shape, and 1.40
+// times less than the rule before it (256 x 256 tiles from 1024 tokens in whole tiles on, 128 x 256 where their rounds
+// were 80 % full, else 128 x 128 staged through registers).
+struct TileCost { int bm, bn, per_cu; float c0, tf, t0, e; };
+enum { TILE_32x64, TILE_64x64, TILE_128x64, TILE_64x128, TILE_128x128, TILE_256x128, TILE_128x256, TILE_256x256, N_TILES };
+constexpr TileCost TILE_COST[N_TILES] = {
+    {32, 64, 3, 3.3f, 0.480f, 0.095f, -0.3f},   {64, 64, 2, 2.7f, 0.435f, 0.146f, 0.1f},
+    {128, 64, 2, 2.3f, 0.683f, 0.271f, 1.2f},   {64, 128, 2, 4.2f, 0.723f, 0.311f, -1.1f},
+    {128, 128, 1, 2.7f, 0.538f, 0.407f, 2.4f},  {256, 128, 1, 2.6f, 0.856f, 0.56f, 4.6f},
+    {128, 256, 1, 3.9f, 0.925f, 0.67f, 2.6f},   {256, 256, 1, 6.7f, 1.544f, 1.011f, 4.4f}};
+
+// Column tiles of a 256 x 256 launch that run as such: a last round that would leave more than half of the CUs idle is
+// cut off and runs as 128 x 256 tiles (twice as many workgroups, half the work each).
+inline int whole_columns(const GemmArgs& g) {
+    const int tiles_m = (g.M + 255) / 256, tiles_n = g.N / 256, cus = cu_count(), total = tiles_m * tiles_n, rem = total % cus;
+    int n = tiles_n;
+    if (total > cus && rem > 0 && 2 * rem <= cus) n = (total - rem) / tiles_m;
+    return (tiles_n - n) * tiles_m * 2 > cus ? tiles_n : n;   // the cut-off part must fit one round
 }
 
 template <int EPI>
-bool dispatch(const GemmArgs& g, hipStream_t st) {
-    const int cls = classify<EPI>(g);
-    if (cls == CLS_STREAM) {
-        run_gemv<EPI>(g, st);
+int choose_tile(const GemmArgs& g) {
+    const int seg = EPI == EPI_QKV ? g.d : g.N;                       // a tile must not straddle two of q | k | v
+    const bool whole256 = g.N % 256 == 0 && seg % 256 == 0 && (int64_t)g.M * g.K * 2 < (1ll << 31) &&   // 32-bit offsets
+                          weight_rows<EPI>(g) * g.K * 2 < (1ll << 31);
+    int best = -1;
+    float best_us = 0.f;
+    for (int i = 0; i < N_TILES; ++i) {
+        const TileCost& t = TILE_COST[i];
+        if (i == TILE_256x256 && !whole256) continue;
+        if (EPI == EPI_QKV && seg % t.bn) continue;
+        if (EPI == EPI_SWIGLU ? (i == TILE_32x64 || i == TILE_64x64 || i == TILE_128x64) : i == TILE_64x128) continue;
+        const int64_t places = (int64_t)t.per_cu * cu_count();
+        int64_t tiles = (int64_t)((g.M + t.bm - 1) / t.bm) * ((g.N + t.bn - 1) / t.bn);
+        float us = t.c0;
+        if (i == TILE_256x256) {                                        // the cut-off columns are half a tile's time
+            const int64_t whole = (int64_t)((g.M + 255) / 256) * whole_columns(g);
+            if (whole < tiles) us += 0.5f * (t.e + t.tf * (g.K / 64));
+            tiles = whole;
+        }
+        const int64_t full = tiles / places, r = tiles % places;
+        const float part = r ? t.t0 + (t.tf - t.t0) * ((float)r / (float)places) : 0.f;
+        us += t.e * (float)(full + (r > 0)) + (float)(g.K / 64) * (t.tf * (float)full + part);
+        // softmax parts come from wavefront tiles of 128 columns only; without them the accept test reads the logits
+        if (EPI == EPI_LOGITS && g.parts && !(t.bn == 256 && g.N % 256 == 0)) us += (float)g.M * (float)g.N * 4.f / 5e6f;
+        if (best < 0 || us < best_us) { best = i; best_us = us; }
+    }
+    return best;
+}
+
+// returns whether the softmax parts were written (LOGITS, wavefront tiles of 128 whole columns)
+template <int EPI>
+bool dispatch(const GemmArgs& g0, hipStream_t st) {
+    if (g0.stream) {   // a handful of tokens: stream the weights (A is in fragment order)
+        run_gemv<EPI>(g0, st);
         return false;
     }
-    const bool mid = cls == CLS_MID, big = cls == CLS_BIG;
-    const int64_t cus64 = cu_count();
-    if (mid) {
-        run_gemm<128, 256, 4, 2, EPI, 64, true>(g, 0, g.N / 256, 1, st);
-    } else if (big) {
-        // Whole rounds of 256x256 tiles, one tile per CU and round.  A last round that would leave more than
-        // half of the CUs idle is cut off and run as 128x256 tiles (twice as many workgroups, half the work each).
-        const int tiles_m = g.M / 256, tiles_n = g.N / 256, cus = cu_count();
-        const int total = tiles_m * tiles_n, rem = total % cus;
-        int n_main = tiles_n;
-        if (total > cus && rem > 0 && 2 * rem <= cus) n_main = (total - rem) / tiles_m;
-        if ((tiles_n - n_main) * tiles_m * 2 > cus) n_main = tiles_n;   // the cut-off part must fit one round
-        run_gemm<256, 256, 4, 2, EPI, 64, true>(g, 0, n_main, 1, st);
-        if (n_main < tiles_n) run_gemm<128, 256, 4, 2, EPI, 64, true>(g, n_main, tiles_n - n_main, 1, st);
-    } else {
-        // One round of tiles (a few hundred tokens: the paper's batch-1 setting) leaves one workgroup per CU, and a
-        // K-step then costs its fixed chain of latencies whatever its depth: 128-deep steps halve their number
-        // (out and down projections at 576 tokens: +16 %).  The sums are the same bits (see the k deal above).
-        const int64_t small_tiles = (int64_t)((g.M + 127) / 128) * ((g.N + 127) / 128);
-        if (g.K % 128 == 0 && g.K >= 256 && small_tiles <= cus64) run_gemm<128, 128, 2, 2, EPI, 128>(g, 0, (g.N + 127) / 128, 1, st);
-        else run_gemm<128, 128, 2, 2, EPI>(g, 0, (g.N + 127) / 128, 2, st);
-        return false;
+    GemmArgs g = g0;
+    const int tile = choose_tile<EPI>(g);
+    const bool parts = EPI == EPI_LOGITS && g.parts && TILE_COST[tile].bn == 256 && g.N % 256 == 0;
+    if (!parts) g.parts = nullptr;
+    switch (tile) {
+        case TILE_32x64: if constexpr (EPI != EPI_SWIGLU) run_ring<32, 64, 1, 2, 6, EPI>(g, st); break;
+        case TILE_64x64: if constexpr (EPI != EPI_SWIGLU) run_ring<64, 64, 2, 2, 5, EPI>(g, st); break;
+        case TILE_128x64: if constexpr (EPI != EPI_SWIGLU) run_ring<128, 64, 2, 2, 3, EPI>(g, st); break;
+        case TILE_64x128: if constexpr (EPI == EPI_SWIGLU) run_ring<64, 128, 2, 2, 3, EPI>(g, st); break;
+        case TILE_128x128: run_ring<128, 128, 2, 2, 5, EPI, true>(g, st); break;
+        case TILE_256x128:   // 4 wavefronts of 128 x 64 (1980 x 4096 x 11008: 152 us against 157 with 8 of 64 x 64), q|k|v and lm-head 8
+            if constexpr (EPI == EPI_SWIGLU || EPI == EPI_RESID) run_ring<256, 128, 2, 2, 3, EPI>(g, st);
+            else run_ring<256, 128, 4, 2, 3, EPI>(g, st);
+            break;
+        case TILE_128x256:
+            if constexpr (EPI == EPI_SWIGLU || EPI == EPI_LOGITS) run_ring<128, 256, 2, 2, 3, EPI>(g, st);
+            else run_ring<128, 256, 2, 4, 3, EPI>(g, st);
+            break;
+        default: {
+            const int tiles_n = g.N / 256, n_main = whole_columns(g);
+            run_gemm<256, 256, 4, 2, EPI>(g, 0, n_main, st);
+            if (n_main < tiles_n) run_gemm<128, 256, 4, 2, EPI>(g, n_main, tiles_n - n_main, st);
+        }
     }
-    return true;
+    return parts;
 }
 
 }  // namespace
@@ -1075,26 +1261,9 @@ void launch_gemm_qkv_bf16(const void* xh, const void* wq, const void* wk, const 
     GemmArgs g{};
     g.stream = sm.stream; g.w_frag = sm.w_frag; g.ksums = sm.ksums;
     g.A = (const bf16*)xh; g.W0 = (const bf16*)wq; g.W1 = (const bf16*)wk;
-    g.M = M; g.N = 2 * d; g.K = d; g.Cb = (bf16*)q_out; g.kc = (bf16*)k_cache; g.d = d; g.ra = ra;
-    if (g.stream) {   // a handful of tokens: q | k | v stream through one launch (xh is in fragment order)
-        g.W2 = (const bf16*)wv; g.vc = (bf16*)v_cache; g.N = 3 * d;
-        run_gemv<EPI_QKV>(g, st);
-        return;
-    }
-    // a few hundred tokens: q | k | v as ONE problem where its 128x256 tiles fill a round (576 tokens: 240 tiles in one
-    // round instead of 320 + 160 on smaller tiles); the same sums, element for element
-    {
-        GemmArgs m3 = g;
-        m3.W2 = (const bf16*)wv; m3.vc = (bf16*)v_cache; m3.N = 3 * d;
-        if (classify<EPI_QKV>(m3) == CLS_MID) {
-            dispatch<EPI_QKV>(m3, st);
-            return;
-        }
-    }
-    dispatch<EPI_QK>(g, st);
-    GemmArgs v{};
-    v.A = (const bf16*)xh; v.W0 = (const bf16*)wv; v.M = M; v.N = d; v.K = d; v.vc = (bf16*)v_cache; v.ra = ra;
-    dispatch<EPI_V>(v, st);
+    g.M = M; g.N = 3 * d; g.K = d; g.Cb = (bf16*)q_out; g.kc = (bf16*)k_cache; g.d = d; g.ra = ra;
+    g.W2 = (const bf16*)wv; g.vc = (bf16*)v_cache;
+    dispatch<EPI_QKV>(g, st);
 }
 
 void launch_gemm_resid_bf16(const void* a, const void* w, float* x, int M, int N, int K, const StreamMode& sm, hipStream_t st) {

@@ -95,6 +95,41 @@ def test_forward_f32_shapes(nh, dh, f, V, B, L, P):
     assert err <= 1e-4
 
 
+@pytest.mark.parametrize("d,nh,f,V", [
+    (768, 6, 8256, 1092),    # gate | up on every tile it has; K of 129 steps for down, a ragged last column tile for the lm-head
+    (768, 6, 704, 16384),    # the lm-head on every tile; K of 11 steps
+    (1024, 16, 2112, 1092),  # down on 128 x 128 tiles at the largest launch; K of 33 steps
+    (128, 2, 192, 260),      # K of 2 and 3 steps, fewer than the ring has stages
+])
+def test_every_tile_gives_the_same_sums(d, nh, f, V):
+    """The projections of a launch run on the tile its sizes ask for; every tile adds the same products in the same order.
+    One sequence alone (161 tokens, checked against the oracle) and as the first and last of launches of up to 2576
+    tokens (each projection changes its tile two to five times on the way; no count is a multiple of a tile): the same
+    logits and cache rows, bit for bit."""
+    m = dict(n_layers=1, d_model=d, n_heads=nh, head_dim=d // nh, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
+    L, P, S, Bmax = 161, 5, 168, 16
+    w = G.make_weights(m, seed=21)
+    ctx, cos, sin = make_ctx(m, w, Bmax, S, 164)
+    kv = mulo.alloc_kv(ctx, DEV)
+    dr, du = pair(m, w, cos, sin, 1, S)
+    pre, blk = G.uniform_tokens((1, P), V, 21, tag=0), G.uniform_tokens((1, L), V, 21, tag=1)
+    for t in (dr, du):
+        t.forward(pre, 0)
+    gpu_forward(ctx, kv, pre, 0)
+    for t in kv:                      # every sequence behind the same prefix rows (a prefix launch of its own would stream or not)
+        t[:, 1:].copy_(t[:, :1].expand_as(t[:, 1:]))
+    one = gpu_forward(ctx, kv, blk, P)
+    check_bf16_logits("161 tokens alone, width %d" % d, one, dr.forward(blk, P).numpy(), du.forward(blk, P).numpy())
+    k1, v1 = kv[0][0, 0, :, P:P + L].clone(), kv[1][0, 0, :, :, P:P + L].clone()
+    for B in (2, 5, 8, 13, 16):
+        many = G.uniform_tokens((B, L), V, 21, tag=2)
+        many[0] = many[-1] = blk[0]
+        z = gpu_forward(ctx, kv, many, P)
+        for b in (0, B - 1):
+            assert np.array_equal(z[b], one[0]), (B, b)
+            assert torch.equal(kv[0][0, b, :, P:P + L], k1) and torch.equal(kv[1][0, b, :, :, P:P + L], v1), (B, b)
+
+
 def test_forward_small_bf16_chained_blocks():
     c = WC.get("cfg2")
     m, B, L, Pn = c["model"], c["B"], c["L"], c["prefix"]
