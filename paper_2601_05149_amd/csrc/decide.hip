@@ -351,14 +351,15 @@ __global__ __launch_bounds__(TPB) void k_accept_parts(const DecideArgs a, const 
 // rejected positions and near ties, then R_X: position t is marked when it is at or after t0 and within Chebyshev
 // distance rho of some rejected position of the block (rho < 0: the raster rule, everything from t0 on).  Writes
 // mask, t0 and stats = (accepted, rejected, marked, near ties); no atomics on global memory anywhere.
-__global__ __launch_bounds__(TPB) void k_decide_finish(const DecideArgs a) {
+// A chain of latencies, so a position per thread up to blocks of 1024 (4 x 1024: 256 threads 7.5 us, 1024 6.4).
+__global__ __launch_bounds__(1024) void k_decide_finish(const DecideArgs a) {
     extern __shared__ uint8_t acc_s[];   // [L]
-    __shared__ int red[WAVES][4];
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    __shared__ int red[16][4];
+    const int b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wv = tid >> 6;
     const uint8_t* acc_g = a.accept + (int64_t)b * a.L;
     uint8_t* mask_g = a.mask + (int64_t)b * a.L;
     int n_acc = 0, n_near = 0, tmin = a.L;
-    for (int t = tid; t < a.L; t += TPB) {
+    for (int t = tid; t < a.L; t += nt) {
         const uint8_t ok = acc_g[t];
         acc_s[t] = ok;
         n_acc += ok;
@@ -378,7 +379,7 @@ __global__ __launch_bounds__(TPB) void k_decide_finish(const DecideArgs a) {
         __syncthreads();
         x = y = w = 0;
         z_min = a.L;
-        for (int i = 0; i < WAVES; ++i) {
+        for (int i = 0; i < (nt >> 6); ++i) {
             x += red[i][0]; y += red[i][1]; w += red[i][3];
             z_min = red[i][2] < z_min ? red[i][2] : z_min;
         }
@@ -387,7 +388,7 @@ __global__ __launch_bounds__(TPB) void k_decide_finish(const DecideArgs a) {
     reduce_counts(n_acc, n_near, tmin, zero);   // the barriers inside also publish acc_s and retire the reads of mask_g
     const int t0 = tmin;
     int n_marked = 0;
-    for (int t = tid; t < a.L; t += TPB) {
+    for (int t = tid; t < a.L; t += nt) {
         int marked = 0;
         if (t >= t0) {
             if (a.rho < 0) {
@@ -662,65 +663,105 @@ __global__ __launch_bounds__(TPB) void k_island_draw(const float* __restrict__ l
 }
 
 // ---- rejection islands (Eq. 8): 8-connected components of the marked set, one workgroup per sequence ----
-// Labels live in LDS (one int per block position: 0 = unmarked, else 1 + a member's position).  Every round
-// a marked position takes the smallest label among itself and its 8 grid neighbours and then jumps to the
-// label of the position that label names (pointer jumping), until a round changes nothing: each island ends
-// with 1 + its smallest position.  The rank of a position is the number of members of its island before it.
-__global__ __launch_bounds__(TPB) void k_islands(const uint8_t* __restrict__ mask, int32_t* __restrict__ island,
-                                                 int32_t* __restrict__ rank, int32_t* __restrict__ counts, int W,
-                                                 int n0, int L) {
-    extern __shared__ int lab[];
-    const int b = blockIdx.x, tid = threadIdx.x;
+// Latency is all there is here (a block of labels, no memory traffic), so every phase is a constant number of passes
+// with one position per thread, whatever the shape of the islands:
+//   union-find in LDS: lab[t] names a marked position of t's island that is not after t (unmarked: -1); a position is
+//     linked to its earlier neighbours (left and the three above) by atomicMin on the larger root, so an island's root
+//     is its smallest position; every find descends strictly, so every loop ends;
+//   members per (segment of the block, island) by atomics, their prefix over the segments, islands and largest island;
+//   ranks: a wavefront per segment walks its 64-position chunks in order; a ballot per island present in the chunk
+//     ranks its members, a counter per (segment, island) carries on to the next chunk.
+// 2 sequences of 1024 positions, nearly all marked: 97 us with min-label rounds and a scan of the island per position,
+// now 6 us.
+constexpr int ISL_TPB = 1024;
+constexpr int ISL_LDS = 160 * 1024 - 256;
+__global__ __launch_bounds__(ISL_TPB) void k_islands(const uint8_t* __restrict__ mask, int32_t* __restrict__ island,
+                                                     int32_t* __restrict__ rank, int32_t* __restrict__ counts, int W,
+                                                     int n0, int L, int segs) {
+    extern __shared__ int lab[];   // [L]
+    int* const cnt = lab + L;      // [segs][L], by root
+    __shared__ int n_isl, largest;
+    const int b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wv = tid >> 6;
     const uint8_t* mk = mask + (int64_t)b * L;
-    for (int t = tid; t < L; t += TPB) lab[t] = mk[t] ? t + 1 : 0;
+    const int seg_len = ((L + segs - 1) / segs + 63) / 64 * 64;
+    if (tid == 0) n_isl = largest = 0;
+    for (int t = tid; t < L; t += nt) lab[t] = mk[t] ? t : -1;
+    for (int i = tid; i < segs * L; i += nt) cnt[i] = 0;
     __syncthreads();
-    while (true) {
-        int changed = 0;
-        for (int t = tid; t < L; t += TPB) {
-            int cur = lab[t];
-            if (!cur) continue;
-            const int g = n0 + t, i = g / W, j = g % W;
-            int best = cur;
-#pragma unroll
-            for (int di = -1; di <= 1; ++di)
-#pragma unroll
-                for (int dj = -1; dj <= 1; ++dj) {
-                    const int jj = j + dj, u = (i + di) * W + jj - n0;
-                    if (jj >= 0 && jj < W && u >= 0 && u < L) {
-                        const int v = lab[u];
-                        if (v && v < best) best = v;
-                    }
-                }
-            const int hop = lab[best - 1];       // the named position is marked, so its label is > 0
-            if (hop < best) best = hop;
-            if (best < cur) { atomicMin(&lab[t], best); changed = 1; }
+    volatile int* const vl = lab;
+    auto find = [&](int x) {   // halves the path on its way: a position that is no root keeps being none, any ancestor will do for it
+        for (int p = vl[x]; p != x; p = vl[x]) {
+            const int q = vl[p];
+            if (q != p) vl[x] = q;
+            x = q;
         }
-        if (!__syncthreads_or(changed)) break;
-    }
-    int n_isl = 0, largest = 0;
-    for (int t = tid; t < L; t += TPB) {
-        const int l = lab[t];
-        int r = -1;
-        if (l) {
-            r = 0;
-            for (int u = l - 1; u < t; ++u) r += lab[u] == l;
-            if (l == t + 1) {                     // the island's first member counts the island and measures it
-                ++n_isl;
-                int sz = 0;
-                for (int u = t; u < L; ++u) sz += lab[u] == l;
-                largest = sz > largest ? sz : largest;
+        return x;
+    };
+    auto unite = [&](int x, int y) {
+        while (true) {
+            x = find(x);
+            y = find(y);
+            if (x == y) return;
+            if (x < y) { const int z = x; x = y; y = z; }
+            const int old = atomicMin(&lab[x], y);
+            if (old == x) return;   // x was still a root
+            x = old;
+        }
+    };
+    for (int t = tid; t < L; t += nt) {
+        if (vl[t] < 0) continue;
+        const int j = (n0 + t) % W;   // the block is whole rows of the grid
+        if (j > 0 && vl[t - 1] >= 0) unite(t, t - 1);
+        if (t >= W) {
+            if (vl[t - W] >= 0) {
+                unite(t, t - W);      // the other two above are its neighbours
+            } else {
+                if (j > 0 && vl[t - W - 1] >= 0) unite(t, t - W - 1);
+                if (j < W - 1 && vl[t - W + 1] >= 0) unite(t, t - W + 1);
             }
         }
-        island[(int64_t)b * L + t] = l;
-        rank[(int64_t)b * L + t] = r;
     }
-    __shared__ int red_n, red_m;
-    if (tid == 0) { red_n = 0; red_m = 0; }
     __syncthreads();
-    if (n_isl) atomicAdd(&red_n, n_isl);
-    if (largest) atomicMax(&red_m, largest);
+    for (int t = tid; t < L; t += nt)
+        if (vl[t] >= 0) {
+            int r = t;
+            for (int p = vl[r]; p != r; p = vl[r]) r = p;   // reads only: a path halved here could undo another thread's vl[t] = r
+            vl[t] = r;
+            atomicAdd(&cnt[(t / seg_len) * L + r], 1);
+        }
     __syncthreads();
-    if (tid == 0) { counts[b * 2] = red_n; counts[b * 2 + 1] = red_m; }
+    for (int t = tid; t < L; t += nt)
+        if (lab[t] == t) {   // an island's root: where each segment's members start, and the island's size
+            int run = 0;
+            for (int s = 0; s < segs; ++s) {
+                const int c = cnt[s * L + t];
+                cnt[s * L + t] = run;
+                run += c;
+            }
+            atomicAdd(&n_isl, 1);
+            atomicMax(&largest, run);
+        }
+    __syncthreads();
+    if (tid == 0) { counts[b * 2] = n_isl; counts[b * 2 + 1] = largest; }
+    if (wv >= segs) return;
+    const int t_end = (wv + 1) * seg_len < L ? (wv + 1) * seg_len : L;
+    for (int t0 = wv * seg_len; t0 < t_end; t0 += 64) {
+        const int t = t0 + lane, l = t < t_end ? lab[t] : -1;
+        int r = -1;
+        for (unsigned long long left = __ballot(l >= 0); left;) {
+            const int lead = __ffsll((long long)left) - 1, ll = __builtin_amdgcn_readlane(l, lead);
+            const unsigned long long m = __ballot(l == ll);
+            volatile int* const c = cnt + wv * L + ll;   // another lane may have written it
+            const int base = *c;
+            if (l == ll) r = base + __popcll(m & ((1ull << lane) - 1ull));
+            if (lane == lead) *c = base + __popcll(m);
+            left &= ~m;
+        }
+        if (t < t_end) {
+            island[(int64_t)b * L + t] = l + 1;
+            rank[(int64_t)b * L + t] = r;
+        }
+    }
 }
 
 template <int NV4>
@@ -773,11 +814,20 @@ void launch_shift_inputs(const int32_t* prev, const int32_t* tokens_hi, int32_t*
                        tokens_hi, inputs, B, L);
 }
 
+// one thread per position of a block, whole wavefronts, between `least` and 1024
+static int block_threads(int L, int least) {
+    const int t = L >= 1024 ? 1024 : (L + 63) / 64 * 64;
+    return t < least ? least : t;
+}
+
 void launch_islands(const uint8_t* mask, int32_t* island, int32_t* rank, int32_t* counts, int B, int W, int n0, int L,
-                    hipStream_t st) {   // L <= 16384 (the caller checks): one label per position in LDS
+                    hipStream_t st) {   // L <= 16384 (the caller checks): labels and at least one set of counters in LDS
     static int attr_state = 0;
-    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(k_islands), 16384 * (int)sizeof(int), &attr_state)) return;
-    hipLaunchKernelGGL(k_islands, dim3(B), dim3(TPB), (size_t)L * sizeof(int), st, mask, island, rank, counts, W, n0, L);
+    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(k_islands), ISL_LDS, &attr_state)) return;
+    const int threads = block_threads(L, 64);
+    const int fit = ISL_LDS / ((int)sizeof(int) * L) - 1, segs = fit < threads / 64 ? fit : threads / 64;   // counters [segs][L] next to the labels [L]
+    hipLaunchKernelGGL(k_islands, dim3(B), dim3(threads), (size_t)(1 + segs) * L * sizeof(int), st, mask, island, rank, counts, W, n0,
+                       L, segs);
 }
 
 void launch_seq_input(const int32_t* prev, const int32_t* tokens, int32_t* inp, int B, int L, int u, hipStream_t st) {
@@ -808,7 +858,7 @@ void launch_island_draw(const float* logits, const int32_t* pos_tab, int32_t* to
 void launch_decide_finish(const DecideArgs& a, hipStream_t st) {   // a.L <= 131072 (the caller checks): flags in LDS
     static int attr_state = 0;
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(k_decide_finish), 131072, &attr_state)) return;
-    hipLaunchKernelGGL(k_decide_finish, dim3(a.B), dim3(TPB), (size_t)a.L, st, a);
+    hipLaunchKernelGGL(k_decide_finish, dim3(a.B), dim3(block_threads(a.L, 256)), (size_t)a.L, st, a);
 }
 
 void launch_accept(const DecideArgs& a, hipStream_t st) {
