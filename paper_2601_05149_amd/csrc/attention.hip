@@ -52,7 +52,7 @@ constexpr int NS_TARGET = 512;      // workgroups a key split aims at (measured:
 constexpr int SPLIT_QUERIES = 32;   // a key split serves at most this many queries per (sequence, head)
 
 template <int DH, int BQ, int BKV, int NTH>
-__global__ __launch_bounds__(NTH, NTH <= 256 ? 2 : 1) void k_attn_bf16(const AttnArgs a) {
+__global__ __launch_bounds__(NTH, BKV <= 64 ? 2 : 1) void k_attn_bf16(const AttnArgs a) {
     constexpr int KS = DH + 8;     // K tile row stride (bf16)
     constexpr int VS = BKV + 8;    // V^T tile row stride
     constexpr int NKK = DH / 16;   // k-steps of the first product
@@ -81,7 +81,7 @@ __global__ __launch_bounds__(NTH, NTH <= 256 ? 2 : 1) void k_attn_bf16(const Att
     }
     const int j0 = qt * BQ, hd = bh % a.nh, b = bh / a.nh;
     // scattered queries run in the short-block configuration only; the long-block one keeps its registers
-    const bool scattered = BQ <= 128 && a.pos_tab != nullptr;
+    const bool scattered = BKV == 64 && a.pos_tab != nullptr;
     const int P = a.P;
     const int64_t hb = ((int64_t)a.layer * a.max_batch + b) * a.nh + hd;
     const bf16* kbase = a.kc + hb * a.max_seq * DH;
@@ -183,7 +183,6 @@ __global__ __launch_bounds__(NTH, NTH <= 256 ? 2 : 1) void k_attn_bf16(const Att
 
     // Hidden rows (scattered queries): one flag per lane and 64-key tile (lane i: key 64 t + i), requested a tile
     // ahead and turned into a 64-bit mask by a ballot, instead of a byte load per score behind the score product.
-    static_assert(BQ > 128 || BKV == 64, "a lane holds the hide flag of one key of a 64-key tile");
     auto hide_flag = [&](int tile) -> uint8_t {
         const int tpos = tile * BKV + lane - a.P0;
         const bool in_block = tpos >= 0 && tpos < a.Lblk;
@@ -191,7 +190,7 @@ __global__ __launch_bounds__(NTH, NTH <= 256 ? 2 : 1) void k_attn_bf16(const Att
         return in_block ? f : (uint8_t)0;
     };
     unsigned long long hide_cur = 0;
-    if constexpr (BQ <= 128) {
+    if constexpr (BKV == 64) {
         if (a.hide && wave_live) hide_cur = __ballot(hide_flag(t_begin) != 0);
     }
     gload(t_begin);
@@ -203,7 +202,7 @@ __global__ __launch_bounds__(NTH, NTH <= 256 ? 2 : 1) void k_attn_bf16(const Att
         if (wave_live && (scattered || kv0 <= P + wave_jmax)) {
             gload(t_next);
             uint8_t hide_next = 0;
-            if constexpr (BQ <= 128) {
+            if constexpr (BKV == 64) {
                 if (a.hide) hide_next = hide_flag(t_next);
             }
             const bf16* k = sK + (t & 1) * BKV * KS;
@@ -231,7 +230,7 @@ __global__ __launch_bounds__(NTH, NTH <= 256 ? 2 : 1) void k_attn_bf16(const Att
                         s[kb][r] = key <= qpos ? s[kb][r] : -__builtin_huge_valf();
                     }
             }
-            if constexpr (BQ <= 128) {
+            if constexpr (BKV == 64) {
                 if (a.hide) {   // scattered queries: rows of positions that are not settled yet (the query's own excepted)
                     if (hide_cur != 0) {   // uniform over the wavefront; bits are set for rows of the block only
 #pragma unroll
@@ -330,23 +329,37 @@ __global__ __launch_bounds__(NTH, NTH <= 256 ? 2 : 1) void k_attn_bf16(const Att
 }
 
 // out[b, hd, :] = sum_s o_s 2^(m_s - M) / sum_s l_s 2^(m_s - M), M = max_s m_s (maxima are in exponent units)
-template <int DH>
+// One memory round trip: all NS >= nsplit shares are requested together (a loop that ends at nsplit pays one per share:
+// 11 us for the 16 shares of a single sequence, now 4.7).  Shares past nsplit re-read share 0 and weigh 2^-inf = 0.
+template <int DH, int NS>
 __global__ __launch_bounds__(DH) void k_attn_combine(const AttnArgs a) {
     const int j = blockIdx.x % a.L, hd = (blockIdx.x / a.L) % a.nh, b = blockIdx.x / (a.L * a.nh), c = threadIdx.x;
-    auto share = [&](int s) { return a.part + ((((int64_t)s * a.B + b) * a.nh + hd) * a.L + j) * (DH + 2); };
+    float o[NS], m[NS], l[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const float* p = a.part + ((((int64_t)(s < a.nsplit ? s : 0) * a.B + b) * a.nh + hd) * a.L + j) * (DH + 2);
+        o[s] = p[c];
+        m[s] = p[DH];
+        l[s] = p[DH + 1];
+    }
     float M = -__builtin_huge_valf();
-    for (int s = 0; s < a.nsplit; ++s) M = fmaxf(M, share(s)[DH]);
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        m[s] = s < a.nsplit ? m[s] : -__builtin_huge_valf();
+        M = fmaxf(M, m[s]);
+    }
     float num = 0.f, den = 0.f;
-    for (int s = 0; s < a.nsplit; ++s) {
-        const float* p = share(s);
-        const float wgt = __builtin_amdgcn_exp2f(p[DH] - M);
-        num += p[c] * wgt;
-        den += p[DH + 1] * wgt;
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+        const float wgt = s < a.nsplit ? __builtin_amdgcn_exp2f(m[s] - M) : 0.f;
+        num += o[s] * wgt;
+        den += l[s] * wgt;
     }
     const int row = b * a.L + j;
     a.out[a.frag ? frag_index(row, hd * DH + c, a.nh * DH) : (int64_t)row * (a.nh * DH) + hd * DH + c] =
         __float2bfloat16(den > 0.f ? num / den : 0.f);
 }
+static_assert(MAX_SPLIT == 16, "the combine kernels");
 
 template <int DH, int BQ, int BKV, int NTH>
 void run_attn_cfg(const AttnArgs& a, hipStream_t st) {
@@ -355,16 +368,31 @@ void run_attn_cfg(const AttnArgs& a, hipStream_t st) {
     static int attr_state = 0;
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds, &attr_state)) return;
     hipLaunchKernelGGL(kern, dim3(((a.L + BQ - 1) / BQ) * a.nh * a.B * a.nsplit), dim3(NTH), lds, st, a);
-    if (a.nsplit > 1) hipLaunchKernelGGL(k_attn_combine<DH>, dim3(a.B * a.nh * a.L), dim3(DH), 0, st, a);
+    if (a.nsplit > 1) {
+        const dim3 grid(a.B * a.nh * a.L);
+        if (a.nsplit <= 4) hipLaunchKernelGGL((k_attn_combine<DH, 4>), grid, dim3(DH), 0, st, a);
+        else if (a.nsplit <= 8) hipLaunchKernelGGL((k_attn_combine<DH, 8>), grid, dim3(DH), 0, st, a);
+        else hipLaunchKernelGGL((k_attn_combine<DH, 16>), grid, dim3(DH), 0, st, a);
+    }
 }
 
-// Blocks of more than 128 queries: 256-query workgroups of 8 wavefronts over 128-key tiles (one per CU).  Shorter
-// ones (single-token decoding above all): 128-query workgroups of 4 wavefronts over 64-key tiles, two per CU.
-constexpr int BKV_SMALL = 64;
+// Heads of 128 and blocks of more than LONG_BLOCK queries: 256-query workgroups of 8 wavefronts over 128-key tiles (one per
+// CU).  Everything else (single-token decoding above all): 128-query workgroups of 4 wavefronts over 64-key tiles, two per
+// CU.  The two add in another order, so which one runs depends on the head and the block, never on the batch: a sequence
+// launched alone gets the bits it gets in a batch.  Measured, 256 x 128 keys / 128 x 64 keys, us: heads of 64: 4 x 256
+// queries, 832 keys 23.7 / 18.0, 1 x 1024, 1524 keys 35.2 / 29.4, 2 x 900, 3900 keys 79 / 70, 16 x 1024, 2024 keys 193 / 176,
+// 8 x 300, 1300 keys 33.1 / 34.8; heads of 128: 4 x 256, 3256 keys 104 / 90, 1 x 200, 1100 keys 37 / 32, 3 x 400, 1400 keys
+// 50 / 59, 4 x 1024, 4224 keys 301 / 348.
+constexpr int BKV_SMALL = 64, LONG_BLOCK = 256;
 template <int DH>
 void run_attn(const AttnArgs& a, hipStream_t st) {
-    if (a.L > 128) run_attn_cfg<DH, 256, 128, 512>(a, st);
-    else run_attn_cfg<DH, 128, BKV_SMALL, 256>(a, st);
+    if constexpr (DH == 128) {
+        if (a.L > LONG_BLOCK) {
+            run_attn_cfg<DH, 256, 128, 512>(a, st);
+            return;
+        }
+    }
+    run_attn_cfg<DH, 128, BKV_SMALL, 256>(a, st);
 }
 
 }  // namespace
