@@ -6,6 +6,8 @@
 // 256 lanes owns one row, keeps it in registers (V <= 16384) and reduces over the
 // codebook with wavefront shuffles, so every logit is read from memory once in
 // the accept pass and once more (with the draft row) only for marked positions.
+#include <type_traits>
+
 #include "mulo_internal.h"
 #include "row_parts.h"
 
@@ -235,6 +237,32 @@ __global__ void k_shift_inputs(const int32_t* __restrict__ prev, const int32_t* 
     inp[gid] = j == 0 ? prev[b] : hi[gid - 1];
 }
 
+// One integer weight of the draw, floor(w 2^40), as a double: sums of up to 256 of them (2^49) are exact there, at half
+// the instructions of the conversion to and the addition of 64-bit integers.
+template <bool USE_Q>
+__device__ __forceinline__ double weight(float z, float q, float m, float inv) {
+    float p = prob(z, m, inv);
+    if constexpr (USE_Q) p = fmaxf(0.f, __fsub_rn(p, q));
+    return (double)truncf(__fmul_rn(p, 1099511627776.0f));
+}
+template <bool USE_Q>
+__device__ __forceinline__ double weight_sum4(const float4 z, const float4 q, float m, float inv) {
+    return (weight<USE_Q>(z.x, q.x, m, inv) + weight<USE_Q>(z.y, q.y, m, inv)) +
+           (weight<USE_Q>(z.z, q.z, m, inv) + weight<USE_Q>(z.w, q.w, m, inv));
+}
+// the same as integers, for the walk inside a chunk: floor(w 2^40) of w = max(0, p - q), or of p (use_p)
+__device__ __forceinline__ void weights4(const float4 z, const float4 qv, float m, float inv, bool use_p,
+                                         unsigned long long w[4]) {
+    const float S = 1099511627776.0f;  // 2^40: w * S is exact in float32
+    float p0 = prob(z.x, m, inv), p1 = prob(z.y, m, inv), p2 = prob(z.z, m, inv), p3 = prob(z.w, m, inv);
+    if (!use_p) {
+        p0 = fmaxf(0.f, __fsub_rn(p0, qv.x)); p1 = fmaxf(0.f, __fsub_rn(p1, qv.y));
+        p2 = fmaxf(0.f, __fsub_rn(p2, qv.z)); p3 = fmaxf(0.f, __fsub_rn(p3, qv.w));
+    }
+    w[0] = (unsigned long long)__fmul_rn(p0, S); w[1] = (unsigned long long)__fmul_rn(p1, S);
+    w[2] = (unsigned long long)__fmul_rn(p2, S); w[3] = (unsigned long long)__fmul_rn(p3, S);
+}
+
 // ---- Step 4: softmax statistics + accept test, one workgroup per position ---
 __device__ __forceinline__ int clamp_tok(int t, int V) { return t < 0 ? 0 : (t >= V ? V - 1 : t); }
 
@@ -242,7 +270,7 @@ __device__ __forceinline__ int clamp_tok(int t, int V) { return t < 0 ? 0 : (t >
 // Eq. 5 (pbar >= tau); leaves the row statistics for the re-draw kernel and parks the near-tie flag in the mask
 // array until k_decide_finish has counted it (per-row atomics on the few counters of a sequence cost a quarter of
 // the accept kernel's time).
-__device__ __forceinline__ void accept_row(const DecideArgs& a, int64_t row, int b, int t, float qt, float pbar,
+__device__ __forceinline__ bool accept_row(const DecideArgs& a, int64_t row, int b, int t, float qt, float pbar,
                                            float m, float inv) {
     const uint32_t w0 = philox_word0((uint32_t)t, (uint32_t)b, a.ctr_lo, a.ctr_hi24, a.key0, a.key1);
     const float u = (float)(w0 >> 8) * 5.9604644775390625e-08f;  // 2^-24, exact
@@ -254,6 +282,7 @@ __device__ __forceinline__ void accept_row(const DecideArgs& a, int64_t row, int
     a.rowmax[row] = m;
     a.rowinv[row] = inv;
     a.mask[row] = fabsf(__fsub_rn(pbar, uq)) < __fmul_rn(NEAR_TIE, tau_rule ? a.tau : qt) ? 1 : 0;
+    return ok;
 }
 
 constexpr int MAX_PARTS = 2048;   // 128 codebook entries per part -> V <= 262144
@@ -321,6 +350,101 @@ __global__ __launch_bounds__(TPB) void k_accept(const DecideArgs a) {
         pbar = block_sum(acc, red);
     }
     if (tid == 0) accept_row(a, row, b, t, qt, pbar, m, inv);
+}
+
+// The same test, which also leaves the chunk sums that the re-draw starts from (chunk c: entries [256 c, 256 c + 256)):
+// the row stays in registers (V <= 2048 NIT), so a marked position reads its logits once, not twice.  The sums are
+// of integers, so they are cdf_draw's whoever adds them; a run of 8 lies in one chunk, 32 lanes share it.  The weights of the
+// draw depend on this row's own decision only (use_p), which is known here; whether the position is marked is not, so
+// an unmarked one has read its draft row for nothing (launch_accept's rule).
+// XCD x takes the x-th eighth of the rows: neighbours, children of one draft row, find it in one L2.
+template <int NIT>
+__global__ __launch_bounds__(TPB) void k_accept_sums(const DecideArgs a, unsigned long long* __restrict__ sums, int rows_per_xcd) {
+    __shared__ float2 parts[NIT * 16];
+    __shared__ float red[WAVES];
+    __shared__ float2 s_stat;
+    __shared__ int s_use_p;
+    const int64_t row = (int64_t)(blockIdx.x & 7) * rows_per_xcd + (blockIdx.x >> 3);
+    if (row >= (int64_t)a.B * a.L) return;                     // uniform over the workgroup, before any barrier
+    const int b = row / a.L, t = row % a.L, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const Guided z{a.logits + row * a.V, a.logits_u ? a.logits_u + row * a.V : nullptr, a.cfg_scale};
+    const int tok = clamp_tok(a.draft_tokens[row], a.V);
+    const int qr = a.q_row ? a.q_row[t] : t;
+    const float* q = a.q ? a.q + b * a.q_batch_stride + (int64_t)qr * a.V : nullptr;
+    float ztok = 0.f, qt = 0.f;
+    if (tid == 0) {
+        if (a.accept_mode == 0) qt = q[tok];
+        ztok = z.at(tok);
+    }
+    const int V = a.V, n_parts = (V + rowparts::PART - 1) / rowparts::PART;
+    const float NEG = rowparts::NEG_INF;
+    float4 lo[NIT], hi[NIT];
+#pragma unroll
+    for (int k = 0; k < NIT; ++k) {
+        const int R = k * TPB + tid;
+        lo[k] = R * 8 + 4 <= V ? z.at4(2 * R) : make_float4(NEG, NEG, NEG, NEG);
+        hi[k] = R * 8 + 8 <= V ? z.at4(2 * R + 1) : make_float4(NEG, NEG, NEG, NEG);
+    }
+#pragma unroll
+    for (int k = 0; k < NIT; ++k) {                            // the part statistics, as in k_accept
+        const int R = k * TPB + tid, n_valid = V - R * 8 >= 8 ? 8 : (V - R * 8 >= 4 ? 4 : 0);
+        const float zz[8] = {lo[k].x, lo[k].y, lo[k].z, lo[k].w, hi[k].x, hi[k].y, hi[k].z, hi[k].w};
+        float m = fmaxf(fmaxf(fmaxf(zz[0], zz[1]), fmaxf(zz[2], zz[3])), fmaxf(fmaxf(zz[4], zz[5]), fmaxf(zz[6], zz[7])));
+        m = fmaxf(m, __shfl_xor(m, 2));
+        m = fmaxf(m, __shfl_xor(m, 4));
+        m = fmaxf(m, __shfl_xor(m, 8));
+        float s = rowparts::run_sum(zz, m, n_valid);
+        s = __fadd_rn(s, __shfl_xor(s, 2));
+        s = __fadd_rn(s, __shfl_xor(s, 4));
+        s = __fadd_rn(s, __shfl_xor(s, 8));
+        const float2 ps = rowparts::merge_halves(m, s, __shfl_xor(m, 1), __shfl_xor(s, 1));
+        if ((tid & 15) == 0 && (R >> 4) < n_parts) parts[R >> 4] = ps;
+    }
+    __syncthreads();
+    if (wv == 0) {
+        const float2 st = rowparts::combine_parts(parts, n_parts, lane);
+        if (lane == 0) s_stat = st;
+    }
+    __syncthreads();
+    const float m = s_stat.x, inv = 1.0f / s_stat.y;
+    float pbar;
+    if (a.pool_k <= 1) {
+        pbar = prob(ztok, m, inv);
+    } else {
+        float acc = 0.f;
+        for (int i = tid; i < a.pool_k; i += TPB)
+            acc += prob(z.at(clamp_tok(a.nbr[(int64_t)tok * a.pool_k + i], a.V)), m, inv);
+        pbar = block_sum(acc, red);
+    }
+    if (tid == 0) {
+        const bool ok = accept_row(a, row, b, t, qt, pbar, m, inv);
+        s_use_p = a.resample_mode == 2 || (a.resample_mode == 1 && ok);
+    }
+    __syncthreads();
+    const bool use_p = s_use_p != 0;                           // uniform: without it q is given
+    const int nchunks = ((V >> 2) + 63) >> 6;
+    const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto chunk_pass = [&](auto with_q) {
+        constexpr bool WITH_Q = decltype(with_q)::value;
+        const float4* q4 = reinterpret_cast<const float4*>(q);
+#pragma unroll
+        for (int k = 0; k < NIT; ++k) {
+            const int R = k * TPB + tid;
+            const bool has_lo = R * 8 + 4 <= V, has_hi = R * 8 + 8 <= V;
+            float4 q_lo = zero4, q_hi = zero4;
+            if constexpr (WITH_Q) {
+                if (has_lo) q_lo = q4[2 * R];
+                if (has_hi) q_hi = q4[2 * R + 1];
+            }
+            // entries that do not exist have z = -inf and weigh 0
+            double sum = weight_sum4<WITH_Q>(lo[k], q_lo, m, inv) + weight_sum4<WITH_Q>(hi[k], q_hi, m, inv);
+#pragma unroll
+            for (int o = 16; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+            if ((tid & 31) == 0 && (R >> 5) < nchunks) sums[row * nchunks + (R >> 5)] = (unsigned long long)sum;
+        }
+    };
+    if (use_p) chunk_pass(std::false_type{});
+    else chunk_pass(std::true_type{});
 }
 
 // The same test when the lm-head GEMM has already left the parts of every row (a verification step): one
@@ -418,18 +542,6 @@ __global__ __launch_bounds__(1024) void k_decide_finish(const DecideArgs a) {
 }
 
 // ---- Step 5 + Eq. 2: neighbourhood mask, then the residual draw -------------
-__device__ __forceinline__ void weights4(const float4 z, const float4 qv, float m, float inv, bool use_p,
-                                         unsigned long long w[4]) {
-    const float S = 1099511627776.0f;  // 2^40: w * S is exact in float32
-    float p0 = prob(z.x, m, inv), p1 = prob(z.y, m, inv), p2 = prob(z.z, m, inv), p3 = prob(z.w, m, inv);
-    if (!use_p) {
-        p0 = fmaxf(0.f, __fsub_rn(p0, qv.x)); p1 = fmaxf(0.f, __fsub_rn(p1, qv.y));
-        p2 = fmaxf(0.f, __fsub_rn(p2, qv.z)); p3 = fmaxf(0.f, __fsub_rn(p3, qv.w));
-    }
-    w[0] = (unsigned long long)__fmul_rn(p0, S); w[1] = (unsigned long long)__fmul_rn(p1, S);
-    w[2] = (unsigned long long)__fmul_rn(p2, S); w[3] = (unsigned long long)__fmul_rn(p3, S);
-}
-
 // Chunk sums of the integer weights of a row (pass 1 of the draw): chunk c covers the 256 codebook entries
 // [256 c, 256 c + 256) = 64 lanes x 4 entries.  G float4 per lane are requested together (both rows), and their G
 // wavefront sums run side by side, so that neither the memory latency nor the latency of a lane exchange is paid
@@ -450,7 +562,7 @@ __device__ __forceinline__ void chunk_sums(const Guided z, const float4* __restr
             if constexpr (GUIDED) zu[g] = zu4[ci];
             if constexpr (USE_Q) qv[g] = q4[ci];
         }
-        unsigned long long sm[G];
+        double sm[G];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const int idx = base + g * TPB + tid;
@@ -458,9 +570,8 @@ __device__ __forceinline__ void chunk_sums(const Guided z, const float4* __restr
             if constexpr (GUIDED)
                 zz = make_float4(guide(zz.x, zu[g].x, z.s), guide(zz.y, zu[g].y, z.s), guide(zz.z, zu[g].z, z.s),
                                  guide(zz.w, zu[g].w, z.s));
-            unsigned long long w[4];
-            weights4(zz, USE_Q ? qv[g] : zero4, m, inv, !USE_Q, w);
-            sm[g] = idx < nv4 ? (w[0] + w[1]) + (w[2] + w[3]) : 0ull;
+            const double s4 = weight_sum4<USE_Q>(zz, USE_Q ? qv[g] : zero4, m, inv);
+            sm[g] = idx < nv4 ? s4 : 0.0;
         }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1)
@@ -470,7 +581,7 @@ __device__ __forceinline__ void chunk_sums(const Guided z, const float4* __restr
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 const int c = (base >> 6) + g * WAVES + wv;
-                if (c < nchunks) chunk[c] = sm[g];
+                if (c < nchunks) chunk[c] = (unsigned long long)sm[g];
             }
         }
     }
@@ -579,6 +690,63 @@ __global__ __launch_bounds__(TPB) void k_mask_sample(const DecideArgs a) {
     const uint32_t word = philox_word0((uint32_t)t, (uint32_t)b, a.ctr_lo, a.ctr_hi24 | (1u << 24),
                                        a.key0, a.key1);
     cdf_draw(z, q4, a.rowmax[row], a.rowinv[row], use_p, word, V, draft, &a.tokens_out[row], chunk, &s_retry);
+}
+
+// The re-draw from the chunk sums that k_accept_sums left (at most 64 chunks, a lane each): one wavefront per position finds
+// the chunk and reads its 256 entries.  The same draw as cdf_draw's, empty residual included.
+__global__ __launch_bounds__(TPB) void k_sample_sums(const DecideArgs a, const unsigned long long* __restrict__ sums) {
+    const int lane = threadIdx.x & 63;
+    const int64_t row = (int64_t)blockIdx.x * WAVES + (threadIdx.x >> 6);
+    if (row >= (int64_t)a.B * a.L) return;                     // uniform over the wavefront; no barrier follows
+    const int b = row / a.L, t = row % a.L, V = a.V, nv4 = V >> 2, nchunks = (nv4 + 63) >> 6;
+    const int draft = clamp_tok(a.draft_tokens[row], V);
+    if (!a.mask[row]) {
+        if (lane == 0) a.tokens_out[row] = draft;
+        return;
+    }
+    const Guided z{a.logits + row * V, a.logits_u ? a.logits_u + row * V : nullptr, a.cfg_scale};
+    bool use_p = a.resample_mode == 2 || (a.resample_mode == 1 && a.accept[row] != 0);
+    const int qr = a.q_row ? a.q_row[t] : t;
+    const float4* q4 = a.q ? reinterpret_cast<const float4*>(a.q + b * a.q_batch_stride + (int64_t)qr * V) : nullptr;
+    const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
+    const float m = a.rowmax[row], inv = a.rowinv[row];
+    unsigned long long v = lane < nchunks ? sums[row * nchunks + lane] : 0ull, tot = wave_sum_u64(v);
+    if (tot == 0 && !use_p) {                                  // empty residual: draw from p instead
+        use_p = true;
+        v = 0;
+        for (int c = 0; c < nchunks; ++c) {
+            const int idx = c * 64 + lane;
+            unsigned long long w[4] = {0, 0, 0, 0};
+            if (idx < nv4) weights4(z.at4(idx), zero4, m, inv, true, w);
+            const unsigned long long s = wave_sum_u64((w[0] + w[1]) + (w[2] + w[3]));
+            if (lane == c) v = s;
+        }
+        tot = wave_sum_u64(v);
+    }
+    if (tot == 0) return;                                      // as cdf_draw: nothing to draw from, nothing written
+    const uint32_t word = philox_word0((uint32_t)t, (uint32_t)b, a.ctr_lo, a.ctr_hi24 | (1u << 24), a.key0, a.key1);
+    const unsigned long long T = __umul64hi((unsigned long long)word << 32, tot);
+    const unsigned long long incl_c = wave_scan_u64(v, lane);
+    const unsigned long long hit_c = __ballot(incl_c > T);
+    const int cidx = hit_c ? __ffsll((long long)hit_c) - 1 : nchunks - 1;
+    const unsigned long long before = __shfl(incl_c - v, cidx);
+    const int idx = cidx * 64 + lane;
+    unsigned long long w[4] = {0, 0, 0, 0};
+    if (idx < nv4) weights4(z.at4(idx), use_p ? zero4 : q4[idx], m, inv, use_p, w);
+    const unsigned long long s = (w[0] + w[1]) + (w[2] + w[3]);
+    const unsigned long long incl = wave_scan_u64(s, lane) + before;
+    const unsigned long long hit = __ballot(incl > T);
+    const int f = hit ? __ffsll((long long)hit) - 1 : 63;
+    if (lane == f) {
+        unsigned long long cum = incl - s;
+        int tok = draft;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            cum += w[e];
+            if (cum > T) { tok = idx * 4 + e; break; }
+        }
+        a.tokens_out[row] = clamp_tok(tok, V);
+    }
 }
 
 // ---- Alg. 1 Step 6, one position: inputs of the single-token forward, then the draw from p ----
@@ -861,8 +1029,27 @@ void launch_decide_finish(const DecideArgs& a, hipStream_t st) {   // a.L <= 131
     hipLaunchKernelGGL(k_decide_finish, dim3(a.B), dim3(block_threads(a.L, 256)), (size_t)a.L, st, a);
 }
 
-void launch_accept(const DecideArgs& a, hipStream_t st) {
+bool launch_accept(const DecideArgs& a, unsigned long long* sums, hipStream_t st) {
+    // Chunk sums with the test where residual weights are drawn from and a neighbourhood marks most positions around the
+    // rejections (4 x 1024 x 16384, radius 2: test + draw 122 -> 89 us).  Radius 0 marks the rejected positions alone, and
+    // reading every draft row would cost more than it saves; draws from p have little to re-read (guided, 2 x 1024, threshold
+    // rule: 62 us, with the sums 65).
+    if (sums && !a.p_probs && a.V <= 16384 && a.resample_mode != 2 && a.rho != 0) {
+        const int rows_per = (int)(((int64_t)a.B * a.L + 7) / 8);
+        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)rows_per * 8), dim3(TPB), 0, st, a, sums, rows_per); };
+        if (a.V <= 2048) go(k_accept_sums<1>);
+        else if (a.V <= 4096) go(k_accept_sums<2>);
+        else if (a.V <= 8192) go(k_accept_sums<4>);
+        else go(k_accept_sums<8>);
+        return true;
+    }
     hipLaunchKernelGGL(k_accept, dim3((unsigned)(a.B * a.L)), dim3(TPB), 0, st, a);
+    return false;
+}
+
+void launch_sample_sums(const DecideArgs& a, const unsigned long long* sums, hipStream_t st) {
+    const int64_t rows = (int64_t)a.B * a.L;
+    hipLaunchKernelGGL(k_sample_sums, dim3((unsigned)((rows + WAVES - 1) / WAVES)), dim3(TPB), 0, st, a, sums);
 }
 
 void launch_accept_from_parts(const DecideArgs& a, const float* parts, int n_parts, hipStream_t st) {

@@ -255,11 +255,16 @@ void enqueue_upsample(mulo_ctx* c, int B, int h, int w, int r, const float* draf
 }
 
 void enqueue_decide(mulo_ctx* c, const DecideArgs& a, bool have_parts = false) {
+    // the row parts' buffer (8 bytes per 128 columns) holds the chunk sums (8 per 256) where no parts are in it
+    unsigned long long* const sums = reinterpret_cast<unsigned long long*>(c->row_parts);
+    bool have_sums = false;
     { PROF(MULO_PROF_ACCEPT);
       if (have_parts) launch_accept_from_parts(a, c->row_parts, (a.V + 127) / 128, c->st);
-      else launch_accept(a, c->st); }
+      else have_sums = launch_accept(a, sums, c->st); }
     { PROF(MULO_PROF_OTHER); launch_decide_finish(a, c->st); }
-    { PROF(MULO_PROF_MASK_SAMPLE); launch_mask_sample(a, c->st); }
+    { PROF(MULO_PROF_MASK_SAMPLE);
+      if (have_sums) launch_sample_sums(a, sums, c->st);
+      else launch_mask_sample(a, c->st); }
 }
 
 void fill_decide(DecideArgs& a, int vocab, float* rowmax, float* rowinv, int B, const mulo_step_params* p) {
@@ -536,7 +541,7 @@ mulo_status mulo_accept_local_resample_static(void* hip_stream, int32_t vocab, i
     a.draft_tokens = draft_tokens; a.tokens_out = tokens_out; a.accept = accept; a.mask = mask;
     a.t0 = t0; a.stats = stats; a.p_probs = p_probs;
     hipStream_t st = (hipStream_t)hip_stream;
-    launch_accept(a, st);
+    launch_accept(a, nullptr, st);   // no workspace to keep sums in
     launch_decide_finish(a, st);
     launch_mask_sample(a, st);
     return check_launch();

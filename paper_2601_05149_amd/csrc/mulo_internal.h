@@ -101,7 +101,10 @@ void launch_island_select(const int32_t* prev, const int32_t* tokens, const uint
                           int cap, int pass, hipStream_t st);
 void launch_island_draw(const float* logits, const int32_t* pos_tab, int32_t* tokens, float* logits_out, int B,
                         int L, int V, int P, int cap, uint64_t seed, uint64_t rng_counter, hipStream_t st);
-void launch_accept(const DecideArgs& a, hipStream_t st);         // softmax statistics + accept test
+// softmax statistics + accept test.  sums: nullptr, or B * L * ceil(V / 256) integers for the chunk sums of the re-draw's
+// weights; returns whether they were written (then launch_sample_sums draws, else launch_mask_sample)
+bool launch_accept(const DecideArgs& a, unsigned long long* sums, hipStream_t st);
+void launch_sample_sums(const DecideArgs& a, const unsigned long long* sums, hipStream_t st);
 // the accept test from row parts (m, s per 128 columns, float pairs [rows, n_parts]) that the lm-head GEMM left;
 // needs pool_k <= 1, no probability output and no guidance
 void launch_accept_from_parts(const DecideArgs& a, const float* parts, int n_parts, hipStream_t st);

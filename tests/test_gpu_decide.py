@@ -335,6 +335,54 @@ def test_guided_decide_parity(B, V, scale, amode):
                                         out["stats"], None)
 
 
+# ------------------------------------------- the draw from the chunk sums that the accept test leaves
+@pytest.mark.parametrize("V", [4, 260, 1028, 2048, 2052, 4096, 10004, 16384, 16388])
+@pytest.mark.parametrize("kw", [dict(radius=1), dict(radius=-1, resample_mode=1), dict(radius=0, resample_mode=2),
+                                dict(radius=2, resample_mode=1, pool=5), dict(radius=1, cfg_scale=3.0), dict(radius=0),
+                                dict(radius=1, accept_mode=1, tau=1e-3, resample_mode=2, cfg_scale=2.0)])
+def test_draw_from_chunk_sums_equals_the_draw_from_the_rows(V, kw):
+    """A bf16 context has room for the chunk sums, so its accept test leaves them for the draw where residual weights are
+    drawn from and the radius is not 0 (vocabularies up to 16384); the entry point without a context reads each marked
+    row again.  All outputs are the same bits: vocabularies at the edges of a chunk, of a lane's run of 8 and of the
+    registers, and in the residual settings rows whose draft distribution IS the target's (an empty residual, re-drawn
+    from p)."""
+    kw = dict(kw)
+    B, W, rows = 3, 8, 7
+    L, pool = W * rows, kw.pop("pool", 1)
+    key = ("sums", V)
+    if key not in _CTX:
+        m = dict(n_layers=1, d_model=128, n_heads=2, head_dim=64, d_ffn=128, vocab=V, dtype="bf16", rms_eps=1e-5)
+        _CTX[key] = make_ctx(m, G.make_weights(m, seed=0), 2 * B, L + 8, L)[0]
+    ctx = _CTX[key]
+    g = torch.Generator(device=DEV).manual_seed(V + len(str(kw)))
+    guided = kw.get("cfg_scale", 0.0) > 0
+    z = torch.randn((2 if guided else 1) * B, L, V, generator=g, device=DEV).mul_(1.5)
+    q = torch.softmax(z[:B] + 0.7 * torch.randn(B, L, V, generator=g, device=DEV), dim=-1).contiguous()
+    toks = torch.randint(0, V, (B, L), generator=g, device=DEV, dtype=torch.int32)
+    toks[:, ::2] = q.argmax(-1)[:, ::2].to(torch.int32)      # where the draft is surest the target is less so: rejections
+    pp = torch.empty(B, L, V, device=DEV)
+    nbr = None
+    if pool > 1:
+        pool = min(pool, V)
+        nbr = torch.randint(0, V, (V, pool), generator=g, device=DEV, dtype=torch.int32)
+        nbr[:, 0] = torch.arange(V, device=DEV)
+    params = mulo.make_params(rows, W, 0, L, kw.pop("radius"), pool_k=pool, nbr=nbr, seed=7, rng_counter=3, **kw)
+    call = lambda f, *head: (lambda o: (f(*head, B, params, z, q, None, L * V, toks, o["tokens_out"], o["accept"], o["mask"],
+                                          o["t0"], o["stats"]), o)[1])(decide_buffers(B, L))
+    # every third row of the draft becomes the target distribution itself, as the library computes it
+    o = decide_buffers(B, L)
+    mulo.mulo_accept_local_resample_static(V, B, params, z, q, None, L * V, toks, o["tokens_out"], o["accept"], o["mask"],
+                                           o["t0"], o["stats"], pp)
+    q[:, ::3] = pp[:, ::3]
+    a = call(mulo.mulo_accept_local_resample, ctx)
+    b = call(lambda *x: mulo.mulo_accept_local_resample_static(V, *x))
+    torch.cuda.synchronize()
+    for k in a:
+        assert torch.equal(a[k], b[k]), (V, kw, k, int((a[k] != b[k]).sum()))
+    assert V == 4 or int(a["stats"][:, 2].sum()) > 0      # four entries, five of them pooled: nothing is rejected
+    assert (a["tokens_out"] >= 0).all() and (a["tokens_out"] < V).all()
+
+
 # --------------------------------------------------------------- rejection islands (Eq. 8)
 def _islands_gpu(ctx, mask, W, n0):
     B, L = mask.shape
