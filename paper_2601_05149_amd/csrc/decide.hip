@@ -475,7 +475,8 @@ __global__ __launch_bounds__(TPB) void k_accept_parts(const DecideArgs a, const 
 // rejected positions and near ties, then R_X: position t is marked when it is at or after t0 and within Chebyshev
 // distance rho of some rejected position of the block (rho < 0: the raster rule, everything from t0 on).  Writes
 // mask, t0 and stats = (accepted, rejected, marked, near ties); no atomics on global memory anywhere.
-// A chain of latencies, so a position per thread up to blocks of 1024 (4 x 1024: 256 threads 7.5 us, 1024 6.4).
+// A chain of latencies, so a position per thread up to blocks of 1024 where there is a window to search (4 x 1024, radius 2:
+// 256 threads 7.5 us, 1024 6.8); without one (2 x 1024, radius 0: 4.7 / 5.3) the larger workgroup only costs.
 __global__ __launch_bounds__(1024) void k_decide_finish(const DecideArgs a) {
     extern __shared__ uint8_t acc_s[];   // [L]
     __shared__ int red[16][4];
@@ -1042,7 +1043,7 @@ void launch_island_draw(const float* logits, const int32_t* pos_tab, int32_t* to
 void launch_decide_finish(const DecideArgs& a, hipStream_t st) {   // a.L <= 131072 (the caller checks): flags in LDS
     static int attr_state = 0;
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(k_decide_finish), 131072, &attr_state)) return;
-    hipLaunchKernelGGL(k_decide_finish, dim3(a.B), dim3(block_threads(a.L, 256)), (size_t)a.L, st, a);
+    hipLaunchKernelGGL(k_decide_finish, dim3(a.B), dim3(a.rho > 0 ? block_threads(a.L, 256) : 256), (size_t)a.L, st, a);
 }
 
 bool launch_accept(const DecideArgs& a, unsigned long long* sums, hipStream_t st) {
