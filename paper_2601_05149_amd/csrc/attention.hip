@@ -51,8 +51,9 @@ constexpr int NS_TARGET = 512;      // workgroups a key split aims at (measured:
                                     // of attention per single-token step at the 7B shape, 4 sequences of 4000 rows)
 constexpr int SPLIT_QUERIES = 32;   // a key split serves at most this many queries per (sequence, head)
 
+// two workgroups per CU where their LDS fits twice (2 x 71.7 KB: 64-key tiles of heads of 128, 128-key tiles of heads of 64)
 template <int DH, int BQ, int BKV, int NTH>
-__global__ __launch_bounds__(NTH, BKV <= 64 ? 2 : 1) void k_attn_bf16(const AttnArgs a) {
+__global__ __launch_bounds__(NTH, DH * BKV <= 8192 ? 2 : 1) void k_attn_bf16(const AttnArgs a) {
     constexpr int KS = DH + 8;     // K tile row stride (bf16)
     constexpr int VS = BKV + 8;    // V^T tile row stride
     constexpr int NKK = DH / 16;   // k-steps of the first product
@@ -376,23 +377,24 @@ void run_attn_cfg(const AttnArgs& a, hipStream_t st) {
     }
 }
 
-// Heads of 128 and blocks of more than LONG_BLOCK queries: 256-query workgroups of 8 wavefronts over 128-key tiles (one per
-// CU).  Everything else (single-token decoding above all): 128-query workgroups of 4 wavefronts over 64-key tiles, two per
-// CU.  The two add in another order, so which one runs depends on the head and the block, never on the batch: a sequence
-// launched alone gets the bits it gets in a batch.  Measured, 256 x 128 keys / 128 x 64 keys, us: heads of 64: 4 x 256
-// queries, 832 keys 23.7 / 18.0, 1 x 1024, 1524 keys 35.2 / 29.4, 2 x 900, 3900 keys 79 / 70, 16 x 1024, 2024 keys 193 / 176,
-// 8 x 300, 1300 keys 33.1 / 34.8; heads of 128: 4 x 256, 3256 keys 104 / 90, 1 x 200, 1100 keys 37 / 32, 3 x 400, 1400 keys
-// 50 / 59, 4 x 1024, 4224 keys 301 / 348.
-constexpr int BKV_SMALL = 64, LONG_BLOCK = 256;
+// Blocks of more than SHORT_BLOCK queries run over 128-key tiles, shorter ones (single-token decoding above all) in 128-query
+// workgroups of 4 wavefronts over 64-key tiles, two per CU.  The two add in another order, so which one runs depends on the
+// block alone, never on the batch: a sequence launched alone gets the bits it gets in a batch, and a row gets the same bits
+// in every block of more than SHORT_BLOCK queries (the key split of a single token per sequence, L == 1, is the exception:
+// its number of shares follows the batch).
+// Over 128-key tiles a wavefront's 32 queries are added up by themselves, so the queries per workgroup do not show in the
+// bits: heads of 128 take 128 (4 wavefronts) where all of those have a CU, else 256 (8 wavefronts: one workgroup per CU
+// either way, 139 KB of LDS); heads of 64 take 128, two workgroups per CU.  Measured, 256 / 128 queries, us: heads of 128:
+// 1 x 256 queries, 3256 keys 99 / 93, 4 x 256, 3256 keys 128 / 119, 3 x 242, 2656 keys 94 / 85, 1 x 576, 1856 keys 63 / 59,
+// 1 x 1024, 4024 keys 139 / 131, 1 x 384, 2795 keys 79.5 / 81.9, and past one workgroup per CU 8 x 200, 3146 keys 130 / 216;
+// heads of 64: 4 x 256, 832 keys 23.7 / 18.4, 4 x 256, 3256 keys 69 / 51, 1 x 1024, 1524 keys 35.7 / 27, 8 x 300, 1300 keys
+// 36 / 35.6, 16 x 1024, 2024 keys 221 / 211, 6 x 512, 1112 keys 32.8 / 33.8.
+constexpr int BKV_SMALL = 64, SHORT_BLOCK = 128;
 template <int DH>
 void run_attn(const AttnArgs& a, hipStream_t st) {
-    if constexpr (DH == 128) {
-        if (a.L > LONG_BLOCK) {
-            run_attn_cfg<DH, 256, 128, 512>(a, st);
-            return;
-        }
-    }
-    run_attn_cfg<DH, 128, BKV_SMALL, 256>(a, st);
+    if (a.L <= SHORT_BLOCK) run_attn_cfg<DH, 128, BKV_SMALL, 256>(a, st);
+    else if (DH == 64 || (int64_t)a.B * a.nh * ((a.L + 127) / 128) <= cu_count()) run_attn_cfg<DH, 128, 128, 256>(a, st);
+    else if constexpr (DH == 128) run_attn_cfg<DH, 256, 128, 512>(a, st);
 }
 
 }  // namespace

@@ -717,18 +717,6 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
     epilogue<EPI, BN, TM, TN, MB, NB>(g, acc, m0, n0, tile_n, wm, wn, l32, lh);
 }
 
-
-static int cu_count() {
-    static int n = 0;
-    if (n == 0) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) n = prop.multiProcessorCount;
-        if (n <= 0) n = 256;
-    }
-    return n;
-}
-
 template <int BM, int BN, int WGM, int WGN, int EPI>
 void run_gemm(GemmArgs g, int tile_n0, int tiles_n, hipStream_t st) {
     auto kern = k_gemm_bf16<BM, BN, WGM, WGN, EPI>;
@@ -1255,6 +1243,17 @@ bool dispatch(const GemmArgs& g0, hipStream_t st) {
 }
 
 }  // namespace
+
+int cu_count() {
+    static int n = 0;
+    if (n == 0) {
+        int dev = 0;
+        hipDeviceProp_t prop;
+        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) n = prop.multiProcessorCount;
+        if (n <= 0) n = 256;
+    }
+    return n;
+}
 
 void launch_gemm_qkv_bf16(const void* xh, const void* wq, const void* wk, const void* wv, void* q_out,
                           void* k_cache, void* v_cache, int M, int d, const RopeArgs& ra, const StreamMode& sm, hipStream_t st) {

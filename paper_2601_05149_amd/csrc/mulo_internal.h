@@ -14,6 +14,8 @@ void note_hip_error(hipError_t e);
 // false, with the error noted, when the runtime refuses.
 bool ensure_dynamic_lds(const void* kern, int bytes, int* state);
 
+int cu_count();   // compute units of the device (gemm.hip)
+
 // Launches of at most STREAM_MAX_TOKENS tokens (single-token decoding of a few sequences, island passes) run every
 // bf16 projection in the weight-streaming kernel.  That kernel feeds its MFMA straight from registers, so its token
 // operand [M, K] is kept in the order the instruction reads it (FRAGMENT ORDER): tokens in groups of 16, k in steps of

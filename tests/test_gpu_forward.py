@@ -95,6 +95,28 @@ def test_forward_f32_shapes(nh, dh, f, V, B, L, P):
     assert err <= 1e-4
 
 
+@pytest.mark.parametrize("nh,dh", [(8, 128), (16, 64)])
+def test_a_row_has_the_same_bits_in_every_block_of_more_than_128_queries(nh, dh):
+    """The attention of a row adds its keys in one order whatever the length of the block and the number of sequences: the
+    rows of a 200-query block (one sequence, and 17 of them: past one 128-query workgroup per CU) are those of blocks of
+    129, 256, 257 and 520 queries that begin with the same tokens, bit for bit."""
+    m = dict(n_layers=1, d_model=nh * dh, n_heads=nh, head_dim=dh, d_ffn=256, vocab=512, dtype="bf16", rms_eps=1e-5)
+    w, P, B = G.make_weights(m, seed=9), 75, 17
+    ctx, cos, sin = make_ctx(m, w, B, 600, 520)
+    kv = mulo.alloc_kv(ctx, DEV)
+    gpu_forward(ctx, kv, G.uniform_tokens((1, P), 512, 9, tag=0), 0)
+    for t in kv:
+        t[:, 1:].copy_(t[:, :1].expand_as(t[:, 1:]))
+    blk = G.uniform_tokens((1, 520), 512, 9, tag=1)
+    ref = gpu_forward(ctx, kv, blk, P)[0]
+    for L in (129, 200, 256, 257, 520):
+        assert np.array_equal(gpu_forward(ctx, kv, blk[:, :L], P)[0], ref[:L]), L
+        many = np.repeat(blk[:, :L], B, axis=0)
+        many[1:-1, 0] = G.uniform_tokens((B - 2,), 512, 9, tag=2)
+        z = gpu_forward(ctx, kv, many, P)
+        assert np.array_equal(z[0], ref[:L]) and np.array_equal(z[-1], ref[:L]), L
+
+
 @pytest.mark.parametrize("d,nh,f,V", [
     (768, 6, 8256, 1092),    # gate | up on every tile it has; K of 129 steps for down, a ragged last column tile for the lm-head
     (768, 6, 704, 16384),    # the lm-head on every tile; K of 11 steps
