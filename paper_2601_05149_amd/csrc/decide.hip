@@ -352,7 +352,7 @@ __global__ __launch_bounds__(TPB) void k_accept(const DecideArgs a) {
     if (tid == 0) accept_row(a, row, b, t, qt, pbar, m, inv);
 }
 
-// The same test, which also leaves the chunk sums that the re-draw starts from (chunk c: entries [256 c, 256 c + 256)):
+// Eq. 1 without pooling, which also leaves the chunk sums that the re-draw starts from (chunk c: entries [256 c, 256 c + 256)):
 // the row stays in registers (V <= 2048 NIT), so a marked position reads its logits once, not twice.  The sums are
 // of integers, so they are cdf_draw's whoever adds them; a run of 8 lies in one chunk, 32 lanes share it.  The weights of the
 // draw depend on this row's own decision only (use_p), which is known here; whether the position is marked is not, so
@@ -361,7 +361,6 @@ __global__ __launch_bounds__(TPB) void k_accept(const DecideArgs a) {
 template <int NIT>
 __global__ __launch_bounds__(TPB) void k_accept_sums(const DecideArgs a, unsigned long long* __restrict__ sums, int rows_per_xcd) {
     __shared__ float2 parts[NIT * 16];
-    __shared__ float red[WAVES];
     __shared__ float2 s_stat;
     __shared__ int s_use_p;
     const int64_t row = (int64_t)(blockIdx.x & 7) * rows_per_xcd + (blockIdx.x >> 3);
@@ -370,10 +369,10 @@ __global__ __launch_bounds__(TPB) void k_accept_sums(const DecideArgs a, unsigne
     const Guided z{a.logits + row * a.V, a.logits_u ? a.logits_u + row * a.V : nullptr, a.cfg_scale};
     const int tok = clamp_tok(a.draft_tokens[row], a.V);
     const int qr = a.q_row ? a.q_row[t] : t;
-    const float* q = a.q ? a.q + b * a.q_batch_stride + (int64_t)qr * a.V : nullptr;
+    const float* q = a.q + b * a.q_batch_stride + (int64_t)qr * a.V;
     float ztok = 0.f, qt = 0.f;
     if (tid == 0) {
-        if (a.accept_mode == 0) qt = q[tok];
+        qt = q[tok];
         ztok = z.at(tok);
     }
     const int V = a.V, n_parts = (V + rowparts::PART - 1) / rowparts::PART;
@@ -407,21 +406,12 @@ __global__ __launch_bounds__(TPB) void k_accept_sums(const DecideArgs a, unsigne
     }
     __syncthreads();
     const float m = s_stat.x, inv = 1.0f / s_stat.y;
-    float pbar;
-    if (a.pool_k <= 1) {
-        pbar = prob(ztok, m, inv);
-    } else {
-        float acc = 0.f;
-        for (int i = tid; i < a.pool_k; i += TPB)
-            acc += prob(z.at(clamp_tok(a.nbr[(int64_t)tok * a.pool_k + i], a.V)), m, inv);
-        pbar = block_sum(acc, red);
-    }
     if (tid == 0) {
-        const bool ok = accept_row(a, row, b, t, qt, pbar, m, inv);
-        s_use_p = a.resample_mode == 2 || (a.resample_mode == 1 && ok);
+        const bool ok = accept_row(a, row, b, t, qt, prob(ztok, m, inv), m, inv);
+        s_use_p = a.resample_mode == 1 && ok;
     }
     __syncthreads();
-    const bool use_p = s_use_p != 0;                           // uniform: without it q is given
+    const bool use_p = s_use_p != 0;                           // uniform
     const int nchunks = ((V >> 2) + 63) >> 6;
     const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
     auto chunk_pass = [&](auto with_q) {
@@ -1048,10 +1038,16 @@ void launch_decide_finish(const DecideArgs& a, hipStream_t st) {   // a.L <= 131
 
 bool launch_accept(const DecideArgs& a, unsigned long long* sums, hipStream_t st) {
     // Chunk sums with the test where residual weights are drawn from and a neighbourhood marks most positions around the
-    // rejections (4 x 1024 x 16384, radius 2: test + draw 122 -> 89 us).  Radius 0 marks the rejected positions alone, and
-    // reading every draft row would cost more than it saves; draws from p have little to re-read (guided, 2 x 1024, threshold
-    // rule: 62 us, with the sums 65).
-    if (sums && !a.p_probs && a.V <= 16384 && a.resample_mode != 2 && a.rho != 0) {
+    // rejections: Eq. 1 without pooling, whose acceptance is 1 - TV(p, q), 0.8 to 0.3 in the workloads.  Unmarked positions
+    // pay for it, so the gain depends on the acceptance a.  4 x 1024 x 16384, test + mask + draw in us, this / the test alone
+    // and a draw that reads the marked rows again:
+    //   draft rows shared by 4 positions: radius 1: a = 0.62 92 / 117, 0.88 92 / 102, 0.96 92 / 81, 0.99 90 / 66;
+    //     radius 2: 0.62 93 / 118, 0.88 94 / 121, 0.96 94 / 103, 0.99 93 / 79; raster rule: 0.99 88 / 106;
+    //   a row each: radius 1: 0.64 113 / 146, 0.88 113 / 110, 0.99 113 / 68; radius 2: 0.88 115 / 149, 0.96 115 / 116.
+    // They cross at a = 0.92 (radius 1) and 0.975 (radius 2).  Not here: pooled and threshold tests, made to accept nearly
+    // everything (and the threshold reads no draft row); radius 0, which marks the rejected positions alone; draws from p,
+    // which have little to re-read (guided, 2 x 1024, threshold rule: 65 / 62).
+    if (sums && !a.p_probs && a.V <= 16384 && a.accept_mode == 0 && a.pool_k <= 1 && a.resample_mode != 2 && a.rho != 0) {
         const int rows_per = (int)(((int64_t)a.B * a.L + 7) / 8);
         auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)rows_per * 8), dim3(TPB), 0, st, a, sums, rows_per); };
         if (a.V <= 2048) go(k_accept_sums<1>);
