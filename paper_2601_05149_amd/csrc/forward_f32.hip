@@ -83,21 +83,19 @@ __device__ __forceinline__ void emit2(const F32Args& g, int m, int n, const floa
     }
 }
 
-// SPLIT: one 16-token x 16-column tile per workgroup, its 4 wavefronts split K (interleaved steps) and add up through
-// LDS in wavefront order.  Otherwise a 64 x 64 tile, 2 x 2 wavefronts of 32 x 32, each over the whole of K: a quarter
-// of the operand bytes per product, for launches that fill the chip that way too.
-template <int EPI, bool SPLIT, bool V4>
+// A 16 R x 16 R tile per workgroup; its 4 wavefronts each compute all of it over a quarter of K (every fourth step) and add up
+// through LDS in wavefront order.  The order of a sum is that of its K alone, whatever R: a sequence gets the same bits
+// alone, in a batch, and a token at a time.
+template <int EPI, int R, bool V4>
 __global__ __launch_bounds__(256) void k_proj_f32(const F32Args g) {
-    constexpr int R = SPLIT ? 1 : 2;                     // 16-row blocks of each operand per wavefront
     constexpr int NA = EPI == F32_SWIGLU ? 2 : 1;
     constexpr bool NORM = EPI == F32_QKV || EPI == F32_SWIGLU;
-    constexpr int U = SPLIT ? 4 : 2;                     // steps in flight
-    __shared__ float part[SPLIT ? 4 : 1][NA][4][64];
-    __shared__ float ssq[4][16];
+    constexpr int U = R == 1 ? 4 : 2;                               // steps in flight
+    __shared__ float part[4][NA][R * R][4][64];
+    __shared__ float ssq[4][R][16];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l16 = lane & 15, q = lane >> 4;
-    const int tiles_n = (g.N + 16 * R * (SPLIT ? 1 : 2) - 1) / (16 * R * (SPLIT ? 1 : 2));
-    const int bm = blockIdx.x / tiles_n, bn = blockIdx.x % tiles_n;
-    const int m0 = SPLIT ? bm * 16 : bm * 64 + (wave >> 1) * 32, n0 = SPLIT ? bn * 16 : bn * 64 + (wave & 1) * 32;
+    const int tiles_n = (g.N + 16 * R - 1) / (16 * R);
+    const int m0 = blockIdx.x / tiles_n * 16 * R, n0 = blockIdx.x % tiles_n * 16 * R;
     const float *pa[R], *pw[NA][R];
 #pragma unroll
     for (int i = 0; i < R; ++i) {
@@ -123,12 +121,12 @@ __global__ __launch_bounds__(256) void k_proj_f32(const F32Args g) {
 #pragma unroll
             for (int j = 0; j < R; ++j) acc[a][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    const int steps = (g.K + 15) / 16, first = SPLIT ? wave : 0, by = SPLIT ? 4 : 1;
+    const int steps = (g.K + 15) / 16;
     f32x4 xa[U][R], xw[U][NA][R], xg[U];
     auto request = [&](int s0) {                          // steps past the last load zeros
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int k = (s0 + u * by) * 16 + q * 4;
+            const int k = (s0 + u * 4) * 16 + q * 4;
 #pragma unroll
             for (int i = 0; i < R; ++i) {
                 xa[u][i] = load4<V4>(pa[i], k, g.K);
@@ -138,8 +136,8 @@ __global__ __launch_bounds__(256) void k_proj_f32(const F32Args g) {
             if constexpr (NORM) xg[u] = load4<V4>(g.gain, k, g.K);
         }
     };
-    request(first);
-    for (int s = first; s < steps; s += U * by) {
+    request(wave);
+    for (int s = wave; s < steps; s += U * 4) {
         f32x4 ca[U][R], cw[U][NA][R];
 #pragma unroll
         for (int u = 0; u < U; ++u)
@@ -154,7 +152,7 @@ __global__ __launch_bounds__(256) void k_proj_f32(const F32Args g) {
 #pragma unroll
                 for (int a = 0; a < NA; ++a) cw[u][a][i] = xw[u][a][i];
             }
-        if (s + U * by < steps) request(s + U * by);
+        if (s + U * 4 < steps) request(s + U * 4);
 #pragma unroll
         for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -167,71 +165,56 @@ __global__ __launch_bounds__(256) void k_proj_f32(const F32Args g) {
                         for (int j = 0; j < R; ++j)
                             acc[a][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(cw[u][a][j][e], ca[u][i][e], acc[a][i][j], 0, 0, 0);
     }
-    // 1 / rms of the lane's tokens: the squares of a row are spread over the four q (and, SPLIT, over the wavefronts)
-    float sc[R];
+    // the squares of a row are spread over the four q and over the wavefronts
 #pragma unroll
     for (int i = 0; i < R; ++i) {
         ss[i] += __shfl_xor(ss[i], 16);
         ss[i] += __shfl_xor(ss[i], 32);
+        if (NORM && q == 0) ssq[wave][i][l16] = ss[i];
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+#pragma unroll
+            for (int a = 0; a < NA; ++a)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) part[wave][a][i * R + j][r][lane] = acc[a][i][j][r];
     }
-    if constexpr (SPLIT) {
+    __syncthreads();
+    // block blk = (i, j) of the tile, columns 4 q + 2 pr, + 1: two pairs of columns per block, dealt to the wavefronts
+    for (int x = wave; x < 2 * R * R; x += 4) {
+        const int blk = x >> 1, pr = x & 1, i = blk / R, m = m0 + i * 16 + l16;
+        float sc = 1.0f;                                  // 1 / rms of the lane's token
+        if constexpr (NORM)
+            sc = 1.0f / sqrtf(((ssq[0][i][l16] + ssq[1][i][l16]) + (ssq[2][i][l16] + ssq[3][i][l16])) / (float)g.K + g.eps);
+        float v[2][2] = {};
 #pragma unroll
         for (int a = 0; a < NA; ++a)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) part[wave][a][r][lane] = acc[a][0][0][r];
-        if (NORM && q == 0) ssq[wave][l16] = ss[0];
-        __syncthreads();
-        if (wave >= 2) return;                            // wavefront pr owns columns 4 q + 2 pr, + 1
-        if constexpr (NORM) ss[0] = (ssq[0][l16] + ssq[1][l16]) + (ssq[2][l16] + ssq[3][l16]);
-    }
-#pragma unroll
-    for (int i = 0; i < R; ++i) sc[i] = NORM ? 1.0f / sqrtf(ss[i] / (float)g.K + g.eps) : 1.0f;
-    auto put = [&](int i, int j, int pr, float (&v0)[2], float (&v1)[2]) {
-        const int m = m0 + i * 16 + l16, n = n0 + j * 16 + 4 * q + 2 * pr;
-        if constexpr (NORM) {
-#pragma unroll
-            for (int e = 0; e < 2; ++e) { v0[e] *= sc[i]; v1[e] *= sc[i]; }
-        }
-        if (m < g.M) emit2<EPI>(g, m, n, v0, v1);
-    };
-    if constexpr (SPLIT) {
-        float v0[2], v1[2] = {0.f, 0.f};
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int r = 2 * wave + e;
-            v0[e] = (part[0][0][r][lane] + part[1][0][r][lane]) + (part[2][0][r][lane] + part[3][0][r][lane]);
-            if constexpr (NA == 2) v1[e] = (part[0][1][r][lane] + part[1][1][r][lane]) + (part[2][1][r][lane] + part[3][1][r][lane]);
-        }
-        put(0, 0, wave, v0, v1);
-    } else {
-#pragma unroll
-        for (int i = 0; i < R; ++i)
-#pragma unroll
-            for (int j = 0; j < R; ++j)
-#pragma unroll
-                for (int pr = 0; pr < 2; ++pr) {
-                    float v0[2] = {acc[0][i][j][2 * pr], acc[0][i][j][2 * pr + 1]};
-                    float v1[2] = {acc[NA - 1][i][j][2 * pr], acc[NA - 1][i][j][2 * pr + 1]};
-                    put(i, j, pr, v0, v1);
-                }
+            for (int e = 0; e < 2; ++e) {
+                const int r = 2 * pr + e;
+                v[a][e] = (part[0][a][blk][r][lane] + part[1][a][blk][r][lane]) + (part[2][a][blk][r][lane] + part[3][a][blk][r][lane]);
+                if constexpr (NORM) v[a][e] *= sc;
+            }
+        if (m < g.M) emit2<EPI>(g, m, n0 + blk % R * 16 + 4 * q + 2 * pr, v[0], v[1]);
     }
 }
 
-// Launches of fewer than this many outputs M N run SPLIT (measured, split / 64 x 64 tiles, us: 576 x 768 outputs 15.2 /
-// 18.3, 1024 x 768 21.8 / 19.1; 1536 x 256 11.9 / 15.8, 2304 x 256 15.5 / 16.2; 576 x 1024 14.5 / 13.9)
-constexpr int64_t SPLIT_BELOW = 600 * 1024;
+// 32 x 32 tiles halve the operand bytes per product and launch a quarter of the workgroups.  Measured, 16 / 32, us: outputs
+// 256 x 768 7.2 / 7.6, 384 x 768 10.5 / 11.0, 384 x 1024 9.2 / 7.8, 512 x 768 12.9 / 10.9, 1024 x 768 19 / 12.7; K = 688:
+// 1024 x 256 11.5 / 10.4, 1536 x 256 15.4 / 13.7, 2304 x 256 21.5 / 19.1; gate | up 256 x 688 8.8 / 9.3, 512 x 688 14.2 / 13.0,
+// 2304 x 688 46 / 36 (64 x 64 tiles, which add in another order: 32).
+constexpr int64_t WIDE_FROM = 300 * 1024;
 
 template <int EPI>
 void run_proj(const F32Args& g, hipStream_t st) {
-    const bool split = (int64_t)g.M * g.N < SPLIT_BELOW, v4 = (g.K & 3) == 0;
-    const int t = split ? 16 : 64;
+    const bool wide = (int64_t)g.M * g.N >= WIDE_FROM, v4 = (g.K & 3) == 0;
+    const int t = wide ? 32 : 16;
     const dim3 grid((unsigned)((int64_t)((g.M + t - 1) / t) * ((g.N + t - 1) / t)));
-    if (split) {
-        if (v4) hipLaunchKernelGGL((k_proj_f32<EPI, true, true>), grid, dim3(256), 0, st, g);
-        else hipLaunchKernelGGL((k_proj_f32<EPI, true, false>), grid, dim3(256), 0, st, g);
+    if (wide) {
+        if (v4) hipLaunchKernelGGL((k_proj_f32<EPI, 2, true>), grid, dim3(256), 0, st, g);
+        else hipLaunchKernelGGL((k_proj_f32<EPI, 2, false>), grid, dim3(256), 0, st, g);
     } else {
-        if (v4) hipLaunchKernelGGL((k_proj_f32<EPI, false, true>), grid, dim3(256), 0, st, g);
-        else hipLaunchKernelGGL((k_proj_f32<EPI, false, false>), grid, dim3(256), 0, st, g);
+        if (v4) hipLaunchKernelGGL((k_proj_f32<EPI, 1, true>), grid, dim3(256), 0, st, g);
+        else hipLaunchKernelGGL((k_proj_f32<EPI, 1, false>), grid, dim3(256), 0, st, g);
     }
 }
 

@@ -95,6 +95,31 @@ def test_forward_f32_shapes(nh, dh, f, V, B, L, P):
     assert err <= 1e-4
 
 
+@pytest.mark.parametrize("nh,dh,f", [(4, 64, 688), (3, 18, 203)])
+def test_forward_f32_has_the_same_bits_alone_in_a_batch_and_token_by_token(nh, dh, f):
+    """Every float32 sum is added in an order that its own length fixes: the logits and cache rows of a sequence are the same
+    bits alone, in batches of up to 9 (up to 1.8 million outputs a projection, past every size at which it changes its
+    tile) and one token at a time.  The widths of the tiny configuration, and rows that are not 16-byte aligned."""
+    m = dict(n_layers=2, d_model=nh * dh, n_heads=nh, head_dim=dh, d_ffn=f, vocab=1024, dtype="f32", rms_eps=1e-5)
+    B, L, P = 9, 200, 11
+    ctx, cos, sin = make_ctx(m, G.make_weights(m, seed=5), B, 224, L)
+    kv = mulo.alloc_kv(ctx, DEV)
+    gpu_forward(ctx, kv, G.uniform_tokens((1, P), 1024, 5, tag=0), 0)
+    for t in kv:
+        t[:, 1:].copy_(t[:, :1].expand_as(t[:, 1:]))
+    many = G.uniform_tokens((B, L), 1024, 5, tag=1)
+    many[:] = np.where(np.arange(B)[:, None] % 4 == 0, many[:1], many)
+    one = gpu_forward(ctx, kv, many[:1], P)[0]
+    k1, v1 = kv[0][:, 0, :, P:P + L].clone(), kv[1][:, 0, :, :, P:P + L].clone()
+    for n in (2, 3, 5, 9):
+        z = gpu_forward(ctx, kv, many[:n], P)
+        for b in range(0, n, 4):
+            assert np.array_equal(z[b], one), (n, b)
+            assert torch.equal(kv[0][:, b, :, P:P + L], k1) and torch.equal(kv[1][:, b, :, :, P:P + L], v1), (n, b)
+    for j in range(40):
+        assert np.array_equal(gpu_forward(ctx, kv, many[:1, j:j + 1], P + j)[0, 0], one[j]), j
+
+
 @pytest.mark.parametrize("nh,dh", [(8, 128), (16, 64)])
 def test_a_row_has_the_same_bits_in_every_block_of_more_than_128_queries(nh, dh):
     """The attention of a row adds its keys in one order whatever the length of the block and the number of sequences: the
