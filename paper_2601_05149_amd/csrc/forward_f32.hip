@@ -287,11 +287,39 @@ __global__ __launch_bounds__(NW * 64) void k_attn_mfma_f32(const float* __restri
         }
         l_run = l_run * alpha + ps;
 #pragma unroll
-        for (int s = 0; s < NB; ++s) {
-            o[s] *= alpha;
+        for (int s = 0; s < NB; ++s) o[s] *= alpha;
+        // A tile that some query sees a part of only: a hidden key's p is 0, and 0 times an infinity or NaN of its V must not
+        // reach that query.  Such values are added to the queries that do see them and taken out of the product.
+        if (k0 + 15 > P + j0) {
+            bool odd = false;
+#pragma unroll
+            for (int s = 0; s < NB; ++s)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) odd |= !__builtin_isfinite(vf[s][e]);
+            if (__ballot(odd)) {                              // uniform over the wavefront
+                for (int g = 0; g < 4; ++g)                   // key 4 g + e of the tile: V and p sit in the lanes with q = g
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const float pk = __shfl(p[e], g * 16 + l16);
+                        const bool seen = k0 + g * 4 + e <= qpos;
+#pragma unroll
+                        for (int s = 0; s < NB; ++s)
+#pragma unroll
+                            for (int r = 0; r < 4; ++r) {
+                                const float v = __shfl(vf[s][e], g * 16 + q * 4 + r);
+                                if (seen && !__builtin_isfinite(v)) o[s][r] += pk * v;
+                            }
+                    }
+#pragma unroll
+                for (int s = 0; s < NB; ++s)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) vf[s][e] = __builtin_isfinite(vf[s][e]) ? vf[s][e] : 0.f;
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < NB; ++s)
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[s][e], p[e], o[s], 0, 0, 0);
-        }
     }
     l_run += __shfl_xor(l_run, 16);
     l_run += __shfl_xor(l_run, 32);

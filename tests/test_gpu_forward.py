@@ -120,6 +120,27 @@ def test_forward_f32_has_the_same_bits_alone_in_a_batch_and_token_by_token(nh, d
         assert np.array_equal(gpu_forward(ctx, kv, many[:1, j:j + 1], P + j)[0, 0], one[j]), j
 
 
+@pytest.mark.parametrize("nh,dh", [(2, 16), (2, 18), (4, 64), (2, 128), (1, 136)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_forward_f32_keeps_non_finite_positions_behind_the_causal_mask(nh, dh, bad):
+    """A position whose embedding is not finite leaves every position before it as it is, bit for bit, and reaches itself
+    and every position after it, wherever it lies in a tile of 16 queries or keys."""
+    d, L, P = nh * dh, 37, 5
+    m = dict(n_layers=2, d_model=d, n_heads=nh, head_dim=dh, d_ffn=48, vocab=64, dtype="f32", rms_eps=1e-5)
+    ctx, cos, sin = make_ctx(m, G.make_weights(m, seed=6, std=0.1), 1, 48, L)
+    kv = mulo.alloc_kv(ctx, DEV)
+    toks = np.zeros((1, L), np.int32)
+    gpu_forward(ctx, kv, G.uniform_tokens((1, P), 64, 6, tag=0), 0)
+    emb = torch.randn(1, L, d, generator=torch.Generator(device=DEV).manual_seed(dh), device=DEV)
+    clean = gpu_forward(ctx, kv, toks, P, emb)[0]
+    for j in (0, 1, 10, 11, 26, 27, 36):
+        e = emb.clone()
+        e[0, j, 3] = bad
+        z = gpu_forward(ctx, kv, toks, P, e)[0]
+        assert np.array_equal(z[:j], clean[:j]), j
+        assert not np.isfinite(z[j:]).any(), j
+
+
 @pytest.mark.parametrize("nh,dh", [(8, 128), (16, 64)])
 def test_a_row_has_the_same_bits_in_every_block_of_more_than_128_queries(nh, dh):
     """The attention of a row adds its keys in one order whatever the length of the block and the number of sequences: the
