@@ -92,9 +92,8 @@ __device__ __forceinline__ int b_row_src(const GemmArgs& g, int n0, int tile_n, 
     return r;
 }
 
-// Whole-tile launches address their operands through buffer descriptors: the descriptor (matrix base and size)
-// and a byte offset of the tile row and K-step live in scalar registers, a lane adds one fixed 32-bit offset
-// (its row and 16-byte chunk inside a pass).  No 64-bit lane addresses to keep or to advance.
+// The tiled kernels address their operands through buffer descriptors: the descriptor (base and size) and a byte offset
+// live in scalar registers, a lane adds a 32-bit offset of its own.
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 __device__ __forceinline__ rsrc_t make_rsrc(const void* p, int64_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)(bytes < 0x7fffffff ? bytes : 0x7fffffff), 0x00020000);
@@ -331,14 +330,16 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_bf16(const GemmArgs g
     int tile = blockIdx.x / nxcd, tile_n = 0, m0 = 0, n0 = 0;
     const int kc8 = (tid % CPR) * 8, trow = tid / CPR;
     // Operand addresses: the rows a lane fetches are a fixed stride apart, so a lane keeps ONE 32-bit offset (its row and
-    // chunk inside a pass) and everything else is scalar: buffer loads through a descriptor of the whole matrix, with
-    // the pass's row and the K-step as scalar offset.  No 64-bit lane addresses to keep or to advance.  N is a multiple
-    // of the tile (choose_tile); token rows past M read as zeros through the descriptor and are not stored.
+    // chunk inside a pass) and everything else is scalar.  No 64-bit lane addresses to keep or to advance.
+    //   tokens: a descriptor per pass that starts at the pass's first row and ends with row M - 1, the K-step as scalar offset.
+    //     Rows past M read as zeros: their lane offset lies outside the descriptor.  (The bounds check sees the lane offset
+    //     for certain, the scalar offset by the hardware's leave, so no row may be in the scalar offset.)
+    //   weights: a descriptor of the whole matrix, the pass's row and the K-step as scalar offset; N is a multiple of the
+    //     tile (choose_tile), every row exists.
     constexpr int RP = NT / CPR;   // tile rows per pass
-    uint32_t sa[LA];   // byte offset of pass i's first row in its matrix
-    uint32_t sb[LB];
+    rsrc_t rA[LA];
+    uint32_t sb[LB];   // byte offset of pass i's first row in its matrix
     const uint32_t voff = (uint32_t)(trow * g.K + kc8) * 2u;
-    const rsrc_t rA = make_rsrc(g.A, (int64_t)g.M * g.K * 2);
     rsrc_t rW[2] = {make_rsrc(g.W0, weight_rows<EPI>(g) * g.K * 2),
                     make_rsrc(EPI == EPI_QKV || EPI == EPI_SWIGLU ? g.W1 : g.W0, weight_rows<EPI>(g) * g.K * 2)};
     // which descriptor pass i of the weight tile reads: gate | up alternate inside a tile (compile-time), q | k is per tile
@@ -350,7 +351,10 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_bf16(const GemmArgs g
         m0 = (rem / gw) * BM;
         n0 = tile_n * BN;
 #pragma unroll
-        for (int i = 0; i < LA; ++i) sa[i] = (uint32_t)((m0 + i * RP) * g.K) * 2u;
+        for (int i = 0; i < LA; ++i) {
+            const int row = m0 + i * RP, left = g.M - row;
+            rA[i] = make_rsrc(g.A + (int64_t)row * g.K, left > 0 ? (int64_t)left * g.K * 2 : 0);
+        }
 #pragma unroll
         for (int i = 0; i < LB; ++i) {
             int which;
@@ -365,7 +369,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_bf16(const GemmArgs g
     u32x4 ra[LA], rb[LB];
     auto gload = [&](int kt) {
 #pragma unroll
-        for (int i = 0; i < LA; ++i) ra[i] = bload(rA, voff, sa[i] + kt * (BK * 2));
+        for (int i = 0; i < LA; ++i) ra[i] = bload(rA[i], voff, kt * (BK * 2));
 #pragma unroll
         for (int i = 0; i < LB; ++i) rb[i] = bload(wsel(i), voff, sb[i] + kt * (BK * 2));
     };
@@ -459,7 +463,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_bf16(const GemmArgs g
                 constexpr int i = decltype(ic)::value;
                 if constexpr (i < LA) {
                     *reinterpret_cast<u32x4*>(na + i * RP * LDS_STRIDE) = ra[i];
-                    ra[i] = bload(rA, voff, sa[i] + (kt + 2) * (BK * 2));
+                    ra[i] = bload(rA[i], voff, (kt + 2) * (BK * 2));
                 } else {
                     constexpr int j = i - LA;
                     *reinterpret_cast<u32x4*>(nb + j * RP * LDS_STRIDE) = rb[j];
@@ -1181,7 +1185,7 @@ inline int whole_columns(const GemmArgs& g) {
 template <int EPI>
 int choose_tile(const GemmArgs& g) {
     const int seg = EPI == EPI_QKV ? g.d : g.N;                       // a tile must not straddle two of q | k | v
-    const bool whole256 = g.N % 256 == 0 && seg % 256 == 0 && (int64_t)g.M * g.K * 2 < (1ll << 31) &&   // 32-bit offsets
+    const bool whole256 = g.N % 256 == 0 && seg % 256 == 0 && (int64_t)g.M * g.K * 2 < (1ll << 31) &&   // 32-bit sizes and offsets
                           weight_rows<EPI>(g) * g.K * 2 < (1ll << 31);
     int best = -1;
     float best_us = 0.f;
