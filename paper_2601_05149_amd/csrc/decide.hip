@@ -832,16 +832,18 @@ __global__ __launch_bounds__(TPB) void k_island_draw(const float* __restrict__ l
 }
 
 // ---- rejection islands (Eq. 8): 8-connected components of the marked set, one workgroup per sequence ----
-// Latency is all there is here (a block of labels, no memory traffic), so every phase is a constant number of passes
-// with one position per thread, whatever the shape of the islands:
+// Latency is all there is here (a block of labels, no memory traffic), so the phases are few, with one position per thread
+// (of 1024; longer blocks take strided passes):
 //   union-find in LDS: lab[t] names a marked position of t's island that is not after t (unmarked: -1); a position is
 //     linked to its earlier neighbours (left and the three above) by atomicMin on the larger root, so an island's root
 //     is its smallest position; every find descends strictly, so every loop ends;
 //   members per (segment of the block, island) by atomics, their prefix over the segments, islands and largest island;
 //   ranks: a wavefront per segment walks its 64-position chunks in order; a ballot per island present in the chunk
 //     ranks its members, a counter per (segment, island) carries on to the next chunk.
-// 2 sequences of 1024 positions, nearly all marked: 97 us with min-label rounds and a scan of the island per position,
-// now 6 us.
+// What is not constant: a find follows the links it meets; a chunk takes a step per island in it; the counters of a segment are
+// L integers of LDS, so 16 wavefronts share the walk of 1024 positions, 8 that of 4096 and one that of 16384.
+// Us, min-label rounds and a scan of the island per position / this: 1024 positions, nothing marked 5.3 / 5.4 (a launch), 0.3 % 62 / 5.4,
+// half 201 / 9.9, all 167 / 8.4; 16384 positions, nothing marked 19.5 / 6.1, 2 % 22000 / 88, half 38000 / 153.
 constexpr int ISL_TPB = 1024;
 constexpr int ISL_LDS = 160 * 1024 - 256;
 __global__ __launch_bounds__(ISL_TPB) void k_islands(const uint8_t* __restrict__ mask, int32_t* __restrict__ island,
@@ -849,14 +851,31 @@ __global__ __launch_bounds__(ISL_TPB) void k_islands(const uint8_t* __restrict__
                                                      int n0, int L, int segs) {
     extern __shared__ int lab[];   // [L]
     int* const cnt = lab + L;      // [segs][L], by root
-    __shared__ int n_isl, largest;
+    __shared__ int n_isl, largest, some[ISL_TPB / 64];
     const int b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wv = tid >> 6;
     const uint8_t* mk = mask + (int64_t)b * L;
     const int seg_len = ((L + segs - 1) / segs + 63) / 64 * 64;
     if (tid == 0) n_isl = largest = 0;
-    for (int t = tid; t < L; t += nt) lab[t] = mk[t] ? t : -1;
+    int marked = 0;
+    for (int t = tid; t < L; t += nt) {
+        const int m = mk[t];
+        marked |= m;
+        lab[t] = m ? t : -1;
+    }
     for (int i = tid; i < segs * L; i += nt) cnt[i] = 0;
+    const unsigned long long in_wave = __ballot(marked != 0);
+    if (lane == 0) some[wv] = in_wave != 0;
     __syncthreads();
+    int any = 0;
+    for (int i = 0; i < (nt >> 6); ++i) any |= some[i];
+    if (!any) {   // nothing is marked: the walk below would still visit every position (39 us for 16384)
+        for (int t = tid; t < L; t += nt) {
+            island[(int64_t)b * L + t] = 0;
+            rank[(int64_t)b * L + t] = -1;
+        }
+        if (tid < 2) counts[b * 2 + tid] = 0;
+        return;
+    }
     volatile int* const vl = lab;
     auto find = [&](int x) {   // halves the path on its way: a position that is no root keeps being none, any ancestor will do for it
         for (int p = vl[x]; p != x; p = vl[x]) {

@@ -423,7 +423,8 @@ def test_rejection_islands_parity():
 @pytest.mark.parametrize("W,rows", [(64, 256), (128, 64), (61, 51), (1, 130), (130, 1), (3, 1)])
 def test_rejection_islands_at_the_sizes_of_the_counters(W, rows):
     """The largest block (one set of member counters in LDS), half of it, an odd one whose segments end inside a row, and
-    grids of one column or one row, each sparse, dense, full, a checkerboard (one island by its diagonals) and a spiral."""
+    grids of one column or one row, each sparse, dense, full, a checkerboard (one island by its diagonals), a spiral, empty,
+    and with one position marked, the last."""
     from oracle import local as LOC
     L = W * rows
     ctx = decide_ctx(1024, 4, 1024)
@@ -436,9 +437,10 @@ def test_rejection_islands_at_the_sizes_of_the_counters(W, rows):
         spiral[r0 + 1, c0] = False
         spiral[r0 + 2 if r0 + 2 < rows else r0, min(c0 + 1, W - 1)] = True
         r0, r1, c0, c1 = r0 + 2, r1 - 2, c0 + 2, c1 - 2
-    mask = np.stack([rng.random(L) < 0.1, rng.random(L) < 0.45, np.ones(L, bool), (i + j) % 2 == 0, spiral.reshape(-1)])
+    mask = np.stack([rng.random(L) < 0.1, rng.random(L) < 0.45, np.ones(L, bool), (i + j) % 2 == 0, spiral.reshape(-1),
+                     np.zeros(L, bool), np.arange(L) == L - 1])
     isl, rk, cnt = _islands_gpu(ctx, mask, W, 0)
-    for b in range(5):
+    for b in range(len(mask)):
         ri, rr, n, largest = LOC.rejection_islands(mask[b], W, 0)
         assert np.array_equal(isl[b], ri) and np.array_equal(rk[b], rr) and cnt[b].tolist() == [n, largest], (W, rows, b)
 
