@@ -733,18 +733,6 @@ void run_gemm(GemmArgs g, int tile_n0, int tiles_n, hipStream_t st) {
     hipLaunchKernelGGL(kern, dim3(total < resident ? total : resident), dim3(WGM * WGN * 64), lds, st, g);
 }
 
-template <int BM, int BN, int WGM, int WGN, int NS, int EPI, bool PAIRED = false>
-void run_ring(GemmArgs g, hipStream_t st) {
-    auto kern = k_gemm_ring<BM, BN, WGM, WGN, NS, EPI, PAIRED>;
-    const size_t lds = (size_t)NS * (BM + BN) * 128;
-    static int attr_state = 0;
-    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds, &attr_state)) return;
-    g.tiles_n = (g.N + BN - 1) / BN;
-    g.tile_n0 = 0;
-    const int64_t total = (int64_t)((g.M + BM - 1) / BM) * g.tiles_n;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(WGM * WGN * 64), lds, st, g);
-}
-
 // Epilogue of the weight-streaming kernels on two adjacent output columns n, n + 1 of token m (v1: the up sums of
 // gate|up).  The same five fused epilogues as the tiled kernels; a bf16 operand of a following projection is written
 // in fragment order.
@@ -1159,19 +1147,31 @@ __global__ __launch_bounds__(256) void k_pack_weights(const bf16* __restrict__ s
 
 // ---- which tile a launch runs on ----
 // Every tile adds the same products in the same order, so the choice is about time alone.  Time of a launch of T tiles on
-// S = (workgroups per CU) x CUs places: c0 + e per round + (K / 64) x (tf per full round; a last round of r tiles between
-// t0, where few CUs fetch, and tf: t0 + (tf - t0) r / S).  The constants (us) are the least-squares fit over 18 token
-// counts from 72 to 4096 and the ten projection shapes of the two bf16 configurations (widths 1024 and 4096), cold
-// weights: rms error 9 to 13 %; over that grid the tile it picks takes 2 % longer than the best of each shape, and 1.40
-// times less than the rule before it (256 x 256 tiles from 1024 tokens in whole tiles on, 128 x 256 where their rounds
-// were 80 % full, else 128 x 128 staged through registers).
-struct TileCost { int bm, bn, per_cu; float c0, tf, t0, e; };
+// S = per_cu x CUs places: c0 + e per round + (K / 64) x (tf per full round; a last round of r tiles between
+// t0, where few CUs fetch, and tf: t0 + (tf - t0) r / S).  per_cu is what the LDS holds, but 1 for 32 x 64, of which two fit:
+// with 257 tiles the CU that has two of them takes twice the bytes, and the fit knows (4096 x 4096: 128 tokens, 256 tiles, 18 us
+// against 22 on 64 x 64; 256 tokens, 512 tiles, 28 against 23).  The constants (us) are the least-squares fit over 18 token
+// counts from 72 to 4096 and the ten projection shapes of the two bf16 configurations (widths 1024 and 4096; no other width
+// was timed), cold weights: rms error 9 to 14 %; over that grid the tile it picks takes 2 % longer than the best of each
+// shape, and 1.40 times less than the rule before it (256 x 256 tiles from 1024 tokens in whole tiles on, 128 x 256 where
+// their rounds were 80 % full, else 128 x 128 staged through registers).
+struct TileCost {
+    int bm, bn, stages, per_cu;   // ring stages of bm + bn rows of 128 bytes; 256 x 256: two padded buffers (144 bytes a row)
+    float c0, tf, t0, e;
+    constexpr int fit() const { return 160 * 1024 / (stages * (bm + bn) * (bm == 256 && bn == 256 ? 144 : 128)); }
+};
 enum { TILE_32x64, TILE_64x64, TILE_128x64, TILE_64x128, TILE_128x128, TILE_256x128, TILE_128x256, TILE_256x256, N_TILES };
 constexpr TileCost TILE_COST[N_TILES] = {
-    {32, 64, 3, 3.3f, 0.480f, 0.095f, -0.3f},   {64, 64, 2, 2.7f, 0.435f, 0.146f, 0.1f},
-    {128, 64, 2, 2.3f, 0.683f, 0.271f, 1.2f},   {64, 128, 2, 4.2f, 0.723f, 0.311f, -1.1f},
-    {128, 128, 1, 2.7f, 0.538f, 0.407f, 2.4f},  {256, 128, 1, 2.6f, 0.856f, 0.56f, 4.6f},
-    {128, 256, 1, 3.9f, 0.925f, 0.67f, 2.6f},   {256, 256, 1, 6.7f, 1.544f, 1.011f, 4.4f}};
+    {32, 64, 6, 1, 3.4f, 0.161f, 0.107f, -0.1f},   {64, 64, 5, 2, 2.7f, 0.435f, 0.146f, 0.1f},
+    {128, 64, 3, 2, 2.3f, 0.683f, 0.271f, 1.2f},   {64, 128, 3, 2, 4.2f, 0.723f, 0.311f, -1.1f},
+    {128, 128, 5, 1, 2.7f, 0.538f, 0.407f, 2.4f},  {256, 128, 3, 1, 2.6f, 0.856f, 0.56f, 4.6f},
+    {128, 256, 3, 1, 3.9f, 0.925f, 0.67f, 2.6f},   {256, 256, 2, 1, 6.7f, 1.544f, 1.011f, 4.4f}};
+constexpr bool tiles_fit() {
+    for (int i = 0; i < N_TILES; ++i)
+        if (TILE_COST[i].fit() != (i == TILE_32x64 ? 2 : TILE_COST[i].per_cu)) return false;
+    return true;
+}
+static_assert(tiles_fit(), "the constants were fitted with these");
 
 // Column tiles of a 256 x 256 launch that run as such: a last round that would leave more than half of the CUs idle is
 // cut off and runs as 128 x 256 tiles (twice as many workgroups, half the work each).
@@ -1212,6 +1212,19 @@ int choose_tile(const GemmArgs& g) {
     return best;
 }
 
+template <int TILE, int WGM, int WGN, int EPI, bool PAIRED = false>
+void run_ring(GemmArgs g, hipStream_t st) {
+    constexpr int BM = TILE_COST[TILE].bm, BN = TILE_COST[TILE].bn, NS = TILE_COST[TILE].stages;
+    auto kern = k_gemm_ring<BM, BN, WGM, WGN, NS, EPI, PAIRED>;
+    const size_t lds = (size_t)NS * (BM + BN) * 128;
+    static int attr_state = 0;
+    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds, &attr_state)) return;
+    g.tiles_n = (g.N + BN - 1) / BN;
+    g.tile_n0 = 0;
+    const int64_t total = (int64_t)((g.M + BM - 1) / BM) * g.tiles_n;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(WGM * WGN * 64), lds, st, g);
+}
+
 // returns whether the softmax parts were written (LOGITS, wavefront tiles of 128 whole columns)
 template <int EPI>
 bool dispatch(const GemmArgs& g0, hipStream_t st) {
@@ -1224,18 +1237,18 @@ bool dispatch(const GemmArgs& g0, hipStream_t st) {
     const bool parts = EPI == EPI_LOGITS && g.parts && TILE_COST[tile].bn == 256 && g.N % 256 == 0;
     if (!parts) g.parts = nullptr;
     switch (tile) {
-        case TILE_32x64: if constexpr (EPI != EPI_SWIGLU) run_ring<32, 64, 1, 2, 6, EPI>(g, st); break;
-        case TILE_64x64: if constexpr (EPI != EPI_SWIGLU) run_ring<64, 64, 2, 2, 5, EPI>(g, st); break;
-        case TILE_128x64: if constexpr (EPI != EPI_SWIGLU) run_ring<128, 64, 2, 2, 3, EPI>(g, st); break;
-        case TILE_64x128: if constexpr (EPI == EPI_SWIGLU) run_ring<64, 128, 2, 2, 3, EPI>(g, st); break;
-        case TILE_128x128: run_ring<128, 128, 2, 2, 5, EPI, true>(g, st); break;
+        case TILE_32x64: if constexpr (EPI != EPI_SWIGLU) run_ring<TILE_32x64, 1, 2, EPI>(g, st); break;
+        case TILE_64x64: if constexpr (EPI != EPI_SWIGLU) run_ring<TILE_64x64, 2, 2, EPI>(g, st); break;
+        case TILE_128x64: if constexpr (EPI != EPI_SWIGLU) run_ring<TILE_128x64, 2, 2, EPI>(g, st); break;
+        case TILE_64x128: if constexpr (EPI == EPI_SWIGLU) run_ring<TILE_64x128, 2, 2, EPI>(g, st); break;
+        case TILE_128x128: run_ring<TILE_128x128, 2, 2, EPI, true>(g, st); break;
         case TILE_256x128:   // 4 wavefronts of 128 x 64 (1980 x 4096 x 11008: 152 us against 157 with 8 of 64 x 64), q|k|v and lm-head 8
-            if constexpr (EPI == EPI_SWIGLU || EPI == EPI_RESID) run_ring<256, 128, 2, 2, 3, EPI>(g, st);
-            else run_ring<256, 128, 4, 2, 3, EPI>(g, st);
+            if constexpr (EPI == EPI_SWIGLU || EPI == EPI_RESID) run_ring<TILE_256x128, 2, 2, EPI>(g, st);
+            else run_ring<TILE_256x128, 4, 2, EPI>(g, st);
             break;
         case TILE_128x256:
-            if constexpr (EPI == EPI_SWIGLU || EPI == EPI_LOGITS) run_ring<128, 256, 2, 2, 3, EPI>(g, st);
-            else run_ring<128, 256, 2, 4, 3, EPI>(g, st);
+            if constexpr (EPI == EPI_SWIGLU || EPI == EPI_LOGITS) run_ring<TILE_128x256, 2, 2, EPI>(g, st);
+            else run_ring<TILE_128x256, 2, 4, EPI>(g, st);
             break;
         default: {
             const int tiles_n = g.N / 256, n_main = whole_columns(g);
