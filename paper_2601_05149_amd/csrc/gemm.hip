@@ -1182,18 +1182,24 @@ inline int whole_columns(const GemmArgs& g) {
     return (tiles_n - n) * tiles_m * 2 > cus ? tiles_n : n;   // the cut-off part must fit one round
 }
 
+// which tiles a projection has
+template <int EPI>
+bool has_tile(const GemmArgs& g, int i) {
+    const int seg = EPI == EPI_QKV ? g.d : g.N;                           // a tile must not straddle two of q | k | v
+    if (i == TILE_256x256 && !(g.N % 256 == 0 && seg % 256 == 0 && (int64_t)g.M * g.K * 2 < (1ll << 31) &&   // 32-bit sizes and offsets
+                               weight_rows<EPI>(g) * g.K * 2 < (1ll << 31)))
+        return false;
+    if (EPI == EPI_QKV && seg % TILE_COST[i].bn) return false;
+    return EPI == EPI_SWIGLU ? i != TILE_32x64 && i != TILE_64x64 && i != TILE_128x64 : i != TILE_64x128;
+}
+
 template <int EPI>
 int choose_tile(const GemmArgs& g) {
-    const int seg = EPI == EPI_QKV ? g.d : g.N;                       // a tile must not straddle two of q | k | v
-    const bool whole256 = g.N % 256 == 0 && seg % 256 == 0 && (int64_t)g.M * g.K * 2 < (1ll << 31) &&   // 32-bit sizes and offsets
-                          weight_rows<EPI>(g) * g.K * 2 < (1ll << 31);
     int best = -1;
     float best_us = 0.f;
     for (int i = 0; i < N_TILES; ++i) {
         const TileCost& t = TILE_COST[i];
-        if (i == TILE_256x256 && !whole256) continue;
-        if (EPI == EPI_QKV && seg % t.bn) continue;
-        if (EPI == EPI_SWIGLU ? (i == TILE_32x64 || i == TILE_64x64 || i == TILE_128x64) : i == TILE_64x128) continue;
+        if (!has_tile<EPI>(g, i)) continue;
         const int64_t places = (int64_t)t.per_cu * cu_count();
         int64_t tiles = (int64_t)((g.M + t.bm - 1) / t.bm) * ((g.N + t.bn - 1) / t.bn);
         float us = t.c0;
@@ -1227,13 +1233,15 @@ void run_ring(GemmArgs g, hipStream_t st) {
 
 // returns whether the softmax parts were written (LOGITS, wavefront tiles of 128 whole columns)
 template <int EPI>
-bool dispatch(const GemmArgs& g0, hipStream_t st) {
-    if (g0.stream) {   // a handful of tokens: stream the weights (A is in fragment order)
-        run_gemv<EPI>(g0, st);
+bool dispatch(GemmArgs g, const StreamMode& sm, hipStream_t st) {
+    g.stream = sm.stream; g.w_frag = sm.w_frag; g.ksums = sm.ksums;
+    *sm.ran = -1;
+    if (g.stream) {   // a handful of tokens: stream the weights (A is in fragment order)
+        run_gemv<EPI>(g, st);
         return false;
     }
-    GemmArgs g = g0;
-    const int tile = choose_tile<EPI>(g);
+    const int tile = sm.tile >= 0 && sm.tile < N_TILES && has_tile<EPI>(g, sm.tile) ? sm.tile : choose_tile<EPI>(g);
+    *sm.ran = tile;
     const bool parts = EPI == EPI_LOGITS && g.parts && TILE_COST[tile].bn == 256 && g.N % 256 == 0;
     if (!parts) g.parts = nullptr;
     switch (tile) {
@@ -1275,37 +1283,33 @@ int cu_count() {
 void launch_gemm_qkv_bf16(const void* xh, const void* wq, const void* wk, const void* wv, void* q_out,
                           void* k_cache, void* v_cache, int M, int d, const RopeArgs& ra, const StreamMode& sm, hipStream_t st) {
     GemmArgs g{};
-    g.stream = sm.stream; g.w_frag = sm.w_frag; g.ksums = sm.ksums;
     g.A = (const bf16*)xh; g.W0 = (const bf16*)wq; g.W1 = (const bf16*)wk;
     g.M = M; g.N = 3 * d; g.K = d; g.Cb = (bf16*)q_out; g.kc = (bf16*)k_cache; g.d = d; g.ra = ra;
     g.W2 = (const bf16*)wv; g.vc = (bf16*)v_cache;
-    dispatch<EPI_QKV>(g, st);
+    dispatch<EPI_QKV>(g, sm, st);
 }
 
 void launch_gemm_resid_bf16(const void* a, const void* w, float* x, int M, int N, int K, const StreamMode& sm, hipStream_t st) {
     GemmArgs g{};
-    g.stream = sm.stream; g.w_frag = sm.w_frag; g.ksums = sm.ksums;
     g.A = (const bf16*)a; g.W0 = (const bf16*)w; g.M = M; g.N = N; g.K = K; g.Cf = x;
-    dispatch<EPI_RESID>(g, st);
+    dispatch<EPI_RESID>(g, sm, st);
 }
 
 void launch_gemm_swiglu_bf16(const void* xh, const void* wg, const void* wu, void* h, int M, int f, int d,
                              const StreamMode& sm, hipStream_t st) {
     GemmArgs g{};
-    g.stream = sm.stream; g.w_frag = sm.w_frag; g.ksums = sm.ksums;
     g.A = (const bf16*)xh; g.W0 = (const bf16*)wg; g.W1 = (const bf16*)wu; g.M = M; g.N = 2 * f; g.K = d;
     g.Cb = (bf16*)h;
-    dispatch<EPI_SWIGLU>(g, st);
+    dispatch<EPI_SWIGLU>(g, sm, st);
 }
 
 bool launch_gemm_logits_bf16(const void* xh, const void* w, float* logits, float* parts, int M, int V, int d,
                              const StreamMode& sm, hipStream_t st) {
     GemmArgs g{};
-    g.stream = sm.stream; g.w_frag = sm.w_frag; g.ksums = sm.ksums;
     g.A = (const bf16*)xh; g.W0 = (const bf16*)w; g.M = M; g.N = V; g.K = d; g.Cf = logits;
     g.parts = reinterpret_cast<float2*>(parts);
     g.n_parts = (V + rowparts::PART - 1) / rowparts::PART;
-    return dispatch<EPI_LOGITS>(g, st) && parts != nullptr;
+    return dispatch<EPI_LOGITS>(g, sm, st) && parts != nullptr;
 }
 
 void launch_pack_weights(const void* src, void* dst, int layers, int rows, int K, hipStream_t st) {

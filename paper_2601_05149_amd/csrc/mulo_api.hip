@@ -63,6 +63,8 @@ struct mulo_ctx {
     // (same layer strides as the caller's, the lm-head padded to whole groups of 16 rows); nullptr without the copy
     const char *pk_wq, *pk_wk, *pk_wv, *pk_wo, *pk_gate, *pk_up, *pk_down, *pk_lm;
     float* ksums;        // with the copy: sums of the K slices of a 65..256-token launch's projections
+    int32_t tile = -1;   // mulo_internal_tiles
+    int32_t tiles_ran[5] = {-1, -1, -1, -1, -1};
     void* base;      // single allocation
     // optional per-launch timing (mulo_profile)
     bool prof_on = false;
@@ -194,7 +196,7 @@ bool enqueue_forward(mulo_ctx* c, mulo_kv* kv, int B, int L, int P, const int32_
     const bool has_copy = c->pk_wq != nullptr;
     const bool frag = dt == MULO_BF16 && M <= (has_copy ? STREAM_MAX_TOKENS_COPY : STREAM_MAX_TOKENS);
     const bool wfrag = frag && has_copy;
-    const StreamMode sm{frag, wfrag, wfrag ? c->ksums : nullptr};
+    auto sm = [&](int projection) { return StreamMode{frag, wfrag, wfrag ? c->ksums : nullptr, c->tile, &c->tiles_ran[projection]}; };
     { PROF(MULO_PROF_NORM_EMBED); launch_embed(c->w.embed, dt, tok, emb, c->x, M, d, V, st); }
     for (int l = 0; l < m.n_layers; ++l) {
         RopeArgs ra{c->w.rope_cos, c->w.rope_sin, L, P, m.n_heads, m.head_dim, m.max_seq, m.max_batch, l};
@@ -211,16 +213,16 @@ bool enqueue_forward(mulo_ctx* c, mulo_kv* kv, int B, int L, int P, const int32_
         const char* g_ffn = (const char*)c->w.ffn_norm + (size_t)l * d * e;
         if (dt == MULO_BF16) {
             { PROF(MULO_PROF_NORM_EMBED); launch_rmsnorm(c->x, g_attn, dt, c->xh, M, d, m.rms_eps, frag, st); }
-            { PROF(MULO_PROF_GEMM_QKV); launch_gemm_qkv_bf16(c->xh, wq, wk, wv, c->qbuf, kv->k, kv->v, M, d, ra, sm, st); }
+            { PROF(MULO_PROF_GEMM_QKV); launch_gemm_qkv_bf16(c->xh, wq, wk, wv, c->qbuf, kv->k, kv->v, M, d, ra, sm(0), st); }
             { PROF(MULO_PROF_ATTENTION);
               if (sc) launch_attention_scattered_bf16(c->qbuf, kv->k, kv->v, c->att, c->attn_part, B, sc->pos_tab, L, sc->hide,
                                                       sc->P0, sc->Lblk, m.n_heads, m.head_dim, m.max_seq, m.max_batch, l, frag, st);
               else launch_attention_bf16(c->qbuf, kv->k, kv->v, c->att, c->attn_part, B, L, P, m.n_heads, m.head_dim,
                                          m.max_seq, m.max_batch, l, frag, st); }
-            { PROF(MULO_PROF_GEMM_OUT); launch_gemm_resid_bf16(c->att, wo, c->x, M, d, d, sm, st); }
+            { PROF(MULO_PROF_GEMM_OUT); launch_gemm_resid_bf16(c->att, wo, c->x, M, d, d, sm(1), st); }
             { PROF(MULO_PROF_NORM_EMBED); launch_rmsnorm(c->x, g_ffn, dt, c->xh, M, d, m.rms_eps, frag, st); }
-            { PROF(MULO_PROF_GEMM_GATE_UP); launch_gemm_swiglu_bf16(c->xh, wg, wu, c->hmid, M, f, d, sm, st); }
-            { PROF(MULO_PROF_GEMM_DOWN); launch_gemm_resid_bf16(c->hmid, wd, c->x, M, d, f, sm, st); }
+            { PROF(MULO_PROF_GEMM_GATE_UP); launch_gemm_swiglu_bf16(c->xh, wg, wu, c->hmid, M, f, d, sm(2), st); }
+            { PROF(MULO_PROF_GEMM_DOWN); launch_gemm_resid_bf16(c->hmid, wd, c->x, M, d, f, sm(3), st); }
         } else {
             { PROF(MULO_PROF_GEMM_QKV);
               launch_qkv_f32(c->x, (const float*)g_attn, m.rms_eps, (const float*)wq, (const float*)wk, (const float*)wv,
@@ -236,7 +238,7 @@ bool enqueue_forward(mulo_ctx* c, mulo_kv* kv, int B, int L, int P, const int32_
     }
     { PROF(MULO_PROF_NORM_EMBED); launch_rmsnorm(c->x, c->w.final_norm, dt, c->xh, M, d, m.rms_eps, frag, st); }
     PROF(MULO_PROF_GEMM_LM_HEAD);
-    if (dt == MULO_BF16) return launch_gemm_logits_bf16(c->xh, wfrag ? (const void*)c->pk_lm : c->w.lm_head, logits, want_parts ? c->row_parts : nullptr, M, V, d, sm, st);
+    if (dt == MULO_BF16) return launch_gemm_logits_bf16(c->xh, wfrag ? (const void*)c->pk_lm : c->w.lm_head, logits, want_parts ? c->row_parts : nullptr, M, V, d, sm(4), st);
     launch_logits_f32((const float*)c->xh, (const float*)c->w.lm_head, logits, M, V, d, st);
     return false;
 }
@@ -448,6 +450,16 @@ mulo_status mulo_workspace_read(mulo_ctx* ctx, int32_t which, void* dst, uint64_
     if ((bytes & 15) || bytes > cap) return MULO_ERR_SHAPE;
     launch_copy_rows((const float*)src, (float*)dst, (int64_t)(bytes / 4), ctx->st);
     return check_launch();
+}
+
+// For the tests of the tiled kernels, and not part of the interface (mulo.h does not declare it): the projections of this
+// context's following bf16 calls run on `tile` (index into gemm.hip's table) where they have it, -1: on the rule's choice.
+// ran: nullptr, or receives the tiles of the last call's q|k|v, out, gate|up, down and lm-head (-1: weight-streaming).
+MULO_API mulo_status mulo_internal_tiles(mulo_ctx* ctx, int32_t tile, int32_t* ran) {
+    if (!ctx) return MULO_ERR_NULL;
+    ctx->tile = tile;
+    for (int i = 0; ran && i < 5; ++i) ran[i] = ctx->tiles_ran[i];
+    return MULO_OK;
 }
 
 mulo_status mulo_profile(mulo_ctx* ctx, int32_t enable) {

@@ -35,7 +35,10 @@ constexpr int STREAM_MAX_TOKENS_COPY = 256;
 //   stream  the token operands are in fragment order and the projections run in the weight-streaming kernels
 //   w_frag  the weight pointers are the context's copies in fragment order
 //   ksums   scratch for the sums of the K slices (stream_ksum_floats) when w_frag, else nullptr
-struct StreamMode { bool stream, w_frag; float* ksums; };
+// and, for the tests of the tiled kernels, which tile a launch that does not stream runs on:
+//   tile    index into the tile table (gemm.hip), taken where the projection has it; -1: the rule's choice
+//   ran     host variable that receives the tile (-1: streamed)
+struct StreamMode { bool stream, w_frag; float* ksums; int tile; int32_t* ran; };
 // K slices per 128-column group in the LDS-sharing kernel: as many as keep the launch within one round of 256
 // workgroups, at most 8, at least 8 k-steps each.  A function of the projection's shape only, so the order of every
 // sum is fixed by the model.

@@ -7,6 +7,8 @@ the device; every pass is held to the oracle's own rounding noise (see
 tests.gpu_util.check_bf16_logits): bf16 rounding makes the forward chaotic, and
 the stated max |logit error| <= 2e-2 lies below that noise except for shallow
 models at the small width, where it is asserted as well."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -74,7 +76,9 @@ def test_forward_tiny_f32():
     (2, 64, 176, 128, 3, 33, 31),     # whole blocks of the head, keys ending on a tile edge
     (2, 128, 90, 64, 1, 16, 49),      # the widest head of the tiled attention
     (1, 136, 64, 64, 2, 5, 7),        # wider: one workgroup per query
-    (2, 16, 1030, 1028, 2, 1024, 0),  # more outputs than the split launches take: the 64 x 64 tiles, ragged columns, K of 1030
+    (2, 16, 1030, 1028, 2, 1024, 0),  # gate|up and lm-head on 32 x 32 tiles with ragged columns; down on 16 x 16 with a K of 1030
+    (17, 18, 310, 308, 2, 512, 9),    # every projection on 32 x 32 tiles, K of 306 and 310 (rows not 16-byte aligned), ragged columns
+    (5, 64, 320, 320, 2, 512, 7),     # the same with aligned rows
 ])
 def test_forward_f32_shapes(nh, dh, f, V, B, L, P):
     """The float32 projections and attention at the edges of their tiles.  Bar: 1e-4 as for the tiny configuration
@@ -164,16 +168,16 @@ def test_a_row_has_the_same_bits_in_every_block_of_more_than_128_queries(nh, dh)
 
 
 @pytest.mark.parametrize("d,nh,f,V", [
-    (768, 6, 8256, 1092),    # gate | up on every tile it has; K of 129 steps for down, a ragged last column tile for the lm-head
-    (768, 6, 704, 16384),    # the lm-head on every tile; K of 11 steps
-    (1024, 16, 2112, 1092),  # down on 128 x 128 tiles at the largest launch; K of 33 steps
+    (768, 6, 8256, 1092),    # gate | up on 64 x 128 and 128 x 256; K of 129 steps for down, a ragged last column tile for the lm-head
+    (768, 6, 704, 16384),    # the lm-head on 128 x 128, 128 x 256 and 256 x 256; K of 11 steps
+    (1024, 16, 2112, 1092),  # down on small tiles up to 128 x 64; K of 33 steps
     (128, 2, 192, 260),      # K of 2 and 3 steps, fewer than the ring has stages
 ])
 def test_every_tile_gives_the_same_sums(d, nh, f, V):
     """The projections of a launch run on the tile its sizes ask for; every tile adds the same products in the same order.
     One sequence alone (161 tokens, checked against the oracle) and as the first and last of launches of up to 2576
-    tokens (each projection changes its tile two to five times on the way; no count is a multiple of a tile): the same
-    logits and cache rows, bit for bit."""
+    tokens (no count is a multiple of a tile): the same logits and cache rows, bit for bit.  Which tiles that comes to
+    is the rule's choice; the test below runs each of them."""
     m = dict(n_layers=1, d_model=d, n_heads=nh, head_dim=d // nh, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
     L, P, S, Bmax = 161, 5, 168, 16
     w = G.make_weights(m, seed=21)
@@ -196,6 +200,63 @@ def test_every_tile_gives_the_same_sums(d, nh, f, V):
         for b in (0, B - 1):
             assert np.array_equal(z[b], one[0]), (B, b)
             assert torch.equal(kv[0][0, b, :, P:P + L], k1) and torch.equal(kv[1][0, b, :, :, P:P + L], v1), (B, b)
+
+
+TILES = [(32, 64), (64, 64), (128, 64), (64, 128), (128, 128), (256, 128), (128, 256), (256, 256)]
+
+
+def tiles_of(ctx, tile):
+    """The tiles the last call's projections ran on; those of the following calls run on `tile` where they have it."""
+    ran = (C.c_int32 * 5)()
+    lib = mulo.load_library()
+    lib.mulo_internal_tiles.argtypes = [C.c_void_p, C.c_int32, C.POINTER(C.c_int32)]
+    assert lib.mulo_internal_tiles(ctx.handle, tile, ran) == 0
+    return list(ran)
+
+
+@pytest.mark.parametrize("d,nh,f,V,B", [
+    (128, 2, 192, 260, (1, 5)),        # K of 2 steps (q|k|v, out, gate|up, lm-head) and 3 (down); ragged columns
+    (256, 4, 320, 1280, (1, 5)),       # 4 and 5; the lm-head and q|k|v on whole 256 x 256 tiles
+    (384, 3, 384, 516, (1, 5)),        # 6 and 6; half a tile of 256 columns for q|k|v, out and the lm-head
+    (768, 6, 1152, 1536, (1, 5)),      # 12 and 18; every projection has 256 x 256 tiles
+    (256, 2, 704, 6656, (16,)),        # 11 x 26 tiles of 256 x 256 for the lm-head: the last columns are cut off (128 x 256)
+])
+def test_every_projection_on_every_tile_it_has(d, nh, f, V, B):
+    """Each of q|k|v, out, gate|up, down and lm-head on each tile of the table that it has, against the rule's choice (which
+    the oracle checks for one sequence): the same logits, cache rows, bit for bit.  161 tokens a sequence: no launch is
+    a whole number of row tiles.  The rings see K from shorter than their stages to several times as long, the paired one
+    (128 x 128, five stages) every remainder of its loop: 2 to 6 steps."""
+    m = dict(n_layers=1, d_model=d, n_heads=nh, head_dim=d // nh, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
+    L, P, S = 161, 5, 168
+    w = G.make_weights(m, seed=23)
+    ctx, cos, sin = make_ctx(m, w, max(B), S, 164)
+    kv = mulo.alloc_kv(ctx, DEV)
+    pre = G.uniform_tokens((1, P), V, 23, tag=0)
+    gpu_forward(ctx, kv, pre, 0)
+    for t in kv:
+        t[:, 1:].copy_(t[:, :1].expand_as(t[:, 1:]))
+    widths = (3 * d, d, 2 * f, d, V)
+    for n in B:
+        toks = G.uniform_tokens((n, L), V, 23, tag=1)
+        base = gpu_forward(ctx, kv, toks, P)
+        if n == 1:
+            dr, du = pair(m, w, cos, sin, 1, S)
+            for t in (dr, du):
+                t.forward(pre, 0)
+            check_bf16_logits("width %d" % d, base, dr.forward(toks, P).numpy(), du.forward(toks, P).numpy())
+        k0, v0 = kv[0][:, :n, :, P:P + L].clone(), kv[1][:, :n, :, :, P:P + L].clone()
+        for i, (bm, bn) in enumerate(TILES):
+            tiles_of(ctx, i)
+            kv[0][:, :, :, P:].fill_(float("nan"))
+            kv[1][:, :, :, :, P:].fill_(float("nan"))
+            z = gpu_forward(ctx, kv, toks, P)
+            for p, t in enumerate(tiles_of(ctx, -1)):
+                whole = widths[p] % 256 == 0 and (p != 0 or d % 256 == 0)
+                has = (i not in (0, 1, 2) if p == 2 else i != 3) and (i != 7 or whole) and (p != 0 or d % bn == 0)
+                assert t == i or not has, (p, i, t)
+            assert np.array_equal(z, base), (n, i)
+            assert torch.equal(kv[0][:, :n, :, P:P + L], k0) and torch.equal(kv[1][:, :n, :, :, P:P + L], v0), (n, i)
+
 
 
 def test_forward_small_bf16_chained_blocks():
