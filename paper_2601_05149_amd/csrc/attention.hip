@@ -1,12 +1,12 @@
 // Causal attention of the drafted block over prefix + block (Alg. 1 Step 3: the
 // j-th conditional sees cache rows 0 .. P+j).
 //
-// bf16 path: flash-style, one workgroup of 8 wavefronts (two per SIMD) per (256
-// queries, head, sequence); K and V^T tiles of 128 keys are staged through LDS
-// (double buffered, 139 KB) and shared by the 8 wavefronts, so a tile is fetched and
-// written to LDS once per 256 queries and the per-tile work (barrier, running
-// maximum, rescale test) is spread over 32 MFMAs per product; each wavefront owns
-// 32 queries and computes
+// bf16 path: flash-style, one workgroup per (128 or 256 queries, head, sequence),
+// 8 wavefronts (two per SIMD) for 256; K and V^T tiles of 64 or 128 keys (run_attn's
+// rule) are staged through LDS (double buffered, 139 KB for 128 keys of a head of 128)
+// and shared by the wavefronts, so a tile is fetched and written to LDS once per
+// workgroup and the per-tile work (barrier, running maximum, rescale test) is spread
+// over up to 32 MFMAs per product; each wavefront owns 32 queries and computes
 // S^T = K Q^T and O^T = V^T P^T with v_mfma_f32_32x32x16_bf16, so that a lane
 // owns ONE query: the softmax row reductions stay inside the lane (plus one
 // cross-half shuffle), and the exponentiated scores are already laid out as the

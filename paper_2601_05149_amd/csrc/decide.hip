@@ -799,8 +799,9 @@ __global__ __launch_bounds__(TPB) void k_island_select(const int32_t* __restrict
     if (tid == 0 && cnt > cap && overflow) atomicAdd(overflow, cnt - cap);   // the caller's bound was too small
 }
 
-// one workgroup per slot: tokens[sequence, u] ~ softmax(logits[slot, :]) for the position u the slot holds.  The row is read
-// once into registers (V <= 1024 NV4; 0: re-read) for the statistics and the copy: 30 -> 13 us for 52 slots of 16384.
+// one workgroup per slot: tokens[sequence, u] ~ softmax(logits[slot, :]) for the position u the slot holds.  The row is copied
+// with 16-byte accesses and the statistics keep it in registers between their two passes (V <= 1024 NV4; 0: re-read); the copy,
+// the statistics and the draw each read it, the second and third time from the L2: 30 -> 13 us for 52 slots of 16384.
 template <int NV4>
 __global__ __launch_bounds__(TPB) void k_island_draw(const float* __restrict__ logits, const int32_t* __restrict__ pos_tab,
                                                      int32_t* __restrict__ tokens, float* __restrict__ logits_out, int L,
