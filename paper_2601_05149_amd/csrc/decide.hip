@@ -1073,6 +1073,7 @@ bool launch_accept(const DecideArgs& a, unsigned long long* sums, hipStream_t st
         if (a.V <= 2048) go(k_accept_sums<1>);
         else if (a.V <= 4096) go(k_accept_sums<2>);
         else if (a.V <= 8192) go(k_accept_sums<4>);
+        else if (a.V <= 12288) go(k_accept_sums<6>);   // 10004 entries, 1152 rows: 50 -> 45 us with 6 of 8 passes
         else go(k_accept_sums<8>);
         return true;
     }
