@@ -379,9 +379,9 @@ void run_attn_cfg(const AttnArgs& a, hipStream_t st) {
 
 // Blocks of more than SHORT_BLOCK queries run over 128-key tiles, shorter ones (single-token decoding above all) in 128-query
 // workgroups of 4 wavefronts over 64-key tiles, two per CU.  The two add in another order, so which one runs depends on the
-// block alone, never on the batch: a sequence launched alone gets the bits it gets in a batch, and a row gets the same bits
-// in every block of more than SHORT_BLOCK queries (the key split of a single token per sequence, L == 1, is the exception:
-// its number of shares follows the batch).
+// block alone, never on the batch: given the same operands a sequence launched alone gets the bits it gets in a batch, and a
+// row the same bits in every block of more than SHORT_BLOCK queries (the key split of a single token per sequence, L == 1, is
+// the exception: its number of shares follows the batch).
 // Over 128-key tiles a wavefront's 32 queries are added up by themselves, so the queries per workgroup do not show in the
 // bits: heads of 128 take 128 (4 wavefronts) where all of those have a CU, else 256 (8 wavefronts: one workgroup per CU
 // either way, 139 KB of LDS); heads of 64 take 128, two workgroups per CU.  Measured, 256 / 128 queries, us: heads of 128:

@@ -525,7 +525,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_bf16(const GemmArgs g
 // The direct load writes lane l's 16 bytes at 16 l, so a row cannot be padded against bank conflicts; instead chunk c
 // of row r sits at chunk position c ^ ((r / 2) % 8): 16 consecutive lanes of a fragment read, 16 rows 128 bytes apart,
 // then touch every bank once (no conflicts counted; with c ^ (r % 8) half of the LDS cycles were conflicts).
-// The k deal, hence every sum, is that of k_gemm_bf16 below, whatever the tile.
+// The k deal, hence every sum, is that of k_gemm_bf16 above, whatever the tile.
 // us per launch, before (128 x 128 tiles, staged through registers) -> here, cold weights: 186 tokens: 4096 x 4096
 // 36 -> 21, 4096 x 11008 83 -> 54, q|k|v 84 -> 40, gate|up 67 -> 58; 1024 tokens of width 1024: out 15 -> 6.6, down
 // 27 -> 12, q|k|v 27 -> 14; 1980 tokens of width 4096: out 73 -> 65, down 174 -> 152.
