@@ -1,6 +1,8 @@
 """Helpers of the GPU parity tests: build a device context from a workload,
 mirror the oracle's cache into the device layout, and compare decision outputs
 with the near-tie allowances the tolerances state."""
+import ctypes as C
+
 import numpy as np
 import torch
 
@@ -42,6 +44,19 @@ def device_weights(weights):
     if make:
         _DEVW[id(weights)] = (weights, {k: v.to(DEV) for k, v in weights.items()})
     return _DEVW[id(weights)][1]
+
+
+# rows x columns of the tiles of the bf16 projections, in the order of the library's table
+TILES = [(32, 64), (64, 64), (128, 64), (64, 128), (128, 128), (256, 128), (128, 256), (256, 256)]
+
+
+def tiles_of(ctx, tile):
+    """The tiles the last call's projections ran on; those of the following calls run on `tile` where they have it."""
+    ran = (C.c_int32 * 5)()
+    lib = mulo.load_library()
+    lib.mulo_internal_tiles.argtypes = [C.c_void_p, C.c_int32, C.POINTER(C.c_int32)]
+    assert lib.mulo_internal_tiles(ctx.handle, tile, ran) == 0
+    return list(ran)
 
 
 def dev(a, dtype=None):

@@ -7,15 +7,13 @@ the device; every pass is held to the oracle's own rounding noise (see
 tests.gpu_util.check_bf16_logits): bf16 rounding makes the forward chaotic, and
 the stated max |logit error| <= 2e-2 lies below that noise except for shallow
 models at the small width, where it is asserted as well."""
-import ctypes as C
-
 import numpy as np
 import pytest
 import torch
 
 import paper_2601_05149_amd as mulo
 from oracle import decoder as OD
-from tests.gpu_util import (DEV, check_bf16_logits, dev, device_weights, make_ctx, make_ctx_from_device, say)
+from tests.gpu_util import (DEV, TILES, check_bf16_logits, dev, device_weights, make_ctx, make_ctx_from_device, say, tiles_of)
 from workloads import configs as WC
 from workloads import generators as G
 
@@ -200,18 +198,6 @@ def test_every_tile_gives_the_same_sums(d, nh, f, V):
         for b in (0, B - 1):
             assert np.array_equal(z[b], one[0]), (B, b)
             assert torch.equal(kv[0][0, b, :, P:P + L], k1) and torch.equal(kv[1][0, b, :, :, P:P + L], v1), (B, b)
-
-
-TILES = [(32, 64), (64, 64), (128, 64), (64, 128), (128, 128), (256, 128), (128, 256), (256, 256)]
-
-
-def tiles_of(ctx, tile):
-    """The tiles the last call's projections ran on; those of the following calls run on `tile` where they have it."""
-    ran = (C.c_int32 * 5)()
-    lib = mulo.load_library()
-    lib.mulo_internal_tiles.argtypes = [C.c_void_p, C.c_int32, C.POINTER(C.c_int32)]
-    assert lib.mulo_internal_tiles(ctx.handle, tile, ran) == 0
-    return list(ran)
 
 
 @pytest.mark.parametrize("d,nh,f,V,B", [

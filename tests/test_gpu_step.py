@@ -10,7 +10,7 @@ import paper_2601_05149_amd as mulo
 from oracle import decoder as OD
 from oracle import resample as RS
 from oracle import step as ST
-from tests.gpu_util import DEV, check_bf16_logits, decide_buffers, make_ctx, say, to_np
+from tests.gpu_util import DEV, TILES, check_bf16_logits, decide_buffers, make_ctx, say, tiles_of, to_np
 from workloads import configs as WC
 from workloads import generators as G
 
@@ -292,3 +292,27 @@ def test_step_with_guidance_equals_its_composition_on_device():
     rep = compare_decisions(to_np(out), ref, thi.cpu().numpy(), q_lo.cpu().numpy(), q_row.cpu().numpy(), label="guided step")
     say("  guided step: acc %.3f marked %.3f %r" % (ref["accept"].mean(), ref["mask"].mean(), rep))
     assert not np.array_equal(z[:B], z[B:])
+
+
+@pytest.mark.parametrize("V,B", [(1280, 2), (6656, 16), (1284, 2)])
+def test_step_decides_alike_whatever_tile_the_lm_head_runs_on(V, B):
+    """Tiles of 256 whole columns leave the softmax statistics of a row with its logits (both of them: 128 x 256 in the ring,
+    256 x 256, and with 16 sequences its cut-off last columns), the others leave the accept test to read the logits: every
+    output of a step is the same bits, those of the three stages called one by one.  1284 columns: no tile leaves any."""
+    m = dict(n_layers=1, d_model=256, n_heads=4, head_dim=64, d_ffn=320, vocab=V, dtype="bf16", rms_eps=1e-5)
+    c = dict(H=12, W=16, w=8, r=2, L=160, radius=1, expand=1)
+    P, n_lo = 6, 40
+    ctx, _, _ = make_ctx(m, G.make_weights(m, seed=31), B, 176, 160)
+    kv = mulo.alloc_kv(ctx, DEV)
+    prefix = G.uniform_tokens((B, P), V, 31, tag=0)
+    mulo.mulo_verify_forward(ctx, kv, B, P, 0, torch.tensor(prefix, device=DEV), None, torch.empty(B, P, V, device=DEV))
+    dl = G.normal_logits((B, n_lo, V), 1.0, 31, tag=1)
+    dt = G.sample_categorical(dl, 31, tag=1)
+    base = gpu_composed(ctx, kv, c, P, 0, dl, dt, prefix[:, -1], 4)
+    assert 0 < int(base["accept"].sum()) < B * c["L"]
+    for i, (bm, bn) in enumerate(TILES):
+        tiles_of(ctx, i)
+        out = gpu_step(ctx, kv, c, P, 0, dl, dt, prefix[:, -1], 4)
+        lm = tiles_of(ctx, -1)[4]
+        assert lm == i or i == 3 or (i == 7 and V % 256), (i, lm)
+        assert_same(out, base)
