@@ -339,16 +339,18 @@ def test_guided_decide_parity(B, V, scale, amode):
 @pytest.mark.parametrize("V", [4, 260, 1028, 2048, 2052, 4096, 8196, 10004, 12288, 12292, 16384, 16388])
 @pytest.mark.parametrize("kw", [dict(radius=1), dict(radius=-1, resample_mode=1), dict(radius=0, resample_mode=2),
                                 dict(radius=2, resample_mode=1, pool=5), dict(radius=1, cfg_scale=3.0), dict(radius=0),
-                                dict(radius=1, accept_mode=1, tau=1e-3, resample_mode=2, cfg_scale=2.0)])
+                                dict(radius=1, accept_mode=1, tau=1e-3, resample_mode=2, cfg_scale=2.0),
+                                dict(radius=1, noise=0.1), dict(radius=2, resample_mode=1, noise=0.1)])
 def test_draw_from_chunk_sums_equals_the_draw_from_the_rows(V, kw):
-    """A bf16 context has room for the chunk sums, so its accept test leaves them for the draw where residual weights are
-    drawn from and the radius is not 0 (vocabularies up to 16384); the entry point without a context reads each marked
-    row again.  All outputs are the same bits: vocabularies at the edges of a chunk, of a lane's run of 8 and of the
-    registers, and in the residual settings rows whose draft distribution IS the target's (an empty residual, re-drawn
-    from p)."""
+    """A bf16 context has room for the chunk sums, so its accept test leaves them for the draw where Eq. 1 is tested without
+    pooling, residual weights are drawn from and the radius is not 0 (vocabularies up to 16384); the entry point without a
+    context reads each marked row again, and so does the context in the other settings.  All outputs are the same bits:
+    vocabularies at the edges of a chunk, of a lane's run of 8 and of the registers, drafts far from the target and close to
+    it (few rejected, many positions not marked), and in the residual settings rows whose draft distribution IS the
+    target's (an empty residual, re-drawn from p)."""
     kw = dict(kw)
     B, W, rows = 3, 8, 7
-    L, pool = W * rows, kw.pop("pool", 1)
+    L, pool, noise = W * rows, kw.pop("pool", 1), kw.pop("noise", 0.7)
     key = ("sums", V)
     if key not in _CTX:
         m = dict(n_layers=1, d_model=128, n_heads=2, head_dim=64, d_ffn=128, vocab=V, dtype="bf16", rms_eps=1e-5)
@@ -357,7 +359,7 @@ def test_draw_from_chunk_sums_equals_the_draw_from_the_rows(V, kw):
     g = torch.Generator(device=DEV).manual_seed(V + len(str(kw)))
     guided = kw.get("cfg_scale", 0.0) > 0
     z = torch.randn((2 if guided else 1) * B, L, V, generator=g, device=DEV).mul_(1.5)
-    q = torch.softmax(z[:B] + 0.7 * torch.randn(B, L, V, generator=g, device=DEV), dim=-1).contiguous()
+    q = torch.softmax(z[:B] + noise * torch.randn(B, L, V, generator=g, device=DEV), dim=-1).contiguous()
     toks = torch.randint(0, V, (B, L), generator=g, device=DEV, dtype=torch.int32)
     toks[:, ::2] = q.argmax(-1)[:, ::2].to(torch.int32)      # where the draft is surest the target is less so: rejections
     pp = torch.empty(B, L, V, device=DEV)
