@@ -274,7 +274,7 @@ def run_workload(mulo, name, wd, rope, steps, warmup, sigma=None, first_block=Fa
     roof = None
     if "gemm_gate_up" in kernels and "achieved" in kernels["gemm_gate_up"]:
         k = kernels["gemm_gate_up"]
-        roof = {"bound": "mfma", "kernel": "gate|up projection + SwiGLU (k_gemm_bf16 or k_gemm_ring, EPI_SWIGLU)",
+        roof = {"bound": "mfma", "kernel": "gate|up projection + SwiGLU (k_gemm_256 or k_gemm_ring, EPI_SWIGLU)",
                 "achieved": k["achieved"], "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": k["frac"],
                 "traffic": None if first_block else traffic_from_profile(c["name"]), "avg_ms": k["avg_ms"],
                 "flops_per_launch": flops["gemm_gate_up"], "measured": "HIP events around every launch of the timed steps"}

@@ -101,12 +101,6 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* p, int64_t bytes) {
 __device__ __forceinline__ u32x4 bload(rsrc_t r, uint32_t lane_off, uint32_t base_off) {
     return __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)base_off, 0);
 }
-// rows of the weight matrices of each fused problem
-template <int EPI>
-__host__ __device__ __forceinline__ int64_t weight_rows(const GemmArgs& g) {
-    return EPI == EPI_QKV ? g.d : EPI == EPI_SWIGLU ? g.N / 2 : g.N;
-}
-
 // Which tile row feeds MFMA row rho: bits 2 and 3 exchanged.  With it, accumulator r of a lane
 // covers, along the MFMA row axis, index 16*(r/8) + 8*lh + r%8: two runs of 8 consecutive indices
 // per 32x32 block, so every lane stores 16-byte (bf16) or 2 x 16-byte (float) pieces.
@@ -125,6 +119,38 @@ __device__ __forceinline__ TokPlace place(const RopeArgs& ra, int m) {
     const int b = m / ra.L, jj = m % ra.L;
     if (ra.pos_tab) return {b, jj, b, ra.pos_tab[m]};   // scattered queries: slot jj of sequence b (L slots each)
     return {b, jj, b, ra.P + jj};
+}
+
+// Softmax statistics of the wavefront tile's 128 columns, per token, for the accept test (Sec. 3.1, Eq. 1): this lane holds
+// half lh of part (tile_n, wn) of token row m, run rr = 2 j + g2 in accumulators 8 g2 .. 8 g2 + 7 of block j; the other half
+// sits in lane + 32.  Whole tiles only (every column exists).
+template <int BN, int TM, int MB, int NB>
+__device__ __forceinline__ void logit_parts(const GemmArgs& g, const f32x16 (&acc)[MB][NB], int m0, int tile_n, int wm, int wn,
+                                            int l32, int lh) {
+    static_for<MB>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        const int m = m0 + wm * TM + i * 32 + l32;
+        float mx = rowparts::NEG_INF;
+        static_for<NB>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[i][j][r]);
+        });
+        float t[8];
+        static_for<NB>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+#pragma unroll
+            for (int g2 = 0; g2 < 2; ++g2) {
+                float zz[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) zz[e] = acc[i][j][g2 * 8 + e];
+                t[j * 2 + g2] = rowparts::run_sum(zz, mx, 8);
+            }
+        });
+        const float sm = rowparts::tree8(t);
+        const float2 ps = rowparts::merge_halves(mx, sm, __shfl_xor(mx, 32), __shfl_xor(sm, 32));
+        if (lh == 0 && m < g.M) g.parts[(int64_t)m * g.n_parts + tile_n * (BN / rowparts::PART) + wn] = ps;
+    });
 }
 
 template <int EPI, int BN, int TM, int TN, int MB, int NB>
@@ -180,35 +206,7 @@ __device__ __forceinline__ void epilogue(const GemmArgs& g, f32x16 (&acc)[MB][NB
         return;
     }
     if constexpr (EPI == EPI_LOGITS && TN == rowparts::PART) {
-        // Softmax statistics of the wavefront tile's 128 columns, per token, for the accept test (Sec. 3.1, Eq. 1):
-        // this lane holds half lh of part (tile_n, wn) of token row m, run rr = 2 j + g2 in accumulators
-        // 8 g2 .. 8 g2 + 7 of block j; the other half sits in lane + 32.  Whole tiles only (every column exists).
-        if (g.parts) {
-            static_for<MB>([&](auto ic) {
-                constexpr int i = decltype(ic)::value;
-                const int m = m0 + wm * TM + i * 32 + l32;
-                float mx = rowparts::NEG_INF;
-                static_for<NB>([&](auto jc) {
-                    constexpr int j = decltype(jc)::value;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[i][j][r]);
-                });
-                float t[8];
-                static_for<NB>([&](auto jc) {
-                    constexpr int j = decltype(jc)::value;
-#pragma unroll
-                    for (int g2 = 0; g2 < 2; ++g2) {
-                        float zz[8];
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) zz[e] = acc[i][j][g2 * 8 + e];
-                        t[j * 2 + g2] = rowparts::run_sum(zz, mx, 8);
-                    }
-                });
-                const float sm = rowparts::tree8(t);
-                const float2 ps = rowparts::merge_halves(mx, sm, __shfl_xor(mx, 32), __shfl_xor(sm, 32));
-                if (lh == 0 && m < g.M) g.parts[(int64_t)m * g.n_parts + tile_n * (BN / rowparts::PART) + wn] = ps;
-            });
-        }
+        if (g.parts) logit_parts<BN, TM, MB, NB>(g, acc, m0, tile_n, wm, wn, l32, lh);
     }
     static_for<MB>([&](auto ic) {
         static_for<NBE>([&](auto jc) {
@@ -300,218 +298,372 @@ __device__ __forceinline__ f32x16 mma(const bf16x8& a, const bf16x8& b, const f3
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a, c, 0, 0, 0);
 }
 
-// ---- BM x BN x 64 tiles, double-buffered LDS, one barrier per K-tile ---------------------------
-template <int BM, int BN, int WGM, int WGN, int EPI>
-__global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_bf16(const GemmArgs g) {
-    constexpr int BK = 64, LDS_STRIDE = BK + 8, CPR = BK / 8;   // 16-byte chunks per tile row
-    constexpr int NT = WGM * WGN * 64;
-    constexpr int TM = BM / WGM, TN = BN / WGN, MB = TM / 32, NB = TN / 32;
-    constexpr int LA = BM * CPR / NT, LB = BN * CPR / NT;  // 16-byte chunks per lane per stage
-    static_assert(BM * CPR % NT == 0 && BN * CPR % NT == 0, "tile/threads");
-    static_assert(EPI != EPI_SWIGLU || NB % 2 == 0, "swiglu needs an even number of column blocks");
+// ---- 256 x 256 tiles: 4 wavefronts of 128 x 128 (one per SIMD) over an LDS ring of five 32 KB items ---------------
+// For launches whose tiles fill the chip.  What bounds them is energy: the shader clock sinks to 1.6 - 1.7 GHz under this
+// load and taking barriers, waits or K-loop loads out (timing only) changes cycles but not time, so what helps is fewer bytes
+// moved per product and no phases in which the matrix pipes rest.
+//   - A wavefront owns 128 x 128 outputs (all 256 accumulators of a SIMD lane's second register half), 16 MFMAs per 8 KB of
+//     fragments: a 64-deep step reads 128 KB of LDS where 8 wavefronts of 64 x 128 read 192.
+//   - Operands go from memory to LDS directly (no staging registers, no ds_write).  An item is 256 rows x 128 bytes of one
+//     operand; items alternate W(0) A(0) W(1) A(1) ..., step kt reads two of the five slots, and loads A(kt + 1) and then
+//     W(kt + 2) into the two that step kt - 1 has read: a wavefront waits for its loads one step (tokens, out of the L2) or
+//     one and a half (weights) after their request, and meets the others once a step.  Chunk c of row r sits at chunk
+//     position c ^ ((r / 2) % 8): no bank conflicts.
+//   - With one wavefront per SIMD nothing else issues while an instruction waits, so every fragment read, load and scalar
+//     update has its place between two MFMAs of the slice before (sched_barrier; left to itself the scheduler collects the
+//     loads behind all MFMAs: +12 % time).  The k deal, hence every sum, is k_gemm_ring's.
+//   - Persistent: one workgroup per CU walks its tiles; the last two steps of a tile load the next one's first (past the last
+//     tile the descriptors are empty, which costs no traffic).
+//   - Epilogues go through LDS (the two slots that are free then) so that every access is whole rows, and the residual
+//     stream's first half is requested before the K loop.  q|k|v tiles of V exchange the operands' roles in the K loop.
+// us per launch, 8 wavefronts staged through registers -> here, cold weights, 4096 tokens: 4096 x 4096 147 -> 115,
+// 4096 x 11008 297 -> 267, q|k|v 334 -> 307, gate|up 572 -> 507, lm-head 439 -> 421.
+constexpr int ER = 272;   // bytes of a row of the epilogues' LDS block: 256 and 16 more, no bank conflicts in either direction
 
+// The float32 output rows of a tile: a descriptor (rows past M lie outside: reads give zeros, writes nothing), this lane's
+// offset, and what access t (4 rows of 64 columns) of block h (32 rows x 64 columns) adds to it.
+__device__ __forceinline__ rsrc_t c_rsrc(const GemmArgs& g, int m0) {
+    const int left = g.M - m0;
+    return make_rsrc(g.Cf + (int64_t)m0 * g.N, (int64_t)(left < 256 ? left : 256) * g.N * 4);
+}
+__device__ __forceinline__ uint32_t c_off(const GemmArgs& g, int n0, int wm, int wn, int lane) {
+    return (uint32_t)((wm * 128 + (lane >> 4)) * g.N + n0 + wn * 128 + (lane & 15) * 4) * 4u;
+}
+__device__ __forceinline__ uint32_t c_step(const GemmArgs& g, int h, int t) {
+    return (uint32_t)((h >> 1) * 32 + t * 4) * (uint32_t)g.N * 4u + (h & 1) * 256u;
+}
+
+// block h of a wavefront's 128 x 128 accumulators to LDS, a row of 64 columns per token
+template <int H>
+__device__ __forceinline__ void put_block(const f32x16 (&acc)[4][4], unsigned char* lds, int l32, int lh) {
+    static_for<2>([&](auto jc) {
+        constexpr int j = decltype(jc)::value;
+        const f32x16& a = acc[H >> 1][(H & 1) * 2 + j];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<f32x4*>(lds + l32 * ER + lh * 32 + j * 128 + (q >> 1) * 64 + (q & 1) * 16) =
+                f32x4{a[q * 4], a[q * 4 + 1], a[q * 4 + 2], a[q * 4 + 3]};
+    });
+}
+
+// residual add, logits.  xv: the first XAHEAD blocks of the stream
+constexpr int XAHEAD = 4;
+template <int EPI, int XN>
+__device__ __forceinline__ void epilogue_c(const GemmArgs& g, const f32x16 (&acc)[4][4], f32x4 (&xv)[XN][8], int m0, int n0, int wm,
+                                           int wn, int lane, unsigned char* lds) {
+    const rsrc_t rc = c_rsrc(g, m0);
+    const uint32_t vo = c_off(g, n0, wm, wn, lane);
+    unsigned char* const rd = lds + (lane >> 4) * ER + (lane & 15) * 16;
+    static_for<8>([&](auto hc) {
+        constexpr int h = decltype(hc)::value;
+        put_block<h>(acc, lds, lane & 31, lane >> 5);
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            f32x4 v = *reinterpret_cast<const f32x4*>(rd + t * 4 * ER);
+            if constexpr (EPI == EPI_RESID) v = xv[h % XN][t] + v;
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rc, (int)(vo + c_step(g, h, t)), 0, 0);
+        }
+        if constexpr (EPI == EPI_RESID && h + XN < 8) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t) xv[h % XN][t] = __builtin_bit_cast(f32x4, bload(rc, vo + c_step(g, h + XN, t), 0));
+        }
+    });
+}
+
+// silu(gate) * up: blocks j of a row are gate columns, j + 2 the up columns of the same 32 feed-forward columns
+__device__ __forceinline__ void epilogue_h(const GemmArgs& g, const f32x16 (&acc)[4][4], int m0, int tile_n, int wm, int wn, int lane,
+                                           unsigned char* lds) {
+    constexpr int HR = 144;   // 64 columns of bf16 and 16 bytes more
+    const int f = g.N / 2, left = g.M - m0;
+    const rsrc_t rc = make_rsrc(g.Cb + (int64_t)m0 * f, (int64_t)(left < 256 ? left : 256) * f * 2);
+    const uint32_t vo = (uint32_t)((wm * 128 + (lane >> 3)) * f + tile_n * 128 + wn * 64 + (lane & 7) * 8) * 2u;
+    unsigned char* const wr = lds + (lane & 31) * HR + (lane >> 5) * 16;
+    unsigned char* const rd = lds + (lane >> 3) * HR + (lane & 7) * 16;
+    static_for<4>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        static_for<2>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+#pragma unroll
+            for (int g2 = 0; g2 < 2; ++g2) {
+                bf16x8s o;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = (__bf16)(silu(acc[i][j][g2 * 8 + e]) * acc[i][j + 2][g2 * 8 + e]);
+                *reinterpret_cast<bf16x8s*>(wr + j * 64 + g2 * 32) = o;
+            }
+        });
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(rd + t * 8 * HR), rc,
+                                                   (int)(vo + (uint32_t)(i * 32 + t * 8) * (uint32_t)f * 2u), 0, 0);
+    });
+}
+
+// q, k: rotary and the rows of the q buffer or the K cache.  Where the wavefront's 128 tokens live is worked out once, two
+// tokens a lane, and kept in LDS behind the block; the table rows of a block are requested a block ahead.
+__device__ __forceinline__ void epilogue_qk(const GemmArgs& g, const f32x16 (&acc)[4][4], int m0, int n0, int wm, int wn, int lane,
+                                            unsigned char* lds) {
+    const int dh = g.ra.head_dim, hsh = dh == 128 ? 7 : 6, mw = m0 + wm * 128, nw = n0 + wn * 128, seg = nw / g.d;
+    struct Row { int pos; uint32_t row; };   // cache row (< 0: nothing is written); rows of d_h before it, head 0 (a cache that fits has fewer than 2^32)
+    Row* const tab = reinterpret_cast<Row*>(lds + 32 * ER);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int m = mw + i * 64 + lane;
+        const TokPlace pl = place(g.ra, m < g.M ? m : g.M - 1);
+        tab[i * 64 + lane] = {m < g.M ? pl.pos : -1, seg == 0 ? (uint32_t)pl.b * g.ra.n_heads * g.ra.L + pl.jj
+                                                              : (uint32_t)pl.bc * g.ra.n_heads * g.ra.max_seq + pl.pos};
+    }
+    const int rows = seg == 0 ? g.ra.L : g.ra.max_seq, cl = nw - seg * g.d + (lane & 7) * 8;
+    bf16* const base = seg == 0 ? g.Cb : g.kc + (int64_t)g.ra.layer * g.ra.max_batch * g.ra.n_heads * g.ra.max_seq * dh;
+    unsigned char* const rd = lds + (lane >> 3) * ER + (lane & 7) * 32;
+    f32x4 cs[2][4], sn[2][4];
+    Row rw[2][4];
+    auto fetch = [&](auto hc) {   // table rows of block h
+        constexpr int h = decltype(hc)::value;
+        const int cc = (cl + (h & 1) * 64) & (dh - 1);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            rw[h & 1][t] = tab[(h >> 1) * 32 + t * 8 + (lane >> 3)];
+            const int pos = rw[h & 1][t].pos < 0 ? 0 : rw[h & 1][t].pos;
+            cs[h & 1][t] = *reinterpret_cast<const f32x4*>(g.ra.cos + (int64_t)pos * (dh / 2) + (cc >> 1));
+            sn[h & 1][t] = *reinterpret_cast<const f32x4*>(g.ra.sin + (int64_t)pos * (dh / 2) + (cc >> 1));
+        }
+    };
+    fetch(std::integral_constant<int, 0>{});
+    static_for<8>([&](auto hc) {
+        constexpr int h = decltype(hc)::value;
+        if constexpr (h < 7) fetch(std::integral_constant<int, h + 1>{});
+        put_block<h>(acc, lds, lane & 31, lane >> 5);
+        const int c = cl + (h & 1) * 64;
+        bf16* const dst = base + (int64_t)(c >> hsh) * rows * dh + (c & (dh - 1));
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const f32x4 lo = *reinterpret_cast<const f32x4*>(rd + t * 8 * ER), hi = *reinterpret_cast<const f32x4*>(rd + t * 8 * ER + 16);
+            const float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+            const f32x4 &cs_ = cs[h & 1][t], &sn_ = sn[h & 1][t];
+            bf16x8s o;
+#pragma unroll
+            for (int pr = 0; pr < 4; ++pr) {
+                o[2 * pr] = (__bf16)(v[2 * pr] * cs_[pr] - v[2 * pr + 1] * sn_[pr]);
+                o[2 * pr + 1] = (__bf16)(v[2 * pr] * sn_[pr] + v[2 * pr + 1] * cs_[pr]);
+            }
+            if (rw[h & 1][t].pos >= 0) *reinterpret_cast<bf16x8s*>(dst + (int64_t)rw[h & 1][t].row * dh) = o;
+        }
+    });
+}
+
+// V, operands exchanged: a lane owns a channel and runs of 8 consecutive tokens (wm: 128 channels, wn: 128 tokens).  Through
+// LDS a lane keeps one run of 8 tokens and stores it for 4 channels per access, 256 contiguous bytes of a row of the
+// transposed cache.  A run that does not lie in 8 consecutive cache columns (the end of a sequence, scattered slots, past M)
+// goes token by token.  The address of a run is a multiple of 2 bytes only: its cache row is the caller's P + j.
+__device__ __forceinline__ void epilogue_v(const GemmArgs& g, const f32x16 (&acc)[4][4], int m0, int n0, int wm, int wn, int lane,
+                                           unsigned char* lds) {
+    const int m = m0 + wn * 128 + (lane & 15) * 8;
+    const TokPlace pl = place(g.ra, m < g.M ? m : g.M - 1);
+    const bool run = !g.ra.pos_tab && m + 8 <= g.M && pl.jj + 8 <= g.ra.L;
+    const int c0 = n0 - 2 * g.d + wm * 128 + (lane >> 4);
+    bf16* const base = g.vc + (int64_t)g.ra.layer * g.ra.max_batch * g.d * g.ra.max_seq;
+    unsigned char* const wr = lds + (lane & 31) * ER + (lane >> 5) * 16;
+    unsigned char* const rd = lds + (lane >> 4) * ER + (lane & 15) * 16;
+    static_for<4>([&](auto ic) {
+        constexpr int i = decltype(ic)::value;
+        static_for<4>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+#pragma unroll
+            for (int g2 = 0; g2 < 2; ++g2) {
+                bf16x8s o;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] = (__bf16)acc[i][j][g2 * 8 + e];
+                *reinterpret_cast<bf16x8s*>(wr + j * 64 + g2 * 32) = o;
+            }
+        });
+        u32x4 v[8];
+#pragma unroll
+        for (int t = 0; t < 8; ++t) v[t] = *reinterpret_cast<const u32x4*>(rd + t * 4 * ER);
+        if (run) {
+#pragma unroll
+            for (int t = 0; t < 8; ++t)
+                __builtin_memcpy(base + ((int64_t)pl.bc * g.d + c0 + i * 32 + t * 4) * g.ra.max_seq + pl.pos, &v[t], 16);
+        } else {
+            for (int e = 0; e < 8 && m + e < g.M; ++e) {
+                const TokPlace pe = place(g.ra, m + e);
+                if (pe.pos < 0) continue;
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const uint32_t w = e < 2 ? v[t].x : e < 4 ? v[t].y : e < 6 ? v[t].z : v[t].w;
+                    const uint16_t x = (uint16_t)(e & 1 ? w >> 16 : w);
+                    __builtin_memcpy(base + ((int64_t)pe.bc * g.d + c0 + i * 32 + t * 4) * g.ra.max_seq + pe.pos, &x, 2);
+                }
+            }
+        }
+    });
+}
+
+template <int EPI, bool PARTS>
+__global__ __launch_bounds__(256, 1) void k_gemm_256(const GemmArgs g) {
+    constexpr int BM = 256, BN = 256, TM = 128, TN = 128, MB = 4, NB = 4;
+    constexpr int RB = 128, ITEM = 256 * RB;   // bytes of an operand row and of an item
+    constexpr int LP = 8;                      // loads of a wavefront per item: 8 rows each, 32 rows apart
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    bf16* sA = reinterpret_cast<bf16*>(smem);                 // [2][BM][LDS_STRIDE]
-    bf16* sB = sA + 2 * BM * LDS_STRIDE;                      // [2][BN][LDS_STRIDE]
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave / WGN, wn = wave % WGN, l32 = lane & 31, lh = lane >> 5;
-    const int fra = l32, frb = kperm(l32);   // fragment rows (MFMA-row operand permuted)
-    // Persistent workgroups.  Workgroup b runs on XCD b % 8 (round-robin dispatch), and each XCD has
-    // its own L2, so the tile sequence is cut into one contiguous chunk per XCD and the sequence
-    // itself walks groups of GW column tiles row by row: the workgroups of one XCD then work, at any
-    // moment, on a near-square patch of output tiles and share its operand rows through that L2.
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1, l32 = lane & 31, lh = lane >> 5;
+    // Workgroup b runs on XCD b % 8 (round-robin dispatch), and each XCD has its own L2, so the tile sequence is cut into one
+    // contiguous chunk per XCD and walks groups of GW column tiles row by row: the workgroups of an XCD work, at any moment,
+    // on a near-square patch of output tiles and share its operand rows through that L2.
     constexpr int GW = 8;
     const int tiles_m = (g.M + BM - 1) / BM, total_tiles = tiles_m * g.tiles_n;
     const int nxcd = (gridDim.x & 7) == 0 ? 8 : 1;
     const int tile_stride = gridDim.x / nxcd, chunk = (total_tiles + nxcd - 1) / nxcd;
     const int chunk_base = (blockIdx.x % nxcd) * chunk;
     const int chunk_len = total_tiles - chunk_base < chunk ? total_tiles - chunk_base : chunk;   // may be <= 0
-    int tile = blockIdx.x / nxcd, tile_n = 0, m0 = 0, n0 = 0;
-    const int kc8 = (tid % CPR) * 8, trow = tid / CPR;
-    // Operand addresses: the rows a lane fetches are a fixed stride apart, so a lane keeps ONE 32-bit offset (its row and
-    // chunk inside a pass) and everything else is scalar.  No 64-bit lane addresses to keep or to advance.
-    //   tokens: a descriptor per pass that starts at the pass's first row and ends with row M - 1, the K-step as scalar offset.
-    //     Rows past M read as zeros: their lane offset lies outside the descriptor.  (The bounds check sees the lane offset
-    //     for certain, the scalar offset by the hardware's leave, so no row may be in the scalar offset.)
-    //   weights: a descriptor of the whole matrix, the pass's row and the K-step as scalar offset; N is a multiple of the
-    //     tile (choose_tile), every row exists.
-    constexpr int RP = NT / CPR;   // tile rows per pass
-    rsrc_t rA[LA];
-    uint32_t sb[LB];   // byte offset of pass i's first row in its matrix
-    const uint32_t voff = (uint32_t)(trow * g.K + kc8) * 2u;
-    rsrc_t rW[2] = {make_rsrc(g.W0, weight_rows<EPI>(g) * g.K * 2),
-                    make_rsrc(EPI == EPI_QKV || EPI == EPI_SWIGLU ? g.W1 : g.W0, weight_rows<EPI>(g) * g.K * 2)};
-    // which descriptor pass i of the weight tile reads: gate | up alternate inside a tile (compile-time), q | k is per tile
-    auto wsel = [&](int i) -> rsrc_t { return rW[EPI == EPI_SWIGLU ? ((i * RP) % TN >= TN / 2 ? 1 : 0) : 0]; };
-    auto setup = [&](int local) {   // operand rows of the chunk's tile `local` (fixed over its K loop)
-        const int t = chunk_base + local, grp = t / (tiles_m * GW), rem = t - grp * tiles_m * GW;
-        const int gw = g.tiles_n - grp * GW < GW ? g.tiles_n - grp * GW : GW;
-        tile_n = g.tile_n0 + grp * GW + rem % gw;
-        m0 = (rem / gw) * BM;
-        n0 = tile_n * BN;
-#pragma unroll
-        for (int i = 0; i < LA; ++i) {
-            const int row = m0 + i * RP, left = g.M - row;
-            rA[i] = make_rsrc(g.A + (int64_t)row * g.K, left > 0 ? (int64_t)left * g.K * 2 : 0);
-        }
-#pragma unroll
-        for (int i = 0; i < LB; ++i) {
-            int which;
-            sb[i] = (uint32_t)(b_row_src<EPI, BN, TN>(g, n0, tile_n, i * RP, which) * g.K) * 2u;
-            if constexpr (EPI == EPI_QKV) {
-                if (i == 0) rW[0] = make_rsrc(which == 0 ? g.W0 : which == 1 ? g.W1 : g.W2, weight_rows<EPI>(g) * g.K * 2);
-            }
-        }
-    };
-
-    f32x16 acc[MB][NB];
-    u32x4 ra[LA], rb[LB];
-    auto gload = [&](int kt) {
-#pragma unroll
-        for (int i = 0; i < LA; ++i) ra[i] = bload(rA[i], voff, kt * (BK * 2));
-#pragma unroll
-        for (int i = 0; i < LB; ++i) rb[i] = bload(wsel(i), voff, sb[i] + kt * (BK * 2));
-    };
-    const int nk = g.K / BK;
-    auto sstore = [&](int buf) {
-        bf16* a = sA + buf * BM * LDS_STRIDE;
-        bf16* b = sB + buf * BN * LDS_STRIDE;
-#pragma unroll
-        for (int i = 0; i < LA; ++i)
-            *reinterpret_cast<u32x4*>(a + (trow + i * (NT / CPR)) * LDS_STRIDE + kc8) = ra[i];
-#pragma unroll
-        for (int i = 0; i < LB; ++i)
-            *reinterpret_cast<u32x4*>(b + (trow + i * (NT / CPR)) * LDS_STRIDE + kc8) = rb[i];
-    };
-    // Fragments of one k-slice, double-buffered in registers.  Inside every 64 consecutive k the index is dealt so
-    // that lane half lh owns k in [32 lh, 32 lh + 32) and MFMA slice kk takes its kk-th 8 (both operands alike, so
-    // the products are unchanged): the same deal, hence the same summation order, as in the kernels that fetch an
-    // operand straight from memory, where it makes a lane's bytes contiguous.
-    bf16x8 af[2][MB], bfr[2][NB];
-    auto lfrag = [&](const bf16* a, const bf16* b, int kk, int slot) {
-        const int ko = kk * 8;
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-            af[slot][i] = *reinterpret_cast<const bf16x8*>(a + i * 32 * LDS_STRIDE + ko);
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-            bfr[slot][j] = *reinterpret_cast<const bf16x8*>(b + j * 32 * LDS_STRIDE + ko);
-    };
-
-    // Pipeline over the flattened sequence of K-steps of all this workgroup's tiles.  While step s is
-    // multiplied out of LDS buffer s & 1, step s+1 is in flight into the staging registers; spread over
-    // the iteration's MFMAs, every staging register is written to the other buffer and requested again
-    // at once for step s+2, so each request has a whole iteration to land and the memory pipeline sees
-    // one request per few MFMAs instead of a burst.  Near the end of a tile the requests run ahead into
-    // the next tile, whose first step is staged while this tile's epilogue runs.  The launcher
-    // guarantees nk >= 2.
+    int tile = blockIdx.x / nxcd;
     if (tile >= chunk_len) return;   // uniform over the workgroup, before any barrier
-    setup(tile);
-    gload(0);
-    sstore(0);
-    gload(1);
-    __syncthreads();
-    constexpr int KS = BK / 16;                      // k-slices (one MFMA deep) per K-step
-    constexpr int NMS = MB * NB, NF = MB + NB;       // MFMAs and fragment reads per k-slice
-    constexpr int NL = LA + LB;                      // staging registers per lane
-    auto mm = [&](int slot) {
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-            for (int j = 0; j < NB; ++j) acc[i][j] = mma(af[slot][i], bfr[slot][j], acc[i][j]);
+    // a tile, and its operands: first rows and sizes of the descriptors (token rows past M lie outside and read as zeros; every
+    // weight row exists).  Past the chunk everything lies outside.
+    struct Tile { int m0, n0, tile_n; const bf16 *a, *w0, *w1; int a_bytes, w_bytes; };
+    auto tile_at = [&](int local) -> Tile {
+        Tile t{};
+        t.a = g.A; t.w0 = g.W0; t.w1 = g.W0;
+        if (local >= chunk_len) return t;
+        const int i = chunk_base + local, grp = i / (tiles_m * GW), rem = i - grp * tiles_m * GW;
+        const int gw = g.tiles_n - grp * GW < GW ? g.tiles_n - grp * GW : GW;
+        t.tile_n = g.tile_n0 + grp * GW + rem % gw;
+        t.m0 = (rem / gw) * BM;
+        t.n0 = t.tile_n * BN;
+        const int left = g.M - t.m0;
+        t.a += (int64_t)t.m0 * g.K;
+        t.a_bytes = (left < BM ? left : BM) * g.K * 2;
+        int which;
+        const int base = b_row_src<EPI, BN, TN>(g, t.n0, t.tile_n, 0, which);
+        t.w0 = (which == 0 ? g.W0 : which == 1 ? g.W1 : g.W2) + (int64_t)base * g.K;
+        t.w1 = EPI == EPI_SWIGLU ? g.W1 + (int64_t)base * g.K : t.w0;
+        t.w_bytes = 0x7fffffff;
+        return t;
     };
-    // One K-step, rotated by one k-slice: the step's first fragments are requested right after the barrier and
-    // the MFMAs of the PREVIOUS step's last slice (fragments already in registers, slot 1) run while they are on
-    // their way, so no wavefront waits for LDS with an empty MFMA queue.  Slice kk lives in slot kk & 1; on return
-    // slot 1 holds the step's last slice, not yet multiplied.
-    auto step_rot = [&](int step) {
-        const bf16* a = sA + (step & 1) * BM * LDS_STRIDE + (wm * TM + fra) * LDS_STRIDE + lh * 32;
-        const bf16* b = sB + (step & 1) * BN * LDS_STRIDE + (wn * TN + frb) * LDS_STRIDE + lh * 32;
+    // Load i of an item covers its rows 32 i + 8 wave .. + 7.  Token rows go into the lane offset, which the bounds check
+    // sees; weight rows into the scalar offset.  Gate|up: rows 0 .. 63 and 128 .. 191 of an item are gate rows, the rest up rows.
+    auto row_key = [](int r) { return (r >> 1) & 7; };   // the same for rows 16 apart
+    const int row0 = wave * 8 + (lane >> 3);
+    const uint32_t voff = (uint32_t)(row0 * g.K + ((lane & 7) ^ row_key(row0)) * 8) * 2u, rows32 = (uint32_t)g.K * 64u;
+    uint32_t va[LP];
 #pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
-            lfrag(a, b, kk, kk & 1);
-            mm((kk + 1) & 1);
-        }
+    for (int i = 0; i < LP; ++i) va[i] = voff + (uint32_t)i * rows32;
+    typedef __attribute__((address_space(3))) void lds_void;
+    auto load_a = [&](rsrc_t r, int i, int koff, int slot) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(smem + slot + (i * 4 + wave) * 1024), 16, (int)va[i], koff, 0, 0);
     };
+    auto load_w = [&](rsrc_t r0, rsrc_t r1, int i, int koff, int slot) {
+        const rsrc_t r = EPI == EPI_SWIGLU && (i & 2) ? r1 : r0;
+        const uint32_t row = EPI == EPI_SWIGLU ? (i & 1) + (i >> 2) * 2 : i;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)(smem + slot + (i * 4 + wave) * 1024), 16, (int)voff, (int)(row * rows32 + koff), 0, 0);
+    };
+    const int nk = g.K / 64;
+    f32x16 acc[MB][NB];
+    int ka[4], kb[4];   // this lane's fragment of slice kk in row block 0: chunk 4 lh + kk
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        const int c = lh * 4 + kk;
+        ka[kk] = (wm * TM + l32) * RB + (c ^ row_key(l32)) * 16;
+        kb[kk] = (wn * TN + kperm(l32)) * RB + (c ^ row_key(kperm(l32))) * 16;
+    }
+    bf16x8 af[2][MB], bfr[2][NB];
+    // this wavefront's loads but the youngest item's have landed and its fragment reads are done; then meet the others
+    auto sync = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LP) : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    Tile cur = tile_at(tile);
+    {
+        const rsrc_t ra = make_rsrc(cur.a, cur.a_bytes), r0 = make_rsrc(cur.w0, cur.w_bytes), r1 = make_rsrc(cur.w1, cur.w_bytes);
+#pragma unroll
+        for (int i = 0; i < LP; ++i) load_w(r0, r1, i, 0, 0);
+#pragma unroll
+        for (int i = 0; i < LP; ++i) load_a(ra, i, 0, ITEM);
+#pragma unroll
+        for (int i = 0; i < LP; ++i) load_w(r0, r1, i, RB, 2 * ITEM);   // K >= 128: step 1 exists
+    }
+    // slots: W and A of the step, W of the next, and where A of the next and W of the one after it go
+    int s_w = 0, s_a = ITEM, s_w1 = 2 * ITEM, s_a1 = 3 * ITEM, s_w2 = 4 * ITEM;
     const bf16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
-    int gs = 0;   // steps done so far: buffer parity
+    sync();
     while (true) {
+        tile += tile_stride;
+        const Tile nxt = tile_at(tile);
+        const bool v_tile = EPI == EPI_QKV && cur.n0 >= 2 * g.d;   // tokens feed the MFMA rows
+        constexpr int XN = EPI == EPI_RESID ? XAHEAD : 1;
+        f32x4 xv[XN][8];
+        if constexpr (EPI == EPI_RESID) {   // the tile's own rows of the stream: nobody else writes them
+            const rsrc_t rc = c_rsrc(g, cur.m0);
+            const uint32_t vo = c_off(g, cur.n0, wm, wn, lane);
+#pragma unroll
+            for (int h = 0; h < XN; ++h)
+#pragma unroll
+                for (int t = 0; t < 8; ++t) xv[h][t] = __builtin_bit_cast(f32x4, bload(rc, vo + c_step(g, h, t), 0));
+        }
 #pragma unroll
         for (int i = 0; i < MB; ++i)
 #pragma unroll
             for (int j = 0; j < NB; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-        // nothing is pending at the start of a tile: slot 1 holds zeros, its MFMAs add nothing
+        // the loop is rotated by one slice, as k_gemm_ring's; nothing is pending at the start of a tile: zeros, which add nothing
 #pragma unroll
         for (int i = 0; i < MB; ++i) af[1][i] = zero8;
 #pragma unroll
         for (int j = 0; j < NB; ++j) bfr[1][j] = zero8;
-        int e_m0 = m0, e_n0 = n0, e_tile_n = tile_n;
-        bool more = true;
-        int kt = 0;
-        // steady state: one scheduling region per K-step.  Fragment reads of slice kk + 1 go in front of the MFMAs
-        // of slice kk; over the MFMAs of the step's slices 1 and 2 every staging register is written to LDS as soon
-        // as its load (requested one iteration ago) is there and is at once requested again for step kt + 2.
-        for (; kt < nk - 2; ++kt, ++gs) {
-            const bf16* a = sA + (gs & 1) * BM * LDS_STRIDE + (wm * TM + fra) * LDS_STRIDE + lh * 32;
-            const bf16* b = sB + (gs & 1) * BN * LDS_STRIDE + (wn * TN + frb) * LDS_STRIDE + lh * 32;
-            bf16* na = sA + ((gs + 1) & 1) * BM * LDS_STRIDE + trow * LDS_STRIDE + kc8;
-            bf16* nb = sB + ((gs + 1) & 1) * BN * LDS_STRIDE + trow * LDS_STRIDE + kc8;
-            auto stage = [&](auto ic) {   // staging register i: to LDS (step kt + 1), then requested again (step kt + 2)
-                constexpr int i = decltype(ic)::value;
-                if constexpr (i < LA) {
-                    *reinterpret_cast<u32x4*>(na + i * RP * LDS_STRIDE) = ra[i];
-                    ra[i] = bload(rA[i], voff, (kt + 2) * (BK * 2));
-                } else {
-                    constexpr int j = i - LA;
-                    *reinterpret_cast<u32x4*>(nb + j * RP * LDS_STRIDE) = rb[j];
-                    rb[j] = bload(wsel(j), voff, sb[j] + (kt + 2) * (BK * 2));
-                }
-            };
-            // The NL write + load pairs are dealt evenly over the first SPAN MFMAs of the iteration; the rest run
-            // bare, so the last LDS writes have landed when the wavefront reaches the barrier.
-            constexpr int SPAN = KS * NMS - NMS / 2;
-            auto before = [](int m) constexpr { return m >= SPAN ? NL : m * NL / SPAN; };   // pairs in front of MFMA m
-            static_for<KS>([&](auto phc) {   // phase 0 multiplies the previous step's last slice
-                constexpr int ph = decltype(phc)::value;
-                lfrag(a, b, ph, ph & 1);
-                static_for<before((ph + 1) * NMS) - before(ph * NMS)>(
-                    [&](auto ic) { stage(std::integral_constant<int, before(ph * NMS) + decltype(ic)::value>{}); });
-                mm((ph + 1) & 1);
-            });
-            static_for<KS>([&](auto phc) {
-                constexpr int ph = decltype(phc)::value;
-                __builtin_amdgcn_sched_group_barrier(0x100, NF, 0);
-                static_for<NMS>([&](auto mc) {
-                    constexpr int m = ph * NMS + decltype(mc)::value;
-                    static_for<before(m + 1) - before(m)>([&](auto) {
-                        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-                        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-                    });
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        // what the step loads: A of the next step, W of the one after it; past the tile's last step the next tile's first
+        const bf16 *pa = cur.a, *pw0 = cur.w0, *pw1 = cur.w1;
+        int a_bytes = cur.a_bytes, w_bytes = cur.w_bytes, ko_a = RB, ko_w = 2 * RB;
+        if (nk == 2) { pw0 = nxt.w0; pw1 = nxt.w1; w_bytes = nxt.w_bytes; ko_w = 0; }
+        int left = nk;
+        do {
+            const unsigned char* const sb = smem + (v_tile ? s_a : s_w);   // the operand of the MFMA rows
+            const unsigned char* const sa = smem + (v_tile ? s_w : s_a);
+            static_for<4>([&](auto kc) {
+                constexpr int kk = decltype(kc)::value, rd = kk & 1, ms = (kk + 1) & 1;
+                static_for<16>([&](auto mc) {   // one MFMA of the slice before and what is issued in front of it
+                    constexpr int m = decltype(mc)::value, i = m >> 2, j = (i & 1) ? 3 - (m & 3) : (m & 3), e = kk * 16 + m;
+                    if constexpr (m < 4) bfr[rd][m] = *reinterpret_cast<const bf16x8*>(sb + kb[kk] + m * 32 * RB);
+                    else if constexpr (m < 8) af[rd][m - 4] = *reinterpret_cast<const bf16x8*>(sa + ka[kk] + (m - 4) * 32 * RB);
+                    if constexpr (e % 4 == 3 && e / 4 < LP) load_a(make_rsrc(pa, a_bytes), e / 4, ko_a, s_a1);
+                    if constexpr (e % 4 == 3 && e / 4 >= LP) load_w(make_rsrc(pw0, w_bytes), make_rsrc(pw1, w_bytes), e / 4 - LP, ko_w, s_w2);
+                    if constexpr (e == 33) ko_a = left == 2 ? 0 : ko_a + RB;
+                    if constexpr (e == 34) pa = left == 2 ? nxt.a : pa;
+                    if constexpr (e == 36) a_bytes = left == 2 ? nxt.a_bytes : a_bytes;
+                    acc[i][j] = mma(af[ms][i], bfr[ms][j], acc[i][j]);
+                    __builtin_amdgcn_sched_barrier(0);
                 });
             });
-            __builtin_amdgcn_sched_barrier(0);   // the bare MFMAs stay in front of the barrier
-            __syncthreads();
-        }
-        for (; kt < nk; ++kt, ++gs) {   // last two steps of the tile: the requests move on to the next tile
-            step_rot(gs);
-            if (kt == nk - 2) {
-                e_m0 = m0; e_n0 = n0; e_tile_n = tile_n;
-                tile += tile_stride;
-                more = tile < chunk_len;
-                if (more) setup(tile);
+            ko_w = left == 3 ? 0 : ko_w + RB;
+            pw0 = left == 3 ? nxt.w0 : pw0;
+            if constexpr (EPI == EPI_SWIGLU) pw1 = left == 3 ? nxt.w1 : pw1;
+            w_bytes = left == 3 ? nxt.w_bytes : w_bytes;
+            {
+                const int w = s_w, a = s_a;
+                s_w = s_w1; s_a = s_a1; s_w1 = s_w2; s_a1 = w; s_w2 = a;
             }
-            if (kt + 1 < nk || more) sstore((gs + 1) & 1);
-            if (more) gload(kt + 2 - nk);
-            __syncthreads();
+            sync();
+        } while (--left > 0);
+#pragma unroll
+        for (int i = 0; i < MB; ++i)   // the tile's last slice
+#pragma unroll
+            for (int j = 0; j < NB; ++j) acc[i][j] = mma(af[1][i], bfr[1][j], acc[i][j]);
+        // the slots of the last step have been read by everybody and are loaded again after the barrier below
+        unsigned char* const lds = smem + (wave >> 1 ? s_w2 : s_a1) + (wave & 1) * (ITEM / 2);
+        if constexpr (PARTS) logit_parts<BN, TM, MB, NB>(g, acc, cur.m0, cur.tile_n, wm, wn, l32, lh);
+        if constexpr (EPI == EPI_QKV) {
+            if (v_tile) epilogue_v(g, acc, cur.m0, cur.n0, wm, wn, lane, lds);
+            else epilogue_qk(g, acc, cur.m0, cur.n0, wm, wn, lane, lds);
+        } else if constexpr (EPI == EPI_SWIGLU) {
+            epilogue_h(g, acc, cur.m0, cur.tile_n, wm, wn, lane, lds);
+        } else {
+            epilogue_c<EPI, XN>(g, acc, xv, cur.m0, cur.n0, wm, wn, lane, lds);
         }
-        mm(1);   // the tile's last slice
-        epilogue<EPI, BN, TM, TN, MB, NB>(g, acc, e_m0, e_n0, e_tile_n, wm, wn, l32, lh);
-        if (!more) break;
+        if (tile >= chunk_len) break;
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        cur = nxt;
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no load into this LDS may outlive the workgroup
 }
 
 // ---- BM x BN x 64 tiles over an LDS ring of NS stages, filled by direct loads (global memory -> LDS) ------------
@@ -525,7 +677,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_bf16(const GemmArgs g
 // The direct load writes lane l's 16 bytes at 16 l, so a row cannot be padded against bank conflicts; instead chunk c
 // of row r sits at chunk position c ^ ((r / 2) % 8): 16 consecutive lanes of a fragment read, 16 rows 128 bytes apart,
 // then touch every bank once (no conflicts counted; with c ^ (r % 8) half of the LDS cycles were conflicts).
-// The k deal, hence every sum, is that of k_gemm_bf16 above, whatever the tile.
+// The k deal, hence every sum, is that of k_gemm_256 above, whatever the tile.
 // us per launch, before (128 x 128 tiles, staged through registers) -> here, cold weights: 186 tokens: 4096 x 4096
 // 36 -> 21, 4096 x 11008 83 -> 54, q|k|v 84 -> 40, gate|up 67 -> 58; 1024 tokens of width 1024: out 15 -> 6.6, down
 // 27 -> 12, q|k|v 27 -> 14; 1980 tokens of width 4096: out 73 -> 65, down 174 -> 152.
@@ -545,14 +697,14 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // NS stages of [BM + BN][RB]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN, l32 = lane & 31, lh = lane >> 5;
-    // one tile per workgroup; tiles to XCDs as in k_gemm_bf16 (the grid is a multiple of 8)
+    // one tile per workgroup; tiles to XCDs as in k_gemm_256 (the grid is a multiple of 8)
     constexpr int GW = 8;
     const int tiles_m = (g.M + BM - 1) / BM, total = tiles_m * g.tiles_n, chunk = (total + 7) / 8;
     const int loc = blockIdx.x >> 3, t = (blockIdx.x & 7) * chunk + loc;
     if (loc >= chunk || t >= total) return;                             // uniform over the workgroup, before any barrier
     const int grp = t / (tiles_m * GW), rem = t - grp * tiles_m * GW;
     const int gw = g.tiles_n - grp * GW < GW ? g.tiles_n - grp * GW : GW;
-    const int tile_n = grp * GW + rem % gw, m0 = (rem / gw) * BM, n0 = tile_n * BN;
+    const int tile_n = g.tile_n0 + grp * GW + rem % gw, m0 = (rem / gw) * BM, n0 = tile_n * BN;
 
     // Operand addresses: a descriptor at the tile's first row, a lane offset per load (its row, clamped to the matrix, and
     // the chunk that belongs at its position), the K-step as scalar offset.
@@ -619,7 +771,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
 #pragma unroll
             for (int j = 0; j < NB; ++j) acc[i][j] = mma(af[slot][i], bfr[slot][j], acc[i][j]);
     };
-    // One K-step, rotated by one slice as in k_gemm_bf16: the MFMAs of the step before's last slice run while the first
+    // One K-step, rotated by one slice as in k_gemm_256: the MFMAs of the step before's last slice run while the first
     // fragments are on their way.  more: load step kt + NS - 1 into the slot of step kt - 1 (PAIRED: steps kt + 3 and
     // kt + 4 into the slots of kt - 2 and kt - 1; a step past the end is the last one again, into a slot nobody reads);
     // first: nothing is pending.
@@ -721,16 +873,17 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
     epilogue<EPI, BN, TM, TN, MB, NB>(g, acc, m0, n0, tile_n, wm, wn, l32, lh);
 }
 
-template <int BM, int BN, int WGM, int WGN, int EPI>
-void run_gemm(GemmArgs g, int tile_n0, int tiles_n, hipStream_t st) {
-    auto kern = k_gemm_bf16<BM, BN, WGM, WGN, EPI>;
-    const size_t lds = (size_t)2 * (BM + BN) * (64 + 8) * sizeof(bf16);
+// column tiles [tile_n0, tile_n0 + tiles_n)
+template <int EPI, bool PARTS>
+void run_256(GemmArgs g, int tile_n0, int tiles_n, hipStream_t st) {
+    auto kern = k_gemm_256<EPI, PARTS>;
+    constexpr int lds = 5 * 256 * 128;
     static int attr_state = 0;  // each instantiation is configured once per process
-    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds, &attr_state)) return;
-    const int tiles_m = (g.M + BM - 1) / BM, total = tiles_m * tiles_n, resident = cu_count();
+    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, &attr_state)) return;
+    const int total = (g.M + 255) / 256 * tiles_n, resident = cu_count();
     g.tiles_n = tiles_n;
     g.tile_n0 = tile_n0;
-    hipLaunchKernelGGL(kern, dim3(total < resident ? total : resident), dim3(WGM * WGN * 64), lds, st, g);
+    hipLaunchKernelGGL(kern, dim3(total < resident ? total : resident), dim3(256), lds, st, g);
 }
 
 // Epilogue of the weight-streaming kernels on two adjacent output columns n, n + 1 of token m (v1: the up sums of
@@ -1158,7 +1311,7 @@ __global__ __launch_bounds__(256) void k_pack_weights(const bf16* __restrict__ s
 struct TileCost {
     int bm, bn, stages, per_cu;   // ring stages of bm + bn rows of 128 bytes; 256 x 256: two padded buffers (144 bytes a row)
     float c0, tf, t0, e;
-    constexpr int fit() const { return 160 * 1024 / (stages * (bm + bn) * (bm == 256 && bn == 256 ? 144 : 128)); }
+    constexpr int fit() const { return bm == 256 && bn == 256 ? 1 : 160 * 1024 / (stages * (bm + bn) * 128); }
 };
 enum { TILE_32x64, TILE_64x64, TILE_128x64, TILE_64x128, TILE_128x128, TILE_256x128, TILE_128x256, TILE_256x256, N_TILES };
 constexpr TileCost TILE_COST[N_TILES] = {
@@ -1186,8 +1339,8 @@ inline int whole_columns(const GemmArgs& g) {
 template <int EPI>
 bool has_tile(const GemmArgs& g, int i) {
     const int seg = EPI == EPI_QKV ? g.d : g.N;                           // a tile must not straddle two of q | k | v
-    if (i == TILE_256x256 && !(g.N % 256 == 0 && seg % 256 == 0 && (int64_t)g.M * g.K * 2 < (1ll << 31) &&   // 32-bit sizes and offsets
-                               weight_rows<EPI>(g) * g.K * 2 < (1ll << 31)))
+    if (i == TILE_256x256 && !(g.N % 256 == 0 && seg % 256 == 0 &&
+                               (int64_t)256 * (g.N > g.K ? g.N : g.K) * 4 < (1ll << 31)))   // 32-bit offsets inside a tile's rows
         return false;
     if (EPI == EPI_QKV && seg % TILE_COST[i].bn) return false;
     return EPI == EPI_SWIGLU ? i != TILE_32x64 && i != TILE_64x64 && i != TILE_128x64 : i != TILE_64x128;
@@ -1218,15 +1371,16 @@ int choose_tile(const GemmArgs& g) {
     return best;
 }
 
+// all columns, or column tiles [tile_n0, tile_n0 + tiles_n)
 template <int TILE, int WGM, int WGN, int EPI, bool PAIRED = false>
-void run_ring(GemmArgs g, hipStream_t st) {
+void run_ring(GemmArgs g, hipStream_t st, int tile_n0 = 0, int tiles_n = 0) {
     constexpr int BM = TILE_COST[TILE].bm, BN = TILE_COST[TILE].bn, NS = TILE_COST[TILE].stages;
     auto kern = k_gemm_ring<BM, BN, WGM, WGN, NS, EPI, PAIRED>;
     const size_t lds = (size_t)NS * (BM + BN) * 128;
     static int attr_state = 0;
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds, &attr_state)) return;
-    g.tiles_n = (g.N + BN - 1) / BN;
-    g.tile_n0 = 0;
+    g.tiles_n = tiles_n ? tiles_n : (g.N + BN - 1) / BN;
+    g.tile_n0 = tile_n0;
     const int64_t total = (int64_t)((g.M + BM - 1) / BM) * g.tiles_n;
     hipLaunchKernelGGL(kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(WGM * WGN * 64), lds, st, g);
 }
@@ -1244,6 +1398,10 @@ bool dispatch(GemmArgs g, const StreamMode& sm, hipStream_t st) {
     *sm.ran = tile;
     const bool parts = EPI == EPI_LOGITS && g.parts && TILE_COST[tile].bn == 256 && g.N % 256 == 0;
     if (!parts) g.parts = nullptr;
+    auto run_128x256 = [&](int n0, int n) {
+        if constexpr (EPI == EPI_SWIGLU || EPI == EPI_LOGITS) run_ring<TILE_128x256, 2, 2, EPI>(g, st, n0, n);
+        else run_ring<TILE_128x256, 2, 4, EPI>(g, st, n0, n);
+    };
     switch (tile) {
         case TILE_32x64: if constexpr (EPI != EPI_SWIGLU) run_ring<TILE_32x64, 1, 2, EPI>(g, st); break;
         case TILE_64x64: if constexpr (EPI != EPI_SWIGLU) run_ring<TILE_64x64, 2, 2, EPI>(g, st); break;
@@ -1254,14 +1412,16 @@ bool dispatch(GemmArgs g, const StreamMode& sm, hipStream_t st) {
             if constexpr (EPI == EPI_SWIGLU || EPI == EPI_RESID) run_ring<TILE_256x128, 2, 2, EPI>(g, st);
             else run_ring<TILE_256x128, 4, 2, EPI>(g, st);
             break;
-        case TILE_128x256:
-            if constexpr (EPI == EPI_SWIGLU || EPI == EPI_LOGITS) run_ring<TILE_128x256, 2, 2, EPI>(g, st);
-            else run_ring<TILE_128x256, 2, 4, EPI>(g, st);
-            break;
+        case TILE_128x256: run_128x256(0, 0); break;
         default: {
             const int tiles_n = g.N / 256, n_main = whole_columns(g);
-            run_gemm<256, 256, 4, 2, EPI>(g, 0, n_main, st);
-            if (n_main < tiles_n) run_gemm<128, 256, 4, 2, EPI>(g, n_main, tiles_n - n_main, st);
+            if constexpr (EPI == EPI_LOGITS) {
+                if (parts) run_256<EPI, true>(g, 0, n_main, st);
+                else run_256<EPI, false>(g, 0, n_main, st);
+            } else {
+                run_256<EPI, false>(g, 0, n_main, st);
+            }
+            if (n_main < tiles_n) run_128x256(n_main, tiles_n - n_main);
         }
     }
     return parts;

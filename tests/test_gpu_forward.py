@@ -244,6 +244,68 @@ def test_every_projection_on_every_tile_it_has(d, nh, f, V, B):
             assert torch.equal(kv[0][:, :n, :, P:P + L], k0) and torch.equal(kv[1][:, :n, :, :, P:P + L], v0), (n, i)
 
 
+@pytest.mark.parametrize("d,nh,f,V,B", [
+    (128, 2, 256, 25600, 5),   # K of 2 steps; the lm-head's 400 tiles are two rounds, the second one partly filled
+    (256, 2, 192, 512, 5),     # down: K of 3 steps, fewer than the ring is deep
+    (256, 4, 192, 512, 13),    # sequences of 161 tokens end inside runs of 8: every V run of them, heads of 64
+])
+def test_256_tiles_at_short_k_and_over_rounds(d, nh, f, V, B):
+    """256 x 256 tiles against 128 x 128 ones where the loads of a workgroup's next tile begin in the first steps of the one
+    before, and where the last tile of a workgroup has no next: the same logits and cache rows, bit for bit, whatever the
+    parity of the cache row a block begins at."""
+    m = dict(n_layers=1, d_model=d, n_heads=nh, head_dim=d // nh, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
+    L = 161
+    w = G.make_weights(m, seed=25)
+    ctx, cos, sin = make_ctx(m, w, B, 176, 164)
+    kv = mulo.alloc_kv(ctx, DEV)
+    toks = G.uniform_tokens((B, L), V, 25, tag=1)
+    for P in (8, 9, 12):
+        got = []
+        for i in (4, 7):
+            tiles_of(ctx, i)
+            for t in kv:
+                t.fill_(0.25)
+            z = gpu_forward(ctx, kv, toks, P)
+            ran = tiles_of(ctx, -1)
+            assert (i == 4) == (7 not in ran), ran
+            got.append((z, kv[0].clone(), kv[1].clone()))
+        assert np.array_equal(got[0][0], got[1][0]), P
+        assert torch.equal(got[0][1], got[1][1]) and torch.equal(got[0][2], got[1][2]), P
+
+
+def test_256_tiles_with_scattered_slots():
+    """An island pass of more slots than stream (13 of each of 23 sequences, two of them unused) on 256 x 256 tiles against
+    128 x 128 ones: cache rows, logit rows and tokens, bit for bit, and nothing written for an unused slot."""
+    d, nh, V, B, L, P, n = 256, 2, 512, 23, 160, 7, 13
+    m = dict(n_layers=2, d_model=d, n_heads=nh, head_dim=d // nh, d_ffn=512, vocab=V, dtype="bf16", rms_eps=1e-5)
+    w = G.make_weights(m, seed=27)
+    ctx, cos, sin = make_ctx(m, w, B, 168, L)
+    kv = mulo.alloc_kv(ctx, DEV)
+    g = torch.Generator(device=DEV).manual_seed(27)
+    for t in kv:
+        t.normal_(generator=g)
+    first = [t.clone() for t in kv]
+    mask = torch.zeros(B, L, dtype=torch.uint8, device=DEV)
+    mask[:, torch.arange(n - 2, device=DEV) * 14 + 3] = 1
+    rank = mask.to(torch.int32) - 1
+    toks = dev(G.uniform_tokens((B, L), V, 27, tag=1))
+    prev = dev(G.uniform_tokens((B,), V, 27, tag=2))
+    got = []
+    for i in (4, 7):
+        tiles_of(ctx, i)
+        for t, t0 in zip(kv, first):
+            t.copy_(t0)
+        out, logits = toks.clone(), torch.zeros(B, L, V, device=DEV)
+        mulo.mulo_resample_islands(ctx, kv, B, P, L, 1, n, 5, 3, prev, mask, rank, out, logits)
+        torch.cuda.synchronize()
+        assert (7 in tiles_of(ctx, -1)) == (i == 7)
+        got.append((out, logits, kv[0].clone(), kv[1].clone()))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    untouched = mask == 0
+    assert torch.equal(got[0][3][:, :, :, :, P:P + L].permute(0, 1, 4, 2, 3)[:, untouched], first[1][:, :, :, :, P:P + L].permute(0, 1, 4, 2, 3)[:, untouched])
+
+
 
 def test_forward_small_bf16_chained_blocks():
     c = WC.get("cfg2")
