@@ -3,10 +3,10 @@
 //
 // bf16 path: flash-style, one workgroup per (128 or 256 queries, head, sequence),
 // 8 wavefronts (two per SIMD) for 256; K and V^T tiles of 64 or 128 keys (run_attn's
-// rule) are staged through LDS (double buffered, 139 KB for 128 keys of a head of 128)
-// and shared by the wavefronts, so a tile is fetched and written to LDS once per
-// workgroup and the per-tile work (barrier, running maximum, rescale test) is spread
-// over up to 32 MFMAs per product; each wavefront owns 32 queries and computes
+// rule) go from memory to LDS directly (double buffered, 128 KB for 128 keys of a head
+// of 128) and are shared by the wavefronts, so a tile is fetched once per workgroup and
+// the per-tile work (barrier, running maximum, rescale test) is spread over up to 32
+// MFMAs per product; each wavefront owns 32 queries and computes
 // S^T = K Q^T and O^T = V^T P^T with v_mfma_f32_32x32x16_bf16, so that a lane
 // owns ONE query: the softmax row reductions stay inside the lane (plus one
 // cross-half shuffle), and the exponentiated scores are already laid out as the
@@ -14,6 +14,8 @@
 // (bits 2 and 3 of the row index swapped) so that a lane's accumulators cover 8
 // consecutive keys, which is what lets V^T be read with 16-byte LDS loads.
 #include <hip/hip_bf16.h>
+
+#include <utility>
 
 #include "mulo_internal.h"
 
@@ -26,7 +28,24 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __hip_bfloat16 bf16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+typedef __attribute__((address_space(3))) void lds_void;
+
 constexpr float LOG2E = 1.4426950408889634f;
+
+// compile-time loop: register arrays indexed by it stay in registers
+template <class F, int... Is>
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, Is...>) {
+    (f(std::integral_constant<int, Is>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+    static_for_impl(static_cast<F&&>(f), std::make_integer_sequence<int, N>{});
+}
+// a descriptor of `bytes` bytes at p (<= 0: nothing; reads outside give zeros)
+__device__ __forceinline__ rsrc_t make_rsrc(const void* p, int64_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)(bytes < 0 ? 0 : bytes < 0x7fffffff ? bytes : 0x7fffffff), 0x00020000);
+}
 
 struct AttnArgs {
     const bf16* q;    // [B, nh, L, dh]
@@ -54,17 +73,19 @@ constexpr int SPLIT_QUERIES = 32;   // a key split serves at most this many quer
 // two workgroups per CU where their LDS fits twice (2 x 71.7 KB: 64-key tiles of heads of 128, 128-key tiles of heads of 64)
 template <int DH, int BQ, int BKV, int NTH>
 __global__ __launch_bounds__(NTH, DH * BKV <= 8192 ? 2 : 1) void k_attn_bf16(const AttnArgs a) {
-    constexpr int KS = DH + 8;     // K tile row stride (bf16)
-    constexpr int VS = BKV + 8;    // V^T tile row stride
     constexpr int NKK = DH / 16;   // k-steps of the first product
     constexpr int NDB = DH / 32;   // 32-row blocks of O^T
-    constexpr int LK = BKV * (DH / 8) / NTH, LV = DH * (BKV / 8) / NTH;  // 16-byte chunks per lane
+    constexpr int NKB = BKV / 32;  // 32-key blocks of S^T
+    constexpr int NW = NTH / 64;
+    constexpr int KRB = DH * 2, VRB = BKV * 2;                            // bytes of a row of the K tile, of the V^T tile
+    constexpr int KT = BKV * KRB, BUF = KT + DH * VRB;                    // the K tile, then the V^T tile
+    constexpr int LK = KT / 1024 / NW, LV = DH * VRB / 1024 / NW;         // loads of a wavefront per tile, a KB of whole rows each
+    constexpr int RK = 1024 / KRB, RV = 1024 / VRB;                       // rows of a load
+    static_assert(LK * NW * 1024 == KT && LV * NW * 1024 == DH * VRB, "whole loads per wavefront");
 
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    bf16* sK = reinterpret_cast<bf16*>(smem);   // [2][BKV][KS]
-    bf16* sV = sK + 2 * BKV * KS;               // [2][DH][VS]
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];  // [2][BUF]
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, lh = lane >> 5;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, lh = lane >> 5;
     // Workgroup id -> (query tile, head).  Consecutive ids go to consecutive XCDs, each with its own L2:
     // all query tiles of one (batch, head) are given to ONE XCD, next to each other in its dispatch
     // order, so that they stream that head's K and V through the same L2 side by side (the cache rows
@@ -130,45 +151,47 @@ __global__ __launch_bounds__(NTH, DH * BKV <= 8192 ? 2 : 1) void k_attn_bf16(con
         return;
     }
 
-    u32x4 rk[LK], rv[LV];
-    auto gload = [&](int t) {
-        const int kv0 = t * BKV;
+    // Tiles go from memory to LDS directly.  16-byte chunk c of row r sits at chunk position c ^ key(r): 16 lanes that read
+    // the same chunk of 16 rows touch every bank once.  (Rows of 128 bytes lie two to a 256-byte line of banks.)
+    auto key_of = [](int r, int row_bytes) { return row_bytes == 256 ? r & 15 : (r >> 1) & 7; };
+    const int krow = wave * RK + lane / (64 / RK), vrow = wave * RV + lane / (64 / RV);   // this lane's row in load 0 (the key repeats: NW RK, NW RV are multiples of 16)
+    const int kchunk = lane % (64 / RK) ^ key_of(krow, KRB), vchunk = lane % (64 / RV) ^ key_of(vrow, VRB);
+    static_assert(NW * RK % 16 == 0 && NW * RV % 16 == 0, "the key of a lane's rows");
+    const int koff = lane / (64 / RK) * KRB + kchunk * 16;
+    const uint32_t voff = (uint32_t)(lane / (64 / RV)) * (uint32_t)a.max_seq * 2u + vchunk * 16;
+    auto load_k = [&](int t) {   // rows and columns past the cache lie outside the descriptors
 #pragma unroll
         for (int i = 0; i < LK; ++i) {
-            const int c = tid + i * NTH, row = c / (DH / 8), col = (c % (DH / 8)) * 8;
-            int key = kv0 + row;
-            key = key < a.max_seq ? key : a.max_seq - 1;
-            rk[i] = *reinterpret_cast<const u32x4*>(kbase + (int64_t)key * DH + col);
-        }
-#pragma unroll
-        for (int i = 0; i < LV; ++i) {
-            const int c = tid + i * NTH, row = c / (BKV / 8), col = (c % (BKV / 8)) * 8;
-            int key = kv0 + col;
-            const int kc_ = key + 8 <= a.max_seq ? key : a.max_seq - 8;
-            rv[i] = *reinterpret_cast<const u32x4*>(vbase + (int64_t)row * a.max_seq + kc_);
-            // cache columns past the last visible key may be uninitialised memory: their
-            // probabilities are 0, and 0 * NaN must not reach the accumulators
-            if (kv0 + BKV - 1 > kmax_blk) {
-                auto keep = [&](int e) -> uint32_t { return key + e <= kmax_blk ? 0xFFFFu : 0u; };
-                rv[i].x &= keep(0) | (keep(1) << 16);
-                rv[i].y &= keep(2) | (keep(3) << 16);
-                rv[i].z &= keep(4) | (keep(5) << 16);
-                rv[i].w &= keep(6) | (keep(7) << 16);
-            }
+            const int64_t row = (int64_t)t * BKV + (i * NW + wave) * RK;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(kbase + row * DH, (a.max_seq - row) * KRB),
+                                                     (lds_void*)(smem + (t & 1) * BUF + (i * NW + wave) * 1024), 16, koff, 0, 0, 0);
         }
     };
-    auto sstore = [&](int buf) {
-        bf16* k = sK + buf * BKV * KS;
-        bf16* v = sV + buf * DH * VS;
-#pragma unroll
-        for (int i = 0; i < LK; ++i) {
-            const int c = tid + i * NTH, row = c / (DH / 8), col = (c % (DH / 8)) * 8;
-            *reinterpret_cast<u32x4*>(k + row * KS + col) = rk[i];
-        }
+    auto load_v = [&](int t) {
 #pragma unroll
         for (int i = 0; i < LV; ++i) {
-            const int c = tid + i * NTH, row = c / (BKV / 8), col = (c % (BKV / 8)) * 8;
-            *reinterpret_cast<u32x4*>(v + row * VS + col) = rv[i];
+            const int64_t at = (int64_t)((i * NW + wave) * RV) * a.max_seq + (int64_t)t * BKV;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(vbase + at, ((int64_t)DH * a.max_seq - at) * 2),
+                                                     (lds_void*)(smem + (t & 1) * BUF + KT + (i * NW + wave) * 1024), 16, (int)voff, 0, 0, 0);
+        }
+    };
+    // this wavefront's loads have landed and its fragment reads are done; meet the others
+    auto meet = [&]() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
+    // Cache columns past the last visible key may be uninitialised memory: their probabilities are 0, and 0 * NaN must not
+    // reach the accumulators.  Between the landing of tile t's V^T and the barrier that shows it to the others, every lane
+    // clears those of the bytes it has loaded itself.
+    auto clear_unseen = [&](int t) {
+        if (t * BKV + BKV - 1 > kmax_blk) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const int key = t * BKV + vchunk * 8;
+            auto keep = [&](int e) -> uint32_t { return (key + e <= kmax_blk ? 0xFFFFu : 0u) | (key + e + 1 <= kmax_blk ? 0xFFFF0000u : 0u); };
+#pragma unroll
+            for (int i = 0; i < LV; ++i) {
+                u32x4* const at = reinterpret_cast<u32x4*>(smem + (t & 1) * BUF + KT + (i * NW + wave) * 1024 + lane * 16);
+                u32x4 v = *at;
+                v.x &= keep(0); v.y &= keep(2); v.z &= keep(4); v.w &= keep(6);
+                *at = v;
+            }
         }
     };
 
@@ -194,110 +217,161 @@ __global__ __launch_bounds__(NTH, DH * BKV <= 8192 ? 2 : 1) void k_attn_bf16(con
     if constexpr (BKV == 64) {
         if (a.hide && wave_live) hide_cur = __ballot(hide_flag(t_begin) != 0);
     }
-    gload(t_begin);
-    sstore(t_begin & 1);
-    __syncthreads();
-    for (int t = t_begin; t < t_end; ++t) {
-        const int kv0 = t * BKV;
-        const int t_next = t + 1 < t_end ? t + 1 : t;   // the last tile is fetched twice: no branch in the body
-        if (wave_live && (scattered || kv0 <= P + wave_jmax)) {
-            gload(t_next);
-            uint8_t hide_next = 0;
-            if constexpr (BKV == 64) {
-                if (a.hide) hide_next = hide_flag(t_next);
-            }
-            const bf16* k = sK + (t & 1) * BKV * KS;
-            const bf16* v = sV + (t & 1) * DH * VS;
-            f32x16 s[BKV / 32];
+    // fragment addresses inside a tile: chunk 2 k + lh of this lane's row, k in bits 5 and up
+    const int kfrag = kperm * KRB + (lh ^ key_of(kperm, KRB)) * 16, vfrag = l32 * VRB + (lh ^ key_of(l32, VRB)) * 16;
+    f32x16 s[NKB];               // the scores of a tile, then
+    float m_safe = 0.f, alpha = 1.f;   // the reference of its exponentials and the factor of what has been added up before it
+    auto score = [&](int t) {
+        const int kv0 = t * BKV, t_next = t + 1 < t_end ? t + 1 : t;
+        uint8_t hide_next = 0;
+        if constexpr (BKV == 64) {
+            if (a.hide) hide_next = hide_flag(t_next);
+        }
+        const unsigned char* const kt = smem + (t & 1) * BUF;
+        // S^T = K Q^T: NKB independent chains, the fragments of a k-step requested during the step before it (left to
+        // itself the compiler keeps two fragments in flight and waits for each: the product took 3 times its MFMAs)
 #pragma unroll
-            for (int kb = 0; kb < BKV / 32; ++kb) {
+        for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
-                const bf16* kr = k + (kb * 32 + kperm) * KS + lh * 8;
+            for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
+        bf16x8 kf[2][NKB];
 #pragma unroll
-                for (int kk = 0; kk < NKK; ++kk)
-                    s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                        *reinterpret_cast<const bf16x8*>(kr + kk * 16), qf[kk], s[kb], 0, 0, 0);
-            }
-            // accumulator r of block kb holds key kv0 + kb*32 + 16*(r/8) + 8*lh + r%8 for query l32
-            const bool need_mask = scattered ? kv0 + BKV > a.P0 : kv0 + BKV - 1 > P + wave_jmin;
-            float mx = -__builtin_huge_valf();
-            if (need_mask) {
-#pragma unroll
-                for (int kb = 0; kb < BKV / 32; ++kb)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int key = kv0 + kb * 32 + 16 * (r >> 3) + 8 * lh + (r & 7);
-                        s[kb][r] = key <= qpos ? s[kb][r] : -__builtin_huge_valf();
-                    }
-            }
-            if constexpr (BKV == 64) {
-                if (a.hide) {   // scattered queries: rows of positions that are not settled yet (the query's own excepted)
-                    if (hide_cur != 0) {   // uniform over the wavefront; bits are set for rows of the block only
-#pragma unroll
-                        for (int kb = 0; kb < BKV / 32; ++kb) {
-                            const uint32_t mine = (uint32_t)(hide_cur >> (kb * 32)) >> (8 * lh);   // this lane's keys: bits 16 (r / 8) + r % 8
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) {
-                                const int key = kv0 + kb * 32 + 16 * (r >> 3) + 8 * lh + (r & 7);
-                                if (((mine >> (16 * (r >> 3) + (r & 7))) & 1u) && key < qpos) s[kb][r] = -__builtin_huge_valf();
-                            }
-                        }
-                    }
-                    hide_cur = __ballot(hide_next != 0);   // requested at the top of the iteration, for tile t_next
-                }
-            }
-#pragma unroll
-            for (int kb = 0; kb < BKV / 32; ++kb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
-            mx = fmaxf(mx, __shfl_xor(mx, 32));
-            // The exponentials are taken against a reference m_run (exponent units: scores times log2(e) / sqrt(dh);
-            // the scale is positive) that follows the running maximum lazily: it moves only when the maximum has
-            // outgrown it by more than 2^LAZY_EXP.  Probabilities then stay below that factor, which float32 and
-            // bf16 hold with the same relative precision, the normalisation divides it out, and the accumulators
-            // are rescaled a few times per query instead of in most tiles.  From -inf the first finite maximum
-            // moves it.
-            const float mxs = mx * a.scale_log2;
-            const float m_new = mxs > m_run + LAZY_EXP ? mxs : m_run;
-            // a query that has seen no key yet (every row of its first tiles hidden) keeps -inf as its maximum:
-            // exponents are then taken against 0, which makes every term exp2(-inf) = 0 instead of NaN
-            const float m_safe = m_new == -__builtin_huge_valf() ? 0.f : m_new;
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
-            m_run = m_new;
-            float ps = 0.f;
-            bf16x8 pf[BKV / 16];
+        for (int kb = 0; kb < NKB; ++kb) kf[0][kb] = *reinterpret_cast<const bf16x8*>(kt + kfrag + kb * 32 * KRB);
+        static_for<NKK>([&](auto kc) {
+            constexpr int kk = decltype(kc)::value;
+            static_for<NKB>([&](auto bc) {
+                constexpr int kb = decltype(bc)::value;
+                if constexpr (kk + 1 < NKK) kf[(kk + 1) & 1][kb] = *reinterpret_cast<const bf16x8*>(kt + (kfrag ^ ((kk + 1) << 5)) + kb * 32 * KRB);
+                s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kk & 1][kb], qf[kk], s[kb], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+        // accumulator r of block kb holds key kv0 + kb*32 + 16*(r/8) + 8*lh + r%8 for query l32
+        const bool need_mask = scattered ? kv0 + BKV > a.P0 : kv0 + BKV - 1 > P + wave_jmin;
+        float mx = -__builtin_huge_valf();
+        if (need_mask) {
 #pragma unroll
             for (int kb = 0; kb < BKV / 32; ++kb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[kb][r], a.scale_log2, -m_safe));
-                    ps += p;
-                    pf[kb * 2 + (r >> 3)][r & 7] = (__bf16)p;
+                    const int key = kv0 + kb * 32 + 16 * (r >> 3) + 8 * lh + (r & 7);
+                    s[kb][r] = key <= qpos ? s[kb][r] : -__builtin_huge_valf();
                 }
-            l_run = l_run * alpha + ps;
-            // the accumulators are rescaled only when some query of the wavefront raised its maximum
-            if (!__all(alpha == 1.0f)) {
-#pragma unroll
-                for (int i = 0; i < NDB; ++i)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) o[i][r] *= alpha;
-            }
-            // O^T += V^T P^T : k-step ks covers keys kv0 + 16 ks .. +15
-#pragma unroll
-            for (int ks = 0; ks < BKV / 16; ++ks) {
-#pragma unroll
-                for (int i = 0; i < NDB; ++i) {
-                    const bf16x8 vf = *reinterpret_cast<const bf16x8*>(v + (i * 32 + l32) * VS + ks * 16 + lh * 8);
-                    o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, pf[ks], o[i], 0, 0, 0);
-                }
-            }
-            sstore((t + 1) & 1);
-        } else {
-            gload(t_next);
-            sstore((t + 1) & 1);
         }
-        __syncthreads();
+        if constexpr (BKV == 64) {
+            if (a.hide) {   // scattered queries: rows of positions that are not settled yet (the query's own excepted)
+                if (hide_cur != 0) {   // uniform over the wavefront; bits are set for rows of the block only
+#pragma unroll
+                    for (int kb = 0; kb < BKV / 32; ++kb) {
+                        const uint32_t mine = (uint32_t)(hide_cur >> (kb * 32)) >> (8 * lh);   // this lane's keys: bits 16 (r / 8) + r % 8
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const int key = kv0 + kb * 32 + 16 * (r >> 3) + 8 * lh + (r & 7);
+                            if (((mine >> (16 * (r >> 3) + (r & 7))) & 1u) && key < qpos) s[kb][r] = -__builtin_huge_valf();
+                        }
+                    }
+                }
+                hide_cur = __ballot(hide_next != 0);   // requested at the top of the iteration, for tile t_next
+            }
+        }
+#pragma unroll
+        for (int kb = 0; kb < BKV / 32; ++kb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        // The exponentials are taken against a reference m_run (exponent units: scores times log2(e) / sqrt(dh);
+        // the scale is positive) that follows the running maximum lazily: it moves only when the maximum has
+        // outgrown it by more than 2^LAZY_EXP.  Probabilities then stay below that factor, which float32 and
+        // bf16 hold with the same relative precision, the normalisation divides it out, and the accumulators
+        // are rescaled a few times per query instead of in most tiles.  From -inf the first finite maximum
+        // moves it.
+        const float mxs = mx * a.scale_log2;
+        const float m_new = mxs > m_run + LAZY_EXP ? mxs : m_run;
+        // a query that has seen no key yet (every row of its first tiles hidden) keeps -inf as its maximum:
+        // exponents are then taken against 0, which makes every term exp2(-inf) = 0 instead of NaN
+        m_safe = m_new == -__builtin_huge_valf() ? 0.f : m_new;
+        alpha = __builtin_amdgcn_exp2f(m_run - m_safe);
+        m_run = m_new;
+    };
+    auto output = [&](int t) {
+        const unsigned char* const vt = smem + (t & 1) * BUF + KT;
+        // O^T += V^T P^T, keys kv0 + 16 ks .. + 15 per step ks; the exponentials of step ks + 1 and its V^T fragments go
+        // between the MFMAs of step ks
+        float ps = 0.f;
+        bf16x8 pf[2], vf[2][NDB];
+        // probabilities 2 g, 2 g + 1 of the tile in three stages a slot apart, so that no instruction waits for the one before
+        float x[2][2], p[2][2];
+        auto arg = [&](auto gc) {
+            constexpr int g = decltype(gc)::value, ks = g / 4, e = 2 * (g % 4);
+            if constexpr (g < BKV / 4) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) x[g & 1][q] = __builtin_fmaf(s[ks >> 1][(ks & 1) * 8 + e + q], a.scale_log2, -m_safe);
+            }
+        };
+        auto expo = [&](auto gc) {
+            constexpr int g = decltype(gc)::value;
+            if constexpr (g < BKV / 4) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) p[g & 1][q] = __builtin_amdgcn_exp2f(x[g & 1][q]);
+            }
+        };
+        auto take = [&](auto gc) {
+            constexpr int g = decltype(gc)::value, ks = g / 4, e = 2 * (g % 4);
+            if constexpr (g < BKV / 4) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    ps += p[g & 1][q];
+                    pf[ks & 1][e + q] = (__bf16)p[g & 1][q];
+                }
+            }
+        };
+#pragma unroll
+        for (int i = 0; i < NDB; ++i) vf[0][i] = *reinterpret_cast<const bf16x8*>(vt + vfrag + i * 32 * VRB);
+        static_for<4>([&](auto gc) { arg(gc); expo(gc); take(gc); });
+        arg(std::integral_constant<int, 4>{});
+        expo(std::integral_constant<int, 4>{});
+        arg(std::integral_constant<int, 5>{});
+        // the accumulators are rescaled only when some query of the wavefront raised its maximum
+        if (!__all(alpha == 1.0f)) {
+#pragma unroll
+            for (int i = 0; i < NDB; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) o[i][r] *= alpha;
+        }
+        static_for<BKV / 16>([&](auto kc) {
+            constexpr int ks = decltype(kc)::value, nxt = ks + 1 < BKV / 16 ? ks + 1 : ks;
+            static_for<NDB>([&](auto ic) {
+                constexpr int i = decltype(ic)::value, n = 4 / NDB;   // pairs per slot
+                if constexpr (nxt > ks) vf[nxt & 1][i] = *reinterpret_cast<const bf16x8*>(vt + (vfrag ^ (nxt << 5)) + i * 32 * VRB);
+                static_for<n>([&](auto qc) {
+                    constexpr int g = 4 * ks + i * n + decltype(qc)::value + 4;
+                    take(std::integral_constant<int, g>{});
+                    expo(std::integral_constant<int, g + 1>{});
+                    arg(std::integral_constant<int, g + 2>{});
+                });
+                o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks & 1][i], pf[ks & 1], o[i], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+        l_run = l_run * alpha + ps;
+    };
+    load_k(t_begin);
+    load_v(t_begin);
+    clear_unseen(t_begin);
+    meet();
+    for (int t = t_begin; t < t_end; ++t) {
+        if (t + 1 < t_end) {   // everybody has read the buffer: the barrier at the end of the tile before
+            load_k(t + 1);
+            load_v(t + 1);
+        }
+        if (wave_live && (scattered || t * BKV <= P + wave_jmax)) {
+            score(t);
+            output(t);
+        }
+        if (t + 1 < t_end) {
+            clear_unseen(t + 1);
+            meet();
+        }
     }
 
     l_run += __shfl_xor(l_run, 32);
@@ -365,7 +439,7 @@ static_assert(MAX_SPLIT == 16, "the combine kernels");
 template <int DH, int BQ, int BKV, int NTH>
 void run_attn_cfg(const AttnArgs& a, hipStream_t st) {
     auto kern = k_attn_bf16<DH, BQ, BKV, NTH>;
-    const size_t lds = (size_t)2 * (BKV * (DH + 8) + DH * (BKV + 8)) * sizeof(bf16);
+    const size_t lds = (size_t)2 * 2 * BKV * DH * sizeof(bf16);
     static int attr_state = 0;
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds, &attr_state)) return;
     hipLaunchKernelGGL(kern, dim3(((a.L + BQ - 1) / BQ) * a.nh * a.B * a.nsplit), dim3(NTH), lds, st, a);
