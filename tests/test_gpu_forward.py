@@ -405,6 +405,24 @@ def test_forward_embeds_input_and_errors():
         assert e.value.status == 2
 
 
+@pytest.mark.parametrize("nh,dh,f,dtype", [(2, 64, 128, "bf16"), (9, 128, 256, "bf16"), (4, 64, 688, "f32"), (3, 18, 203, "f32")])
+def test_embeddings_may_start_at_any_element(nh, dh, f, dtype):
+    """Rows that allow 16-byte accesses and rows that do not (a start off by one element, a width of 54) are the same copy:
+    one row, and several, given as tokens, as aligned embeddings and as unaligned ones have the same bits."""
+    m = dict(n_layers=1, d_model=nh * dh, n_heads=nh, head_dim=dh, d_ffn=f, vocab=256, dtype=dtype, rms_eps=1e-5)
+    w = G.make_weights(m, seed=9, std=0.05)
+    ctx, cos, sin = make_ctx(m, w, 2, 64, 32)
+    kv = mulo.alloc_kv(ctx, DEV)
+    for B, L in ((1, 1), (2, 31)):
+        toks = G.uniform_tokens((B, L), 256, 9)
+        want = gpu_forward(ctx, kv, toks, 0)
+        rows = w["embed"][torch.as_tensor(toks).long()].to(DEV).contiguous()
+        off = torch.empty(rows.numel() + 1, dtype=rows.dtype, device=DEV)[1:].view(rows.shape).copy_(rows)
+        assert rows.data_ptr() % 16 == 0 and off.data_ptr() % 16 != 0
+        for e in (rows, off):
+            assert np.array_equal(gpu_forward(ctx, kv, toks * 0, 0, embeds=e), want), (B, L)
+
+
 @pytest.mark.timeout(900)
 def test_forward_7b_first_block_and_teacher_forced_layers():
     """7B-class decoder, batch 1: real prefill of the 128-token prefix, then the
