@@ -398,22 +398,35 @@ __device__ __forceinline__ void epilogue_h(const GemmArgs& g, const f32x16 (&acc
     });
 }
 
-// q, k: rotary and the rows of the q buffer or the K cache.  Where the wavefront's 128 tokens live is worked out once, two
-// tokens a lane, and kept in LDS behind the block; the table rows of a block are requested a block ahead.
-__device__ __forceinline__ void epilogue_qk(const GemmArgs& g, const f32x16 (&acc)[4][4], int m0, int n0, int wm, int wn, int lane,
-                                            unsigned char* lds) {
-    const int dh = g.ra.head_dim, hsh = dh == 128 ? 7 : 6, mw = m0 + wm * 128, nw = n0 + wn * 128, seg = nw / g.d;
-    struct Row { int pos; uint32_t row; };   // cache row (< 0: nothing is written); rows of d_h before it, head 0 (a cache that fits has fewer than 2^32)
+// q | k | v.  Every block of 32 rows x 64 columns goes through LDS as it is, whatever the tile is of, and only what a lane does with
+// the 8 values it reads back differs; where the 128 tokens live is worked out once, two tokens a lane, and kept behind the block.
+// (With an epilogue of its own per kind of tile, hence the accumulators in two branches, the kernel kept 65 registers in scratch
+// memory, which the runtime allocates at the first dispatch: 4096 tokens of width 4096 325 us, so 315.)
+//   q, k   a row is a token: rotary, then 8 channels of its row of the q buffer or the K cache.  The table rows of a block are
+//          requested a block ahead.
+//   V      operands exchanged: a row is a channel (wm: 128 channels), the columns are tokens (wn: 128 tokens): 8 tokens go to
+//          the channel's row of the transposed cache, 128 contiguous bytes per 8 lanes.  A run that does not lie in 8 consecutive
+//          cache columns (the end of a sequence, scattered slots, past M) goes token by token.  The address of a run is a
+//          multiple of 2 bytes only: its cache row is the caller's P + j.
+__device__ __forceinline__ void epilogue_qkv(const GemmArgs& g, const f32x16 (&acc)[4][4], bool v_tile, int m0, int n0, int wm, int wn,
+                                             int lane, unsigned char* lds) {
+    const int dh = g.ra.head_dim, hsh = dh == 128 ? 7 : 6, mw = m0 + (v_tile ? wn : wm) * 128, nw = n0 + (v_tile ? wm : wn) * 128;
+    const int seg = nw / g.d;
+    // cache row (< 0: nothing is written); rows in front of the token's own in its buffer, head 0 (a cache that fits has fewer than
+    // 2^32): of d_h channels for q and k, of max_seq columns for V
+    struct Row { int pos; uint32_t row; };
     Row* const tab = reinterpret_cast<Row*>(lds + 32 * ER);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int m = mw + i * 64 + lane;
         const TokPlace pl = place(g.ra, m < g.M ? m : g.M - 1);
-        tab[i * 64 + lane] = {m < g.M ? pl.pos : -1, seg == 0 ? (uint32_t)pl.b * g.ra.n_heads * g.ra.L + pl.jj
-                                                              : (uint32_t)pl.bc * g.ra.n_heads * g.ra.max_seq + pl.pos};
+        tab[i * 64 + lane] = {m < g.M ? pl.pos : -1, seg == 0   ? (uint32_t)pl.b * g.ra.n_heads * g.ra.L + pl.jj
+                                                     : seg == 1 ? (uint32_t)pl.bc * g.ra.n_heads * g.ra.max_seq + pl.pos
+                                                                : (uint32_t)pl.bc * g.d};
     }
     const int rows = seg == 0 ? g.ra.L : g.ra.max_seq, cl = nw - seg * g.d + (lane & 7) * 8;
-    bf16* const base = seg == 0 ? g.Cb : g.kc + (int64_t)g.ra.layer * g.ra.max_batch * g.ra.n_heads * g.ra.max_seq * dh;
+    const int64_t layer_elems = (int64_t)g.ra.max_batch * g.d * g.ra.max_seq;
+    bf16* const base = seg == 0 ? g.Cb : (seg == 1 ? g.kc : g.vc) + g.ra.layer * layer_elems;
     unsigned char* const rd = lds + (lane >> 3) * ER + (lane & 7) * 32;
     f32x4 cs[2][4], sn[2][4];
     Row rw[2][4];
@@ -428,70 +441,56 @@ __device__ __forceinline__ void epilogue_qk(const GemmArgs& g, const f32x16 (&ac
             sn[h & 1][t] = *reinterpret_cast<const f32x4*>(g.ra.sin + (int64_t)pos * (dh / 2) + (cc >> 1));
         }
     };
-    fetch(std::integral_constant<int, 0>{});
+    if (!v_tile) fetch(std::integral_constant<int, 0>{});
     static_for<8>([&](auto hc) {
         constexpr int h = decltype(hc)::value;
-        if constexpr (h < 7) fetch(std::integral_constant<int, h + 1>{});
+        if constexpr (h < 7) {
+            if (!v_tile) fetch(std::integral_constant<int, h + 1>{});
+        }
         put_block<h>(acc, lds, lane & 31, lane >> 5);
-        const int c = cl + (h & 1) * 64;
-        bf16* const dst = base + (int64_t)(c >> hsh) * rows * dh + (c & (dh - 1));
+        f32x4 lo[4], hi[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const f32x4 lo = *reinterpret_cast<const f32x4*>(rd + t * 8 * ER), hi = *reinterpret_cast<const f32x4*>(rd + t * 8 * ER + 16);
-            const float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-            const f32x4 &cs_ = cs[h & 1][t], &sn_ = sn[h & 1][t];
-            bf16x8s o;
-#pragma unroll
-            for (int pr = 0; pr < 4; ++pr) {
-                o[2 * pr] = (__bf16)(v[2 * pr] * cs_[pr] - v[2 * pr + 1] * sn_[pr]);
-                o[2 * pr + 1] = (__bf16)(v[2 * pr] * sn_[pr] + v[2 * pr + 1] * cs_[pr]);
-            }
-            if (rw[h & 1][t].pos >= 0) *reinterpret_cast<bf16x8s*>(dst + (int64_t)rw[h & 1][t].row * dh) = o;
+            lo[t] = *reinterpret_cast<const f32x4*>(rd + t * 8 * ER);
+            hi[t] = *reinterpret_cast<const f32x4*>(rd + t * 8 * ER + 16);
         }
-    });
-}
-
-// V, operands exchanged: a lane owns a channel and runs of 8 consecutive tokens (wm: 128 channels, wn: 128 tokens).  Through
-// LDS a lane keeps one run of 8 tokens and stores it for 4 channels per access, 256 contiguous bytes of a row of the
-// transposed cache.  A run that does not lie in 8 consecutive cache columns (the end of a sequence, scattered slots, past M)
-// goes token by token.  The address of a run is a multiple of 2 bytes only: its cache row is the caller's P + j.
-__device__ __forceinline__ void epilogue_v(const GemmArgs& g, const f32x16 (&acc)[4][4], int m0, int n0, int wm, int wn, int lane,
-                                           unsigned char* lds) {
-    const int m = m0 + wn * 128 + (lane & 15) * 8;
-    const TokPlace pl = place(g.ra, m < g.M ? m : g.M - 1);
-    const bool run = !g.ra.pos_tab && m + 8 <= g.M && pl.jj + 8 <= g.ra.L;
-    const int c0 = n0 - 2 * g.d + wm * 128 + (lane >> 4);
-    bf16* const base = g.vc + (int64_t)g.ra.layer * g.ra.max_batch * g.d * g.ra.max_seq;
-    unsigned char* const wr = lds + (lane & 31) * ER + (lane >> 5) * 16;
-    unsigned char* const rd = lds + (lane >> 4) * ER + (lane & 15) * 16;
-    static_for<4>([&](auto ic) {
-        constexpr int i = decltype(ic)::value;
-        static_for<4>([&](auto jc) {
-            constexpr int j = decltype(jc)::value;
+        if (!v_tile) {
+            const int c = cl + (h & 1) * 64;
+            bf16* const dst = base + (int64_t)(c >> hsh) * rows * dh + (c & (dh - 1));
 #pragma unroll
-            for (int g2 = 0; g2 < 2; ++g2) {
+            for (int t = 0; t < 4; ++t) {
+                const float v[8] = {lo[t][0], lo[t][1], lo[t][2], lo[t][3], hi[t][0], hi[t][1], hi[t][2], hi[t][3]};
+                const f32x4 &cs_ = cs[h & 1][t], &sn_ = sn[h & 1][t];
                 bf16x8s o;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] = (__bf16)acc[i][j][g2 * 8 + e];
-                *reinterpret_cast<bf16x8s*>(wr + j * 64 + g2 * 32) = o;
+                for (int pr = 0; pr < 4; ++pr) {
+                    o[2 * pr] = (__bf16)(v[2 * pr] * cs_[pr] - v[2 * pr + 1] * sn_[pr]);
+                    o[2 * pr + 1] = (__bf16)(v[2 * pr] * sn_[pr] + v[2 * pr + 1] * cs_[pr]);
+                }
+                if (rw[h & 1][t].pos >= 0) *reinterpret_cast<bf16x8s*>(dst + (int64_t)rw[h & 1][t].row * dh) = o;
             }
-        });
-        u32x4 v[8];
-#pragma unroll
-        for (int t = 0; t < 8; ++t) v[t] = *reinterpret_cast<const u32x4*>(rd + t * 4 * ER);
-        if (run) {
-#pragma unroll
-            for (int t = 0; t < 8; ++t)
-                __builtin_memcpy(base + ((int64_t)pl.bc * g.d + c0 + i * 32 + t * 4) * g.ra.max_seq + pl.pos, &v[t], 16);
         } else {
-            for (int e = 0; e < 8 && m + e < g.M; ++e) {
-                const TokPlace pe = place(g.ra, m + e);
-                if (pe.pos < 0) continue;
+            const Row* const run = tab + (h & 1) * 64 + (lane & 7) * 8;   // this lane's 8 tokens
+            const Row first = run[0], last = run[7];
+            bf16* const chan = base + (int64_t)(nw - 2 * g.d + (h >> 1) * 32 + (lane >> 3)) * rows;   // its first channel, sequence 0
+            if (!g.ra.pos_tab && last.pos >= 0 && last.row == first.row) {
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const uint32_t w = e < 2 ? v[t].x : e < 4 ? v[t].y : e < 6 ? v[t].z : v[t].w;
-                    const uint16_t x = (uint16_t)(e & 1 ? w >> 16 : w);
-                    __builtin_memcpy(base + ((int64_t)pe.bc * g.d + c0 + i * 32 + t * 4) * g.ra.max_seq + pe.pos, &x, 2);
+                for (int t = 0; t < 4; ++t) {
+                    bf16x8s o;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) o[e] = (__bf16)(e < 4 ? lo[t][e & 3] : hi[t][e & 3]);
+                    __builtin_memcpy(chan + ((int64_t)first.row + t * 8) * rows + first.pos, &o, 16);
+                }
+            } else {
+#pragma unroll 1
+                for (int e = 0; e < 8; ++e) {
+                    const Row one = run[e];
+                    if (one.pos < 0) continue;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        const __bf16 x = (__bf16)*reinterpret_cast<const float*>(rd + t * 8 * ER + e * 4);
+                        __builtin_memcpy(chan + ((int64_t)one.row + t * 8) * rows + one.pos, &x, 2);
+                    }
                 }
             }
         }
@@ -652,8 +651,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_256(const GemmArgs g) {
         unsigned char* const lds = smem + (wave >> 1 ? s_w2 : s_a1) + (wave & 1) * (ITEM / 2);
         if constexpr (PARTS) logit_parts<BN, TM, MB, NB>(g, acc, cur.m0, cur.tile_n, wm, wn, l32, lh);
         if constexpr (EPI == EPI_QKV) {
-            if (v_tile) epilogue_v(g, acc, cur.m0, cur.n0, wm, wn, lane, lds);
-            else epilogue_qk(g, acc, cur.m0, cur.n0, wm, wn, lane, lds);
+            epilogue_qkv(g, acc, v_tile, cur.m0, cur.n0, wm, wn, lane, lds);
         } else if constexpr (EPI == EPI_SWIGLU) {
             epilogue_h(g, acc, cur.m0, cur.tile_n, wm, wn, lane, lds);
         } else {

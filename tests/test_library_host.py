@@ -3,7 +3,9 @@ header declares, and its host-only argument checks behave.  No compute."""
 import ctypes as C
 import os
 import re
+import struct
 
+import msgpack
 import pytest
 
 import paper_2601_05149_amd as mulo
@@ -125,6 +127,44 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=300, cwd=root)
     assert r.returncode != 0
     assert "ONE GPU" in r.stderr + r.stdout and '"metric"' not in r.stdout
+
+
+def kernel_records(path):
+    """The records of every kernel in the device code of the library built here, out of the notes of its code objects."""
+    blob, magic, records = open(path, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__", []
+    for m in re.finditer(magic, blob):
+        at, (n,) = m.end() + 8, struct.unpack_from("<Q", blob, m.end())
+        for _ in range(n):
+            off, size, name = struct.unpack_from("<QQQ", blob, at)
+            if b"gfx950" in blob[at + 24:at + 24 + name]:
+                records += code_object_kernels(blob[m.start() + off:m.start() + off + size])
+            at += 24 + name
+    return records
+
+
+def code_object_kernels(elf):
+    headers, = struct.unpack_from("<Q", elf, 40)
+    size, count = struct.unpack_from("<HH", elf, 58)
+    kernels = []
+    for i in range(count):
+        kind, = struct.unpack_from("<I", elf, headers + i * size + 4)
+        at, length = struct.unpack_from("<QQ", elf, headers + i * size + 24)
+        end = at + length
+        while kind == 7 and at < end:                           # a section of notes
+            n_name, n_desc, note = struct.unpack_from("<III", elf, at)
+            desc = at + 12 + (n_name + 3) // 4 * 4
+            if note == 32 and elf[at + 12:at + 12 + n_name] == b"AMDGPU\0":
+                kernels += msgpack.unpackb(elf[desc:desc + n_desc])["amdhsa.kernels"]
+            at = desc + (n_desc + 3) // 4 * 4
+    return kernels
+
+
+def test_no_tiled_projection_needs_scratch_memory(lib):
+    """No call after mulo_create allocates: a kernel that keeps registers in scratch memory would have the runtime set that up
+    at its first dispatch, outside the workspace."""
+    tiled = [k for k in kernel_records(BD.LIB_PATH) if re.search("k_gemm_(256|ring)", k[".name"])]
+    assert len(tiled) > 20
+    assert [k[".name"] for k in tiled if k[".private_segment_fixed_size"]] == []
 
 
 def test_static_entry_point_rejects_bad_arguments_before_any_gpu_call(lib):
