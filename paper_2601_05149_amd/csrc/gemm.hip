@@ -1116,7 +1116,6 @@ __global__ __launch_bounds__(512) void k_gemv_shared(const GemmArgs g, int ncols
     constexpr int PIECES = CH * MTB * 64 / 512;   // 16-byte pieces of a chunk per thread
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // fragment (group t, step j) at (t CH + j) KB
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l16 = lane & 15, q = lane >> 4;
     const int cg = blockIdx.x % ncg, kw = blockIdx.x / ncg;   // neighbouring workgroups share a K slice of the token operand
     const int n_w = cg * 128 + wave * 16;                     // this wavefront's first column
     const int steps = g.K / 32, per = (steps + g.ksplit - 1) / g.ksplit;
@@ -1183,7 +1182,9 @@ __global__ __launch_bounds__(512) void k_gemv_shared(const GemmArgs g, int ncols
         }
         chunk(sc0, std::false_type{});   // the last chunk requests nothing
     }
-    // this slice's sums: D[weight row 4 q + i][token l16] -> ksums[kw][m][n_w + 4 q + i]
+    // this slice's sums: D[weight row 4 q + i][token l16] -> ksums[kw][m][n_w + 4 q + i].  The lane is counted anew: kept over the
+    // loop it was one register too many with 12, 15 and 16 token groups and went to scratch memory.
+    const int lane_ = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), l16 = lane_ & 15, q = lane_ >> 4;
 #pragma unroll
     for (int t = 0; t < MTB; ++t) {
         const int m = t * 16 + l16, n = n_w + 4 * q;
