@@ -244,19 +244,24 @@ def test_every_projection_on_every_tile_it_has(d, nh, f, V, B):
             assert torch.equal(kv[0][:, :n, :, P:P + L], k0) and torch.equal(kv[1][:, :n, :, :, P:P + L], v0), (n, i)
 
 
-@pytest.mark.parametrize("d,nh,f,V,B", [
-    (128, 2, 256, 25600, 5),   # K of 2 steps; the lm-head's 400 tiles are two rounds, the second one partly filled
-    (256, 2, 192, 512, 5),     # down: K of 3 steps, fewer than the ring is deep
-    (256, 4, 192, 512, 13),    # sequences of 161 tokens end inside runs of 8: every V run of them, heads of 64
+@pytest.mark.parametrize("d,nh,f,V,B,L", [
+    (128, 2, 256, 25600, 5, 161),   # K of 2 steps; the lm-head's 400 tiles are two rounds, the second one partly filled
+    (384, 3, 256, 25600, 5, 161),   # the same with K of 6 steps
+    (256, 2, 192, 512, 5, 161),     # down: K of 3 steps, fewer than the ring is deep
+    (256, 4, 192, 512, 13, 161),    # sequences of 161 tokens end inside runs of 8: every V run of them, heads of 64
+    (256, 2, 256, 512, 90, 3),      # three sequences in a run of 8
+    (512, 4, 640, 512, 41, 811),    # 130 row tiles: q|k|v 780 tiles, out 260, gate|up 650, down 260 (K of 10 steps), lm-head 260
+    (512, 8, 192, 768, 41, 811),    # down: K of 3 steps over two rounds; the lm-head 390 tiles; heads of 64
 ])
-def test_256_tiles_at_short_k_and_over_rounds(d, nh, f, V, B):
+def test_256_tiles_at_short_k_and_over_rounds(d, nh, f, V, B, L):
     """256 x 256 tiles against 128 x 128 ones where the loads of a workgroup's next tile begin in the first steps of the one
     before, and where the last tile of a workgroup has no next: the same logits and cache rows, bit for bit, whatever the
-    parity of the cache row a block begins at."""
+    parity of the cache row a block begins at.  In a launch of more tiles than CUs a workgroup goes from one to the next: from
+    one rotary or V tile to the other kind, and from one residual tile's stores to the next one's requests."""
     m = dict(n_layers=1, d_model=d, n_heads=nh, head_dim=d // nh, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
-    L = 161
+    S = (L + 22) // 8 * 8
     w = G.make_weights(m, seed=25)
-    ctx, cos, sin = make_ctx(m, w, B, 176, 164)
+    ctx, cos, sin = make_ctx(m, w, B, S, (L + 3) // 4 * 4)
     kv = mulo.alloc_kv(ctx, DEV)
     toks = G.uniform_tokens((B, L), V, 25, tag=1)
     for P in (8, 9, 12):
