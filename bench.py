@@ -132,18 +132,31 @@ def resample_bench(mulo, ctx, kv, c, B, L, P, V, rate, seed, gen):
         "ms_per_island_pass": round(ms_isl / max(passes, 1), 3)}), flush=True)
 
 
-def traffic_from_profile(workload):
-    """HBM bytes per launch of the roofline kernel (both kernels of the gate|up projection): FETCH_SIZE and WRITE_SIZE
+def kernel_symbol(name):
+    """The mangled template instance of a kernel as the profiler prints it: k_gemm_256<2, false> -> k_gemm_256ILi2ELb0EE."""
+    base, _, args = name.rstrip(">").partition("<")
+    return base + "I" + "".join("Lb%dE" % (a == "true") if a in ("true", "false") else "Li%sE" % a
+                                for a in args.split(", ")) + "E"
+
+
+def traffic_from_profile(workload, profiles=os.path.join(ROOT, "profiles"), library=None):
+    """HBM bytes per launch of the roofline kernel (all kernels of the gate|up projection): FETCH_SIZE and WRITE_SIZE
     of two rocprofv3 --pmc runs of this benchmark, scaled by the copy-kernel calibration; read from the line
-    `roofline kernel traffic per launch: N bytes` of profiles/verify_step_<workload>_hbm_traffic.md (bench.py
-    cannot run the profiler on itself).  None when that summary is absent."""
+    `roofline kernel traffic per launch (kernel + kernel ...): N bytes` of
+    profiles/verify_step_<workload>_hbm_traffic.md (bench.py cannot run the profiler on itself).  None when that summary
+    is absent, or was taken on a kernel that the library does not hold."""
     import re
-    path = os.path.join(ROOT, "profiles", "verify_step_%s_hbm_traffic.md" % workload)
+
+    from paper_2601_05149_amd.binding import LIB_PATH
     try:
-        m = re.search(r"roofline kernel traffic per launch:\s*([0-9.eE+]+)\s*bytes", open(path).read())
-        return float(m.group(1)) if m else None
+        text = open(os.path.join(profiles, "verify_step_%s_hbm_traffic.md" % workload)).read()
+        held = open(library or LIB_PATH, "rb").read()
     except OSError:
         return None
+    m = re.search(r"roofline kernel traffic per launch \((.+)\):\s*([0-9.eE+]+)\s*bytes", text)
+    if not m or not all(kernel_symbol(k).encode() in held for k in m.group(1).split(" + ")):
+        return None
+    return float(m.group(2))
 
 
 def run_workload(mulo, name, wd, rope, steps, warmup, sigma=None, first_block=False, profile="roofline", want_ctx=False,

@@ -129,6 +129,19 @@ def test_bench_refuses_more_than_one_gpu():
     assert "ONE GPU" in r.stderr + r.stdout and '"metric"' not in r.stdout
 
 
+def test_bench_reports_the_traffic_of_the_kernels_it_runs(lib, tmp_path):
+    """The bytes per launch that the benchmark reads from a profile summary are those of kernels that the library holds."""
+    import bench
+    now, gone = "k_gemm_256<2, false> + k_gemm_ring<128, 256, 2, 2, 3, 2, false>", "k_gemm_bf16<256, 256, 4, 2, 2>"
+    for text, want in (("roofline kernel traffic per launch (%s): 1.25e+09 bytes" % now, 1.25e9),
+                       ("roofline kernel traffic per launch (%s): 1.25e+09 bytes" % gone, None),
+                       ("roofline kernel traffic per launch (%s + %s): 1.25e+09 bytes" % (now, gone), None),
+                       ("roofline kernel traffic per launch: 1.25e+09 bytes", None)):
+        (tmp_path / "verify_step_w_hbm_traffic.md").write_text("a table\n\n%s\n" % text)
+        assert bench.traffic_from_profile("w", str(tmp_path)) == want, text
+    assert bench.traffic_from_profile("another", str(tmp_path)) is None
+
+
 def kernel_records(path):
     """The records of every kernel in the device code of the library built here, out of the notes of its code objects."""
     blob, magic, records = open(path, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__", []
