@@ -76,7 +76,7 @@ template <> struct Four<__hip_bfloat16> { typedef __attribute__((ext_vector_type
 // once with 16-byte loads and kept in registers (d <= 256 * 4 * NV4); NV4 == 0 re-reads it instead.
 // A chain of latencies between two launches that move all the bytes, so the gains are requested with the row, in one access per
 // four, results leave the same way, and the sum crosses lanes without LDS where it can: with the embedding's 16-byte pieces a
-// token of one sequence over 8 layers (17 norms) 971 -> 944 us, of four 1187 -> 1163.
+// token of one sequence over 8 layers (17 norms) 964 - 966 -> 939 - 942 us, of four 1181 - 1184 -> 1158 - 1159 (three pairs of runs).
 template <typename T, int NV4>
 __global__ __launch_bounds__(TPB) void k_rmsnorm(const float* __restrict__ x, const T* __restrict__ gain,
                                                  T* __restrict__ out, int d, float eps, int frag) {

@@ -259,8 +259,6 @@ __device__ __forceinline__ void epilogue(const GemmArgs& g, f32x16 (&acc)[MB][NB
                         if (seg == 2) {
                             // a lane holds 8 consecutive channels of ONE token, the 32 lanes of a half are 32
                             // consecutive tokens = 64 contiguous bytes of a row of the transposed cache per store
-                            // (4096 x 12288 x 4096: 345 us in one launch, 350 with a V projection of its own whose lanes
-                            // hold 8 consecutive tokens; 2560 tokens: 224 against 276)
                             if (pl.pos >= 0) {
                                 const int64_t hb = ((int64_t)g.ra.layer * g.ra.max_batch + pl.bc) * g.ra.n_heads + hd;
 #pragma unroll
@@ -299,9 +297,10 @@ __device__ __forceinline__ f32x16 mma(const bf16x8& a, const bf16x8& b, const f3
 }
 
 // ---- 256 x 256 tiles: 4 wavefronts of 128 x 128 (one per SIMD) over an LDS ring of five 32 KB items ---------------
-// For launches whose tiles fill the chip.  What bounds them is energy: the shader clock sinks to 1.6 - 1.7 GHz under this
-// load and taking barriers, waits or K-loop loads out (timing only) changes cycles but not time, so what helps is fewer bytes
-// moved per product and no phases in which the matrix pipes rest.
+// For launches whose tiles fill the chip.  What bounds them is energy: the matrix pipes are busy in 72 to 80 % of the cycles, but
+// the shader clock sinks to 1.66 - 1.72 GHz under this load (counters at 4096 tokens; on weights that are all alike the same
+// launches of 16384 tokens take 77 to 81 % of the time), so what helps is fewer bytes moved per product and no phases in which
+// the matrix pipes rest.
 //   - A wavefront owns 128 x 128 outputs (all 256 accumulators of a SIMD lane's second register half), 16 MFMAs per 8 KB of
 //     fragments: a 64-deep step reads 128 KB of LDS where 8 wavefronts of 64 x 128 read 192.
 //   - Operands go from memory to LDS directly (no staging registers, no ds_write).  An item is 256 rows x 128 bytes of one
@@ -318,7 +317,8 @@ __device__ __forceinline__ f32x16 mma(const bf16x8& a, const bf16x8& b, const f3
 //     stream's first half is requested before the K loop.  q|k|v tiles of V exchange the operands' roles in the K loop.
 // us per launch, 8 wavefronts staged through registers -> here, cold weights, 4096 tokens: 4096 x 4096 147 -> 115,
 // 4096 x 11008 297 -> 267, q|k|v 334 -> 307, gate|up 572 -> 507, lm-head 439 -> 421.
-constexpr int ER = 272;   // bytes of a row of the epilogues' LDS block: 256 and 16 more, no bank conflicts in either direction
+constexpr int LDS_256 = 5 * 256 * 128;
+constexpr int ER = 272;   // bytes of a row of the epilogues' LDS block: 256 and 16 more (conflicts in at most 0.8 % of a launch's cycles)
 
 // The float32 output rows of a tile: a descriptor (rows past M lie outside: reads give zeros, writes nothing), this lane's
 // offset, and what access t (4 rows of 64 columns) of block h (32 rows x 64 columns) adds to it.
@@ -875,7 +875,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
 template <int EPI, bool PARTS>
 void run_256(GemmArgs g, int tile_n0, int tiles_n, hipStream_t st) {
     auto kern = k_gemm_256<EPI, PARTS>;
-    constexpr int lds = 5 * 256 * 128;
+    constexpr int lds = LDS_256;
     static int attr_state = 0;  // each instantiation is configured once per process
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds, &attr_state)) return;
     const int total = (g.M + 255) / 256 * tiles_n, resident = cu_count();
@@ -1304,26 +1304,28 @@ __global__ __launch_bounds__(256) void k_pack_weights(const bf16* __restrict__ s
 // with 257 tiles the CU that has two of them takes twice the bytes, and the fit knows (4096 x 4096: 128 tokens, 256 tiles, 18 us
 // against 22 on 64 x 64; 256 tokens, 512 tiles, 28 against 23).  The constants (us) are the least-squares fit over 18 token
 // counts from 72 to 4096 and the ten projection shapes of the two bf16 configurations (widths 1024 and 4096; no other width
-// was timed), cold weights: rms error 9 to 14 %; over that grid the tile it picks takes 2 % longer than the best of each
-// shape, and 1.40 times less than the rule before it (256 x 256 tiles from 1024 tokens in whole tiles on, 128 x 256 where
-// their rounds were 80 % full, else 128 x 128 staged through registers).
+// was timed), cold weights: rms error 9 to 14 %.  The row of 256 x 256 was fitted to tiles of 8 wavefronts staged through
+// registers, cut-off columns included, which took up to 22 % longer than the kernel that is here now.  Against every tile timed by
+// itself at 19 token counts from 192 to 4096 the picks take 0.8 % longer than the best on average; the worst are q|k|v and gate|up
+// of 288 tokens of width 4096 (66 us on 64 x 64 against 52 on 256 x 128; 93 on 64 x 128 against 82 on 256 x 256), then the
+// lm-head of 3072 tokens of width 1024 (68 on 128 x 256 against 61 on 256 x 256).
 struct TileCost {
-    int bm, bn, stages, per_cu;   // ring stages of bm + bn rows of 128 bytes; 256 x 256: two padded buffers (144 bytes a row)
+    int bm, bn, stages, per_cu;   // ring stages of bm + bn rows of 128 bytes; 256 x 256: 0, it has a ring of its own
     float c0, tf, t0, e;
-    constexpr int fit() const { return bm == 256 && bn == 256 ? 1 : 160 * 1024 / (stages * (bm + bn) * 128); }
+    constexpr int fit() const { return 160 * 1024 / (stages ? stages * (bm + bn) * 128 : LDS_256); }
 };
 enum { TILE_32x64, TILE_64x64, TILE_128x64, TILE_64x128, TILE_128x128, TILE_256x128, TILE_128x256, TILE_256x256, N_TILES };
 constexpr TileCost TILE_COST[N_TILES] = {
     {32, 64, 6, 1, 3.4f, 0.161f, 0.107f, -0.1f},   {64, 64, 5, 2, 2.7f, 0.435f, 0.146f, 0.1f},
     {128, 64, 3, 2, 2.3f, 0.683f, 0.271f, 1.2f},   {64, 128, 3, 2, 4.2f, 0.723f, 0.311f, -1.1f},
     {128, 128, 5, 1, 2.7f, 0.538f, 0.407f, 2.4f},  {256, 128, 3, 1, 2.6f, 0.856f, 0.56f, 4.6f},
-    {128, 256, 3, 1, 3.9f, 0.925f, 0.67f, 2.6f},   {256, 256, 2, 1, 6.7f, 1.544f, 1.011f, 4.4f}};
+    {128, 256, 3, 1, 3.9f, 0.925f, 0.67f, 2.6f},   {256, 256, 0, 1, 6.7f, 1.544f, 1.011f, 4.4f}};
 constexpr bool tiles_fit() {
     for (int i = 0; i < N_TILES; ++i)
         if (TILE_COST[i].fit() != (i == TILE_32x64 ? 2 : TILE_COST[i].per_cu)) return false;
     return true;
 }
-static_assert(tiles_fit(), "the constants were fitted with these");
+static_assert(tiles_fit(), "workgroups per CU");
 
 // Column tiles of a 256 x 256 launch that run as such: a last round that would leave more than half of the CUs idle is
 // cut off and runs as 128 x 256 tiles (twice as many workgroups, half the work each).
