@@ -30,6 +30,7 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 typedef __attribute__((address_space(3))) void lds_void;
+typedef const __attribute__((address_space(1))) void glb_void;
 
 constexpr float LOG2E = 1.4426950408889634f;
 
@@ -157,23 +158,32 @@ __global__ __launch_bounds__(NTH, DH * BKV <= 8192 ? 2 : 1) void k_attn_bf16(con
     const int krow = wave * RK + lane / (64 / RK), vrow = wave * RV + lane / (64 / RV);   // this lane's row in load 0 (the key repeats: NW RK, NW RV are multiples of 16)
     const int kchunk = lane % (64 / RK) ^ key_of(krow, KRB), vchunk = lane % (64 / RV) ^ key_of(vrow, VRB);
     static_assert(NW * RK % 16 == 0 && NW * RV % 16 == 0, "the key of a lane's rows");
-    const int koff = lane / (64 / RK) * KRB + kchunk * 16;
-    const uint32_t voff = (uint32_t)(lane / (64 / RV)) * (uint32_t)a.max_seq * 2u + vchunk * 16;
-    auto load_k = [&](int t) {   // rows and columns past the cache lie outside the descriptors
+    // A tile that runs past the end of the cache takes the last row and columns again: nothing sees those keys (max_seq is a multiple
+    // of 8, a tile begins in front of it).  One scalar address per operand and tile and a lane offset, not a descriptor per load:
+    // building those took about 180 scalar instructions and lane reads a tile, which a CU with one workgroup has nothing to hide
+    // behind (32 heads of 128, us: 98 queries, 2949 keys 86 -> 68, 4 x 128, 3128 keys 90 -> 73, 1 x 576, 1856 keys 45 -> 43,
+    // 4 x 1024, 4224 keys 272 -> 264).
+    const int max_seq = a.max_seq;
+    const uint32_t voff = (uint32_t)(lane / (64 / RV)) * (uint32_t)max_seq * 2u;
+    const unsigned char* const kbytes = reinterpret_cast<const unsigned char*>(kbase);
+    const unsigned char* const vbytes = reinterpret_cast<const unsigned char*>(vbase + (int64_t)wave * RV * max_seq);
+    const int64_t vstep = (int64_t)NW * RV * max_seq * 2;   // bytes from a load to the next
+    auto to_lds = [](const unsigned char* base, uint32_t off, unsigned char* lds) {
+        __builtin_amdgcn_global_load_lds((glb_void*)(base + off), (lds_void*)lds, 16, 0, 0);
+    };
+    auto load_kv = [&](int t) {
+        unsigned char* const lds = smem + (t & 1) * BUF + wave * 1024;
+        const unsigned char* const kt = kbytes + (int64_t)t * (BKV * KRB);
+        const unsigned char* const vt = vbytes + (int64_t)t * VRB;
+        const int left = max_seq - t * BKV;   // rows of the cache from the tile's first on
 #pragma unroll
         for (int i = 0; i < LK; ++i) {
-            const int64_t row = (int64_t)t * BKV + (i * NW + wave) * RK;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(kbase + row * DH, (a.max_seq - row) * KRB),
-                                                     (lds_void*)(smem + (t & 1) * BUF + (i * NW + wave) * 1024), 16, koff, 0, 0, 0);
+            const int row = krow + i * NW * RK;
+            to_lds(kt, (uint32_t)(row < left ? row : left - 1) * KRB + kchunk * 16, lds + i * NW * 1024);
         }
-    };
-    auto load_v = [&](int t) {
+        const uint32_t vo = voff + (uint32_t)(vchunk * 8 < left - 8 ? vchunk * 8 : left - 8) * 2u;
 #pragma unroll
-        for (int i = 0; i < LV; ++i) {
-            const int64_t at = (int64_t)((i * NW + wave) * RV) * a.max_seq + (int64_t)t * BKV;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(vbase + at, ((int64_t)DH * a.max_seq - at) * 2),
-                                                     (lds_void*)(smem + (t & 1) * BUF + KT + (i * NW + wave) * 1024), 16, (int)voff, 0, 0, 0);
-        }
+        for (int i = 0; i < LV; ++i) to_lds(vt + i * vstep, vo, lds + KT + i * NW * 1024);
     };
     // this wavefront's loads have landed and its fragment reads are done; meet the others
     auto meet = [&]() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
@@ -267,6 +277,7 @@ __global__ __launch_bounds__(NTH, DH * BKV <= 8192 ? 2 : 1) void k_attn_bf16(con
                     for (int r = 0; r < 16; ++r) {
                         const int key = kv0 + kb * 32 + 16 * (r >> 3) + 8 * lh + (r & 7);
                         if (((mine >> (16 * (r >> 3) + (r & 7))) & 1u) && key < qpos) s[kb][r] = -__builtin_huge_valf();
+                        if ((r & 3) == 3) __builtin_amdgcn_sched_barrier(0);   // all 64 comparisons at once need more scalars than there are
                     }
                 }
             }
@@ -352,9 +363,10 @@ __global__ __launch_bounds__(NTH, DH * BKV <= 8192 ? 2 : 1) void k_attn_bf16(con
         });
         l_run = l_run * alpha + ps;
     };
-    load_k(t_begin);
-    load_v(t_begin);
+    load_kv(t_begin);
     clear_unseen(t_begin);
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) asm volatile("" : "+v"(qf[kk]));   // wait for the queries here: among the tiles' loads that wait is for those as well
     meet();
     for (int t = t_begin; t < t_end; ++t) {
         uint32_t hide_next = 0;
@@ -362,8 +374,7 @@ __global__ __launch_bounds__(NTH, DH * BKV <= 8192 ? 2 : 1) void k_attn_bf16(con
             if constexpr (BKV == 64) {
                 if (a.hide && wave_live) hide_next = hide_flag(t + 1);
             }
-            load_k(t + 1);
-            load_v(t + 1);
+            load_kv(t + 1);
         }
         if (wave_live && (scattered || t * BKV <= P + wave_jmax)) {
             score(t);

@@ -520,6 +520,40 @@ def test_forward_single_token_steps_with_split_keys(dh, nh, copy):
                           dr.forward(t, Pn + step).numpy(), du.forward(t, Pn + step).numpy(), strict=True)
 
 
+@pytest.mark.parametrize("dh,nh", [(64, 4), (128, 2)])
+@pytest.mark.parametrize("L,P,S", [
+    (1, 71, 72),       # a token whose cache ends 8 rows into a 64-key tile (keys dealt to several workgroups)
+    (7, 113, 120),     # and 56 rows into one
+    (100, 92, 192),    # whole tiles
+    (128, 128, 264),   # 8 free rows behind the block
+    (130, 134, 264),   # 128-key tiles: 8 rows into the last one
+    (300, 204, 504),   # 120 rows into it
+])
+def test_attention_at_the_end_of_the_cache(dh, nh, L, P, S):
+    """A cache that ends inside a tile of keys against one with 128 more rows, NaN in every row that nothing has written: the same
+    logits and cache rows, bit for bit."""
+    m = dict(n_layers=2, d_model=dh * nh, n_heads=nh, head_dim=dh, d_ffn=256, vocab=512, dtype="bf16", rms_eps=1e-5)
+    B = 2
+    w = G.make_weights(m, seed=29)
+    toks = G.uniform_tokens((B, L), m["vocab"], 29, tag=1)
+    g = torch.Generator(device=DEV).manual_seed(29)
+    k0 = torch.randn(2, B, nh, P, dh, generator=g, device=DEV)
+    v0 = torch.randn(2, B, nh, dh, P, generator=g, device=DEV)
+    got = []
+    for rows in (S, S + 128):
+        ctx, cos, sin = make_ctx(m, w, B, rows, (L + 3) // 4 * 4)
+        kv = mulo.alloc_kv(ctx, DEV)
+        for t in kv:
+            t.fill_(float("nan"))
+        kv[0][:, :, :, :P] = k0
+        kv[1][:, :, :, :, :P] = v0
+        z = gpu_forward(ctx, kv, toks, P)
+        assert np.isfinite(z).all()
+        got.append((z, kv[0][:, :, :, :P + L].clone(), kv[1][:, :, :, :, :P + L].clone()))
+    assert np.array_equal(got[0][0], got[1][0])
+    assert torch.equal(got[0][1], got[1][1]) and torch.equal(got[0][2], got[1][2])
+
+
 def frag_to_rows(buf, M, K):
     """Undo the fragment order of a [M, K] token operand (include/mulo.h, mulo_workspace_read): element (m, k)
     sits at ((m / 16) * (K / 32) + k / 32) * 512 + ((k % 32) / 8 * 16 + m % 16) * 8 + k % 8."""

@@ -181,6 +181,13 @@ def test_no_kernel_needs_scratch_memory(lib):
     assert [k[".name"] for k in kernels if k[".private_segment_fixed_size"]] == []
 
 
+def test_attention_keeps_its_scalars_in_registers(lib):
+    """Scalars that do not fit are written to and read back from vector lanes around every tile of keys, in front of its loads."""
+    attention = [k for k in kernel_records(BD.LIB_PATH) if "k_attn_bf16" in k[".name"]]
+    assert len(attention) >= 5
+    assert [k[".name"] for k in attention if k[".sgpr_spill_count"]] == []
+
+
 def test_static_entry_point_rejects_bad_arguments_before_any_gpu_call(lib):
     """mulo_accept_local_resample_static checks its arguments on the host first (no device is touched)."""
     V, B, L = 1024, 1, 64
