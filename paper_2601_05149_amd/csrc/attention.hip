@@ -65,10 +65,10 @@ struct AttnArgs {
     const uint8_t* hide;   // [B, Lblk]
     int P0, Lblk;
 };
-constexpr float LAZY_EXP = 8.0f;     // 4 x 1024 queries against 4096 keys: 0 -> 278, 4 -> 287, 8 -> 277 and 279 us, within the noise of a card
+constexpr float LAZY_EXP = 8.0f;     // 4 x 1024 queries against 4096 keys: 0 -> 278 and 281, 8 -> 278 and 273 us, within the noise of a card
 constexpr int MAX_SPLIT = 16;
 constexpr int NS_TARGET = 512;      // workgroups a key split aims at (a token of 4 sequences of 4000 rows, 32 heads of 128, us in front of the
-                                    // combine: 256 -> 66, 512 -> 49, 1024 -> 52, 2048 -> 56)
+                                    // combine: 256 -> 58, 512 -> 49, 1024 -> 51, 2048 -> 54)
 constexpr int SPLIT_QUERIES = 32;   // a key split serves at most this many queries per (sequence, head)
 
 // two workgroups per CU where their LDS fits twice (2 x 64 KB: 64-key tiles of heads of 128, 128-key tiles of heads of 64)
@@ -475,11 +475,11 @@ void run_attn_cfg(const AttnArgs& a, hipStream_t st) {
 // Over 128-key tiles a wavefront's 32 queries are added up by themselves, so the queries per workgroup do not show in the
 // bits: heads of 128 take 128 (4 wavefronts) where all of those have a CU, else 256 (8 wavefronts: one workgroup per CU
 // either way, 128 KB of LDS); heads of 64 take 128, two workgroups per CU.  Measured, 256 / 128 queries, us: 32 heads of 128:
-// 1 x 256 queries, 3256 keys 81 / 73, 4 x 256, 3256 keys 103 / 94, 3 x 242, 2656 keys 77 / 68, 1 x 576, 1856 keys 46 / 43,
-// 1 x 1024, 4024 keys 103 / 95, 1 x 384, 2795 keys 65 / 61, and past one workgroup per CU 8 x 200, 3146 keys 106 / 160,
-// 4 x 1024, 4224 keys 261 / 382; 16 heads of 64: 4 x 256, 832 keys 18.0 / 15.0, 4 x 256, 3256 keys 55 / 44, 1 x 1024, 1524 keys
-// 27.9 / 23.2, but past one workgroup per CU 8 x 300, 1300 keys 25.5 / 28.7, 6 x 512, 1112 keys 23.4 / 25.7, 16 x 1024,
-// 2024 keys 171 / 175 (there the line is not where these figures put it).
+// 1 x 256 queries, 3256 keys 79 / 68, 4 x 256, 3256 keys 100 / 94, 3 x 242, 2656 keys 72 / 69, 1 x 576, 1856 keys 47 / 43,
+// 1 x 1024, 4024 keys 106 / 96, 1 x 384, 2795 keys 65 / 59, and past one workgroup per CU 8 x 200, 3146 keys 114 / 164,
+// 4 x 1024, 4224 keys 261 / 403; 16 heads of 64: 4 x 256, 832 keys 18.3 / 14.6, 4 x 256, 3256 keys 57 / 43, 1 x 1024, 1524 keys
+// 28.6 / 22.0, 16 x 1024, 2024 keys 188 / 179, but 8 x 300, 1300 keys 28.0 / 30.0 and 6 x 512, 1112 keys 25.8 / 27.3: between one
+// and two workgroups per CU the line is not where these figures put it.
 constexpr int BKV_SMALL = 64, SHORT_BLOCK = 128;
 template <int DH>
 void run_attn(const AttnArgs& a, hipStream_t st) {
