@@ -297,8 +297,8 @@ __device__ __forceinline__ f32x16 mma(const bf16x8& a, const bf16x8& b, const f3
 }
 
 // ---- 256 x 256 tiles: 4 wavefronts of 128 x 128 (one per SIMD) over an LDS ring of five 32 KB items ---------------
-// For launches whose tiles fill the chip.  What bounds them is energy: the matrix pipes are busy in 72 to 80 % of the cycles, but
-// the shader clock sinks to 1.66 - 1.72 GHz under this load (counters at 4096 tokens; on weights that are all alike the same
+// For launches whose tiles fill the chip.  What bounds them is energy: the matrix pipes are busy in 71 to 80 % of the cycles, but
+// the shader clock sinks to 1.66 - 1.75 GHz under this load (counters at 4096 tokens; on weights that are all alike the same
 // launches of 16384 tokens take 77 to 81 % of the time), so what helps is fewer bytes moved per product and no phases in which
 // the matrix pipes rest.
 //   - A wavefront owns 128 x 128 outputs (all 256 accumulators of a SIMD lane's second register half), 16 MFMAs per 8 KB of
