@@ -931,7 +931,8 @@ __device__ __forceinline__ void stream_epilogue(const GemmArgs& g, int m, int n,
 
 // ---- up to 64 tokens (single-token decoding of a few sequences, island passes): weight-streaming kernel ----
 // The work is reading every weight once, so nothing is staged: a workgroup owns 16 output columns (for
-// gate|up: 16 feed-forward columns = 16 gate rows + 16 up rows), its 8 wavefronts split K, and every lane
+// gate|up: 16 feed-forward columns = 16 gate rows + 16 up rows), or up to four such blocks where several token groups
+// share them, or 8 feed-forward columns (run_gemv's rules; a sum is the same in each), its 8 wavefronts split K, and every lane
 // feeds v_mfma_f32_16x16x32_bf16 from registers loaded straight from global memory.  In that instruction's operand
 // layout the four lanes l16, l16 + 16, l16 + 32, l16 + 48 hold 4 x 8 consecutive k of weight row l16, so one load
 // instruction of a wavefront reads 64 contiguous bytes of each of 16 rows: whole 64-byte sectors (with the 32-row
@@ -942,13 +943,21 @@ __device__ __forceinline__ void stream_epilogue(const GemmArgs& g, int m, int n,
 // D[weight row 4 q + i][token l16], q = lane / 16: a lane owns 4 consecutive output columns of one token.  The
 // 8 partial sums are added in a fixed order through LDS and the epilogue runs on pairs of adjacent columns.
 typedef __attribute__((ext_vector_type(4))) float f32x4v;
-template <int EPI, int MT, bool WFRAG>
+enum { UNIT_HALF = 0 };   // gate|up in workgroups of 8 feed-forward columns: 8 gate rows and 8 up rows are one MFMA's 16
+template <int EPI, int MT, int NB, bool WFRAG>
 __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
-    constexpr int NA = EPI == EPI_SWIGLU ? 2 : 1;   // weight matrices (accumulator sets) per column
+    constexpr bool HALF = NB == UNIT_HALF;
+    constexpr int NBLK = HALF ? 1 : NB;                            // column blocks of the workgroup
+    constexpr int NA = EPI == EPI_SWIGLU && !HALF ? 2 : 1;         // weight matrices (accumulator sets) per column
+    constexpr int NR = NA * NBLK;                                  // 16-row weight blocks a step multiplies
+    constexpr int COLS = HALF ? 8 : 16;                            // columns of a block
+    static_assert(!HALF || (EPI == EPI_SWIGLU && MT == 1), "half blocks are gate|up's, one token group");
     // 32-deep k-steps in flight per wavefront: what 16 requests of 16 bytes per lane allow, at least 4 (measured at
-    // the 7B shape: 16 -> 181 ms, 24 -> 185, 32 -> 186 for a re-sampling run of 21 island passes)
-    constexpr int U = 16 / (NA + MT) < 4 ? 4 : 16 / (NA + MT);
-    __shared__ float part[8][NA * MT][4][64];
+    // the 7B shape: 16 -> 181 ms, 24 -> 185, 32 -> 186 for a re-sampling run of 21 island passes); with several column blocks
+    // one workgroup has a CU to itself, and 24 requests are what its registers hold
+    constexpr int U = NBLK > 1 ? (24 / (NR + MT) < 2 ? 2 : 24 / (NR + MT)) : 16 / (NR + MT) < 4 ? 4 : 16 / (NR + MT);
+    constexpr int NBUF = NBLK > 1 ? 2 : 1;
+    __shared__ float part[NBUF][8][NA * MT][4][64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, q = lane >> 4;
     // Weight loads use another lane order than the MFMA: lane 4 r + c fetches chunk c (16 bytes) of row r, so that
@@ -961,36 +970,38 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
     // operand arrives in fragment order and needs none.
     const int lrow = lane >> 2, lchunk = lane & 3;
     const int from_lane = (4 * l16 + q) << 2;   // byte address of the source lane for ds_bpermute
-    const int n_blk = blockIdx.x * 16;     // first output column (gate|up: first feed-forward column)
-    const int steps = g.K / 32, per = (steps + 7) / 8;
+    const int cols = EPI == EPI_SWIGLU ? g.N / 2 : g.N, nblocks = (cols + COLS - 1) / COLS;
+    const int blk0 = blockIdx.x * NBLK;    // first block of columns (gate|up: of feed-forward columns)
+    const int steps = g.K / 32, per = ((steps + 7) / 8 + 1) & ~1;   // whole 128-byte lines of a weight row per wavefront
     const int s0 = wave * per, s1 = s0 + per < steps ? s0 + per : steps;
 
     // weight row(s) this lane fetches; with a copy in fragment order (WFRAG) the KB of (16-row block, step) is
     // contiguous in the MFMA's own lane order: lane l owns its bytes [16 l, 16 l + 16), no exchange afterwards
-    const bf16* w[NA];
-    if constexpr (WFRAG) {
-        int blk = blockIdx.x;   // 16-row block inside its matrix
-        const bf16* base = g.W0;
+    const bf16* w[NR];
+#pragma unroll
+    for (int nb = 0; nb < NBLK; ++nb) {
+        int blk = blk0 + nb < nblocks ? blk0 + nb : nblocks - 1;   // a block past the last column re-reads the last one
+        const bf16 *base0 = g.W0, *base1 = g.W1;
         if constexpr (EPI == EPI_QKV) {
-            const int seg = n_blk / g.d;
-            base = seg == 0 ? g.W0 : seg == 1 ? g.W1 : g.W2;
+            const int seg = blk * 16 / g.d;                        // a block never straddles q | k | v (d % 16 == 0)
+            base0 = seg == 0 ? g.W0 : seg == 1 ? g.W1 : g.W2;
             blk -= seg * (g.d / 16);
         }
-        w[0] = base + (int64_t)blk * steps * 512 + lane * 8;
-        if constexpr (EPI == EPI_SWIGLU) w[1] = g.W1 + (int64_t)blk * steps * 512 + lane * 8;
-    } else {
-        int r = n_blk + lrow;
-        if constexpr (EPI == EPI_QKV) {
-            const int seg = n_blk / g.d;                       // a block never straddles q | k | v (d % 16 == 0)
-            w[0] = (seg == 0 ? g.W0 : seg == 1 ? g.W1 : g.W2) + (int64_t)(r - seg * g.d) * g.K;
-        } else if constexpr (EPI == EPI_SWIGLU) {
-            const int f = g.N / 2;
-            r = r < f ? r : f - 1;
-            w[0] = g.W0 + (int64_t)r * g.K;
-            w[1] = g.W1 + (int64_t)r * g.K;
+        if constexpr (HALF) {
+            if constexpr (WFRAG) {   // rows 0 .. 7 of the MFMA: half of the gate matrix's 16-row block, rows 8 .. 15: of the up matrix's
+                w[0] = (l16 < 8 ? base0 : base1) + (int64_t)(blk >> 1) * steps * 512 + (q * 16 + (blk & 1) * 8 + (l16 & 7)) * 8;
+            } else {
+                const int r = blk * 8 + (lrow & 7);
+                w[0] = (lrow < 8 ? base0 : base1) + (int64_t)(r < cols ? r : cols - 1) * g.K;
+            }
+        } else if constexpr (WFRAG) {
+            w[nb * NA] = base0 + (int64_t)blk * steps * 512 + lane * 8;
+            if constexpr (NA == 2) w[nb * NA + 1] = base1 + (int64_t)blk * steps * 512 + lane * 8;
         } else {
-            r = r < g.N ? r : g.N - 1;
-            w[0] = g.W0 + (int64_t)r * g.K;
+            int r = blk * 16 + lrow;
+            if constexpr (EPI != EPI_QKV) r = r < cols ? r : cols - 1;
+            w[nb * NA] = base0 + (int64_t)r * g.K;
+            if constexpr (NA == 2) w[nb * NA + 1] = base1 + (int64_t)r * g.K;
         }
     }
     // The token operand is stored in fragment order: the KB of (token group t, step s) is contiguous and lane l owns
@@ -1001,7 +1012,7 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
     for (int t = 0; t < MT; ++t) has_x[t] = t * 16 + l16 < g.M;
     if constexpr (!WFRAG) {
 #pragma unroll
-        for (int i = 0; i < NA; ++i) w[i] += lchunk * 8;
+        for (int i = 0; i < NR; ++i) w[i] += lchunk * 8;
     }
     auto to_mfma_order = [&](u32x4 v) {
         u32x4 r;
@@ -1012,9 +1023,9 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
         return r;
     };
 
-    f32x4v acc[NA][MT];
+    f32x4v acc[NR][MT];
 #pragma unroll
-    for (int i = 0; i < NA; ++i)
+    for (int i = 0; i < NR; ++i)
 #pragma unroll
         for (int t = 0; t < MT; ++t) acc[i][t] = f32x4v{0.f, 0.f, 0.f, 0.f};
     const u32x4 zero = {0u, 0u, 0u, 0u};
@@ -1024,7 +1035,7 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
     // per batch).  No branch on the step index: steps past the end of the slice re-read the matrix's last step and
     // are multiplied by zeros (a branch there makes the compiler wait for every load in flight).  The last batch
     // requests nothing.
-    u32x4 wv[NA][U], xv[MT][U];
+    u32x4 wv[NR][U], xv[MT][U];
 #pragma unroll
     for (int t = 0; t < MT; ++t)
 #pragma unroll
@@ -1032,23 +1043,23 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
     auto request = [&](int u, int s) {
         const int sc = s < steps ? s : steps - 1;
 #pragma unroll
-        for (int i = 0; i < NA; ++i) wv[i][u] = *reinterpret_cast<const u32x4*>(w[i] + sc * (WFRAG ? 512 : 32));
+        for (int i = 0; i < NR; ++i) wv[i][u] = *reinterpret_cast<const u32x4*>(w[i] + sc * (WFRAG ? 512 : 32));
 #pragma unroll
         for (int t = 0; t < MT; ++t)   // lanes whose token does not exist request nothing (a 4-token launch reads 4 x 64 bytes of the KB)
             if (has_x[t]) xv[t][u] = *reinterpret_cast<const u32x4*>(xg + ((int64_t)t * steps + sc) * 512);
     };
-    auto permute = [&](int u, int s, bf16x8 (&wf)[NA], bf16x8 (&xf)[MT]) {
+    auto permute = [&](int u, int s, bf16x8 (&wf)[NR], bf16x8 (&xf)[MT]) {
         const bool in_slice = s < s1;
 #pragma unroll
-        for (int i = 0; i < NA; ++i) wf[i] = __builtin_bit_cast(bf16x8, WFRAG ? wv[i][u] : to_mfma_order(wv[i][u]));
+        for (int i = 0; i < NR; ++i) wf[i] = __builtin_bit_cast(bf16x8, WFRAG ? wv[i][u] : to_mfma_order(wv[i][u]));
 #pragma unroll
         for (int t = 0; t < MT; ++t) xf[t] = __builtin_bit_cast(bf16x8, (in_slice && has_x[t]) ? xv[t][u] : zero);
     };
-    auto multiply = [&](const bf16x8 (&wf)[NA], const bf16x8 (&xf)[MT]) {
+    auto multiply = [&](const bf16x8 (&wf)[NR], const bf16x8 (&xf)[MT]) {
 #pragma unroll
-        for (int t = 0; t < MT; ++t)
+        for (int i = 0; i < NR; ++i)
 #pragma unroll
-            for (int i = 0; i < NA; ++i)
+            for (int t = 0; t < MT; ++t)
                 acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[i], xf[t], acc[i][t], 0, 0, 0);
     };
     if (s0 < s1) {   // uniform over the wavefront
@@ -1058,7 +1069,7 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
         for (; sb + U < s1; sb += U) {
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                bf16x8 wf[NA], xf[MT];
+                bf16x8 wf[NR], xf[MT];
                 permute(u, sb + u, wf, xf);
                 request(u, sb + U + u);
                 multiply(wf, xf);
@@ -1066,38 +1077,42 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            bf16x8 wf[NA], xf[MT];
+            bf16x8 wf[NR], xf[MT];
             permute(u, sb + u, wf, xf);
             multiply(wf, xf);
         }
     }
-    // reduce the K-slices in a fixed order through LDS; thread (pr, t, lane) of the first 2 * MT wavefronts then
-    // owns accumulators 2 pr, 2 pr + 1 of token group t = two adjacent columns of token t * 16 + l16
-#pragma unroll
-    for (int a = 0; a < NA; ++a)
-#pragma unroll
-        for (int t = 0; t < MT; ++t)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) part[wave][a * MT + t][r][lane] = acc[a][t][r];
-    __syncthreads();
+    // reduce the K-slices in a fixed order through LDS, a column block at a time (its successor goes to the other buffer, so one
+    // barrier a block); thread (pr, t, lane) of the first 2 * MT wavefronts then owns accumulators 2 pr, 2 pr + 1 of token
+    // group t = two adjacent columns of token t * 16 + l16
     const int pr = wave & 1, tg = wave >> 1;
     const int m = tg * 16 + l16;
-    if (wave >= 2 * MT || m >= g.M) return;
-    {
-        float v0[2], v1[2] = {0.f, 0.f};
+    static_for<NBLK>([&](auto nbc) {
+        constexpr int nb = decltype(nbc)::value, buf = nb % NBUF;
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            float sum0 = 0.f, sum1 = 0.f;
+        for (int a = 0; a < NA; ++a)
 #pragma unroll
-            for (int ww = 0; ww < 8; ++ww) {
-                sum0 += part[ww][tg][2 * pr + e][lane];
-                if constexpr (EPI == EPI_SWIGLU) sum1 += part[ww][MT + tg][2 * pr + e][lane];
+            for (int t = 0; t < MT; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) part[buf][wave][a * MT + t][r][lane] = acc[nb * NA + a][t][r];
+        __syncthreads();
+        if (wave < 2 * MT && m < g.M && blk0 + nb < nblocks && (!HALF || q < 2)) {
+            float v0[2], v1[2] = {0.f, 0.f};
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                float sum0 = 0.f, sum1 = 0.f;
+#pragma unroll
+                for (int ww = 0; ww < 8; ++ww) {
+                    sum0 += part[buf][ww][tg][2 * pr + e][lane];
+                    if constexpr (HALF) sum1 += part[buf][ww][tg][2 * pr + e][lane ^ 32];
+                    else if constexpr (NA == 2) sum1 += part[buf][ww][MT + tg][2 * pr + e][lane];
+                }
+                v0[e] = sum0;
+                v1[e] = sum1;
             }
-            v0[e] = sum0;
-            v1[e] = sum1;
+            stream_epilogue<EPI>(g, m, (blk0 + nb) * COLS + 4 * q + 2 * pr, v0, v1);
         }
-        stream_epilogue<EPI>(g, m, n_blk + 4 * q + 2 * pr, v0, v1);
-    }
+    });
 }
 
 // ---- 65 to 256 tokens with the weight copy in fragment order: the token operand goes through LDS ----
@@ -1255,6 +1270,20 @@ void run_gemv_shared(GemmArgs g, hipStream_t st) {
     hipLaunchKernelGGL((k_stream_finish<EPI>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, g, ncols);
 }
 
+// Column blocks a workgroup of k_gemv_bf16 takes, with mt > 1 token groups: every workgroup fetches the whole token operand, a KB per
+// group and k-step, next to a KB per column block, and a CU takes in about 50 GB/s of the two, so the fewest KB per CU are taken
+// (several blocks where that still leaves one round of workgroups).  Per launch, one block -> the rule's choice, 52 tokens of width
+// 4096 from the weight copy, us: q|k|v 43.4 -> 29.4 (3 blocks), gate|up 48.1 -> 34.9 (3), lm-head 48.7 -> 34 (4); out and down have
+// 256 blocks and keep one.
+inline int gemv_blocks(int blocks, int mt, int na) {
+    int best = 1, best_cost = 0x7fffffff;
+    for (int nb = 1; nb <= (na == 2 ? 3 : 4); ++nb) {
+        const int wgs = (blocks + nb - 1) / nb, rounds = (wgs + cu_count() - 1) / cu_count(), cost = rounds * (nb * na + mt);
+        if (cost < best_cost) { best = nb; best_cost = cost; }
+    }
+    return best;
+}
+
 template <int EPI>
 void run_gemv(const GemmArgs& g, hipStream_t st) {
     if (g.M > STREAM_SHARED_MIN_TOKENS && g.w_frag && g.ksums) {   // several token groups: the token operand goes through LDS
@@ -1265,19 +1294,36 @@ void run_gemv(const GemmArgs& g, hipStream_t st) {
         note_hip_error(hipErrorInvalidValue);
         return;
     }
-    const int cols = EPI == EPI_SWIGLU ? g.N / 2 : g.N;
-    const dim3 grid((cols + 15) / 16);
-    if (g.w_frag) {
-        if (g.M <= 16) hipLaunchKernelGGL((k_gemv_bf16<EPI, 1, true>), grid, dim3(512), 0, st, g);
-        else if (g.M <= 32) hipLaunchKernelGGL((k_gemv_bf16<EPI, 2, true>), grid, dim3(512), 0, st, g);
-        else if (g.M <= 48) hipLaunchKernelGGL((k_gemv_bf16<EPI, 3, true>), grid, dim3(512), 0, st, g);
-        else hipLaunchKernelGGL((k_gemv_bf16<EPI, 4, true>), grid, dim3(512), 0, st, g);
-        return;
+    const int cols = EPI == EPI_SWIGLU ? g.N / 2 : g.N, mt = (g.M + 15) / 16;
+    if constexpr (EPI == EPI_SWIGLU) {
+        // One token group: 8 feed-forward columns a workgroup where 16 would be more than a round of CUs.  It is the same bytes in
+        // twice the workgroups, so the last ones leave less of the chip waiting (width 4096, 11008 columns, one token: 40.2 -> 35.0 us,
+        // from the copy, four tokens, 35.2 -> 32.6); with fewer the tokens are fetched twice as often for nothing (8 layers of
+        // width 1024, 2816 columns, 16 tokens: 340 us with 16 columns, 354 with 8).
+        if (mt == 1 && (cols + 15) / 16 > cu_count()) {
+            const dim3 grid((cols + 7) / 8);
+            if (g.w_frag) hipLaunchKernelGGL((k_gemv_bf16<EPI, 1, UNIT_HALF, true>), grid, dim3(512), 0, st, g);
+            else hipLaunchKernelGGL((k_gemv_bf16<EPI, 1, UNIT_HALF, false>), grid, dim3(512), 0, st, g);
+            return;
+        }
     }
-    if (g.M <= 16) hipLaunchKernelGGL((k_gemv_bf16<EPI, 1, false>), grid, dim3(512), 0, st, g);
-    else if (g.M <= 32) hipLaunchKernelGGL((k_gemv_bf16<EPI, 2, false>), grid, dim3(512), 0, st, g);
-    else if (g.M <= 48) hipLaunchKernelGGL((k_gemv_bf16<EPI, 3, false>), grid, dim3(512), 0, st, g);
-    else hipLaunchKernelGGL((k_gemv_bf16<EPI, 4, false>), grid, dim3(512), 0, st, g);
+    const int blocks = (cols + 15) / 16, nb = mt == 1 ? 1 : gemv_blocks(blocks, mt, EPI == EPI_SWIGLU ? 2 : 1);
+    auto launch = [&](auto mtc, auto nbc) {
+        constexpr int MT = decltype(mtc)::value, NB = decltype(nbc)::value;
+        const dim3 grid((blocks + NB - 1) / NB);
+        if (g.w_frag) hipLaunchKernelGGL((k_gemv_bf16<EPI, MT, NB, true>), grid, dim3(512), 0, st, g);
+        else hipLaunchKernelGGL((k_gemv_bf16<EPI, MT, NB, false>), grid, dim3(512), 0, st, g);
+    };
+    auto with_groups = [&](auto nbc) {
+        if (mt == 2) launch(std::integral_constant<int, 2>{}, nbc);
+        else if (mt == 3) launch(std::integral_constant<int, 3>{}, nbc);
+        else launch(std::integral_constant<int, 4>{}, nbc);
+    };
+    if (mt == 1) { launch(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{}); return; }
+    if (nb == 1) with_groups(std::integral_constant<int, 1>{});
+    else if (nb == 2) with_groups(std::integral_constant<int, 2>{});
+    else if (nb == 3) with_groups(std::integral_constant<int, 3>{});
+    else if constexpr (EPI != EPI_SWIGLU) with_groups(std::integral_constant<int, 4>{});
 }
 
 // one thread per 16-byte piece of the copy: piece p of block (nb, s) is lane p % 64

@@ -597,3 +597,29 @@ def test_forward_few_tokens_keeps_its_operands_in_fragment_order(B, L, copy):
         tol = 2.0 ** -5 * (np.abs(want) + np.sqrt((want ** 2).mean()))
         say("  %s in fragment order, %d tokens: max|err| %.3g, beyond tolerance %d of %d" % (name, M, err.max(), (err > tol).sum(), err.size))
         assert (err > tol).mean() <= 0.005 and err.max() <= 0.25 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("d,nh,f,V", [
+    (1408, 11, 4160, 12308),   # q|k|v 264 blocks of 16 columns: two a workgroup; gate|up 260 (halves for one token group); lm-head 770, a ragged last one
+    (768, 6, 8256, 16388),     # gate|up 516 blocks: two and three; lm-head 1025: a workgroup's last blocks lie past the end
+])
+def test_streamed_sums_do_not_depend_on_the_columns_a_workgroup_takes(d, nh, f, V):
+    """Blocks of 16, 17, 40 and 64 tokens (one to four token groups: other column blocks per workgroup), with the weight copy
+    and without: the rows they share are the same bits, and those of 64 tokens are the oracle's."""
+    m = dict(n_layers=1, d_model=d, n_heads=nh, head_dim=d // nh, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
+    w, P, S = G.make_weights(m, seed=31), 9, 80
+    pre, blk = G.uniform_tokens((1, P), V, 31, tag=0), G.uniform_tokens((1, 64), V, 31, tag=1)
+    ref = None
+    for copy in (False, True):
+        ctx, cos, sin = make_ctx(m, w, 1, S, 64, stream_copy=copy)
+        kv = mulo.alloc_kv(ctx, DEV)
+        gpu_forward(ctx, kv, pre, 0)
+        for L in (64, 40, 17, 16):
+            z = gpu_forward(ctx, kv, blk[:, :L], P)
+            if ref is None:
+                dr, du = pair(m, w, cos, sin, 1, S)
+                for t in (dr, du):
+                    t.forward(pre, 0)
+                check_bf16_logits("64 streamed tokens, width %d" % d, z, dr.forward(blk, P).numpy(), du.forward(blk, P).numpy())
+                ref = z
+            assert np.array_equal(z, ref[:, :L]), (copy, L)
