@@ -77,12 +77,14 @@ template <> struct Four<__hip_bfloat16> { typedef __attribute__((ext_vector_type
 // A chain of latencies between two launches that move all the bytes, so the gains are requested with the row, in one access per
 // four, results leave the same way, and the sum crosses lanes without LDS where it can: with the embedding's 16-byte pieces a
 // token of one sequence over 8 layers (17 norms) 964 - 966 -> 939 - 942 us, of four 1181 - 1184 -> 1158 - 1159 (three pairs of runs).
-template <typename T, int NV4>
-__global__ __launch_bounds__(TPB) void k_rmsnorm(const float* __restrict__ x, const T* __restrict__ gain,
-                                                 T* __restrict__ out, int d, float eps, int frag) {
+// NS > 0: x first takes the sums of up to NS slices of a projection's K (slices past the last weigh nothing), requested
+// with the row.  It saves the launch that would add them, and its round trip over x.
+template <typename T, int NV4, int NS>
+__global__ __launch_bounds__(TPB) void k_rmsnorm(float* __restrict__ x, const T* __restrict__ gain, T* __restrict__ out, int d,
+                                                 float eps, int frag, const float* __restrict__ sums, int n_slices) {
     __shared__ float red[TPB / 64];
     const int64_t m = blockIdx.x;
-    const float* xr = x + m * d;
+    float* const xr = x + m * d;
     const int nv4 = d >> 2, tid = threadIdx.x;
     typedef typename Four<T>::type T4;
     typedef T4 T4g __attribute__((aligned(sizeof(T))));   // a layer's gains start anywhere an element may
@@ -95,10 +97,31 @@ __global__ __launch_bounds__(TPB) void k_rmsnorm(const float* __restrict__ x, co
             const int idx = i * TPB + tid;
             if (idx < nv4) gn[i] = reinterpret_cast<const T4g*>(gain)[idx];
             v[i] = idx < nv4 ? reinterpret_cast<const float4*>(xr)[idx] : make_float4(0.f, 0.f, 0.f, 0.f);
+            if constexpr (NS > 0) {
+                if (idx < nv4) {
+                    float4 p[NS], s = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                    for (int k = 0; k < NS; ++k) p[k] = reinterpret_cast<const float4*>(sums + ((int64_t)(k < n_slices ? k : 0) * gridDim.x + m) * d)[idx];
+#pragma unroll
+                    for (int k = 0; k < NS; ++k)
+                        if (k < n_slices) { s.x += p[k].x; s.y += p[k].y; s.z += p[k].z; s.w += p[k].w; }
+                    v[i].x += s.x; v[i].y += s.y; v[i].z += s.z; v[i].w += s.w;
+                    reinterpret_cast<float4*>(xr)[idx] = v[i];
+                }
+            }
             ss += (v[i].x * v[i].x + v[i].y * v[i].y) + (v[i].z * v[i].z + v[i].w * v[i].w);
         }
     } else {
-        for (int c = tid; c < d; c += TPB) { const float t = xr[c]; ss += t * t; }
+        for (int c = tid; c < d; c += TPB) {
+            float t = xr[c];
+            if constexpr (NS > 0) {
+                float s = 0.f;
+                for (int k = 0; k < n_slices; ++k) s += sums[((int64_t)k * gridDim.x + m) * d + c];
+                t += s;
+                xr[c] = t;   // read again below by the thread that wrote it
+            }
+            ss += t * t;
+        }
     }
     ss = wave_sum(ss);
     if ((tid & 63) == 0) red[tid >> 6] = ss;
@@ -141,18 +164,23 @@ void launch_embed(const void* embed, int dtype, const int32_t* tok, const void* 
     else embed_dispatch((const float*)embed, tok, (const float*)in_embeds, x, M, d, V, s);
 }
 
-template <typename T>
-static void rmsnorm_dispatch(const float* x, const T* gain, T* out, int M, int d, float eps, int frag, hipStream_t s) {
-    if ((d & 3) == 0 && d <= 1024) hipLaunchKernelGGL((k_rmsnorm<T, 1>), dim3(M), dim3(TPB), 0, s, x, gain, out, d, eps, frag);
-    else if ((d & 3) == 0 && d <= 4096) hipLaunchKernelGGL((k_rmsnorm<T, 4>), dim3(M), dim3(TPB), 0, s, x, gain, out, d, eps, frag);
-    else if ((d & 3) == 0 && d <= 8192) hipLaunchKernelGGL((k_rmsnorm<T, 8>), dim3(M), dim3(TPB), 0, s, x, gain, out, d, eps, frag);
-    else hipLaunchKernelGGL((k_rmsnorm<T, 0>), dim3(M), dim3(TPB), 0, s, x, gain, out, d, eps, frag);
+template <typename T, int NS>
+static void rmsnorm_dispatch(float* x, const T* gain, T* out, int M, int d, float eps, int frag, Slices add, hipStream_t s) {
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3(M), dim3(TPB), 0, s, x, gain, out, d, eps, frag, add.sums, add.n); };
+    if ((d & 3) == 0 && d <= 1024) go(k_rmsnorm<T, 1, NS>);
+    else if ((d & 3) == 0 && d <= 4096) go(k_rmsnorm<T, 4, NS>);
+    else if ((d & 3) == 0 && d <= 8192) go(k_rmsnorm<T, 8, NS>);
+    else go(k_rmsnorm<T, 0, NS>);
 }
 
-void launch_rmsnorm(const float* x, const void* gain, int dtype, void* out, int M, int d, float eps, bool frag,
+void launch_rmsnorm(float* x, const void* gain, int dtype, void* out, int M, int d, float eps, bool frag, Slices add,
                     hipStream_t s) {
-    if (dtype == 1) rmsnorm_dispatch(x, (const __hip_bfloat16*)gain, (__hip_bfloat16*)out, M, d, eps, frag ? 1 : 0, s);
-    else rmsnorm_dispatch(x, (const float*)gain, (float*)out, M, d, eps, 0, s);
+    typedef __hip_bfloat16 bf16;
+    if (dtype != 1) rmsnorm_dispatch<float, 0>(x, (const float*)gain, (float*)out, M, d, eps, 0, add, s);
+    else if (add.n == 0) rmsnorm_dispatch<bf16, 0>(x, (const bf16*)gain, (bf16*)out, M, d, eps, frag ? 1 : 0, add, s);
+    else if (add.n <= 2) rmsnorm_dispatch<bf16, 2>(x, (const bf16*)gain, (bf16*)out, M, d, eps, frag ? 1 : 0, add, s);
+    else if (add.n <= 4) rmsnorm_dispatch<bf16, 4>(x, (const bf16*)gain, (bf16*)out, M, d, eps, frag ? 1 : 0, add, s);
+    else rmsnorm_dispatch<bf16, 8>(x, (const bf16*)gain, (bf16*)out, M, d, eps, frag ? 1 : 0, add, s);
 }
 
 }  // namespace mulo

@@ -971,9 +971,18 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
     const int lrow = lane >> 2, lchunk = lane & 3;
     const int from_lane = (4 * l16 + q) << 2;   // byte address of the source lane for ds_bpermute
     const int cols = EPI == EPI_SWIGLU ? g.N / 2 : g.N, nblocks = (cols + COLS - 1) / COLS;
-    const int blk0 = blockIdx.x * NBLK;    // first block of columns (gate|up: of feed-forward columns)
-    const int steps = g.K / 32, per = ((steps + 7) / 8 + 1) & ~1;   // whole 128-byte lines of a weight row per wavefront
-    const int s0 = wave * per, s1 = s0 + per < steps ? s0 + per : steps;
+    const int steps = g.K / 32;
+    int wg = blockIdx.x, kw = 0, sl0 = 0, sl1 = steps;   // this workgroup's columns and its slice of K (out, down: g.ksplit slices)
+    if constexpr (EPI == EPI_RESID) {
+        const int groups = (nblocks + NBLK - 1) / NBLK, per_slice = (steps + g.ksplit - 1) / g.ksplit;
+        kw = wg / groups;
+        wg -= kw * groups;
+        sl0 = kw * per_slice;
+        sl1 = sl0 + per_slice < steps ? sl0 + per_slice : steps;
+    }
+    const int blk0 = wg * NBLK;            // first block of columns (gate|up: of feed-forward columns)
+    const int eighth = (sl1 - sl0 + 7) / 8, per = EPI != EPI_RESID || g.ksplit == 1 ? (eighth + 1) & ~1 : eighth;   // whole 128-byte lines of a weight row per wavefront
+    const int s0 = sl0 + wave * per, s1 = s0 + per < sl1 ? s0 + per : sl1;
 
     // weight row(s) this lane fetches; with a copy in fragment order (WFRAG) the KB of (16-row block, step) is
     // contiguous in the MFMA's own lane order: lane l owns its bytes [16 l, 16 l + 16), no exchange afterwards
@@ -1110,7 +1119,11 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
                 v0[e] = sum0;
                 v1[e] = sum1;
             }
-            stream_epilogue<EPI>(g, m, (blk0 + nb) * COLS + 4 * q + 2 * pr, v0, v1);
+            const int n = (blk0 + nb) * COLS + 4 * q + 2 * pr;
+            if (EPI == EPI_RESID && g.ksplit > 1)
+                *reinterpret_cast<float2*>(g.ksums + ((int64_t)kw * g.M + m) * g.N + n) = make_float2(v0[0], v0[1]);
+            else
+                stream_epilogue<EPI>(g, m, n, v0, v1);
         }
     });
 }
@@ -1240,7 +1253,7 @@ __global__ __launch_bounds__(256) void k_stream_finish(const GemmArgs g, int nco
 }
 
 template <int EPI>
-void run_gemv_shared(GemmArgs g, hipStream_t st) {
+int run_gemv_shared(GemmArgs g, hipStream_t st) {
     const int ncols = g.N, seg_rows = EPI == EPI_QKV ? g.d : EPI == EPI_SWIGLU ? g.N / 2 : g.N;
     const int ncg = (ncols + 127) / 128;
     g.ksplit = stream_ksplit(ncols, g.K);
@@ -1265,9 +1278,13 @@ void run_gemv_shared(GemmArgs g, hipStream_t st) {
         case 15: launch(k_gemv_shared<15>, 15); break;
         default: launch(k_gemv_shared<16>, 16); break;
     }
-    const int cols = EPI == EPI_SWIGLU ? ncols / 2 : ncols;
-    const int64_t threads = (int64_t)g.M * (cols / 2);
-    hipLaunchKernelGGL((k_stream_finish<EPI>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, g, ncols);
+    if constexpr (EPI != EPI_RESID) {
+        const int cols = EPI == EPI_SWIGLU ? ncols / 2 : ncols;
+        const int64_t threads = (int64_t)g.M * (cols / 2);
+        hipLaunchKernelGGL((k_stream_finish<EPI>), dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, g, ncols);
+        return 0;
+    }
+    return g.ksplit;
 }
 
 // Column blocks a workgroup of k_gemv_bf16 takes, with mt > 1 token groups: every workgroup fetches the whole token operand, a KB per
@@ -1275,24 +1292,23 @@ void run_gemv_shared(GemmArgs g, hipStream_t st) {
 // (several blocks where that still leaves one round of workgroups).  Per launch, one block -> the rule's choice, 52 tokens of width
 // 4096 from the weight copy, us: q|k|v 43.4 -> 29.4 (3 blocks), gate|up 48.1 -> 34.9 (3), lm-head 48.7 -> 34 (4); out and down have
 // 256 blocks and keep one.
-inline int gemv_blocks(int blocks, int mt, int na) {
+inline int gemv_blocks(int blocks, int mt, int na, int ksplit) {
     int best = 1, best_cost = 0x7fffffff;
     for (int nb = 1; nb <= (na == 2 ? 3 : 4); ++nb) {
-        const int wgs = (blocks + nb - 1) / nb, rounds = (wgs + cu_count() - 1) / cu_count(), cost = rounds * (nb * na + mt);
+        const int wgs = (blocks + nb - 1) / nb * ksplit, rounds = (wgs + cu_count() - 1) / cu_count(), cost = rounds * (nb * na + mt);
         if (cost < best_cost) { best = nb; best_cost = cost; }
     }
     return best;
 }
 
+// returns how many slices of K the projection left in g.ksums (RESID: for the norm behind it; 0: the sums are where they belong)
 template <int EPI>
-void run_gemv(const GemmArgs& g, hipStream_t st) {
-    if (g.M > STREAM_SHARED_MIN_TOKENS && g.w_frag && g.ksums) {   // several token groups: the token operand goes through LDS
-        run_gemv_shared<EPI>(g, st);
-        return;
-    }
+int run_gemv(GemmArgs g, hipStream_t st) {
+    if (g.M > STREAM_SHARED_MIN_TOKENS && g.w_frag && g.ksums)     // several token groups: the token operand goes through LDS
+        return run_gemv_shared<EPI>(g, st);
     if (g.M > STREAM_MAX_TOKENS) {   // the kernel below holds four token groups
         note_hip_error(hipErrorInvalidValue);
-        return;
+        return 0;
     }
     const int cols = EPI == EPI_SWIGLU ? g.N / 2 : g.N, mt = (g.M + 15) / 16;
     if constexpr (EPI == EPI_SWIGLU) {
@@ -1304,13 +1320,15 @@ void run_gemv(const GemmArgs& g, hipStream_t st) {
             const dim3 grid((cols + 7) / 8);
             if (g.w_frag) hipLaunchKernelGGL((k_gemv_bf16<EPI, 1, UNIT_HALF, true>), grid, dim3(512), 0, st, g);
             else hipLaunchKernelGGL((k_gemv_bf16<EPI, 1, UNIT_HALF, false>), grid, dim3(512), 0, st, g);
-            return;
+            return 0;
         }
     }
-    const int blocks = (cols + 15) / 16, nb = mt == 1 ? 1 : gemv_blocks(blocks, mt, EPI == EPI_SWIGLU ? 2 : 1);
+    g.ksplit = EPI == EPI_RESID && g.ksums && mt > 1 ? stream_resid_split(g.K) : 1;
+    const int blocks = (cols + 15) / 16;
+    const int nb = mt == 1 ? 1 : gemv_blocks(blocks, mt, EPI == EPI_SWIGLU ? 2 : 1, g.ksplit);
     auto launch = [&](auto mtc, auto nbc) {
         constexpr int MT = decltype(mtc)::value, NB = decltype(nbc)::value;
-        const dim3 grid((blocks + NB - 1) / NB);
+        const dim3 grid((blocks + NB - 1) / NB * g.ksplit);
         if (g.w_frag) hipLaunchKernelGGL((k_gemv_bf16<EPI, MT, NB, true>), grid, dim3(512), 0, st, g);
         else hipLaunchKernelGGL((k_gemv_bf16<EPI, MT, NB, false>), grid, dim3(512), 0, st, g);
     };
@@ -1319,11 +1337,15 @@ void run_gemv(const GemmArgs& g, hipStream_t st) {
         else if (mt == 3) launch(std::integral_constant<int, 3>{}, nbc);
         else launch(std::integral_constant<int, 4>{}, nbc);
     };
-    if (mt == 1) { launch(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{}); return; }
+    if (mt == 1) {
+        launch(std::integral_constant<int, 1>{}, std::integral_constant<int, 1>{});
+        return 0;
+    }
     if (nb == 1) with_groups(std::integral_constant<int, 1>{});
     else if (nb == 2) with_groups(std::integral_constant<int, 2>{});
     else if (nb == 3) with_groups(std::integral_constant<int, 3>{});
     else if constexpr (EPI != EPI_SWIGLU) with_groups(std::integral_constant<int, 4>{});
+    return g.ksplit > 1 ? g.ksplit : 0;
 }
 
 // one thread per 16-byte piece of the copy: piece p of block (nb, s) is lane p % 64
@@ -1432,14 +1454,14 @@ void run_ring(GemmArgs g, hipStream_t st, int tile_n0 = 0, int tiles_n = 0) {
     hipLaunchKernelGGL(kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(WGM * WGN * 64), lds, st, g);
 }
 
-// returns whether the softmax parts were written (LOGITS, wavefront tiles of 128 whole columns)
+// returns whether the softmax parts were written (LOGITS, wavefront tiles of 128 whole columns), or the K slices that the norm
+// behind the projection has to add (RESID)
 template <int EPI>
-bool dispatch(GemmArgs g, const StreamMode& sm, hipStream_t st) {
+int dispatch(GemmArgs g, const StreamMode& sm, hipStream_t st) {
     g.stream = sm.stream; g.w_frag = sm.w_frag; g.ksums = sm.ksums;
     *sm.ran = -1;
     if (g.stream) {   // a handful of tokens: stream the weights (A is in fragment order)
-        run_gemv<EPI>(g, st);
-        return false;
+        return run_gemv<EPI>(g, st);
     }
     const int tile = sm.tile >= 0 && sm.tile < N_TILES && has_tile<EPI>(g, sm.tile) ? sm.tile : choose_tile<EPI>(g);
     *sm.ran = tile;
@@ -1471,7 +1493,7 @@ bool dispatch(GemmArgs g, const StreamMode& sm, hipStream_t st) {
             if (n_main < tiles_n) run_128x256(n_main, tiles_n - n_main);
         }
     }
-    return parts;
+    return parts ? 1 : 0;
 }
 
 }  // namespace
@@ -1496,10 +1518,10 @@ void launch_gemm_qkv_bf16(const void* xh, const void* wq, const void* wk, const 
     dispatch<EPI_QKV>(g, sm, st);
 }
 
-void launch_gemm_resid_bf16(const void* a, const void* w, float* x, int M, int N, int K, const StreamMode& sm, hipStream_t st) {
+Slices launch_gemm_resid_bf16(const void* a, const void* w, float* x, int M, int N, int K, const StreamMode& sm, hipStream_t st) {
     GemmArgs g{};
     g.A = (const bf16*)a; g.W0 = (const bf16*)w; g.M = M; g.N = N; g.K = K; g.Cf = x;
-    dispatch<EPI_RESID>(g, sm, st);
+    return {sm.ksums, dispatch<EPI_RESID>(g, sm, st)};
 }
 
 void launch_gemm_swiglu_bf16(const void* xh, const void* wg, const void* wu, void* h, int M, int f, int d,
@@ -1516,7 +1538,7 @@ bool launch_gemm_logits_bf16(const void* xh, const void* w, float* logits, float
     g.A = (const bf16*)xh; g.W0 = (const bf16*)w; g.M = M; g.N = V; g.K = d; g.Cf = logits;
     g.parts = reinterpret_cast<float2*>(parts);
     g.n_parts = (V + rowparts::PART - 1) / rowparts::PART;
-    return dispatch<EPI_LOGITS>(g, sm, st) && parts != nullptr;
+    return dispatch<EPI_LOGITS>(g, sm, st) != 0 && parts != nullptr;
 }
 
 void launch_pack_weights(const void* src, void* dst, int layers, int rows, int K, hipStream_t st) {

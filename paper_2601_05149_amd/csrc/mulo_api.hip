@@ -95,8 +95,12 @@ size_t stream_copy_elems(const mulo_model_cfg& c) {
 size_t ksum_bytes(const mulo_model_cfg& c) {
     const size_t M = (size_t)c.max_batch * c.max_block;
     const int Ms = (int)(M < (size_t)STREAM_MAX_TOKENS_COPY ? M : (size_t)STREAM_MAX_TOKENS_COPY);
+    const int Mf = (int)(M < (size_t)STREAM_MAX_TOKENS ? M : (size_t)STREAM_MAX_TOKENS);
     const int d = c.d_model, f = c.d_ffn, V = c.vocab;
+    const size_t few = (size_t)stream_resid_split(d > f ? d : f) * Mf * d;
+    if (!c.stream_copy) return few * sizeof(float);
     size_t n = stream_ksum_floats(Ms, 3 * d, d);
+    n = few > n ? few : n;
     const size_t others[4] = {stream_ksum_floats(Ms, d, d), stream_ksum_floats(Ms, 2 * f, d), stream_ksum_floats(Ms, d, f),
                               stream_ksum_floats(Ms, V, d)};
     for (size_t o : others) n = o > n ? o : n;
@@ -112,7 +116,7 @@ Layout plan(const mulo_model_cfg& c) {
                               c.dtype == MULO_BF16 ? attention_scratch_bytes(c.max_batch, c.n_heads, c.head_dim) : 0,
                               M * 4, M, c.dtype == MULO_BF16 ? M * ((V + 127) / 128) * 8 : 0,
                               c.dtype == MULO_BF16 && c.stream_copy ? stream_copy_elems(c) * 2 : 0,
-                              c.dtype == MULO_BF16 && c.stream_copy ? ksum_bytes(c) : 0};
+                              c.dtype == MULO_BF16 ? ksum_bytes(c) : 0};
     Layout l{};
     size_t o = 0;
     for (int i = 0; i < N_BUF; ++i) {
@@ -196,7 +200,8 @@ bool enqueue_forward(mulo_ctx* c, mulo_kv* kv, int B, int L, int P, const int32_
     const bool has_copy = c->pk_wq != nullptr;
     const bool frag = dt == MULO_BF16 && M <= (has_copy ? STREAM_MAX_TOKENS_COPY : STREAM_MAX_TOKENS);
     const bool wfrag = frag && has_copy;
-    auto sm = [&](int projection) { return StreamMode{frag, wfrag, wfrag ? c->ksums : nullptr, c->tile, &c->tiles_ran[projection]}; };
+    auto sm = [&](int projection) { return StreamMode{frag, wfrag, frag ? c->ksums : nullptr, c->tile, &c->tiles_ran[projection]}; };
+    Slices add{nullptr, 0};   // what the last residual projection left for the norm behind it to add
     { PROF(MULO_PROF_NORM_EMBED); launch_embed(c->w.embed, dt, tok, emb, c->x, M, d, V, st); }
     for (int l = 0; l < m.n_layers; ++l) {
         RopeArgs ra{c->w.rope_cos, c->w.rope_sin, L, P, m.n_heads, m.head_dim, m.max_seq, m.max_batch, l};
@@ -212,17 +217,17 @@ bool enqueue_forward(mulo_ctx* c, mulo_kv* kv, int B, int L, int P, const int32_
         const char* g_attn = (const char*)c->w.attn_norm + (size_t)l * d * e;
         const char* g_ffn = (const char*)c->w.ffn_norm + (size_t)l * d * e;
         if (dt == MULO_BF16) {
-            { PROF(MULO_PROF_NORM_EMBED); launch_rmsnorm(c->x, g_attn, dt, c->xh, M, d, m.rms_eps, frag, st); }
+            { PROF(MULO_PROF_NORM_EMBED); launch_rmsnorm(c->x, g_attn, dt, c->xh, M, d, m.rms_eps, frag, add, st); }
             { PROF(MULO_PROF_GEMM_QKV); launch_gemm_qkv_bf16(c->xh, wq, wk, wv, c->qbuf, kv->k, kv->v, M, d, ra, sm(0), st); }
             { PROF(MULO_PROF_ATTENTION);
               if (sc) launch_attention_scattered_bf16(c->qbuf, kv->k, kv->v, c->att, c->attn_part, B, sc->pos_tab, L, sc->hide,
                                                       sc->P0, sc->Lblk, m.n_heads, m.head_dim, m.max_seq, m.max_batch, l, frag, st);
               else launch_attention_bf16(c->qbuf, kv->k, kv->v, c->att, c->attn_part, B, L, P, m.n_heads, m.head_dim,
                                          m.max_seq, m.max_batch, l, frag, st); }
-            { PROF(MULO_PROF_GEMM_OUT); launch_gemm_resid_bf16(c->att, wo, c->x, M, d, d, sm(1), st); }
-            { PROF(MULO_PROF_NORM_EMBED); launch_rmsnorm(c->x, g_ffn, dt, c->xh, M, d, m.rms_eps, frag, st); }
+            { PROF(MULO_PROF_GEMM_OUT); add = launch_gemm_resid_bf16(c->att, wo, c->x, M, d, d, sm(1), st); }
+            { PROF(MULO_PROF_NORM_EMBED); launch_rmsnorm(c->x, g_ffn, dt, c->xh, M, d, m.rms_eps, frag, add, st); }
             { PROF(MULO_PROF_GEMM_GATE_UP); launch_gemm_swiglu_bf16(c->xh, wg, wu, c->hmid, M, f, d, sm(2), st); }
-            { PROF(MULO_PROF_GEMM_DOWN); launch_gemm_resid_bf16(c->hmid, wd, c->x, M, d, f, sm(3), st); }
+            { PROF(MULO_PROF_GEMM_DOWN); add = launch_gemm_resid_bf16(c->hmid, wd, c->x, M, d, f, sm(3), st); }
         } else {
             { PROF(MULO_PROF_GEMM_QKV);
               launch_qkv_f32(c->x, (const float*)g_attn, m.rms_eps, (const float*)wq, (const float*)wk, (const float*)wv,
@@ -236,7 +241,7 @@ bool enqueue_forward(mulo_ctx* c, mulo_kv* kv, int B, int L, int P, const int32_
             { PROF(MULO_PROF_GEMM_DOWN); launch_resid_f32((const float*)c->hmid, (const float*)wd, c->x, M, d, f, st); }
         }
     }
-    { PROF(MULO_PROF_NORM_EMBED); launch_rmsnorm(c->x, c->w.final_norm, dt, c->xh, M, d, m.rms_eps, frag, st); }
+    { PROF(MULO_PROF_NORM_EMBED); launch_rmsnorm(c->x, c->w.final_norm, dt, c->xh, M, d, m.rms_eps, frag, add, st); }
     PROF(MULO_PROF_GEMM_LM_HEAD);
     if (dt == MULO_BF16) return launch_gemm_logits_bf16(c->xh, wfrag ? (const void*)c->pk_lm : c->w.lm_head, logits, want_parts ? c->row_parts : nullptr, M, V, d, sm(4), st);
     launch_logits_f32((const float*)c->xh, (const float*)c->w.lm_head, logits, M, V, d, st);
@@ -398,7 +403,7 @@ mulo_status mulo_create(const mulo_model_cfg* cfg, const mulo_weights* w, void* 
     c->isl_hide = (uint8_t*)(b + l.off[14]);
     c->row_parts = c->esz == 2 ? (float*)(b + l.off[15]) : nullptr;
     c->pk_wq = c->pk_wk = c->pk_wv = c->pk_wo = c->pk_gate = c->pk_up = c->pk_down = c->pk_lm = nullptr;
-    c->ksums = cfg->stream_copy ? (float*)(b + l.off[17]) : nullptr;
+    c->ksums = c->esz == 2 ? (float*)(b + l.off[17]) : nullptr;
     if (cfg->stream_copy) {   // bf16 (checked): the second copy of the weights, made once on the context's stream
         const int nl = cfg->n_layers, d = cfg->d_model, f = cfg->d_ffn;
         char* p = b + l.off[16];

@@ -34,7 +34,7 @@ constexpr int STREAM_MAX_TOKENS_COPY = 256;
 // How a launch of few tokens runs its projections (decided once per forward, the same for every kernel of it):
 //   stream  the token operands are in fragment order and the projections run in the weight-streaming kernels
 //   w_frag  the weight pointers are the context's copies in fragment order
-//   ksums   scratch for the sums of the K slices (stream_ksum_floats) when w_frag, else nullptr
+//   ksums   scratch for the sums of the K slices (stream_ksum_floats, stream_resid_split) when the launch streams, else nullptr
 // and, for the tests of the tiled kernels, which tile a launch that does not stream runs on:
 //   tile    index into the tile table (gemm.hip), taken where the projection has it; -1: the rule's choice
 //   ran     host variable that receives the tile (-1: streamed)
@@ -48,6 +48,14 @@ inline int stream_ksplit(int ncols, int K) {
     ks = ks < 1 ? 1 : (ks > 8 ? 8 : ks);
     const int most = steps / 8 > 1 ? steps / 8 : 1;
     return ks > most ? most : ks;
+}
+// K slices of the out and down projections of 17 to STREAM_MAX_TOKENS tokens, 64 k-steps or more each: with them a workgroup takes
+// several column blocks and fetches the token operand of its slice alone, and the norm behind the projection adds the slices.
+// 52 tokens, from the copy, us: 4096 x 4096 13.2 -> 11.7, 4096 x 11008 32.8 -> 25.4, the norms 5.1 -> 6.2.  One group of tokens loses
+// by it (4096 x 11008: 22 -> 26, from the copy 19.6 -> 20.7: four times the workgroups, a quarter of the steps each).
+inline int stream_resid_split(int K) {
+    const int ks = K / 32 / 64;
+    return ks < 1 ? 1 : ks > 4 ? 4 : ks;
 }
 // floats of partial sums such a launch of M tokens over `ncols` output columns (gate|up: 2 f, q|k|v: 3 d) needs
 inline size_t stream_ksum_floats(int M, int ncols, int K) { return (size_t)stream_ksplit(ncols, K) * M * ncols; }
@@ -131,16 +139,19 @@ struct RopeArgs {
 // x[m, :] = embed[clamp(tok[m])]  (float32 residual stream); T = float or bf16 storage
 void launch_embed(const void* embed, int dtype, const int32_t* tok, const void* in_embeds, float* x,
                   int M, int d, int V, hipStream_t st);
-// frag: write `out` in fragment order (bf16 launches that stream the weights)
-void launch_rmsnorm(const float* x, const void* gain, int dtype, void* out, int M, int d, float eps, bool frag,
+// Sums of the K slices of a projection whose residual add is still to come: n slices [M, d] in `sums` (n == 0: none).
+struct Slices { const float* sums; int n; };
+// frag: write `out` in fragment order (bf16 launches that stream the weights); x first takes the slices, added in index order
+void launch_rmsnorm(float* x, const void* gain, int dtype, void* out, int M, int d, float eps, bool frag, Slices add,
                     hipStream_t st);
 
 // bf16 MFMA GEMMs, C = A[M,K] * W[N,K]^T with fused epilogues
 void launch_gemm_qkv_bf16(const void* xh, const void* wq, const void* wk, const void* wv, void* q_out,
                           void* k_cache, void* v_cache, int M, int d, const RopeArgs& ra, const StreamMode& sm,
                           hipStream_t st);
-void launch_gemm_resid_bf16(const void* a, const void* w, float* x, int M, int N, int K, const StreamMode& sm,
-                            hipStream_t st);
+// x += A W^T; or, where K is dealt to several workgroups, the slices' sums, which the norm behind it adds to x
+Slices launch_gemm_resid_bf16(const void* a, const void* w, float* x, int M, int N, int K, const StreamMode& sm,
+                              hipStream_t st);
 void launch_gemm_swiglu_bf16(const void* xh, const void* wg, const void* wu, void* h, int M, int f,
                              int d, const StreamMode& sm, hipStream_t st);
 // Copies `layers` bf16 matrices [rows, K] (contiguous, rows % 16 == 0 or layers == 1) into fragment order: rows in

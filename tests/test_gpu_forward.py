@@ -601,11 +601,12 @@ def test_forward_few_tokens_keeps_its_operands_in_fragment_order(B, L, copy):
 
 @pytest.mark.parametrize("d,nh,f,V", [
     (1408, 11, 4160, 12308),   # q|k|v 264 blocks of 16 columns: two a workgroup; gate|up 260 (halves for one token group); lm-head 770, a ragged last one
-    (768, 6, 8256, 16388),     # gate|up 516 blocks: two and three; lm-head 1025: a workgroup's last blocks lie past the end
+    (768, 6, 8256, 16388),     # gate|up 516 blocks: two and three; lm-head 1025: a workgroup's last blocks lie past the end; down: 258 steps in 4 slices
 ])
 def test_streamed_sums_do_not_depend_on_the_columns_a_workgroup_takes(d, nh, f, V):
-    """Blocks of 16, 17, 40 and 64 tokens (one to four token groups: other column blocks per workgroup), with the weight copy
-    and without: the rows they share are the same bits, and those of 64 tokens are the oracle's."""
+    """Blocks of 17, 40 and 64 tokens (two to four token groups: other column blocks per workgroup; K of 4096 and more in slices
+    that the norm adds), with the weight copy and without: the rows they share are the same bits, those of 64 tokens are the
+    oracle's.  One group, which deals K in one slice: the same cache rows, and logits within the oracle's bound."""
     m = dict(n_layers=1, d_model=d, n_heads=nh, head_dim=d // nh, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
     w, P, S = G.make_weights(m, seed=31), 9, 80
     pre, blk = G.uniform_tokens((1, P), V, 31, tag=0), G.uniform_tokens((1, 64), V, 31, tag=1)
@@ -620,6 +621,12 @@ def test_streamed_sums_do_not_depend_on_the_columns_a_workgroup_takes(d, nh, f, 
                 dr, du = pair(m, w, cos, sin, 1, S)
                 for t in (dr, du):
                     t.forward(pre, 0)
-                check_bf16_logits("64 streamed tokens, width %d" % d, z, dr.forward(blk, P).numpy(), du.forward(blk, P).numpy())
+                zr, zu = dr.forward(blk, P).numpy(), du.forward(blk, P).numpy()
+                check_bf16_logits("64 streamed tokens, width %d" % d, z, zr, zu)
                 ref = z
-            assert np.array_equal(z, ref[:, :L]), (copy, L)
+                k1, v1 = kv[0][0, 0, :, P:P + 64].clone(), kv[1][0, 0, :, :, P:P + 64].clone()
+            if L > 16:
+                assert np.array_equal(z, ref[:, :L]), (copy, L)
+            else:
+                check_bf16_logits("%d streamed tokens, width %d" % (L, d), z, zr[:, :L], zu[:, :L])
+            assert torch.equal(kv[0][0, 0, :, P:P + L], k1[:, :L]) and torch.equal(kv[1][0, 0, :, :, P:P + L], v1[:, :, :L]), (copy, L)
