@@ -95,12 +95,8 @@ size_t stream_copy_elems(const mulo_model_cfg& c) {
 size_t ksum_bytes(const mulo_model_cfg& c) {
     const size_t M = (size_t)c.max_batch * c.max_block;
     const int Ms = (int)(M < (size_t)STREAM_MAX_TOKENS_COPY ? M : (size_t)STREAM_MAX_TOKENS_COPY);
-    const int Mf = (int)(M < (size_t)STREAM_MAX_TOKENS ? M : (size_t)STREAM_MAX_TOKENS);
     const int d = c.d_model, f = c.d_ffn, V = c.vocab;
-    const size_t few = (size_t)stream_resid_split(d > f ? d : f) * Mf * d;
-    if (!c.stream_copy) return few * sizeof(float);
     size_t n = stream_ksum_floats(Ms, 3 * d, d);
-    n = few > n ? few : n;
     const size_t others[4] = {stream_ksum_floats(Ms, d, d), stream_ksum_floats(Ms, 2 * f, d), stream_ksum_floats(Ms, d, f),
                               stream_ksum_floats(Ms, V, d)};
     for (size_t o : others) n = o > n ? o : n;
@@ -116,7 +112,7 @@ Layout plan(const mulo_model_cfg& c) {
                               c.dtype == MULO_BF16 ? attention_scratch_bytes(c.max_batch, c.n_heads, c.head_dim) : 0,
                               M * 4, M, c.dtype == MULO_BF16 ? M * ((V + 127) / 128) * 8 : 0,
                               c.dtype == MULO_BF16 && c.stream_copy ? stream_copy_elems(c) * 2 : 0,
-                              c.dtype == MULO_BF16 ? ksum_bytes(c) : 0};
+                              c.dtype == MULO_BF16 && c.stream_copy ? ksum_bytes(c) : 0};
     Layout l{};
     size_t o = 0;
     for (int i = 0; i < N_BUF; ++i) {
@@ -200,7 +196,10 @@ bool enqueue_forward(mulo_ctx* c, mulo_kv* kv, int B, int L, int P, const int32_
     const bool has_copy = c->pk_wq != nullptr;
     const bool frag = dt == MULO_BF16 && M <= (has_copy ? STREAM_MAX_TOKENS_COPY : STREAM_MAX_TOKENS);
     const bool wfrag = frag && has_copy;
-    auto sm = [&](int projection) { return StreamMode{frag, wfrag, frag ? c->ksums : nullptr, c->tile, &c->tiles_ran[projection]}; };
+    // The slices of at most 64 tokens (4 x 64 rows at most) go to the attention's partial results (512 rows of d and more), which
+    // are done with before the out projection and not begun before the next layer's attention: the norm in between takes them.
+    static_assert(4 * STREAM_MAX_TOKENS <= 512, "rows of slices");
+    auto sm = [&](int projection) { return StreamMode{frag, wfrag, M <= STREAM_MAX_TOKENS ? c->attn_part : c->ksums, c->tile, &c->tiles_ran[projection]}; };
     Slices add{nullptr, 0};   // what the last residual projection left for the norm behind it to add
     { PROF(MULO_PROF_NORM_EMBED); launch_embed(c->w.embed, dt, tok, emb, c->x, M, d, V, st); }
     for (int l = 0; l < m.n_layers; ++l) {
@@ -403,7 +402,7 @@ mulo_status mulo_create(const mulo_model_cfg* cfg, const mulo_weights* w, void* 
     c->isl_hide = (uint8_t*)(b + l.off[14]);
     c->row_parts = c->esz == 2 ? (float*)(b + l.off[15]) : nullptr;
     c->pk_wq = c->pk_wk = c->pk_wv = c->pk_wo = c->pk_gate = c->pk_up = c->pk_down = c->pk_lm = nullptr;
-    c->ksums = c->esz == 2 ? (float*)(b + l.off[17]) : nullptr;
+    c->ksums = cfg->stream_copy ? (float*)(b + l.off[17]) : nullptr;
     if (cfg->stream_copy) {   // bf16 (checked): the second copy of the weights, made once on the context's stream
         const int nl = cfg->n_layers, d = cfg->d_model, f = cfg->d_ffn;
         char* p = b + l.off[16];

@@ -34,7 +34,7 @@ constexpr int STREAM_MAX_TOKENS_COPY = 256;
 // How a launch of few tokens runs its projections (decided once per forward, the same for every kernel of it):
 //   stream  the token operands are in fragment order and the projections run in the weight-streaming kernels
 //   w_frag  the weight pointers are the context's copies in fragment order
-//   ksums   scratch for the sums of the K slices (stream_ksum_floats, stream_resid_split) when the launch streams, else nullptr
+//   ksums   scratch for the sums of the K slices when the launch streams (stream_ksum_floats; stream_resid_split(K) [M, d] up to 64 tokens)
 // and, for the tests of the tiled kernels, which tile a launch that does not stream runs on:
 //   tile    index into the tile table (gemm.hip), taken where the projection has it; -1: the rule's choice
 //   ran     host variable that receives the tile (-1: streamed)
