@@ -178,11 +178,22 @@ __device__ __forceinline__ void row_write_probs(const Guided src, float* __restr
 }
 
 // ---- Step 2: softmax of the draft logits, one workgroup per low-res cell ----
+// up.hi: the workgroup also writes its cell's token to the r x r children, x~[b, (rI+a) W + rJ+c] = y~[b, I w + J], and (first sequence)
+// their q_row: a launch of 4.7 us less in front of the step.
 template <int NV4>
 __global__ __launch_bounds__(TPB) void k_softmax_rows(const float* __restrict__ in,
-                                                      float* __restrict__ out, int V) {
+                                                      float* __restrict__ out, int V, const UpTokens up) {
     __shared__ float red[WAVES];
     const int64_t row = blockIdx.x;
+    if (up.hi) {
+        const int n_lo = up.h * up.w, W = up.w * up.r, b = (int)(row / n_lo), par = (int)(row % n_lo), I = par / up.w, J = par % up.w;
+        const int tok = up.lo[row];
+        for (int c = threadIdx.x; c < up.r * up.r; c += TPB) {
+            const int u = (I * up.r + c / up.r) * W + J * up.r + c % up.r;
+            up.hi[(int64_t)b * n_lo * up.r * up.r + u] = tok;
+            if (b == 0) up.q_row[u] = par;
+        }
+    }
     RowRegs<NV4> rr;
     float m, inv;
     const Guided src{in + row * V, nullptr, 1.f};
@@ -227,14 +238,6 @@ __global__ __launch_bounds__(TPB) void k_gather_rows(const float* __restrict__ q
     const float4* s = reinterpret_cast<const float4*>(q_lo + ((int64_t)b * n_lo + q_row[u]) * V);
     float4* d = reinterpret_cast<float4*>(q_hi + ((int64_t)b * n_hi + u) * V);
     for (int i = threadIdx.x; i < (V >> 2); i += TPB) d[i] = s[i];
-}
-
-__global__ void k_shift_inputs(const int32_t* __restrict__ prev, const int32_t* __restrict__ hi,
-                               int32_t* __restrict__ inp, int B, int L) {
-    const int64_t gid = (int64_t)blockIdx.x * TPB + threadIdx.x;
-    if (gid >= (int64_t)B * L) return;
-    const int b = gid / L, j = gid % L;
-    inp[gid] = j == 0 ? prev[b] : hi[gid - 1];
 }
 
 // One integer weight of the draw, floor(w 2^40), as a double: sums of up to 256 of them (2^49) are exact there, at half
@@ -358,15 +361,19 @@ __global__ __launch_bounds__(TPB) void k_accept(const DecideArgs a) {
 // draw depend on this row's own decision only (use_p), which is known here; whether the position is marked is not, so
 // an unmarked one has read its draft row for nothing (launch_accept's rule).
 // XCD x takes the x-th eighth of the rows: neighbours, children of one draft row, find it in one L2.
-template <int NIT>
-__global__ __launch_bounds__(TPB) void k_accept_sums(const DecideArgs a, unsigned long long* __restrict__ sums, int rows_per_xcd) {
+// Latency bounds it, four workgroups a CU with a row each (the arithmetic of the weights taken out: no difference; the draft row taken
+// out: 66 of 82 us), so requests go out without a branch, several passes of the draft row together: a branch around an access
+// (the end of the row, guidance) had the compiler wait for it before the next.  4 x 1024 rows of 16384, us: 82 -> 74.
+// Two positions a workgroup with the draft row they share in LDS: 93 (half as many workgroups to hide behind each other).
+template <int NIT, bool GUIDED>
+__global__ __launch_bounds__(TPB, GUIDED ? 3 : 4) void k_accept_sums(const DecideArgs a, unsigned long long* __restrict__ sums, int rows_per_xcd) {
     __shared__ float2 parts[NIT * 16];
     __shared__ float2 s_stat;
     __shared__ int s_use_p;
     const int64_t row = (int64_t)(blockIdx.x & 7) * rows_per_xcd + (blockIdx.x >> 3);
     if (row >= (int64_t)a.B * a.L) return;                     // uniform over the workgroup, before any barrier
     const int b = row / a.L, t = row % a.L, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const Guided z{a.logits + row * a.V, a.logits_u ? a.logits_u + row * a.V : nullptr, a.cfg_scale};
+    const Guided z{a.logits + row * a.V, GUIDED ? a.logits_u + row * a.V : nullptr, a.cfg_scale};
     const int tok = clamp_tok(a.draft_tokens[row], a.V);
     const int qr = a.q_row ? a.q_row[t] : t;
     const float* q = a.q + b * a.q_batch_stride + (int64_t)qr * a.V;
@@ -378,15 +385,27 @@ __global__ __launch_bounds__(TPB) void k_accept_sums(const DecideArgs a, unsigne
     const int V = a.V, n_parts = (V + rowparts::PART - 1) / rowparts::PART;
     const float NEG = rowparts::NEG_INF;
     float4 lo[NIT], hi[NIT];
+    const int nv4 = V >> 2;
+    auto entry = [&](int i4) { return i4 < nv4 ? i4 : 0; };    // entries that do not exist re-read the row's first
+    const float4 *c4 = reinterpret_cast<const float4*>(z.zc), *u4 = reinterpret_cast<const float4*>(z.zu);
+    auto with = [&](const float4 c, const float4 u) { return make_float4(guide(c.x, u.x, z.s), guide(c.y, u.y, z.s), guide(c.z, u.z, z.s), guide(c.w, u.w, z.s)); };
 #pragma unroll
     for (int k = 0; k < NIT; ++k) {
         const int R = k * TPB + tid;
-        lo[k] = R * 8 + 4 <= V ? z.at4(2 * R) : make_float4(NEG, NEG, NEG, NEG);
-        hi[k] = R * 8 + 8 <= V ? z.at4(2 * R + 1) : make_float4(NEG, NEG, NEG, NEG);
+        lo[k] = c4[entry(2 * R)];
+        hi[k] = c4[entry(2 * R + 1)];
+        if constexpr (GUIDED) {
+            lo[k] = with(lo[k], u4[entry(2 * R)]);
+            hi[k] = with(hi[k], u4[entry(2 * R + 1)]);
+            if (k & 1) asm volatile("" ::: "memory");          // two passes in flight: all of both rows do not fit the registers
+        }
     }
 #pragma unroll
     for (int k = 0; k < NIT; ++k) {                            // the part statistics, as in k_accept
-        const int R = k * TPB + tid, n_valid = V - R * 8 >= 8 ? 8 : (V - R * 8 >= 4 ? 4 : 0);
+        const int R = k * TPB + tid;
+        if (2 * R >= nv4) lo[k] = make_float4(NEG, NEG, NEG, NEG);
+        if (2 * R + 1 >= nv4) hi[k] = make_float4(NEG, NEG, NEG, NEG);
+        const int n_valid = V - R * 8 >= 8 ? 8 : (V - R * 8 >= 4 ? 4 : 0);
         const float zz[8] = {lo[k].x, lo[k].y, lo[k].z, lo[k].w, hi[k].x, hi[k].y, hi[k].z, hi[k].w};
         float m = fmaxf(fmaxf(fmaxf(zz[0], zz[1]), fmaxf(zz[2], zz[3])), fmaxf(fmaxf(zz[4], zz[5]), fmaxf(zz[6], zz[7])));
         m = fmaxf(m, __shfl_xor(m, 2));
@@ -417,20 +436,37 @@ __global__ __launch_bounds__(TPB) void k_accept_sums(const DecideArgs a, unsigne
     auto chunk_pass = [&](auto with_q) {
         constexpr bool WITH_Q = decltype(with_q)::value;
         const float4* q4 = reinterpret_cast<const float4*>(q);
+        constexpr int G = NIT <= 2 ? NIT : GUIDED ? 2 : NIT % 4 == 0 ? 4 : 3;   // passes whose draft entries are requested together
 #pragma unroll
-        for (int k = 0; k < NIT; ++k) {
-            const int R = k * TPB + tid;
-            const bool has_lo = R * 8 + 4 <= V, has_hi = R * 8 + 8 <= V;
-            float4 q_lo = zero4, q_hi = zero4;
-            if constexpr (WITH_Q) {
-                if (has_lo) q_lo = q4[2 * R];
-                if (has_hi) q_hi = q4[2 * R + 1];
+        for (int k0 = 0; k0 < NIT; k0 += G) {
+            float4 q_lo[G], q_hi[G];
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                const int R = (k0 + j) * TPB + tid;
+                q_lo[j] = WITH_Q ? q4[entry(2 * R)] : zero4;
+                q_hi[j] = WITH_Q ? q4[entry(2 * R + 1)] : zero4;
             }
-            // entries that do not exist have z = -inf and weigh 0
-            double sum = weight_sum4<WITH_Q>(lo[k], q_lo, m, inv) + weight_sum4<WITH_Q>(hi[k], q_hi, m, inv);
+            if (WITH_Q && nv4 < NIT * 2 * TPB) {               // a row that ends inside the passes: entries that do not exist weigh 0
 #pragma unroll
-            for (int o = 16; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
-            if ((tid & 31) == 0 && (R >> 5) < nchunks) sums[row * nchunks + (R >> 5)] = (unsigned long long)sum;
+                for (int j = 0; j < G; ++j) {
+                    const int R = (k0 + j) * TPB + tid;
+                    if (2 * R >= nv4) q_lo[j] = zero4;
+                    if (2 * R + 1 >= nv4) q_hi[j] = zero4;
+                }
+            }
+            double sum[G];
+#pragma unroll
+            for (int j = 0; j < G; ++j)
+                sum[j] = weight_sum4<WITH_Q>(lo[k0 + j], q_lo[j], m, inv) + weight_sum4<WITH_Q>(hi[k0 + j], q_hi[j], m, inv);
+#pragma unroll
+            for (int o = 16; o > 0; o >>= 1)
+#pragma unroll
+                for (int j = 0; j < G; ++j) sum[j] += __shfl_xor(sum[j], o);
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                const int R = (k0 + j) * TPB + tid;
+                if ((tid & 31) == 0 && (R >> 5) < nchunks) sums[row * nchunks + (R >> 5)] = (unsigned long long)sum[j];
+            }
         }
     };
     if (use_p) chunk_pass(std::false_type{});
@@ -954,19 +990,19 @@ __global__ __launch_bounds__(ISL_TPB) void k_islands(const uint8_t* __restrict__
 }
 
 template <int NV4>
-void softmax_rows_inst(const float* in, float* out, int64_t rows, int V, hipStream_t st) {
-    hipLaunchKernelGGL(k_softmax_rows<NV4>, dim3((unsigned)rows), dim3(TPB), 0, st, in, out, V);
+void softmax_rows_inst(const float* in, float* out, int64_t rows, int V, const UpTokens& up, hipStream_t st) {
+    hipLaunchKernelGGL(k_softmax_rows<NV4>, dim3((unsigned)rows), dim3(TPB), 0, st, in, out, V, up);
 }
 }  // namespace
 
-void launch_softmax_rows(const float* in, float* out, int64_t rows, int V, hipStream_t st) {
+void launch_softmax_rows(const float* in, float* out, int64_t rows, int V, const UpTokens& up, hipStream_t st) {
     if (rows <= 0) return;
-    if (V <= 1024) softmax_rows_inst<1>(in, out, rows, V, st);
-    else if (V <= 2048) softmax_rows_inst<2>(in, out, rows, V, st);
-    else if (V <= 4096) softmax_rows_inst<4>(in, out, rows, V, st);
-    else if (V <= 8192) softmax_rows_inst<8>(in, out, rows, V, st);
-    else if (V <= 16384) softmax_rows_inst<16>(in, out, rows, V, st);
-    else softmax_rows_inst<0>(in, out, rows, V, st);
+    if (V <= 1024) softmax_rows_inst<1>(in, out, rows, V, up, st);
+    else if (V <= 2048) softmax_rows_inst<2>(in, out, rows, V, up, st);
+    else if (V <= 4096) softmax_rows_inst<4>(in, out, rows, V, up, st);
+    else if (V <= 8192) softmax_rows_inst<8>(in, out, rows, V, up, st);
+    else if (V <= 16384) softmax_rows_inst<16>(in, out, rows, V, up, st);
+    else softmax_rows_inst<0>(in, out, rows, V, up, st);
 }
 
 void launch_copy_rows(const float* in, float* out, int64_t n_floats, hipStream_t st) {
@@ -994,13 +1030,6 @@ void launch_upsample_tokens(const int32_t* draft_tokens, int32_t* tokens_hi, int
 void launch_gather_rows(const float* q_lo, const int32_t* q_row, float* q_hi, int B, int n_lo,
                         int n_hi, int V, hipStream_t st) {
     hipLaunchKernelGGL(k_gather_rows, dim3(n_hi, B), dim3(TPB), 0, st, q_lo, q_row, q_hi, n_lo, n_hi, V);
-}
-
-void launch_shift_inputs(const int32_t* prev, const int32_t* tokens_hi, int32_t* inputs, int B,
-                         int L, hipStream_t st) {
-    const int64_t n = (int64_t)B * L;
-    hipLaunchKernelGGL(k_shift_inputs, dim3((unsigned)((n + TPB - 1) / TPB)), dim3(TPB), 0, st, prev,
-                       tokens_hi, inputs, B, L);
 }
 
 // one thread per position of a block, whole wavefronts, between `least` and 1024
@@ -1069,12 +1098,16 @@ bool launch_accept(const DecideArgs& a, unsigned long long* sums, hipStream_t st
     // which have little to re-read (guided, 2 x 1024, threshold rule: 65 / 62).
     if (sums && !a.p_probs && a.V <= 16384 && a.accept_mode == 0 && a.pool_k <= 1 && a.resample_mode != 2 && a.rho != 0) {
         const int rows_per = (int)(((int64_t)a.B * a.L + 7) / 8);
-        auto go = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)rows_per * 8), dim3(TPB), 0, st, a, sums, rows_per); };
-        if (a.V <= 2048) go(k_accept_sums<1>);
-        else if (a.V <= 4096) go(k_accept_sums<2>);
-        else if (a.V <= 8192) go(k_accept_sums<4>);
-        else if (a.V <= 12288) go(k_accept_sums<6>);   // 10004 entries, 1152 rows: 50 -> 45 us with 6 of 8 passes
-        else go(k_accept_sums<8>);
+        auto go = [&](auto nit) {
+            constexpr int NIT = decltype(nit)::value;
+            if (a.logits_u) hipLaunchKernelGGL((k_accept_sums<NIT, true>), dim3((unsigned)rows_per * 8), dim3(TPB), 0, st, a, sums, rows_per);
+            else hipLaunchKernelGGL((k_accept_sums<NIT, false>), dim3((unsigned)rows_per * 8), dim3(TPB), 0, st, a, sums, rows_per);
+        };
+        if (a.V <= 2048) go(std::integral_constant<int, 1>{});
+        else if (a.V <= 4096) go(std::integral_constant<int, 2>{});
+        else if (a.V <= 8192) go(std::integral_constant<int, 4>{});
+        else if (a.V <= 12288) go(std::integral_constant<int, 6>{});   // 10004 entries, 1152 rows: 50 -> 45 us with 6 of 8 passes
+        else go(std::integral_constant<int, 8>{});
         return true;
     }
     hipLaunchKernelGGL(k_accept, dim3((unsigned)(a.B * a.L)), dim3(TPB), 0, st, a);

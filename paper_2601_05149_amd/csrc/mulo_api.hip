@@ -184,9 +184,9 @@ struct Scatter {
 };
 
 // want_parts: also leave the softmax statistics of every 128-column part of every logit row in c->row_parts
-// (returns whether the lm-head kernel that ran produces them)
+// (returns whether the lm-head kernel that ran produces them).  up: the inputs are a step's, from its draft tokens.
 bool enqueue_forward(mulo_ctx* c, mulo_kv* kv, int B, int L, int P, const int32_t* tok, const void* emb,
-                     float* logits, const Scatter* sc = nullptr, bool want_parts = false) {
+                     float* logits, const Scatter* sc = nullptr, bool want_parts = false, const StepTokens* up = nullptr) {
     const mulo_model_cfg& m = c->cfg;
     const int M = B * L, d = m.d_model, f = m.d_ffn, V = m.vocab, dt = m.dtype;
     const size_t e = c->esz;
@@ -201,7 +201,7 @@ bool enqueue_forward(mulo_ctx* c, mulo_kv* kv, int B, int L, int P, const int32_
     static_assert(4 * STREAM_MAX_TOKENS <= 512, "rows of slices");
     auto sm = [&](int projection) { return StreamMode{frag, wfrag, M <= STREAM_MAX_TOKENS ? c->attn_part : c->ksums, c->tile, &c->tiles_ran[projection]}; };
     Slices add{nullptr, 0};   // what the last residual projection left for the norm behind it to add
-    { PROF(MULO_PROF_NORM_EMBED); launch_embed(c->w.embed, dt, tok, emb, c->x, M, d, V, st); }
+    { PROF(MULO_PROF_NORM_EMBED); launch_embed(c->w.embed, dt, tok, emb, up ? *up : StepTokens{}, c->x, M, d, V, st); }
     for (int l = 0; l < m.n_layers; ++l) {
         RopeArgs ra{c->w.rope_cos, c->w.rope_sin, L, P, m.n_heads, m.head_dim, m.max_seq, m.max_batch, l};
         if (sc) ra.pos_tab = sc->pos_tab;
@@ -252,11 +252,12 @@ void enqueue_upsample(mulo_ctx* c, int B, int h, int w, int r, const float* draf
     PROF(MULO_PROF_UPSAMPLE);
     const int V = c->cfg.vocab;
     const int64_t rows = (int64_t)B * h * w;
-    if (draft) {   // the threshold rule with target re-draws needs no draft distribution
-        if (input_is_probs) launch_copy_rows(draft, q_lo, rows * V, c->st);
-        else launch_softmax_rows(draft, q_lo, rows, V, c->st);
+    if (input_is_probs) {
+        launch_copy_rows(draft, q_lo, rows * V, c->st);
+        launch_upsample_tokens(draft_tokens, tokens_hi, q_row, B, h, w, r, c->st);
+    } else {
+        launch_softmax_rows(draft, q_lo, rows, V, UpTokens{draft_tokens, tokens_hi, q_row, h, w, r}, c->st);
     }
-    launch_upsample_tokens(draft_tokens, tokens_hi, q_row, B, h, w, r, c->st);
     if (q_hi) launch_gather_rows(q_lo, q_row, q_hi, B, h * w, h * r * w * r, V, c->st);
 }
 
@@ -585,20 +586,18 @@ mulo_status mulo_verify_step(mulo_ctx* ctx, mulo_kv* kv, int32_t B, int32_t P, c
     hipStream_t st = ctx->st;
     int32_t* thi = tokens_hi ? tokens_hi : ctx->tokens_hi;
     float* lg = logits ? logits : ctx->logits;
-    // Step 2, the tokens (the draft distributions follow the target pass, see below)
-    enqueue_upsample(ctx, B, h_blk, w, r, nullptr, input_is_probs, draft_tokens, thi, ctx->q_lo, ctx->q_row, nullptr);
+    // Step 2, the tokens, by the embedding of their inputs (the draft distributions follow the target pass, see below), and
     // Step 3: inputs [prev, x~_0 .. x~_{L-2}] so that logit row j is p of draft position j
-    { mulo_ctx* c = ctx; PROF(MULO_PROF_OTHER); launch_shift_inputs(prev_tokens, thi, ctx->inputs, B, L, st);
-      if (cfg_on) launch_shift_inputs(prev_tokens, thi, ctx->inputs + (int64_t)B * L, B, L, st); }
+    const StepTokens up{UpTokens{draft_tokens, thi, ctx->q_row, h_blk, w, r}, prev_tokens, B};
     // the accept test needs only the softmax statistics of a logit row and the draft token's logit: when it is the
     // plain test (no pooling, no guidance) the lm-head's epilogue leaves the statistics and the rows are not re-read
     const bool plain = p->pool_k <= 1 && !cfg_on;
-    const bool have_parts = enqueue_forward(ctx, kv, B2, L, P, ctx->inputs, nullptr, lg, nullptr, plain);
+    const bool have_parts = enqueue_forward(ctx, kv, B2, L, P, nullptr, nullptr, lg, nullptr, plain, &up);
     // Step 2, the draft distributions q_lo: only the decision stage reads them, and run here they separate the
     // lm-head's writes of the logits from the re-draw's reads of them (both kernels measured faster in this order)
     if (need_q) { mulo_ctx* c = ctx; PROF(MULO_PROF_UPSAMPLE);
         if (input_is_probs) launch_copy_rows(draft, ctx->q_lo, (int64_t)B * n_lo * V, st);
-        else launch_softmax_rows(draft, ctx->q_lo, (int64_t)B * n_lo, V, st); }
+        else launch_softmax_rows(draft, ctx->q_lo, (int64_t)B * n_lo, V, UpTokens{}, st); }
     // Steps 4-5 + residual re-draw
     DecideArgs a{};
     fill_decide(a, ctx->cfg.vocab, ctx->rowmax, ctx->rowinv, B, p);

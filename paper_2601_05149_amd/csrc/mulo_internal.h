@@ -94,7 +94,10 @@ struct DecideArgs {
     // children of a draft row on one XCD next to each other, so that the row is fetched into one L2 once.
     int up_r, up_w;
 };
-void launch_softmax_rows(const float* in, float* out, int64_t rows, int V, hipStream_t st);
+// Replication of the draft's tokens (h x w cells a sequence, ratio r) to their children, with the table of the children's draft rows
+struct UpTokens { const int32_t* lo; int32_t *hi, *q_row; int h, w, r; };
+// up.hi: also what launch_upsample_tokens does, for the cells whose rows these are; nullptr: not
+void launch_softmax_rows(const float* in, float* out, int64_t rows, int V, const UpTokens& up, hipStream_t st);
 void launch_copy_rows(const float* in, float* out, int64_t n_floats, hipStream_t st);
 // dst[b * dst_stride + c] = src[b * V + c] for B rows of V floats (V a multiple of 4)
 void launch_copy_rows_strided(const float* src, float* dst, int B, int V, int64_t dst_stride, hipStream_t st);
@@ -123,8 +126,6 @@ void launch_sample_sums(const DecideArgs& a, const unsigned long long* sums, hip
 void launch_accept_from_parts(const DecideArgs& a, const float* parts, int n_parts, hipStream_t st);
 void launch_decide_finish(const DecideArgs& a, hipStream_t st);  // t0, Eq. 6-7 mask, the step's counters
 void launch_mask_sample(const DecideArgs& a, hipStream_t st);    // residual draw of the marked positions
-void launch_shift_inputs(const int32_t* prev, const int32_t* tokens_hi, int32_t* inputs, int B,
-                         int L, hipStream_t st);
 
 // ---- decoder forward (elementwise.hip, gemm.hip, attention.hip) ------------
 struct RopeArgs {
@@ -136,8 +137,12 @@ struct RopeArgs {
     // m % L of sequence m / L, at cache row P + m % L.
     const int32_t* pos_tab = nullptr;
 };
-// x[m, :] = embed[clamp(tok[m])]  (float32 residual stream); T = float or bf16 storage
-void launch_embed(const void* embed, int dtype, const int32_t* tok, const void* in_embeds, float* x,
+// The inputs of a step: row j of sequence b (of seqs; those behind them are their unconditional twins) takes prev[b] (j == 0) or the
+// up-sampled token of position j - 1
+struct StepTokens { UpTokens up; const int32_t* prev; int seqs; };
+// x[m, :] = embed[clamp(tok[m])]  (float32 residual stream); T = float or bf16 storage.  in.up.lo: the tokens are those of a step,
+// and the up-sampled tokens and the table of draft rows are written on the way.
+void launch_embed(const void* embed, int dtype, const int32_t* tok, const void* in_embeds, const StepTokens& in, float* x,
                   int M, int d, int V, hipStream_t st);
 // Sums of the K slices of a projection whose residual add is still to come: n slices [M, d] in `sums` (n == 0: none).
 struct Slices { const float* sums; int n; };
