@@ -973,15 +973,17 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
     const int cols = EPI == EPI_SWIGLU ? g.N / 2 : g.N, nblocks = (cols + COLS - 1) / COLS;
     const int steps = g.K / 32;
     int wg = blockIdx.x, kw = 0, sl0 = 0, sl1 = steps;   // this workgroup's columns and its slice of K (out, down: g.ksplit slices)
-    if constexpr (EPI == EPI_RESID) {
-        const int groups = (nblocks + NBLK - 1) / NBLK, per_slice = (steps + g.ksplit - 1) / g.ksplit;
-        kw = wg / groups;
-        wg -= kw * groups;
-        sl0 = kw * per_slice;
-        sl1 = sl0 + per_slice < steps ? sl0 + per_slice : steps;
+    if constexpr (EPI == EPI_RESID && MT > 1) {
+        if (g.ksplit > 1) {
+            const int groups = (nblocks + NBLK - 1) / NBLK, per_slice = (steps + g.ksplit - 1) / g.ksplit;
+            kw = wg / groups;
+            wg -= kw * groups;
+            sl0 = kw * per_slice;
+            sl1 = sl0 + per_slice < steps ? sl0 + per_slice : steps;
+        }
     }
     const int blk0 = wg * NBLK;            // first block of columns (gate|up: of feed-forward columns)
-    const int eighth = (sl1 - sl0 + 7) / 8, per = EPI != EPI_RESID || g.ksplit == 1 ? (eighth + 1) & ~1 : eighth;   // whole 128-byte lines of a weight row per wavefront
+    const int per = (sl1 - sl0 + 7) / 8;
     const int s0 = sl0 + wave * per, s1 = s0 + per < sl1 ? s0 + per : sl1;
 
     // weight row(s) this lane fetches; with a copy in fragment order (WFRAG) the KB of (16-row block, step) is
@@ -989,7 +991,7 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
     const bf16* w[NR];
 #pragma unroll
     for (int nb = 0; nb < NBLK; ++nb) {
-        int blk = blk0 + nb < nblocks ? blk0 + nb : nblocks - 1;   // a block past the last column re-reads the last one
+        int blk = NBLK == 1 || blk0 + nb < nblocks ? blk0 + nb : nblocks - 1;   // a block past the last column re-reads the last one
         const bf16 *base0 = g.W0, *base1 = g.W1;
         if constexpr (EPI == EPI_QKV) {
             const int seg = blk * 16 / g.d;                        // a block never straddles q | k | v (d % 16 == 0)
@@ -1105,7 +1107,7 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
 #pragma unroll
                 for (int r = 0; r < 4; ++r) part[buf][wave][a * MT + t][r][lane] = acc[nb * NA + a][t][r];
         __syncthreads();
-        if (wave < 2 * MT && m < g.M && blk0 + nb < nblocks && (!HALF || q < 2)) {
+        if (wave < 2 * MT && m < g.M && (NBLK == 1 || blk0 + nb < nblocks) && (!HALF || q < 2)) {
             float v0[2], v1[2] = {0.f, 0.f};
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
@@ -1120,7 +1122,7 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
                 v1[e] = sum1;
             }
             const int n = (blk0 + nb) * COLS + 4 * q + 2 * pr;
-            if (EPI == EPI_RESID && g.ksplit > 1)
+            if (EPI == EPI_RESID && MT > 1 && g.ksplit > 1)
                 *reinterpret_cast<float2*>(g.ksums + ((int64_t)kw * g.M + m) * g.N + n) = make_float2(v0[0], v0[1]);
             else
                 stream_epilogue<EPI>(g, m, n, v0, v1);
