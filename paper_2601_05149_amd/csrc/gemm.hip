@@ -682,7 +682,8 @@ __global__ __launch_bounds__(256, 1) void k_gemm_256(const GemmArgs g) {
 // PAIRED (5 stages): loads go out for two K-steps at a time, every other step, both halves of a 256-byte row segment one
 // behind the other, where a row's next 128 bytes otherwise follow a whole step later: 128 x 128 tiles over K = 11008, 576
 // tokens 94 -> 87 us, 1024 tokens 111 -> 99; the smaller tiles, which keep fewer bytes in flight, lose by it.
-template <int BM, int BN, int WGM, int WGN, int NS, int EPI, bool PAIRED>
+// SPLIT (out, down): a workgroup takes a slice of K and stores its sums to g.ksums; the norm behind the projection adds the slices.
+template <int BM, int BN, int WGM, int WGN, int NS, int EPI, bool PAIRED, bool SPLIT>
 __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g) {
     constexpr int NW = WGM * WGN, TM = BM / WGM, TN = BN / WGN, MB = TM / 32, NB = TN / 32;
     constexpr int RB = 128;                                             // bytes of a tile row
@@ -697,9 +698,16 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
     const int wm = wave / WGN, wn = wave % WGN, l32 = lane & 31, lh = lane >> 5;
     // one tile per workgroup; tiles to XCDs as in k_gemm_256 (the grid is a multiple of 8)
     constexpr int GW = 8;
-    const int tiles_m = (g.M + BM - 1) / BM, total = tiles_m * g.tiles_n, chunk = (total + 7) / 8;
-    const int loc = blockIdx.x >> 3, t = (blockIdx.x & 7) * chunk + loc;
-    if (loc >= chunk || t >= total) return;                             // uniform over the workgroup, before any barrier
+    const int tiles_m = (g.M + BM - 1) / BM, tiles = tiles_m * g.tiles_n, total = SPLIT ? tiles * g.ksplit : tiles, chunk = (total + 7) / 8;
+    const int loc = blockIdx.x >> 3, unit = (blockIdx.x & 7) * chunk + loc;
+    if (loc >= chunk || unit >= total) return;                          // uniform over the workgroup, before any barrier
+    int t = unit, k0 = 0, nk = g.K / 64;                                // the tile and its K-steps [k0, k0 + nk)
+    if constexpr (SPLIT) {
+        const int kw = unit / tiles, per = (nk + g.ksplit - 1) / g.ksplit;
+        t = unit - kw * tiles;
+        k0 = kw * per;
+        nk = nk - k0 < per ? nk - k0 : per;
+    }
     const int grp = t / (tiles_m * GW), rem = t - grp * tiles_m * GW;
     const int gw = g.tiles_n - grp * GW < GW ? g.tiles_n - grp * GW : GW;
     const int tile_n = g.tile_n0 + grp * GW + rem % gw, m0 = (rem / gw) * BM, n0 = tile_n * BN;
@@ -709,7 +717,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
     const int lrow = lane >> 3, lch = lane & 7;
     auto row_key = [](int r) { return (r >> 1) & 7; };
     uint32_t va[LA], vb[LB];
-    const rsrc_t rA = make_rsrc(g.A + (int64_t)m0 * g.K, 0x7fffffff);
+    const rsrc_t rA = make_rsrc(g.A + (int64_t)m0 * g.K + k0 * 64, 0x7fffffff);
     rsrc_t rW[2];
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
@@ -720,8 +728,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
         int which;
         const int base = b_row_src<EPI, BN, TN>(g, n0, tile_n, 0, which);
         const bf16* w0 = which == 0 ? g.W0 : which == 1 ? g.W1 : g.W2;
-        rW[0] = make_rsrc(w0 + (int64_t)base * g.K, 0x7fffffff);
-        rW[1] = make_rsrc((EPI == EPI_SWIGLU ? g.W1 : w0) + (int64_t)base * g.K, 0x7fffffff);
+        rW[0] = make_rsrc(w0 + (int64_t)base * g.K + k0 * 64, 0x7fffffff);
+        rW[1] = make_rsrc((EPI == EPI_SWIGLU ? g.W1 : w0) + (int64_t)base * g.K + k0 * 64, 0x7fffffff);
 #pragma unroll
         for (int i = 0; i < LB; ++i) {
             const int r = (i * NW + wave) * 8 + lrow;
@@ -741,7 +749,6 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rW[w], (lds_void*)(st + BM * RB + (j * NW + wave) * 1024), 16, (int)vb[j], kt * RB, 0, 0);
         }
     };
-    const int nk = g.K / 64;
     f32x16 acc[MB][NB];
 #pragma unroll
     for (int i = 0; i < MB; ++i)
@@ -868,7 +875,14 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
         }
     }
     mm(1);
-    epilogue<EPI, BN, TM, TN, MB, NB>(g, acc, m0, n0, tile_n, wm, wn, l32, lh);
+    if constexpr (SPLIT) {
+        GemmArgs gs = g;
+        gs.Cf = g.ksums + (int64_t)(unit / tiles) * g.M * g.N;
+        gs.parts = nullptr;
+        epilogue<EPI_LOGITS, BN, TM, TN, MB, NB>(gs, acc, m0, n0, tile_n, wm, wn, l32, lh);
+    } else {
+        epilogue<EPI, BN, TM, TN, MB, NB>(g, acc, m0, n0, tile_n, wm, wn, l32, lh);
+    }
 }
 
 // column tiles [tile_n0, tile_n0 + tiles_n)
@@ -1443,16 +1457,16 @@ int choose_tile(const GemmArgs& g) {
 }
 
 // all columns, or column tiles [tile_n0, tile_n0 + tiles_n)
-template <int TILE, int WGM, int WGN, int EPI, bool PAIRED = false>
+template <int TILE, int WGM, int WGN, int EPI, bool PAIRED = false, bool SPLIT = false>
 void run_ring(GemmArgs g, hipStream_t st, int tile_n0 = 0, int tiles_n = 0) {
     constexpr int BM = TILE_COST[TILE].bm, BN = TILE_COST[TILE].bn, NS = TILE_COST[TILE].stages;
-    auto kern = k_gemm_ring<BM, BN, WGM, WGN, NS, EPI, PAIRED>;
+    auto kern = k_gemm_ring<BM, BN, WGM, WGN, NS, EPI, PAIRED, SPLIT>;
     const size_t lds = (size_t)NS * (BM + BN) * 128;
     static int attr_state = 0;
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds, &attr_state)) return;
     g.tiles_n = tiles_n ? tiles_n : (g.N + BN - 1) / BN;
     g.tile_n0 = tile_n0;
-    const int64_t total = (int64_t)((g.M + BM - 1) / BM) * g.tiles_n;
+    const int64_t total = (int64_t)((g.M + BM - 1) / BM) * g.tiles_n * (SPLIT ? g.ksplit : 1);
     hipLaunchKernelGGL(kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(WGM * WGN * 64), lds, st, g);
 }
 
@@ -1464,6 +1478,15 @@ int dispatch(GemmArgs g, const StreamMode& sm, hipStream_t st) {
     *sm.ran = -1;
     if (g.stream) {   // a handful of tokens: stream the weights (A is in fragment order)
         return run_gemv<EPI>(g, st);
+    }
+    if constexpr (EPI == EPI_RESID) {
+        if (sm.tile < 0 && g.ksums && splits_resid(g.M, g.N, g.K)) {
+            g.ksplit = RING_SPLIT;
+            *sm.ran = g.M <= 128 ? TILE_128x64 : TILE_128x128;
+            if (g.M <= 128) run_ring<TILE_128x64, 2, 2, EPI, false, true>(g, st);
+            else run_ring<TILE_128x128, 2, 2, EPI, true, true>(g, st);
+            return RING_SPLIT;
+        }
     }
     const int tile = sm.tile >= 0 && sm.tile < N_TILES && has_tile<EPI>(g, sm.tile) ? sm.tile : choose_tile<EPI>(g);
     *sm.ran = tile;

@@ -630,3 +630,36 @@ def test_streamed_sums_do_not_depend_on_the_columns_a_workgroup_takes(d, nh, f, 
             else:
                 check_bf16_logits("%d streamed tokens, width %d" % (L, d), z, zr[:, :L], zu[:, :L])
             assert torch.equal(kv[0][0, 0, :, P:P + L], k1[:, :L]) and torch.equal(kv[1][0, 0, :, :, P:P + L], v1[:, :, :L]), (copy, L)
+
+
+@pytest.mark.parametrize("L", [65, 128, 129, 192])
+def test_sliced_residual_projections_of_a_few_hundred_tokens(L):
+    """65 to 192 tokens whose out and down weights are long (3072 x 4096 and more) deal K to several workgroups (65 and 128 tokens
+    on 128 x 64 tiles, 129 and 192 on 128 x 128, the last K slice shorter): logits, residual stream and cache rows against the oracle,
+    and against the same rows of a launch of 193 tokens, which takes K whole."""
+    nh, dh, f, V = 24, 128, 4160, 12 * 1024
+    m = dict(n_layers=1, d_model=nh * dh, n_heads=nh, head_dim=dh, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
+    w, P, S = G.make_weights(m, seed=33), 5, 200
+    ctx, cos, sin = make_ctx(m, w, 1, S, 196)
+    kv = mulo.alloc_kv(ctx, DEV)
+    pre, blk = G.uniform_tokens((1, P), V, 33, tag=0), G.uniform_tokens((1, 193), V, 33, tag=1)
+    gpu_forward(ctx, kv, pre, 0)
+    whole = gpu_forward(ctx, kv, blk, P)
+    assert min(tiles_of(ctx, -1)) >= 0
+    k1, v1 = kv[0][0, 0, :, P:P + L].clone(), kv[1][0, 0, :, :, P:P + L].clone()
+    x = torch.empty(193, nh * dh, device=DEV)
+    mulo.mulo_workspace_read(ctx, mulo.MULO_WS_RESIDUAL, x)
+    z = gpu_forward(ctx, kv, blk[:, :L], P)
+    xs = torch.empty(L, nh * dh, device=DEV)
+    mulo.mulo_workspace_read(ctx, mulo.MULO_WS_RESIDUAL, xs)
+    torch.cuda.synchronize()
+    dr, du = pair(m, w, cos, sin, 1, S)
+    for t in (dr, du):
+        t.forward(pre, 0)
+    check_bf16_logits("%d tokens, K in slices" % L, z, dr.forward(blk[:, :L], P).numpy(), du.forward(blk[:, :L], P).numpy())
+    assert torch.equal(kv[0][0, 0, :, P:P + L], k1) and torch.equal(kv[1][0, 0, :, :, P:P + L], v1)   # layer 0: nothing sliced in front of them
+    # one layer: the two differ by the order of float32 sums of 4160 products, and by what a norm's bf16 roundings make of that (a
+    # flipped one moves a row's products by 2^-8 of one term): 2^-7 of a residual's size bounds both
+    err = (xs - x[:L]).abs().max() / x[:L].abs().max()
+    say("  residual stream, slices against whole K: %.3g of the largest" % float(err))
+    assert float(err) <= 2.0 ** -7 and np.abs(z - whole[:, :L]).max() <= 2.0 ** -5 * np.abs(whole).max()
