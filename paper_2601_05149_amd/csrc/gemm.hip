@@ -28,7 +28,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __hip_bfloat16 bf16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
+enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3, EPI_SLICE = 4 };   // SLICE: sums of a slice of K, for the norm behind to add
 
 struct GemmArgs {
     const bf16* A;        // [M, K]
@@ -683,8 +683,8 @@ __global__ __launch_bounds__(256, 1) void k_gemm_256(const GemmArgs g) {
 // PAIRED (5 stages): loads go out for two K-steps at a time, every other step, both halves of a 256-byte row segment one
 // behind the other, where a row's next 128 bytes otherwise follow a whole step later: 128 x 128 tiles over K = 11008, 576
 // tokens 94 -> 87 us, 1024 tokens 111 -> 99; the smaller tiles, which keep fewer bytes in flight, lose by it.
-// SPLIT (out, down): a workgroup takes a slice of K and stores its sums to g.ksums; the norm behind the projection adds the slices.
-template <int BM, int BN, int WGM, int WGN, int NS, int EPI, bool PAIRED, bool SPLIT>
+// EPI_SLICE (out, down): a workgroup takes a slice of K and stores its sums to g.ksums; the norm behind the projection adds the slices.
+template <int BM, int BN, int WGM, int WGN, int NS, int EPI, bool PAIRED>
 __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g) {
     constexpr int NW = WGM * WGN, TM = BM / WGM, TN = BN / WGN, MB = TM / 32, NB = TN / 32;
     constexpr int RB = 128;                                             // bytes of a tile row
@@ -694,6 +694,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
     static_assert(EPI != EPI_SWIGLU || (NB % 2 == 0 && (TN / 2) % (8 * NW) == 0), "a load never straddles gate and up");
     static_assert((NS - 2) * LPS < 64 && NS >= 3, "the wait counts loads in 6 bits");
     static_assert(!PAIRED || NS == 5, "two pairs and the step between them");
+    constexpr bool SPLIT = EPI == EPI_SLICE;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // NS stages of [BM + BN][RB]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN, l32 = lane & 31, lh = lane >> 5;
@@ -1462,16 +1463,16 @@ int choose_tile(const GemmArgs& g) {
 }
 
 // all columns, or column tiles [tile_n0, tile_n0 + tiles_n)
-template <int TILE, int WGM, int WGN, int EPI, bool PAIRED = false, bool SPLIT = false>
+template <int TILE, int WGM, int WGN, int EPI, bool PAIRED = false>
 void run_ring(GemmArgs g, hipStream_t st, int tile_n0 = 0, int tiles_n = 0) {
     constexpr int BM = TILE_COST[TILE].bm, BN = TILE_COST[TILE].bn, NS = TILE_COST[TILE].stages;
-    auto kern = k_gemm_ring<BM, BN, WGM, WGN, NS, EPI, PAIRED, SPLIT>;
+    auto kern = k_gemm_ring<BM, BN, WGM, WGN, NS, EPI, PAIRED>;
     const size_t lds = (size_t)NS * (BM + BN) * 128;
     static int attr_state = 0;
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds, &attr_state)) return;
     g.tiles_n = tiles_n ? tiles_n : (g.N + BN - 1) / BN;
     g.tile_n0 = tile_n0;
-    const int64_t total = (int64_t)((g.M + BM - 1) / BM) * g.tiles_n * (SPLIT ? g.ksplit : 1);
+    const int64_t total = (int64_t)((g.M + BM - 1) / BM) * g.tiles_n * (EPI == EPI_SLICE ? g.ksplit : 1);
     hipLaunchKernelGGL(kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(WGM * WGN * 64), lds, st, g);
 }
 
@@ -1488,8 +1489,8 @@ int dispatch(GemmArgs g, const StreamMode& sm, hipStream_t st) {
         if (sm.tile < 0 && g.ksums && splits_resid(g.M, g.N, g.K)) {
             g.ksplit = RING_SPLIT;
             *sm.ran = g.M <= 128 ? TILE_128x64 : TILE_128x128;
-            if (g.M <= 128) run_ring<TILE_128x64, 2, 2, EPI, false, true>(g, st);
-            else run_ring<TILE_128x128, 2, 2, EPI, true, true>(g, st);
+            if (g.M <= 128) run_ring<TILE_128x64, 2, 2, EPI_SLICE>(g, st);
+            else run_ring<TILE_128x128, 2, 2, EPI_SLICE, true>(g, st);
             return RING_SPLIT;
         }
     }
