@@ -270,9 +270,9 @@ __device__ __forceinline__ void weights4(const float4 z, const float4 qv, float 
 __device__ __forceinline__ int clamp_tok(int t, int V) { return t < 0 ? 0 : (t >= V ? V - 1 : t); }
 
 // The accept test of one position, by one lane: Eq. 1 without the division (u q < pbar), or the threshold rule of
-// Eq. 5 (pbar >= tau); leaves the row statistics for the re-draw kernel and parks the near-tie flag in the mask
-// array until k_decide_finish has counted it (per-row atomics on the few counters of a sequence cost a quarter of
-// the accept kernel's time).
+// Eq. 5 (pbar >= tau); leaves the row statistics for the re-draw kernel, the near-tie flag as the sign of the inverse sum,
+// for finish_sequence to count (per-row atomics on the few counters of a sequence cost a quarter of the accept
+// kernel's time).
 __device__ __forceinline__ bool accept_row(const DecideArgs& a, int64_t row, int b, int t, float qt, float pbar,
                                            float m, float inv) {
     const uint32_t w0 = philox_word0((uint32_t)t, (uint32_t)b, a.ctr_lo, a.ctr_hi24, a.key0, a.key1);
@@ -283,8 +283,8 @@ __device__ __forceinline__ bool accept_row(const DecideArgs& a, int64_t row, int
     const bool ok = tau_rule ? pbar >= uq : uq < pbar;
     a.accept[row] = ok ? 1 : 0;
     a.rowmax[row] = m;
-    a.rowinv[row] = inv;
-    a.mask[row] = fabsf(__fsub_rn(pbar, uq)) < __fmul_rn(NEAR_TIE, tau_rule ? a.tau : qt) ? 1 : 0;
+    const bool near = fabsf(__fsub_rn(pbar, uq)) < __fmul_rn(NEAR_TIE, tau_rule ? a.tau : qt);
+    a.rowinv[row] = __builtin_copysignf(inv, near ? -1.f : 1.f);
     return ok;
 }
 
@@ -503,18 +503,17 @@ __global__ __launch_bounds__(TPB) void k_accept_parts(const DecideArgs a, const 
 // mask, t0 and stats = (accepted, rejected, marked, near ties); no atomics on global memory anywhere.
 // A chain of latencies, so a position per thread up to blocks of 1024 where there is a window to search (4 x 1024, radius 2:
 // 256 threads 7.5 us, 1024 6.8); without one (2 x 1024, radius 0: 4.7 / 5.3) the larger workgroup only costs.
-__global__ __launch_bounds__(1024) void k_decide_finish(const DecideArgs a) {
-    extern __shared__ uint8_t acc_s[];   // [L]
-    __shared__ int red[16][4];
-    const int b = blockIdx.x, tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wv = tid >> 6;
+__device__ __forceinline__ void finish_sequence(const DecideArgs& a, int b, uint8_t* acc_s, int (*red)[4]) {   // acc_s: [L] of LDS
+    const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wv = tid >> 6;
     const uint8_t* acc_g = a.accept + (int64_t)b * a.L;
+    const float* inv_g = a.rowinv + (int64_t)b * a.L;
     uint8_t* mask_g = a.mask + (int64_t)b * a.L;
     int n_acc = 0, n_near = 0, tmin = a.L;
     for (int t = tid; t < a.L; t += nt) {
         const uint8_t ok = acc_g[t];
         acc_s[t] = ok;
         n_acc += ok;
-        n_near += mask_g[t];
+        n_near += __builtin_signbit(inv_g[t]) != 0;
         if (!ok && t < tmin) tmin = t;
     }
     auto reduce_counts = [&](int& x, int& y, int& z_min, int& w) {   // sums of x, y, w and the minimum of z_min over the workgroup
@@ -536,7 +535,7 @@ __global__ __launch_bounds__(1024) void k_decide_finish(const DecideArgs a) {
         }
     };
     int zero = 0;
-    reduce_counts(n_acc, n_near, tmin, zero);   // the barriers inside also publish acc_s and retire the reads of mask_g
+    reduce_counts(n_acc, n_near, tmin, zero);   // the barriers inside also publish acc_s
     const int t0 = tmin;
     int n_marked = 0;
     for (int t = tid; t < a.L; t += nt) {
@@ -566,6 +565,32 @@ __global__ __launch_bounds__(1024) void k_decide_finish(const DecideArgs a) {
         a.stats[b * 4 + 2] = n_marked;
         a.stats[b * 4 + 3] = n_near;
     }
+}
+
+__global__ __launch_bounds__(1024) void k_decide_finish(const DecideArgs a) {
+    extern __shared__ uint8_t acc_s[];   // [L]
+    __shared__ int red[16][4];
+    finish_sequence(a, blockIdx.x, acc_s, red);
+}
+
+// Blocks of up to FUSED_L positions have no launch for it: the first workgroups of the re-draw run finish_sequence, a sequence each
+// (n_fin of them, whole rounds of XCDs), while those of the positions find out for themselves whether theirs is marked,
+// a wavefront over the flags in front of it and in its window.  A chain of latencies of 6.6 us less in a decision stage.
+constexpr int FUSED_L = 4096;
+__device__ __forceinline__ bool position_marked(const DecideArgs& a, int b, int t, int lane) {
+    const uint8_t* const acc = a.accept + (int64_t)b * a.L;
+    bool before = false, near = false;   // a rejected position at or before t (t >= t0), one inside its window
+#pragma unroll 4
+    for (int u = lane; u <= t; u += 64) before |= acc[u] == 0;
+    if (a.rho >= 0) {
+        const int g = a.n0 + t, gi = g / a.W, gj = g % a.W, r0 = a.n0 / a.W, r1 = (a.n0 + a.L - 1) / a.W;
+        const int i_lo = gi - a.rho > r0 ? gi - a.rho : r0, i_hi = gi + a.rho < r1 ? gi + a.rho : r1;
+        const int j_lo = gj - a.rho > 0 ? gj - a.rho : 0, j_hi = gj + a.rho < a.W - 1 ? gj + a.rho : a.W - 1, nj = j_hi - j_lo + 1;
+        for (int c = lane; c < (i_hi - i_lo + 1) * nj; c += 64) near |= acc[(i_lo + c / nj) * a.W + j_lo + c % nj - a.n0] == 0;
+    } else {
+        near = before;
+    }
+    return __any(before) && __any(near);
 }
 
 // ---- Step 5 + Eq. 2: neighbourhood mask, then the residual draw -------------
@@ -682,16 +707,23 @@ __device__ __forceinline__ void cdf_draw(const Guided z, const float4* __restric
     }
 }
 
-__global__ __launch_bounds__(TPB) void k_mask_sample(const DecideArgs a) {
+__global__ __launch_bounds__(TPB) void k_mask_sample(const DecideArgs a, int n_fin) {
     __shared__ unsigned long long chunk[MAX_CHUNKS];
     __shared__ int s_retry;
+    if ((int)blockIdx.x < n_fin) {                     // uniform over the workgroup
+        __shared__ int red[16][4];
+        static_assert(FUSED_L <= MAX_CHUNKS * 8, "the flags of a block");
+        if ((int)blockIdx.x < a.B) finish_sequence(a, blockIdx.x, reinterpret_cast<uint8_t*>(chunk), red);
+        return;
+    }
+    const int wg = blockIdx.x - n_fin;
     // Which position this workgroup handles.  Workgroup ids go round-robin over the 8 XCDs (each with its own L2).
     // When the draft rows are shared by r x r children (replication up-sampling), the children of a draft row are
     // given to consecutive workgroups of ONE XCD, so that the row comes from memory once instead of once per child.
-    int64_t row = blockIdx.x;
+    int64_t row = wg;
     if (a.up_r > 1) {
         const int r2 = a.up_r * a.up_r, n_par = a.L / r2;
-        const int x = blockIdx.x & 7, k = blockIdx.x >> 3;
+        const int x = wg & 7, k = wg >> 3;
         const int64_t pseq = (int64_t)(k / r2) * 8 + x;
         if (pseq >= (int64_t)a.B * n_par) return;      // uniform over the workgroup (the grid is rounded up)
         const int child = k % r2, bb = pseq / n_par, par = pseq % n_par;
@@ -700,8 +732,8 @@ __global__ __launch_bounds__(TPB) void k_mask_sample(const DecideArgs a) {
     }
     const int b = row / a.L, t = row % a.L, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
 
-    // R_X membership of this position (Eq. 6-7) was decided by k_decide_finish
-    const int marked = a.mask[row];
+    // R_X membership of this position (Eq. 6-7)
+    const bool marked = n_fin ? position_marked(a, b, t, lane) : a.mask[row] != 0;
     const int draft = clamp_tok(a.draft_tokens[row], a.V);
     if (!marked) {   // uniform over the workgroup
         if (tid == 0) a.tokens_out[row] = draft;
@@ -716,18 +748,24 @@ __global__ __launch_bounds__(TPB) void k_mask_sample(const DecideArgs a) {
     const float4* q4 = reinterpret_cast<const float4*>(a.q ? a.q + b * a.q_batch_stride + (int64_t)qr * V : z.zc);
     const uint32_t word = philox_word0((uint32_t)t, (uint32_t)b, a.ctr_lo, a.ctr_hi24 | (1u << 24),
                                        a.key0, a.key1);
-    cdf_draw(z, q4, a.rowmax[row], a.rowinv[row], use_p, word, V, draft, &a.tokens_out[row], chunk, &s_retry);
+    cdf_draw(z, q4, a.rowmax[row], fabsf(a.rowinv[row]), use_p, word, V, draft, &a.tokens_out[row], chunk, &s_retry);
 }
 
 // The re-draw from the chunk sums that k_accept_sums left (at most 64 chunks, a lane each): one wavefront per position finds
 // the chunk and reads its 256 entries.  The same draw as cdf_draw's, empty residual included.
-__global__ __launch_bounds__(TPB) void k_sample_sums(const DecideArgs a, const unsigned long long* __restrict__ sums) {
+__global__ __launch_bounds__(TPB) void k_sample_sums(const DecideArgs a, const unsigned long long* __restrict__ sums, int n_fin) {
+    if ((int)blockIdx.x < n_fin) {                             // uniform over the workgroup
+        __shared__ uint8_t acc_s[FUSED_L];
+        __shared__ int red[16][4];
+        if ((int)blockIdx.x < a.B) finish_sequence(a, blockIdx.x, acc_s, red);
+        return;
+    }
     const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * WAVES + (threadIdx.x >> 6);
+    const int64_t row = (int64_t)(blockIdx.x - n_fin) * WAVES + (threadIdx.x >> 6);
     if (row >= (int64_t)a.B * a.L) return;                     // uniform over the wavefront; no barrier follows
     const int b = row / a.L, t = row % a.L, V = a.V, nv4 = V >> 2, nchunks = (nv4 + 63) >> 6;
     const int draft = clamp_tok(a.draft_tokens[row], V);
-    if (!a.mask[row]) {
+    if (!(n_fin ? position_marked(a, b, t, lane) : a.mask[row] != 0)) {
         if (lane == 0) a.tokens_out[row] = draft;
         return;
     }
@@ -736,7 +774,7 @@ __global__ __launch_bounds__(TPB) void k_sample_sums(const DecideArgs a, const u
     const int qr = a.q_row ? a.q_row[t] : t;
     const float4* q4 = a.q ? reinterpret_cast<const float4*>(a.q + b * a.q_batch_stride + (int64_t)qr * V) : nullptr;
     const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
-    const float m = a.rowmax[row], inv = a.rowinv[row];
+    const float m = a.rowmax[row], inv = fabsf(a.rowinv[row]);
     unsigned long long v = lane < nchunks ? sums[row * nchunks + lane] : 0ull, tot = wave_sum_u64(v);
     if (tot == 0 && !use_p) {                                  // empty residual: draw from p instead
         use_p = true;
@@ -1079,10 +1117,13 @@ void launch_island_draw(const float* logits, const int32_t* pos_tab, int32_t* to
     else go(k_island_draw<0>);
 }
 
-void launch_decide_finish(const DecideArgs& a, hipStream_t st) {   // a.L <= 131072 (the caller checks): flags in LDS
+// the counters and the mask, in front of a re-draw that does not make them itself; returns how many workgroups of it do (0: none)
+static int decide_finish(const DecideArgs& a, hipStream_t st) {   // a.L <= 131072 (the caller checks): flags in LDS
+    if (a.L <= FUSED_L) return (a.B + 7) / 8 * 8;
     static int attr_state = 0;
-    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(k_decide_finish), 131072, &attr_state)) return;
+    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(k_decide_finish), 131072, &attr_state)) return 0;
     hipLaunchKernelGGL(k_decide_finish, dim3(a.B), dim3(a.rho > 0 ? block_threads(a.L, 256) : 256), (size_t)a.L, st, a);
+    return 0;
 }
 
 bool launch_accept(const DecideArgs& a, unsigned long long* sums, hipStream_t st) {
@@ -1116,7 +1157,8 @@ bool launch_accept(const DecideArgs& a, unsigned long long* sums, hipStream_t st
 
 void launch_sample_sums(const DecideArgs& a, const unsigned long long* sums, hipStream_t st) {
     const int64_t rows = (int64_t)a.B * a.L;
-    hipLaunchKernelGGL(k_sample_sums, dim3((unsigned)((rows + WAVES - 1) / WAVES)), dim3(TPB), 0, st, a, sums);
+    const int n_fin = decide_finish(a, st);
+    hipLaunchKernelGGL(k_sample_sums, dim3((unsigned)((rows + WAVES - 1) / WAVES + n_fin)), dim3(TPB), 0, st, a, sums, n_fin);
 }
 
 void launch_accept_from_parts(const DecideArgs& a, const float* parts, int n_parts, hipStream_t st) {
@@ -1132,7 +1174,8 @@ void launch_mask_sample(const DecideArgs& a, hipStream_t st) {
         const int64_t parents = (int64_t)a.B * (a.L / r2);
         blocks = (unsigned)(((parents + 7) / 8) * 8 * r2);
     }
-    hipLaunchKernelGGL(k_mask_sample, dim3(blocks), dim3(TPB), 0, st, a);
+    const int n_fin = decide_finish(a, st);
+    hipLaunchKernelGGL(k_mask_sample, dim3(blocks + n_fin), dim3(TPB), 0, st, a, n_fin);
 }
 
 }  // namespace mulo

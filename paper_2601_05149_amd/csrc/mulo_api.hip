@@ -272,7 +272,6 @@ void enqueue_decide(mulo_ctx* c, const DecideArgs& a, bool have_parts = false) {
     { PROF(MULO_PROF_ACCEPT);
       if (have_parts) launch_accept_from_parts(a, c->row_parts, (a.V + 127) / 128, c->st);
       else have_sums = launch_accept(a, sums, c->st); }
-    { PROF(MULO_PROF_OTHER); launch_decide_finish(a, c->st); }
     { PROF(MULO_PROF_MASK_SAMPLE);
       if (have_sums) launch_sample_sums(a, sums, c->st);
       else launch_mask_sample(a, c->st); }
@@ -564,7 +563,6 @@ mulo_status mulo_accept_local_resample_static(void* hip_stream, int32_t vocab, i
     a.t0 = t0; a.stats = stats; a.p_probs = p_probs;
     hipStream_t st = (hipStream_t)hip_stream;
     launch_accept(a, nullptr, st);   // no workspace to keep sums in
-    launch_decide_finish(a, st);
     launch_mask_sample(a, st);
     return check_launch();
 }

@@ -96,7 +96,7 @@ struct DecideArgs {
     int32_t* stats;   // [B, 4]
     float* p_probs;   // [B, L, V] or nullptr
     float* rowmax;    // [B*L] workspace
-    float* rowinv;    // [B*L] workspace: 1 / sum exp
+    float* rowinv;    // [B*L] workspace: 1 / sum exp, negative: a near tie
     // Replication geometry of the draft rows (a verification step): position (r I + a) W + r J + c of the block reads
     // draft row I up_w + J, W = up_r * up_w.  0: unknown (q_row is the caller's).  Only used to place the r * r
     // children of a draft row on one XCD next to each other, so that the row is fetched into one L2 once.
@@ -126,14 +126,13 @@ void launch_island_select(const int32_t* prev, const int32_t* tokens, const uint
 void launch_island_draw(const float* logits, const int32_t* pos_tab, int32_t* tokens, float* logits_out, int B,
                         int L, int V, int P, int cap, uint64_t seed, uint64_t rng_counter, hipStream_t st);
 // softmax statistics + accept test.  sums: nullptr, or B * L * ceil(V / 256) integers for the chunk sums of the re-draw's
-// weights; returns whether they were written (then launch_sample_sums draws, else launch_mask_sample)
+// weights; returns whether they were written (then launch_sample_sums finishes and draws, else launch_mask_sample)
 bool launch_accept(const DecideArgs& a, unsigned long long* sums, hipStream_t st);
 void launch_sample_sums(const DecideArgs& a, const unsigned long long* sums, hipStream_t st);
 // the accept test from row parts (m, s per 128 columns, float pairs [rows, n_parts]) that the lm-head GEMM left;
 // needs pool_k <= 1, no probability output and no guidance
 void launch_accept_from_parts(const DecideArgs& a, const float* parts, int n_parts, hipStream_t st);
-void launch_decide_finish(const DecideArgs& a, hipStream_t st);  // t0, Eq. 6-7 mask, the step's counters
-void launch_mask_sample(const DecideArgs& a, hipStream_t st);    // residual draw of the marked positions
+void launch_mask_sample(const DecideArgs& a, hipStream_t st);    // t0, Eq. 6-7 mask and the step's counters, residual draw of the marked positions
 
 // ---- decoder forward (elementwise.hip, gemm.hip, attention.hip) ------------
 struct RopeArgs {
