@@ -386,6 +386,40 @@ def test_draw_from_chunk_sums_equals_the_draw_from_the_rows(V, kw):
 
 
 # --------------------------------------------------------------- rejection islands (Eq. 8)
+@pytest.mark.parametrize("W,rows", [(64, 64), (64, 65), (4097, 1), (1, 4096), (61, 67)])
+@pytest.mark.parametrize("rho", [-1, 0, 2, 70])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])   # a bf16 context draws from chunk sums where there is a window (k_sample_sums)
+def test_mask_and_counters_on_both_sides_of_the_longest_fused_block(W, rows, rho, dtype):
+    """Blocks of 4096 positions (the re-draw makes mask and counters itself) and a few more (a launch in front of it does): few and late
+    rejections, so that windows hold rejections in front of, behind and at the position, and sequences that accept everything.
+    t0, mask and counters from the flags by numpy, and every unmarked token kept."""
+    B, L, V = 3, W * rows, 8
+    key = (dtype, V, 3, 4160)
+    if key not in _CTX:
+        m = dict(n_layers=1, d_model=128, n_heads=2, head_dim=64, d_ffn=128, vocab=V, dtype=dtype, rms_eps=1e-5)
+        _CTX[key] = make_ctx(m, G.make_weights(m, seed=0, threads=4), 3, 4168, 4160)[0]
+    ctx = _CTX[key]
+    rng = np.random.default_rng(7)
+    zp = np.zeros((B, L, V), np.float32)
+    q = np.full((B, L, V), 1.0 / V, np.float32)
+    toks = rng.integers(0, V, (B, L)).astype(np.int32)
+    for b, at in ((0, [L // 3, L // 3 + 7, L - 1]), (1, [L - 2])):
+        zp[b, at, toks[b, at]] = -40.0                                  # p of the draft token is 0: rejected whatever the uniform
+    res = run_decide(ctx, zp, q, toks, H=rows, W=W, n0=0, L=L, radius=rho, seed=3, rng_counter=1)
+    for b in range(B):
+        rej = np.flatnonzero(res["accept"][b] == 0)
+        t0 = int(rej[0]) if rej.size else L
+        assert rej.size == (3, 1, 0)[b] and res["t0"][b] == t0
+        ii, jj = np.arange(L) // W, np.arange(L) % W
+        hit = np.zeros(L, bool) if rho >= 0 else np.full(L, rej.size > 0)
+        for t in rej if rho >= 0 else ():
+            hit |= np.maximum(abs(ii - t // W), abs(jj - t % W)) <= rho
+        want = hit & (np.arange(L) >= t0)
+        assert np.array_equal(res["mask"][b] != 0, want)
+        assert list(res["stats"][b][:3]) == [L - rej.size, rej.size, int(want.sum())]
+        assert np.array_equal(res["tokens_out"][b][~want], toks[b][~want])
+
+
 def _islands_gpu(ctx, mask, W, n0):
     B, L = mask.shape
     isl = torch.empty(B, L, dtype=torch.int32, device=DEV)
