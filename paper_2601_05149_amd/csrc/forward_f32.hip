@@ -224,7 +224,9 @@ void run_proj(const F32Args& g, hipStream_t st) {
 // straight from memory in the order of the projections above: a lane holds keys 4 q .. 4 q + 3 of query lane % 16, which
 // is what the second product takes, so the probabilities never leave their registers.  NB = ceil(head_dim / 16).
 // 256 queries, 288 keys, 4 heads: 21 -> 12 us (one workgroup per query before: scores in LDS, strided key reads).
-template <int NB, int NW>
+// FULL: head_dim is 16 NB and max_seq a multiple of 4, so every access is one of 16 bytes inside its row, without the branches that
+// the ends of rows ask for (four a load, 36 loads a tile).
+template <int NB, int NW, bool FULL>
 __global__ __launch_bounds__(NW * 64) void k_attn_mfma_f32(const float* __restrict__ qb, const float* __restrict__ kc,
                                                        const float* __restrict__ vc, float* __restrict__ out, int L, int P,
                                                        int nh, int dh, int max_seq, int max_batch, int layer) {
@@ -239,10 +241,11 @@ __global__ __launch_bounds__(NW * 64) void k_attn_mfma_f32(const float* __restri
     const float* vb = vc + hb * dh * max_seq;
     const float* qp = qb + (((int64_t)b * nh + hd) * L + jq) * dh;
     const float scale = 1.0f / sqrtf((float)dh), NEG = -__builtin_huge_valf();
+    auto at = [](const float* p) { f32x4 v; __builtin_memcpy(&v, p, sizeof(v)); return v; };
     f32x4 qf[NB], o[NB];
 #pragma unroll
     for (int s = 0; s < NB; ++s) {
-        qf[s] = load4<false>(qp, s * 16 + q * 4, dh);
+        qf[s] = FULL ? at(qp + s * 16 + q * 4) : load4<false>(qp, s * 16 + q * 4, dh);
         o[s] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     float m_run = NEG, l_run = 0.f;
@@ -251,11 +254,12 @@ __global__ __launch_bounds__(NW * 64) void k_attn_mfma_f32(const float* __restri
         const int key = k0 + l16 < kmax ? k0 + l16 : kmax;
         const float* kr = kb + (int64_t)key * dh;
 #pragma unroll
-        for (int s = 0; s < NB; ++s) nk[s] = load4<false>(kr, s * 16 + q * 4, dh);
+        for (int s = 0; s < NB; ++s) nk[s] = FULL ? at(kr + s * 16 + q * 4) : load4<false>(kr, s * 16 + q * 4, dh);
+        const int kv = k0 + q * 4 < max_seq ? k0 + q * 4 : max_seq - 4;   // FULL: columns past the cache are the last four again
 #pragma unroll
-        for (int s = 0; s < NB; ++s) {                    // columns past the last key may be uninitialised: zeros
+        for (int s = 0; s < NB; ++s) {                    // columns past the last key may be uninitialised: zeros (FULL: below)
             const int c = s * 16 + l16;
-            nv[s] = load4<false>(vb + (int64_t)(c < dh ? c : dh - 1) * max_seq, k0 + q * 4, kmax + 1);
+            nv[s] = FULL ? at(vb + (int64_t)c * max_seq + kv) : load4<false>(vb + (int64_t)(c < dh ? c : dh - 1) * max_seq, k0 + q * 4, kmax + 1);
         }
     };
     if (wave * 16 <= kmax) request(wave * 16);
@@ -263,6 +267,12 @@ __global__ __launch_bounds__(NW * 64) void k_attn_mfma_f32(const float* __restri
         f32x4 kf[NB], vf[NB];
 #pragma unroll
         for (int s = 0; s < NB; ++s) { kf[s] = nk[s]; vf[s] = nv[s]; }
+        if (FULL && k0 + 15 > kmax) {                     // uniform over the workgroup
+#pragma unroll
+            for (int s = 0; s < NB; ++s)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) vf[s][e] = k0 + q * 4 + e <= kmax ? vf[s][e] : 0.f;
+        }
         if (k0 + 16 * NW <= kmax) request(k0 + 16 * NW);
         f32x4 p = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -426,10 +436,15 @@ void launch_attention_f32(const float* q, const float* k_cache, const float* v_c
         hipLaunchKernelGGL(kern, dim3((L + 15) / 16, n_heads, B), dim3(waves * 64), 0, st, q, k_cache, v_cache, out, L, P, n_heads,
                            head_dim, max_seq, max_batch, layer);
     };
-    if (head_dim <= 16) go(k_attn_mfma_f32<1, 8>, 8);
-    else if (head_dim <= 32) go(k_attn_mfma_f32<2, 8>, 8);
-    else if (head_dim <= 64) go(k_attn_mfma_f32<4, 8>, 8);
-    else if (head_dim <= 128) go(k_attn_mfma_f32<8, 4>, 4);
+    const bool full = (max_seq & 3) == 0;
+    if (head_dim == 16 && full) go(k_attn_mfma_f32<1, 8, true>, 8);
+    else if (head_dim <= 16) go(k_attn_mfma_f32<1, 8, false>, 8);
+    else if (head_dim == 32 && full) go(k_attn_mfma_f32<2, 8, true>, 8);
+    else if (head_dim <= 32) go(k_attn_mfma_f32<2, 8, false>, 8);
+    else if (head_dim == 64 && full) go(k_attn_mfma_f32<4, 8, true>, 8);
+    else if (head_dim <= 64) go(k_attn_mfma_f32<4, 8, false>, 8);
+    else if (head_dim == 128 && full) go(k_attn_mfma_f32<8, 4, true>, 4);
+    else if (head_dim <= 128) go(k_attn_mfma_f32<8, 4, false>, 4);
     else
         hipLaunchKernelGGL(k_attn_wide_f32, dim3(L, n_heads, B), dim3(256), (size_t)(head_dim + P + L) * sizeof(float), st, q,
                            k_cache, v_cache, out, L, P, n_heads, head_dim, max_seq, max_batch, layer);
