@@ -1392,13 +1392,12 @@ __global__ __launch_bounds__(256) void k_pack_weights(const bf16* __restrict__ s
 // S = per_cu x CUs places: c0 + e per round + (K / 64) x (tf per full round; a last round of r tiles between
 // t0, where few CUs fetch, and tf: t0 + (tf - t0) r / S).  per_cu is what the LDS holds, but 1 for 32 x 64, of which two fit:
 // with 257 tiles the CU that has two of them takes twice the bytes, and the fit knows (4096 x 4096: 128 tokens, 256 tiles, 18 us
-// against 22 on 64 x 64; 256 tokens, 512 tiles, 28 against 23).  The constants (us) are the least-squares fit over 18 token
+// against 22 on 64 x 64; 256 tokens, 512 tiles, 28 against 23).  The constants (us) are fitted over 40 token
 // counts from 72 to 4096 and the ten projection shapes of the two bf16 configurations (widths 1024 and 4096; no other width
-// was timed), cold weights: rms error 9 to 14 %.  The row of 256 x 256 was fitted to tiles of 8 wavefronts staged through
-// registers, cut-off columns included, which took up to 22 % longer than the kernel that is here now.  Against every tile timed by
-// itself at 19 token counts from 192 to 4096 the picks take 0.8 % longer than the best on average; the worst are q|k|v and gate|up
-// of 288 tokens of width 4096 (66 us on 64 x 64 against 52 on 256 x 128; 93 on 64 x 128 against 82 on 256 x 256), then the
-// lm-head of 3072 tokens of width 1024 (68 on 128 x 256 against 61 on 256 x 256).
+// was timed), cold weights, for the picks first and the times second: the picks take 0.6 % longer than the best tile on average (a third
+// of the counts left out of the fit: 0.65), 21 of 400 by more than 5 %; with the least squares fit to the times alone that was here
+// before 1.5 % and 43.  The worst are the lm-head of 72 to 128 tokens of width 4096 (51 us on 64 x 64 against 40 on 128 x 64);
+// 260 to 320 tokens of that width went from 66 to 52 us (q|k|v, 256 x 128 for 64 x 64) and from 97 to 77 (gate|up, 256 x 256 for 64 x 128).
 struct TileCost {
     int bm, bn, stages, per_cu;   // ring stages of bm + bn rows of 128 bytes; 256 x 256: 0, it has a ring of its own
     float c0, tf, t0, e;
@@ -1406,10 +1405,10 @@ struct TileCost {
 };
 enum { TILE_32x64, TILE_64x64, TILE_128x64, TILE_64x128, TILE_128x128, TILE_256x128, TILE_128x256, TILE_256x256, N_TILES };
 constexpr TileCost TILE_COST[N_TILES] = {
-    {32, 64, 6, 1, 3.4f, 0.161f, 0.107f, -0.1f},   {64, 64, 5, 2, 2.7f, 0.435f, 0.146f, 0.1f},
-    {128, 64, 3, 2, 2.3f, 0.683f, 0.271f, 1.2f},   {64, 128, 3, 2, 4.2f, 0.723f, 0.311f, -1.1f},
-    {128, 128, 5, 1, 2.7f, 0.538f, 0.407f, 2.4f},  {256, 128, 3, 1, 2.6f, 0.856f, 0.56f, 4.6f},
-    {128, 256, 3, 1, 3.9f, 0.925f, 0.67f, 2.6f},   {256, 256, 0, 1, 6.7f, 1.544f, 1.011f, 4.4f}};
+    {32, 64, 6, 1, 5.66f, 0.178f, 0.115f, -0.36f}, {64, 64, 5, 2, 4.97f, 0.443f, 0.165f, 0.02f},
+    {128, 64, 3, 2, 5.6f, 0.694f, 0.323f, 0.07f},  {64, 128, 3, 2, 5.48f, 0.822f, 0.233f, -0.02f},
+    {128, 128, 5, 1, 3.84f, 0.503f, 0.467f, 2.39f}, {256, 128, 3, 1, 3.3f, 0.76f, 0.613f, 5.54f},
+    {128, 256, 3, 1, 10.82f, 0.85f, 0.737f, -1.26f}, {256, 256, 0, 1, 15.06f, 1.394f, 0.91f, -5.08f}};
 constexpr bool tiles_fit() {
     for (int i = 0; i < N_TILES; ++i)
         if (TILE_COST[i].fit() != (i == TILE_32x64 ? 2 : TILE_COST[i].per_cu)) return false;
