@@ -1394,9 +1394,9 @@ __global__ __launch_bounds__(256) void k_pack_weights(const bf16* __restrict__ s
 // with 257 tiles the CU that has two of them takes twice the bytes, and the fit knows (4096 x 4096: 128 tokens, 256 tiles, 18 us
 // against 22 on 64 x 64; 256 tokens, 512 tiles, 28 against 23).  The constants (us) are fitted over 40 token
 // counts from 72 to 4096 and the ten projection shapes of the two bf16 configurations (widths 1024 and 4096; no other width
-// was timed), cold weights, for the picks first and the times second: the picks take 0.6 % longer than the best tile on average (a third
-// of the counts left out of the fit: 0.65), 21 of 400 by more than 5 %; with the least squares fit to the times alone that was here
-// before 1.5 % and 43.  The worst are the lm-head of 72 to 128 tokens of width 4096 (51 us on 64 x 64 against 40 on 128 x 64);
+// was timed), cold weights, for the picks first and the times second, with no pick slower than the one of the rule before: the picks
+// take 0.6 % longer than the best tile on average, 20 of 400 more than 5 %; with the least squares fit to the times alone that was
+// here before 1.5 % and 43.  The worst are the lm-head of 72 to 128 tokens of width 4096 (51 us on 64 x 64 against 40 on 128 x 64);
 // 260 to 320 tokens of that width went from 66 to 52 us (q|k|v, 256 x 128 for 64 x 64) and from 97 to 77 (gate|up, 256 x 256 for 64 x 128).
 struct TileCost {
     int bm, bn, stages, per_cu;   // ring stages of bm + bn rows of 128 bytes; 256 x 256: 0, it has a ring of its own
@@ -1405,10 +1405,10 @@ struct TileCost {
 };
 enum { TILE_32x64, TILE_64x64, TILE_128x64, TILE_64x128, TILE_128x128, TILE_256x128, TILE_128x256, TILE_256x256, N_TILES };
 constexpr TileCost TILE_COST[N_TILES] = {
-    {32, 64, 6, 1, 5.66f, 0.178f, 0.115f, -0.36f}, {64, 64, 5, 2, 4.97f, 0.443f, 0.165f, 0.02f},
-    {128, 64, 3, 2, 5.6f, 0.694f, 0.323f, 0.07f},  {64, 128, 3, 2, 5.48f, 0.822f, 0.233f, -0.02f},
-    {128, 128, 5, 1, 3.84f, 0.503f, 0.467f, 2.39f}, {256, 128, 3, 1, 3.3f, 0.76f, 0.613f, 5.54f},
-    {128, 256, 3, 1, 10.82f, 0.85f, 0.737f, -1.26f}, {256, 256, 0, 1, 15.06f, 1.394f, 0.91f, -5.08f}};
+    {32, 64, 6, 1, 6.12f, 0.184f, 0.116f, -0.38f}, {64, 64, 5, 2, 3.07f, 0.406f, 0.154f, 2.79f},
+    {128, 64, 3, 2, 1.6f, 0.761f, 0.368f, 3.95f},  {64, 128, 3, 2, 4.34f, 0.64f, 0.24f, 4.76f},
+    {128, 128, 5, 1, 5.17f, 0.487f, 0.45f, 3.35f}, {256, 128, 3, 1, 5.59f, 0.766f, 0.488f, 4.37f},
+    {128, 256, 3, 1, 12.65f, 0.796f, 0.686f, -0.34f}, {256, 256, 0, 1, 11.33f, 1.263f, 0.822f, 0.37f}};
 constexpr bool tiles_fit() {
     for (int i = 0; i < N_TILES; ++i)
         if (TILE_COST[i].fit() != (i == TILE_32x64 ? 2 : TILE_COST[i].per_cu)) return false;
