@@ -1154,10 +1154,10 @@ bool launch_accept(const DecideArgs& a, unsigned long long* sums, hipStream_t st
     // rejections: Eq. 1 without pooling, whose acceptance is 1 - TV(p, q), 0.8 to 0.3 in the workloads.  Unmarked positions
     // pay for it, so the gain depends on the acceptance a.  4 x 1024 x 16384, test + mask + draw in us, this / the test alone
     // and a draw that reads the marked rows again:
-    //   draft rows shared by 4 positions: radius 1: a = 0.62 92 / 117, 0.88 92 / 102, 0.96 92 / 81, 0.99 90 / 66;
-    //     radius 2: 0.62 93 / 118, 0.88 94 / 121, 0.96 94 / 103, 0.99 93 / 79; raster rule: 0.99 88 / 106;
-    //   a row each: radius 1: 0.64 113 / 146, 0.88 113 / 110, 0.99 113 / 68; radius 2: 0.88 115 / 149, 0.96 115 / 116.
-    // They cross at a = 0.92 (radius 1) and 0.975 (radius 2).  Not here: pooled and threshold tests, made to accept nearly
+    //   draft rows shared by 4 positions: radius 1: a = 0.38 90 / 111, 0.88 88 / 87, 0.96 88 / 73, 0.99 88 / 64;
+    //     radius 2: 0.38 89 / 111, 0.88 85 / 102, 0.96 85 / 85, 0.99 86 / 70;
+    //   a row each: radius 1: 0.62 104 / 136, 0.88 103 / 104, 0.96 103 / 77; radius 2: 0.62 104 / 139, 0.88 109 / 135, 0.96 109 / 95.
+    // They cross at a = 0.88 (radius 1) and 0.95 (radius 2).  Not here: pooled and threshold tests, made to accept nearly
     // everything (and the threshold reads no draft row); radius 0, which marks the rejected positions alone; draws from p,
     // which have little to re-read (guided, 2 x 1024, threshold rule: 65 / 62).
     if (sums && !a.p_probs && a.V <= 16384 && a.accept_mode == 0 && a.pool_k <= 1 && a.resample_mode != 2 && a.rho != 0) {
