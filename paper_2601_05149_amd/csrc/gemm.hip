@@ -1153,7 +1153,7 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
 // once per workgroup, 8 k-steps at a time, and every wavefront feeds its MFMAs from there (one 16-byte LDS read per
 // lane and token group); only the weights, contiguous KB blocks of the fragment-order copy, come through the memory
 // pipeline, 8 steps in flight per wavefront.  K is dealt to `ksplit` workgroups per column group; each leaves its sums
-// [M, 128] in `ksums`, and k_stream_finish adds the slices in index order and runs the epilogue (no float atomics:
+// [M, 128] in `ksums`, and k_stream_finish (out, down: the norm behind them) adds the slices in index order and runs the epilogue (no float atomics:
 // the result does not depend on which workgroup finishes first).  Gate|up and q|k|v are concatenations of their weight
 // matrices (`seg_rows` rows each) along the column axis.
 template <int MTB, int NW>
