@@ -1148,12 +1148,12 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
 
 // ---- 65 to 256 tokens with the weight copy in fragment order: the token operand goes through LDS ----
 // With several token groups the kernel above spends its time on the token operand: every workgroup (16 columns) reads
-// all of it through its vector L1, a KB per token group and KB of weights.  Here a workgroup owns 128 columns (a
-// wavefront 16 of them) and a slice of K: the slice's token operand, which arrives in fragment order, is copied to LDS
+// all of it through its vector L1, a KB per token group and KB of weights.  Here a workgroup owns 128 or 192 columns (a
+// wavefront 16 of them; run_gemv_shared's rule: 160 tokens of width 4096, gate|up 65 -> 48 us with 192) and a slice of K: the slice's token operand, which arrives in fragment order, is copied to LDS
 // once per workgroup, 8 k-steps at a time, and every wavefront feeds its MFMAs from there (one 16-byte LDS read per
 // lane and token group); only the weights, contiguous KB blocks of the fragment-order copy, come through the memory
 // pipeline, 8 steps in flight per wavefront.  K is dealt to `ksplit` workgroups per column group; each leaves its sums
-// [M, 128] in `ksums`, and k_stream_finish (out, down: the norm behind them) adds the slices in index order and runs the epilogue (no float atomics:
+// [M, its columns] in `ksums`, and k_stream_finish (out, down: the norm behind them) adds the slices in index order and runs the epilogue (no float atomics:
 // the result does not depend on which workgroup finishes first).  Gate|up and q|k|v are concatenations of their weight
 // matrices (`seg_rows` rows each) along the column axis.
 template <int MTB, int NW>
