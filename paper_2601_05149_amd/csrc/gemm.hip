@@ -28,7 +28,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __hip_bfloat16 bf16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3, EPI_SLICE = 4 };   // SLICE: sums of a slice of K, for the norm behind to add
+enum { EPI_QKV = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
 
 struct GemmArgs {
     const bf16* A;        // [M, K]
@@ -683,7 +683,6 @@ __global__ __launch_bounds__(256, 1) void k_gemm_256(const GemmArgs g) {
 // PAIRED (5 stages): loads go out for two K-steps at a time, every other step, both halves of a 256-byte row segment one
 // behind the other, where a row's next 128 bytes otherwise follow a whole step later: 128 x 128 tiles over K = 11008, 576
 // tokens 94 -> 87 us, 1024 tokens 111 -> 99; the smaller tiles, which keep fewer bytes in flight, lose by it.
-// EPI_SLICE (out, down): a workgroup takes a slice of K and stores its sums to g.ksums; the norm behind the projection adds the slices.
 template <int BM, int BN, int WGM, int WGN, int NS, int EPI, bool PAIRED>
 __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g) {
     constexpr int NW = WGM * WGN, TM = BM / WGM, TN = BN / WGN, MB = TM / 32, NB = TN / 32;
@@ -694,22 +693,14 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
     static_assert(EPI != EPI_SWIGLU || (NB % 2 == 0 && (TN / 2) % (8 * NW) == 0), "a load never straddles gate and up");
     static_assert((NS - 2) * LPS < 64 && NS >= 3, "the wait counts loads in 6 bits");
     static_assert(!PAIRED || NS == 5, "two pairs and the step between them");
-    constexpr bool SPLIT = EPI == EPI_SLICE;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // NS stages of [BM + BN][RB]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN, l32 = lane & 31, lh = lane >> 5;
     // one tile per workgroup; tiles to XCDs as in k_gemm_256 (the grid is a multiple of 8)
     constexpr int GW = 8;
-    const int tiles_m = (g.M + BM - 1) / BM, tiles = tiles_m * g.tiles_n, total = SPLIT ? tiles * g.ksplit : tiles, chunk = (total + 7) / 8;
-    const int loc = blockIdx.x >> 3, unit = (blockIdx.x & 7) * chunk + loc;
-    if (loc >= chunk || unit >= total) return;                          // uniform over the workgroup, before any barrier
-    int t = unit, k0 = 0, nk = g.K / 64;                                // the tile and its K-steps [k0, k0 + nk)
-    if constexpr (SPLIT) {
-        const int kw = unit / tiles, per = (nk + g.ksplit - 1) / g.ksplit;
-        t = unit - kw * tiles;
-        k0 = kw * per;
-        nk = nk - k0 < per ? nk - k0 : per;
-    }
+    const int tiles_m = (g.M + BM - 1) / BM, total = tiles_m * g.tiles_n, chunk = (total + 7) / 8;
+    const int loc = blockIdx.x >> 3, t = (blockIdx.x & 7) * chunk + loc;
+    if (loc >= chunk || t >= total) return;                             // uniform over the workgroup, before any barrier
     const int grp = t / (tiles_m * GW), rem = t - grp * tiles_m * GW;
     const int gw = g.tiles_n - grp * GW < GW ? g.tiles_n - grp * GW : GW;
     const int tile_n = g.tile_n0 + grp * GW + rem % gw, m0 = (rem / gw) * BM, n0 = tile_n * BN;
@@ -719,7 +710,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
     const int lrow = lane >> 3, lch = lane & 7;
     auto row_key = [](int r) { return (r >> 1) & 7; };
     uint32_t va[LA], vb[LB];
-    const rsrc_t rA = make_rsrc(g.A + (int64_t)m0 * g.K + k0 * 64, 0x7fffffff);
+    const rsrc_t rA = make_rsrc(g.A + (int64_t)m0 * g.K, 0x7fffffff);
     rsrc_t rW[2];
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
@@ -730,8 +721,8 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
         int which;
         const int base = b_row_src<EPI, BN, TN>(g, n0, tile_n, 0, which);
         const bf16* w0 = which == 0 ? g.W0 : which == 1 ? g.W1 : g.W2;
-        rW[0] = make_rsrc(w0 + (int64_t)base * g.K + k0 * 64, 0x7fffffff);
-        rW[1] = make_rsrc((EPI == EPI_SWIGLU ? g.W1 : w0) + (int64_t)base * g.K + k0 * 64, 0x7fffffff);
+        rW[0] = make_rsrc(w0 + (int64_t)base * g.K, 0x7fffffff);
+        rW[1] = make_rsrc((EPI == EPI_SWIGLU ? g.W1 : w0) + (int64_t)base * g.K, 0x7fffffff);
 #pragma unroll
         for (int i = 0; i < LB; ++i) {
             const int r = (i * NW + wave) * 8 + lrow;
@@ -751,6 +742,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rW[w], (lds_void*)(st + BM * RB + (j * NW + wave) * 1024), 16, (int)vb[j], kt * RB, 0, 0);
         }
     };
+    const int nk = g.K / 64;
     f32x16 acc[MB][NB];
 #pragma unroll
     for (int i = 0; i < MB; ++i)
@@ -877,14 +869,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, 1) void k_gemm_ring(const GemmArgs g
         }
     }
     mm(1);
-    if constexpr (SPLIT) {
-        GemmArgs gs = g;
-        gs.Cf = g.ksums + (int64_t)(unit / tiles) * g.M * g.N;
-        gs.parts = nullptr;
-        epilogue<EPI_LOGITS, BN, TM, TN, MB, NB>(gs, acc, m0, n0, tile_n, wm, wn, l32, lh);
-    } else {
-        epilogue<EPI, BN, TM, TN, MB, NB>(g, acc, m0, n0, tile_n, wm, wn, l32, lh);
-    }
+    epilogue<EPI, BN, TM, TN, MB, NB>(g, acc, m0, n0, tile_n, wm, wn, l32, lh);
 }
 
 // column tiles [tile_n0, tile_n0 + tiles_n)
@@ -1471,27 +1456,18 @@ void run_ring(GemmArgs g, hipStream_t st, int tile_n0 = 0, int tiles_n = 0) {
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds, &attr_state)) return;
     g.tiles_n = tiles_n ? tiles_n : (g.N + BN - 1) / BN;
     g.tile_n0 = tile_n0;
-    const int64_t total = (int64_t)((g.M + BM - 1) / BM) * g.tiles_n * (EPI == EPI_SLICE ? g.ksplit : 1);
+    const int64_t total = (int64_t)((g.M + BM - 1) / BM) * g.tiles_n;
     hipLaunchKernelGGL(kern, dim3((unsigned)((total + 7) / 8 * 8)), dim3(WGM * WGN * 64), lds, st, g);
 }
 
-// returns whether the softmax parts were written (LOGITS, wavefront tiles of 128 whole columns), or the K slices that the norm
-// behind the projection has to add (RESID)
+// returns whether the softmax parts were written (LOGITS, wavefront tiles of 128 whole columns), or how many K slices a streamed
+// launch left for the norm behind it to add (RESID)
 template <int EPI>
 int dispatch(GemmArgs g, const StreamMode& sm, hipStream_t st) {
     g.stream = sm.stream; g.w_frag = sm.w_frag; g.ksums = sm.ksums; g.ksum_floats = sm.ksum_floats;
     *sm.ran = -1;
     if (g.stream) {   // a handful of tokens: stream the weights (A is in fragment order)
         return run_gemv<EPI>(g, st);
-    }
-    if constexpr (EPI == EPI_RESID) {
-        if (sm.tile < 0 && g.ksums && splits_resid(g.M, g.N, g.K)) {
-            g.ksplit = RING_SPLIT;
-            *sm.ran = g.M <= 128 ? TILE_128x64 : TILE_128x128;
-            if (g.M <= 128) run_ring<TILE_128x64, 2, 2, EPI_SLICE>(g, st);
-            else run_ring<TILE_128x128, 2, 2, EPI_SLICE, true>(g, st);
-            return RING_SPLIT;
-        }
     }
     const int tile = sm.tile >= 0 && sm.tile < N_TILES && has_tile<EPI>(g, sm.tile) ? sm.tile : choose_tile<EPI>(g);
     *sm.ran = tile;

@@ -200,10 +200,7 @@ bool enqueue_forward(mulo_ctx* c, mulo_kv* kv, int B, int L, int P, const int32_
     // The slices of at most 64 tokens (4 x 64 rows at most) go to the attention's partial results (512 rows of d and more), which
     // are done with before the out projection and not begun before the next layer's attention: the norm in between takes them.
     static_assert(4 * STREAM_MAX_TOKENS <= 512, "rows of slices");
-    // Those of the tiled kernels go to the step's logits, which nothing holds until the lm-head writes them, where a row of logits is as
-    // long as the slices of a row.
-    float* const tile_sums = V >= RING_SPLIT * d ? c->logits : nullptr;
-    auto sm = [&](int projection) { return StreamMode{frag, wfrag, M <= STREAM_MAX_TOKENS ? c->attn_part : frag ? c->ksums : tile_sums, c->ksum_floats, c->tile, &c->tiles_ran[projection]}; };
+    auto sm = [&](int projection) { return StreamMode{frag, wfrag, M <= STREAM_MAX_TOKENS ? c->attn_part : c->ksums, c->ksum_floats, c->tile, &c->tiles_ran[projection]}; };
     Slices add{nullptr, 0};   // what the last residual projection left for the norm behind it to add
     { PROF(MULO_PROF_NORM_EMBED); launch_embed(c->w.embed, dt, tok, emb, up ? *up : StepTokens{}, c->x, M, d, V, st); }
     for (int l = 0; l < m.n_layers; ++l) {

@@ -56,15 +56,6 @@ inline int stream_resid_split(int K) {
     const int ks = K / 32 / 64;
     return ks < 1 ? 1 : ks > 4 ? 4 : ks;
 }
-// Out and down projections of 65 to 192 tokens that do not stream: K in RING_SPLIT slices, where the weights are long enough to be
-// what the launch spends its time on (24 MB).  Without slices only small tiles have a workgroup for every CU, and those fetch more
-// bytes per product; with them 128 x 128 tiles (128 x 64 up to 128 tokens) do.  Us, whole K -> slices, 186 tokens: 4096 x 4096
-// 20.5 -> 14.6, 4096 x 11008 55 -> 33, the norms behind them 5.1 -> 6.5; 8 layers of width 4096: 65 tokens 1187 -> 1120, 96 1334 ->
-// 1193, 128 1391 -> 1278, 160 1518 -> 1412, 192 1612 -> 1442.  From 193 tokens on a row's bits do not depend on the rows beside it.
-constexpr int RING_SPLIT = 4, RING_SPLIT_TOKENS = 192;
-inline bool splits_resid(int M, int N, int K) {
-    return M > STREAM_MAX_TOKENS && M <= RING_SPLIT_TOKENS && K >= 4096 && (int64_t)N * K >= (12 << 20);
-}
 // floats of partial sums such a launch of M tokens over `ncols` output columns (gate|up: 2 f, q|k|v: 3 d) needs
 inline size_t stream_ksum_floats(int M, int ncols, int K) { return (size_t)stream_ksplit(ncols, K) * M * ncols; }
 __host__ __device__ inline int64_t frag_index(int m, int k, int K) {   // in elements; runs of 8 k stay contiguous

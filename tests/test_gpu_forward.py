@@ -633,10 +633,10 @@ def test_streamed_sums_do_not_depend_on_the_columns_a_workgroup_takes(d, nh, f, 
 
 
 @pytest.mark.parametrize("L", [65, 128, 129, 192])
-def test_sliced_residual_projections_of_a_few_hundred_tokens(L):
-    """65 to 192 tokens whose out and down weights are long (3072 x 4096 and more) deal K to several workgroups (65 and 128 tokens
-    on 128 x 64 tiles, 129 and 192 on 128 x 128, the last K slice shorter): logits, residual stream and cache rows against the oracle,
-    and against the same rows of a launch of 193 tokens, which takes K whole."""
+def test_a_few_hundred_tokens_with_long_residual_projections(L):
+    """65 to 192 tokens, out and down of 3072 x 3072 and 3072 x 4160: logits, residual stream and cache rows against the oracle, and
+    against the same rows of a launch of 193 tokens: the same bits from 129 tokens on (up to 128 the attention adds its keys over
+    other tiles)."""
     nh, dh, f, V = 24, 128, 4160, 12 * 1024
     m = dict(n_layers=1, d_model=nh * dh, n_heads=nh, head_dim=dh, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
     w, P, S = G.make_weights(m, seed=33), 5, 200
@@ -656,10 +656,62 @@ def test_sliced_residual_projections_of_a_few_hundred_tokens(L):
     dr, du = pair(m, w, cos, sin, 1, S)
     for t in (dr, du):
         t.forward(pre, 0)
-    check_bf16_logits("%d tokens, K in slices" % L, z, dr.forward(blk[:, :L], P).numpy(), du.forward(blk[:, :L], P).numpy())
-    assert torch.equal(kv[0][0, 0, :, P:P + L], k1) and torch.equal(kv[1][0, 0, :, :, P:P + L], v1)   # layer 0: nothing sliced in front of them
-    # one layer: the two differ by the order of float32 sums of 4160 products, and by what a norm's bf16 roundings make of that (a
-    # flipped one moves a row's products by 2^-8 of one term): 2^-7 of a residual's size bounds both
+    check_bf16_logits("%d tokens" % L, z, dr.forward(blk[:, :L], P).numpy(), du.forward(blk[:, :L], P).numpy())
+    assert torch.equal(kv[0][0, 0, :, P:P + L], k1) and torch.equal(kv[1][0, 0, :, :, P:P + L], v1)
+    if L > 128:
+        assert torch.equal(xs, x[:L]) and np.array_equal(z, whole[:, :L])
+    # up to 128 tokens the attention's sums differ in float32, and by what bf16 roundings make of that (a flipped one moves a row's
+    # products by 2^-8 of one term): 2^-7 of a residual's size bounds both
     err = (xs - x[:L]).abs().max() / x[:L].abs().max()
-    say("  residual stream, slices against whole K: %.3g of the largest" % float(err))
+    say("  residual stream against 193 tokens: %.3g of the largest" % float(err))
     assert float(err) <= 2.0 ** -7 and np.abs(z - whole[:, :L]).max() <= 2.0 ** -5 * np.abs(whole).max()
+
+
+_RANDOM_WEIGHTS = {}
+
+
+def _random_device_weights(m):
+    """Weights N(0, 0.02) made on the device, norms of gain 1."""
+    key = tuple(sorted((k, str(v)) for k, v in m.items()))
+    if key not in _RANDOM_WEIGHTS:
+        _RANDOM_WEIGHTS.clear()
+        nl, d, f, V = m["n_layers"], m["d_model"], m["d_ffn"], m["vocab"]
+        g = torch.Generator(device=DEV).manual_seed(1)
+        shapes = dict(embed=(V, d), wq=(nl, d, d), wk=(nl, d, d), wv=(nl, d, d), wo=(nl, d, d), w_gate=(nl, f, d), w_up=(nl, f, d),
+                      w_down=(nl, d, f), lm_head=(V, d))
+        w = {k: torch.empty(s, dtype=torch.bfloat16, device=DEV).normal_(0.0, 0.02, generator=g) for k, s in shapes.items()}
+        w.update({k: torch.ones(s, dtype=torch.bfloat16, device=DEV) for k, s in (("attn_norm", (nl, d)), ("ffn_norm", (nl, d)), ("final_norm", (d,)))})
+        _RANDOM_WEIGHTS[key] = w
+    return _RANDOM_WEIGHTS[key]
+
+
+def _same_bits_alone_and_in_batches(m, w, L, batches, P=8, copy=False, blocks=(256,)):
+    """Sequence 0's logits, residual stream and cache rows in launches of `batches` sequences, in a context for each of `blocks`: the
+    same bits."""
+    nh, dh, d = m["n_heads"], m["head_dim"], m["d_model"]
+    g = torch.Generator(device=DEV).manual_seed(L)
+    pre = [torch.randn(m["n_layers"], 1, *s, generator=g, device=DEV).to(torch.bfloat16) for s in ((nh, P, dh), (nh, dh, P))]
+    toks = G.uniform_tokens((max(batches), L), m["vocab"], 41, tag=L)
+    ref = None
+    for block in blocks:
+        for B in batches if block == blocks[-1] else batches[:1]:
+            ctx, _, _ = make_ctx_from_device(m, w, B if block < blocks[-1] else max(batches), 264, block, stream_copy=copy)
+            kv = mulo.alloc_kv(ctx, DEV)
+            kv[0][:, :, :, :P], kv[1][:, :, :, :, :P] = pre
+            z = gpu_forward(ctx, kv, toks[:B], P)
+            x = torch.empty(B * L, d, device=DEV)
+            mulo.mulo_workspace_read(ctx, mulo.MULO_WS_RESIDUAL, x)
+            torch.cuda.synchronize()
+            got = (torch.tensor(z[0]), x[:L].clone(), kv[0][:, 0, :, P:P + L].clone(), kv[1][:, 0, :, :, P:P + L].clone())
+            ref = ref or got
+            for name, a, b in zip(("logits", "residual stream", "keys", "values"), got, ref):
+                assert torch.equal(a, b), (name, B, block)
+
+
+@pytest.mark.parametrize("L,batches", [(65, (1, 2, 3)), (96, (1, 2, 3)), (128, (1, 2)), (161, (1, 2)), (192, (1, 2))])
+def test_wide_projections_have_the_same_bits_alone_and_in_a_batch(L, batches):
+    """Width 4096, 4160 feed-forward columns, two layers (the second one's cache rows see the first one's out and down): a block of 65 to
+    192 tokens alone and as the first of two or three sequences (130 to 384 tokens) adds every sum in the same order."""
+    d, nh, f, V = 4096, 32, 4160, 16384
+    m = dict(n_layers=2, d_model=d, n_heads=nh, head_dim=128, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
+    _same_bits_alone_and_in_batches(m, _random_device_weights(m), L, batches)
