@@ -49,7 +49,6 @@ struct GemmArgs {
     bool w_frag;          // weight-streaming launches: W0 .. W2 point at copies in fragment order
     float* ksums;         // more than STREAM_SHARED_MIN_TOKENS tokens: sums of the K slices [ksplit, M, columns]
     int ksplit;           // set by the launcher
-    int64_t ksum_floats;  // what ksums holds
     RopeArgs ra;
 };
 
@@ -57,11 +56,11 @@ struct GemmArgs {
 // compile-time loop: the body sees its index as a constant, so accumulator arrays
 // indexed by it stay in registers whatever the unroller decides
 template <class F, int... Is>
-__host__ __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, Is...>) {
+__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, Is...>) {
     (f(std::integral_constant<int, Is>{}), ...);
 }
 template <int N, class F>
-__host__ __device__ __forceinline__ void static_for(F&& f) {
+__device__ __forceinline__ void static_for(F&& f) {
     static_for_impl(static_cast<F&&>(f), std::make_integer_sequence<int, N>{});
 }
 
@@ -1133,23 +1132,24 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
 
 // ---- 65 to 256 tokens with the weight copy in fragment order: the token operand goes through LDS ----
 // With several token groups the kernel above spends its time on the token operand: every workgroup (16 columns) reads
-// all of it through its vector L1, a KB per token group and KB of weights.  Here a workgroup owns 128 or 192 columns (a
-// wavefront 16 of them; run_gemv_shared's rule: 160 tokens of width 4096, gate|up 65 -> 48 us with 192) and a slice of K: the slice's token operand, which arrives in fragment order, is copied to LDS
+// all of it through its vector L1, a KB per token group and KB of weights.  Here a workgroup owns 128 columns (a
+// wavefront 16 of them) and a slice of K: the slice's token operand, which arrives in fragment order, is copied to LDS
 // once per workgroup, 8 k-steps at a time, and every wavefront feeds its MFMAs from there (one 16-byte LDS read per
 // lane and token group); only the weights, contiguous KB blocks of the fragment-order copy, come through the memory
 // pipeline, 8 steps in flight per wavefront.  K is dealt to `ksplit` workgroups per column group; each leaves its sums
-// [M, its columns] in `ksums`, and k_stream_finish (out, down: the norm behind them) adds the slices in index order and runs the epilogue (no float atomics:
-// the result does not depend on which workgroup finishes first).  Gate|up and q|k|v are concatenations of their weight
+// [M, 128] in `ksums`, and k_stream_finish (out, down: the norm behind them) adds the slices in index order and runs the
+// epilogue (no float atomics: the result does not depend on which workgroup finishes first).  Gate|up and q|k|v are concatenations of their weight
 // matrices (`seg_rows` rows each) along the column axis.
-template <int MTB, int NW>
-__global__ __launch_bounds__(NW * 64) void k_gemv_shared(const GemmArgs g, int ncols, int seg_rows, int ncg) {
-    constexpr int CH = 8;                              // k-steps per LDS chunk = weight steps in flight per wavefront
-    constexpr int PIECES = (CH * MTB + NW - 1) / NW;   // 16-byte pieces of a chunk per thread
-    constexpr bool RAGGED = CH * MTB % NW != 0;        // the last pieces are not everybody's
+// Workgroups of 12 wavefronts and 192 columns were faster at 65 to 160 tokens of width 4096 (gate|up 65 -> 48 us), but by more K slices
+// than 161 tokens have, so that a row's sums followed the rows beside it.
+template <int MTB>
+__global__ __launch_bounds__(512) void k_gemv_shared(const GemmArgs g, int ncols, int seg_rows, int ncg) {
+    constexpr int CH = 8;                         // k-steps per LDS chunk = weight steps in flight per wavefront
+    constexpr int PIECES = CH * MTB * 64 / 512;   // 16-byte pieces of a chunk per thread
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // fragment (group t, step j) at (t CH + j) KB
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cg = blockIdx.x % ncg, kw = blockIdx.x / ncg;   // neighbouring workgroups share a K slice of the token operand
-    const int n_w = cg * (NW * 16) + wave * 16;               // this wavefront's first column
+    const int n_w = cg * 128 + wave * 16;                     // this wavefront's first column
     const int steps = g.K / 32, per = (steps + g.ksplit - 1) / g.ksplit;
     const int s0 = kw * per, s1 = s0 + per < steps ? s0 + per : steps;
     const int n_groups = (g.M + 15) >> 4;
@@ -1176,7 +1176,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemv_shared(const GemmArgs g, int n
     auto xload = [&](int sc0) {
 #pragma unroll
         for (int i = 0; i < PIECES; ++i) {
-            const int p = tid + i * (NW * 64), t = p / (CH * 64), j = (p / 64) % CH;
+            const int p = tid + i * 512, t = p / (CH * 64), j = (p / 64) % CH;
             xr[i] = zero;
             if (t < n_groups && sc0 + j < s1)
                 xr[i] = *reinterpret_cast<const u32x4*>(g.A + ((int64_t)t * steps + sc0 + j) * 512 + (p & 63) * 8);
@@ -1184,8 +1184,7 @@ __global__ __launch_bounds__(NW * 64) void k_gemv_shared(const GemmArgs g, int n
     };
     auto xstore = [&]() {
 #pragma unroll
-        for (int i = 0; i < PIECES; ++i)
-            if (!RAGGED || i + 1 < PIECES || wave + i * NW < CH * MTB) *reinterpret_cast<u32x4*>(smem + (size_t)(tid + i * (NW * 64)) * 16) = xr[i];
+        for (int i = 0; i < PIECES; ++i) *reinterpret_cast<u32x4*>(smem + (size_t)(tid + i * 512) * 16) = xr[i];
     };
     auto chunk = [&](int sc0, auto req) {
 #pragma unroll
@@ -1260,31 +1259,29 @@ __global__ __launch_bounds__(256) void k_stream_finish(const GemmArgs g, int nco
 template <int EPI>
 int run_gemv_shared(GemmArgs g, hipStream_t st) {
     const int ncols = g.N, seg_rows = EPI == EPI_QKV ? g.d : EPI == EPI_SWIGLU ? g.N / 2 : g.N;
-    // 12 wavefronts (192 columns) where that gives more CUs a workgroup or a shorter slice, as the bytes a CU takes in say it for ten
-    // token groups: a KB per group and per wavefront and k-step.  Its slices must fit the scratch.
-    auto kb = [&](int nw, int ks) { return (g.K / 32 + ks - 1) / ks * (10 + nw) * (((ncols + nw * 16 - 1) / (nw * 16) * ks + 255) / 256); };
-    const int ks8 = stream_ksplit(ncols, g.K, 128), ks12 = stream_ksplit(ncols, g.K, 192);
-    constexpr int WIDE_GROUPS = 10;   // more do not fit the registers of 12 wavefronts
-    const int mt = (g.M + 15) / 16;
-    const bool wide = mt <= WIDE_GROUPS && kb(12, ks12) < kb(8, ks8) && (int64_t)ks12 * g.M * ncols <= g.ksum_floats;
-    const int nw = wide ? 12 : 8, ncg = (ncols + nw * 16 - 1) / (nw * 16);
-    g.ksplit = wide ? ks12 : ks8;
+    const int ncg = (ncols + 127) / 128;
+    g.ksplit = stream_ksplit(ncols, g.K);
     const dim3 grid(ncg * g.ksplit);
     auto launch = [&](auto kern, int mtb) {
         static int attr_state = 0;   // one per kernel instantiation (the lambda's call operator is a template)
         if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), mtb * 8 * 1024, &attr_state)) return;
-        hipLaunchKernelGGL(kern, grid, dim3(nw * 64), (size_t)mtb * 8 * 1024, st, g, ncols, seg_rows, ncg);
+        hipLaunchKernelGGL(kern, grid, dim3(512), (size_t)mtb * 8 * 1024, st, g, ncols, seg_rows, ncg);
     };
-    auto launch_mt = [&](auto mtc) {
-        constexpr int MT = decltype(mtc)::value;
-        if constexpr (MT <= WIDE_GROUPS) if (wide) { launch(k_gemv_shared<MT, 12>, MT); return; }
-        launch(k_gemv_shared<MT, 8>, MT);
-    };
-    // one instantiation per number of token groups: LDS reads and MFMAs follow it
-    static_for<13>([&](auto ic) {
-        constexpr int MT = decltype(ic)::value + 4;
-        if (mt == MT || (MT == 4 && mt < 4) || (MT == 16 && mt > 16)) launch_mt(std::integral_constant<int, MT>{});
-    });
+    switch ((g.M + 15) / 16) {   // one instantiation per number of token groups: LDS reads and MFMAs follow it
+        case 1: case 2: case 3: case 4: launch(k_gemv_shared<4>, 4); break;
+        case 5: launch(k_gemv_shared<5>, 5); break;
+        case 6: launch(k_gemv_shared<6>, 6); break;
+        case 7: launch(k_gemv_shared<7>, 7); break;
+        case 8: launch(k_gemv_shared<8>, 8); break;
+        case 9: launch(k_gemv_shared<9>, 9); break;
+        case 10: launch(k_gemv_shared<10>, 10); break;
+        case 11: launch(k_gemv_shared<11>, 11); break;
+        case 12: launch(k_gemv_shared<12>, 12); break;
+        case 13: launch(k_gemv_shared<13>, 13); break;
+        case 14: launch(k_gemv_shared<14>, 14); break;
+        case 15: launch(k_gemv_shared<15>, 15); break;
+        default: launch(k_gemv_shared<16>, 16); break;
+    }
     if constexpr (EPI != EPI_RESID) {
         const int cols = EPI == EPI_SWIGLU ? ncols / 2 : ncols;
         const int64_t threads = (int64_t)g.M * (cols / 2);
@@ -1464,7 +1461,7 @@ void run_ring(GemmArgs g, hipStream_t st, int tile_n0 = 0, int tiles_n = 0) {
 // launch left for the norm behind it to add (RESID)
 template <int EPI>
 int dispatch(GemmArgs g, const StreamMode& sm, hipStream_t st) {
-    g.stream = sm.stream; g.w_frag = sm.w_frag; g.ksums = sm.ksums; g.ksum_floats = sm.ksum_floats;
+    g.stream = sm.stream; g.w_frag = sm.w_frag; g.ksums = sm.ksums;
     *sm.ran = -1;
     if (g.stream) {   // a handful of tokens: stream the weights (A is in fragment order)
         return run_gemv<EPI>(g, st);

@@ -38,11 +38,12 @@ constexpr int STREAM_MAX_TOKENS_COPY = 256;
 // and, for the tests of the tiled kernels, which tile a launch that does not stream runs on:
 //   tile    index into the tile table (gemm.hip), taken where the projection has it; -1: the rule's choice
 //   ran     host variable that receives the tile (-1: streamed)
-struct StreamMode { bool stream, w_frag; float* ksums; int64_t ksum_floats; int tile; int32_t* ran; };
-// K slices per column group (128 or 192 columns) in the LDS-sharing kernel: as many as keep the launch within one round of 256
-// workgroups, at most 8, at least 8 k-steps each.
-inline int stream_ksplit(int ncols, int K, int group = 128) {
-    const int groups = (ncols + group - 1) / group, steps = K / 32;
+struct StreamMode { bool stream, w_frag; float* ksums; int tile; int32_t* ran; };
+// K slices per 128-column group in the LDS-sharing kernel: as many as keep the launch within one round of 256
+// workgroups, at most 8, at least 8 k-steps each.  A function of the projection's shape only, so the order of every
+// sum is fixed by the model.
+inline int stream_ksplit(int ncols, int K) {
+    const int groups = (ncols + 127) / 128, steps = K / 32;
     int ks = 256 / groups;
     ks = ks < 1 ? 1 : (ks > 8 ? 8 : ks);
     const int most = steps / 8 > 1 ? steps / 8 : 1;

@@ -715,3 +715,30 @@ def test_wide_projections_have_the_same_bits_alone_and_in_a_batch(L, batches):
     d, nh, f, V = 4096, 32, 4160, 16384
     m = dict(n_layers=2, d_model=d, n_heads=nh, head_dim=128, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
     _same_bits_alone_and_in_batches(m, _random_device_weights(m), L, batches)
+
+
+@pytest.mark.parametrize("L,batches", [(65, (1, 2, 3)), (100, (1, 2)), (128, (1, 2))])
+@pytest.mark.parametrize("d,nh,f,V", [(1408, 11, 4160, 12308), (768, 6, 8256, 16388)])
+def test_streamed_blocks_have_the_same_bits_alone_in_a_batch_and_in_any_context(d, nh, f, V, L, batches):
+    """65 to 256 tokens with the weight copy, out and down in up to eight K slices that the norm adds: the deal is the projection's
+    alone, so a block gets the same bits alone, in a batch of up to 256 tokens, and in a context that holds nothing but the block
+    (the smallest scratch).  The lm-heads end inside a group of 128 columns."""
+    m = dict(n_layers=2, d_model=d, n_heads=nh, head_dim=d // nh, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
+    _same_bits_alone_and_in_batches(m, _random_device_weights(m), L, batches, copy=True, blocks=((L + 3) // 4 * 4, 256))
+
+
+@pytest.mark.parametrize("L", [65, 81, 128, 145, 160, 161, 256])
+def test_streamed_blocks_of_a_few_hundred_tokens_against_the_oracle(L):
+    """The same model and weight copy: five to sixteen token groups, the last one ragged or whole, down (4160 products, eight slices, the last
+    one shorter) added by the final norm, against the oracle."""
+    d, nh, f, V = 1408, 11, 4160, 12308
+    m = dict(n_layers=1, d_model=d, n_heads=nh, head_dim=d // nh, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
+    w, P, S = G.make_weights(m, seed=35), 9, 272
+    ctx, cos, sin = make_ctx(m, w, 1, S, 256, stream_copy=True)
+    kv = mulo.alloc_kv(ctx, DEV)
+    pre, blk = G.uniform_tokens((1, P), V, 35, tag=0), G.uniform_tokens((1, L), V, 35, tag=1)
+    gpu_forward(ctx, kv, pre, 0)
+    dr, du = pair(m, w, cos, sin, 1, S)
+    for t in (dr, du):
+        t.forward(pre, 0)
+    check_bf16_logits("%d streamed tokens" % L, gpu_forward(ctx, kv, blk, P), dr.forward(blk, P).numpy(), du.forward(blk, P).numpy())
