@@ -93,6 +93,8 @@ template <> struct Four<__hip_bfloat16> { typedef __attribute__((ext_vector_type
 // token of one sequence over 8 layers (17 norms) 964 - 966 -> 939 - 942 us, of four 1181 - 1184 -> 1158 - 1159 (three pairs of runs).
 // NS > 0: x first takes the sums of up to NS slices of a projection's K (slices past the last weigh nothing), requested
 // with the row.  It saves the launch that would add them, and its round trip over x.
+// The sum of squares is written out in fused operations: left to the compiler, which of two squares it rounds first differed
+// between these instantiations, and the row's scale in its last bit with them.
 template <typename T, int NV4, int NS>
 __global__ __launch_bounds__(TPB) void k_rmsnorm(float* __restrict__ x, const T* __restrict__ gain, T* __restrict__ out, int d,
                                                  float eps, int frag, const float* __restrict__ sums, int n_slices) {
@@ -123,7 +125,7 @@ __global__ __launch_bounds__(TPB) void k_rmsnorm(float* __restrict__ x, const T*
                     reinterpret_cast<float4*>(xr)[idx] = v[i];
                 }
             }
-            ss += (v[i].x * v[i].x + v[i].y * v[i].y) + (v[i].z * v[i].z + v[i].w * v[i].w);
+            ss += fmaf(v[i].y, v[i].y, __fmul_rn(v[i].x, v[i].x)) + fmaf(v[i].z, v[i].z, __fmul_rn(v[i].w, v[i].w));
         }
     } else {
         for (int c = tid; c < d; c += TPB) {
@@ -134,7 +136,7 @@ __global__ __launch_bounds__(TPB) void k_rmsnorm(float* __restrict__ x, const T*
                 t += s;
                 xr[c] = t;   // read again below by the thread that wrote it
             }
-            ss += t * t;
+            ss = fmaf(t, t, ss);
         }
     }
     ss = wave_sum(ss);

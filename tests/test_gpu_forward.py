@@ -742,3 +742,23 @@ def test_streamed_blocks_of_a_few_hundred_tokens_against_the_oracle(L):
     for t in (dr, du):
         t.forward(pre, 0)
     check_bf16_logits("%d streamed tokens" % L, gpu_forward(ctx, kv, blk, P), dr.forward(blk, P).numpy(), du.forward(blk, P).numpy())
+
+
+@pytest.mark.parametrize("d,nh,f", [(1024, 8, 4096), (1408, 11, 4160), (3072, 24, 4096)])
+@pytest.mark.parametrize("copy", [False, True])
+def test_a_norm_gives_the_same_bits_with_slices_to_add_and_without(d, nh, f, copy):
+    """Weights of zero for down: whatever its K slices, they add nothing, so the norm behind it sees the same residual stream in every
+    launch.  Four sequences of 16 tokens together (64 tokens: several slices from 4096 products on) and each alone (16: none): the
+    same logits, bit for bit.  A scale that differs in its last bit shows in one bf16 value of 2^15 or fewer: 1024 rows, three norms
+    each.  (The embedding's own values are of 8 bits, whose squares are exact: out adds the others.)"""
+    V = 512
+    m = dict(n_layers=3, d_model=d, n_heads=nh, head_dim=d // nh, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
+    w = dict(_random_device_weights(m))
+    w["w_down"] = torch.zeros_like(w["w_down"])
+    ctx, _, _ = make_ctx_from_device(m, w, 4, 16, 16, stream_copy=copy)
+    kv = mulo.alloc_kv(ctx, DEV)
+    for seed in range(16):
+        emb = torch.randn(4, 16, d, generator=torch.Generator(device=DEV).manual_seed(seed), device=DEV).to(torch.bfloat16)
+        z = gpu_forward(ctx, kv, np.zeros((4, 16), np.int32), 0, emb)
+        for b in range(4):
+            assert np.array_equal(gpu_forward(ctx, kv, np.zeros((1, 16), np.int32), 0, emb[b:b + 1].contiguous())[0], z[b]), (seed, b)
