@@ -972,19 +972,9 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
     const int from_lane = (4 * l16 + q) << 2;   // byte address of the source lane for ds_bpermute
     const int cols = EPI == EPI_SWIGLU ? g.N / 2 : g.N, nblocks = (cols + COLS - 1) / COLS;
     const int steps = g.K / 32;
-    int wg = blockIdx.x, kw = 0, sl0 = 0, sl1 = steps;   // this workgroup's columns and its slice of K (out, down: g.ksplit slices)
-    if constexpr (EPI == EPI_RESID && MT > 1) {
-        if (g.ksplit > 1) {
-            const int groups = (nblocks + NBLK - 1) / NBLK, per_slice = (steps + g.ksplit - 1) / g.ksplit;
-            kw = wg / groups;
-            wg -= kw * groups;
-            sl0 = kw * per_slice;
-            sl1 = sl0 + per_slice < steps ? sl0 + per_slice : steps;
-        }
-    }
-    const int blk0 = wg * NBLK;            // first block of columns (gate|up: of feed-forward columns)
-    const int per = (sl1 - sl0 + 7) / 8;
-    const int s0 = sl0 + wave * per, s1 = s0 + per < sl1 ? s0 + per : sl1;
+    const int blk0 = blockIdx.x * NBLK;    // first block of columns (gate|up: of feed-forward columns)
+    const int per = (steps + 7) / 8;
+    const int s0 = wave * per, s1 = s0 + per < steps ? s0 + per : steps;
 
     // weight row(s) this lane fetches; with a copy in fragment order (WFRAG) the KB of (16-row block, step) is
     // contiguous in the MFMA's own lane order: lane l owns its bytes [16 l, 16 l + 16), no exchange afterwards
@@ -1122,34 +1112,33 @@ __global__ __launch_bounds__(512) void k_gemv_bf16(const GemmArgs g) {
                 v1[e] = sum1;
             }
             const int n = (blk0 + nb) * COLS + 4 * q + 2 * pr;
-            if (EPI == EPI_RESID && MT > 1 && g.ksplit > 1)
-                *reinterpret_cast<float2*>(g.ksums + ((int64_t)kw * g.M + m) * g.N + n) = make_float2(v0[0], v0[1]);
-            else
-                stream_epilogue<EPI>(g, m, n, v0, v1);
+            stream_epilogue<EPI>(g, m, n, v0, v1);
         }
     });
 }
 
-// ---- 65 to 256 tokens with the weight copy in fragment order: the token operand goes through LDS ----
+// ---- 65 to 256 tokens with the weight copy in fragment order, out and down of 17 to 64 tokens: the token operand goes through LDS ----
 // With several token groups the kernel above spends its time on the token operand: every workgroup (16 columns) reads
 // all of it through its vector L1, a KB per token group and KB of weights.  Here a workgroup owns 128 columns (a
-// wavefront 16 of them) and a slice of K: the slice's token operand, which arrives in fragment order, is copied to LDS
-// once per workgroup, 8 k-steps at a time, and every wavefront feeds its MFMAs from there (one 16-byte LDS read per
-// lane and token group); only the weights, contiguous KB blocks of the fragment-order copy, come through the memory
+// wavefront 16 of them; 64 columns and four wavefronts: run_gemv's rule) and a slice of K: the slice's token operand, which arrives
+// in fragment order, is copied to LDS once per workgroup, 8 k-steps at a time, and every wavefront feeds its MFMAs from there (one
+// 16-byte LDS read per lane and token group); only the weights, contiguous KB blocks of the fragment-order copy (or, up to 64 tokens,
+// rows as they come, exchanged between lanes as above), come through the memory
 // pipeline, 8 steps in flight per wavefront.  K is dealt to `ksplit` workgroups per column group; each leaves its sums
-// [M, 128] in `ksums`, and k_stream_finish (out, down: the norm behind them) adds the slices in index order and runs the
-// epilogue (no float atomics: the result does not depend on which workgroup finishes first).  Gate|up and q|k|v are concatenations of their weight
-// matrices (`seg_rows` rows each) along the column axis.
+// [M, its columns] in `ksums`, and k_stream_finish (out, down: the norm behind them) adds the slices in index order and runs the
+// epilogue (no float atomics: the result does not depend on which workgroup finishes first).  Gate|up and q|k|v are concatenations of
+// their weight matrices (`seg_rows` rows each) along the column axis.
 // Workgroups of 12 wavefronts and 192 columns were faster at 65 to 160 tokens of width 4096 (gate|up 65 -> 48 us), but by more K slices
 // than 161 tokens have, so that a row's sums followed the rows beside it.
-template <int MTB>
-__global__ __launch_bounds__(512) void k_gemv_shared(const GemmArgs g, int ncols, int seg_rows, int ncg) {
+template <int MTB, bool WFRAG, int NW>
+__global__ __launch_bounds__(NW * 64) void k_gemv_shared(const GemmArgs g, int ncols, int seg_rows, int ncg) {
     constexpr int CH = 8;                         // k-steps per LDS chunk = weight steps in flight per wavefront
-    constexpr int PIECES = CH * MTB * 64 / 512;   // 16-byte pieces of a chunk per thread
+    constexpr int PIECES = CH * MTB / NW;         // 16-byte pieces of a chunk per thread
+    static_assert(CH % NW == 0, "whole pieces");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // fragment (group t, step j) at (t CH + j) KB
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cg = blockIdx.x % ncg, kw = blockIdx.x / ncg;   // neighbouring workgroups share a K slice of the token operand
-    const int n_w = cg * 128 + wave * 16;                     // this wavefront's first column
+    const int n_w = cg * (NW * 16) + wave * 16;                     // this wavefront's first column
     const int steps = g.K / 32, per = (steps + g.ksplit - 1) / g.ksplit;
     const int s0 = kw * per, s1 = s0 + per < steps ? s0 + per : steps;
     const int n_groups = (g.M + 15) >> 4;
@@ -1159,16 +1148,29 @@ __global__ __launch_bounds__(512) void k_gemv_shared(const GemmArgs g, int ncols
         const int last = (ncols - 1) / 16 * 16;               // a wavefront past the last column re-reads the last block
         const int n_c = n_w < last ? n_w : last;
         const int seg = n_c / seg_rows;                        // 16 columns never straddle two matrices (seg_rows % 16 == 0)
-        w = (seg == 0 ? g.W0 : seg == 1 ? g.W1 : g.W2) + (int64_t)((n_c - seg * seg_rows) / 16) * steps * 512 + lane * 8;
+        const bf16* const base = seg == 0 ? g.W0 : seg == 1 ? g.W1 : g.W2;
+        if constexpr (WFRAG) {
+            w = base + (int64_t)((n_c - seg * seg_rows) / 16) * steps * 512 + lane * 8;
+        } else {                                               // chunk lane % 4 of row lane / 4, as in k_gemv_bf16
+            const int r = n_c - seg * seg_rows + (lane >> 2);
+            w = base + (int64_t)(r < seg_rows ? r : seg_rows - 1) * g.K + (lane & 3) * 8;
+        }
     }
+    const int from_lane = (4 * (lane & 15) + (lane >> 4)) << 2;
     f32x4v acc[MTB];
 #pragma unroll
     for (int t = 0; t < MTB; ++t) acc[t] = f32x4v{0.f, 0.f, 0.f, 0.f};
     const u32x4 zero = {0u, 0u, 0u, 0u};
     u32x4 wv[CH], xr[PIECES];
     auto request = [&](int u, int s) {
-        const int sc = s < steps ? s : steps - 1;
-        wv[u] = *reinterpret_cast<const u32x4*>(w + (int64_t)sc * 512);
+        const int sc = s < s1 ? s : s1 - 1;
+        wv[u] = *reinterpret_cast<const u32x4*>(w + (int64_t)sc * (WFRAG ? 512 : 32));
+    };
+    auto to_mfma_order = [&](u32x4 v) {
+        if constexpr (!WFRAG)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = (uint32_t)__builtin_amdgcn_ds_bpermute(from_lane, (int)v[i]);
+        return v;
     };
     // chunk of steps [sc0, sc0 + CH): piece p = ((t CH + j) 64 + lane position); steps past the slice and token groups
     // that do not exist are zeros (tokens past M inside the last group are whatever the buffer holds: they only reach
@@ -1176,7 +1178,7 @@ __global__ __launch_bounds__(512) void k_gemv_shared(const GemmArgs g, int ncols
     auto xload = [&](int sc0) {
 #pragma unroll
         for (int i = 0; i < PIECES; ++i) {
-            const int p = tid + i * 512, t = p / (CH * 64), j = (p / 64) % CH;
+            const int p = tid + i * (NW * 64), t = p / (CH * 64), j = (p / 64) % CH;
             xr[i] = zero;
             if (t < n_groups && sc0 + j < s1)
                 xr[i] = *reinterpret_cast<const u32x4*>(g.A + ((int64_t)t * steps + sc0 + j) * 512 + (p & 63) * 8);
@@ -1184,12 +1186,12 @@ __global__ __launch_bounds__(512) void k_gemv_shared(const GemmArgs g, int ncols
     };
     auto xstore = [&]() {
 #pragma unroll
-        for (int i = 0; i < PIECES; ++i) *reinterpret_cast<u32x4*>(smem + (size_t)(tid + i * 512) * 16) = xr[i];
+        for (int i = 0; i < PIECES; ++i) *reinterpret_cast<u32x4*>(smem + (size_t)(tid + i * (NW * 64)) * 16) = xr[i];
     };
     auto chunk = [&](int sc0, auto req) {
 #pragma unroll
         for (int u = 0; u < CH; ++u) {
-            const bf16x8 wf = __builtin_bit_cast(bf16x8, wv[u]);
+            const bf16x8 wf = __builtin_bit_cast(bf16x8, to_mfma_order(wv[u]));
             if constexpr (decltype(req)::value) request(u, sc0 + CH + u);
 #pragma unroll
             for (int t = 0; t < MTB; ++t) {
@@ -1256,31 +1258,34 @@ __global__ __launch_bounds__(256) void k_stream_finish(const GemmArgs g, int nco
     stream_epilogue<EPI>(g, m, n, v0, v1);
 }
 
+// the sums of g.ksplit slices of K over `ncols` columns into g.ksums; WFRAG: the weights are in fragment order, NW: wavefronts a workgroup
+template <int MTB, bool WFRAG, int NW>
+void launch_gemv_shared(const GemmArgs& g, int ncols, int seg_rows, hipStream_t st) {
+    auto kern = k_gemv_shared<MTB, WFRAG, NW>;
+    static int attr_state = 0;
+    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), MTB * 8 * 1024, &attr_state)) return;
+    const int ncg = (ncols + NW * 16 - 1) / (NW * 16);
+    hipLaunchKernelGGL(kern, dim3(ncg * g.ksplit), dim3(NW * 64), (size_t)MTB * 8 * 1024, st, g, ncols, seg_rows, ncg);
+}
+
 template <int EPI>
 int run_gemv_shared(GemmArgs g, hipStream_t st) {
     const int ncols = g.N, seg_rows = EPI == EPI_QKV ? g.d : EPI == EPI_SWIGLU ? g.N / 2 : g.N;
-    const int ncg = (ncols + 127) / 128;
     g.ksplit = stream_ksplit(ncols, g.K);
-    const dim3 grid(ncg * g.ksplit);
-    auto launch = [&](auto kern, int mtb) {
-        static int attr_state = 0;   // one per kernel instantiation (the lambda's call operator is a template)
-        if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), mtb * 8 * 1024, &attr_state)) return;
-        hipLaunchKernelGGL(kern, grid, dim3(512), (size_t)mtb * 8 * 1024, st, g, ncols, seg_rows, ncg);
-    };
     switch ((g.M + 15) / 16) {   // one instantiation per number of token groups: LDS reads and MFMAs follow it
-        case 1: case 2: case 3: case 4: launch(k_gemv_shared<4>, 4); break;
-        case 5: launch(k_gemv_shared<5>, 5); break;
-        case 6: launch(k_gemv_shared<6>, 6); break;
-        case 7: launch(k_gemv_shared<7>, 7); break;
-        case 8: launch(k_gemv_shared<8>, 8); break;
-        case 9: launch(k_gemv_shared<9>, 9); break;
-        case 10: launch(k_gemv_shared<10>, 10); break;
-        case 11: launch(k_gemv_shared<11>, 11); break;
-        case 12: launch(k_gemv_shared<12>, 12); break;
-        case 13: launch(k_gemv_shared<13>, 13); break;
-        case 14: launch(k_gemv_shared<14>, 14); break;
-        case 15: launch(k_gemv_shared<15>, 15); break;
-        default: launch(k_gemv_shared<16>, 16); break;
+        case 1: case 2: case 3: case 4: launch_gemv_shared<4, true, 8>(g, ncols, seg_rows, st); break;
+        case 5: launch_gemv_shared<5, true, 8>(g, ncols, seg_rows, st); break;
+        case 6: launch_gemv_shared<6, true, 8>(g, ncols, seg_rows, st); break;
+        case 7: launch_gemv_shared<7, true, 8>(g, ncols, seg_rows, st); break;
+        case 8: launch_gemv_shared<8, true, 8>(g, ncols, seg_rows, st); break;
+        case 9: launch_gemv_shared<9, true, 8>(g, ncols, seg_rows, st); break;
+        case 10: launch_gemv_shared<10, true, 8>(g, ncols, seg_rows, st); break;
+        case 11: launch_gemv_shared<11, true, 8>(g, ncols, seg_rows, st); break;
+        case 12: launch_gemv_shared<12, true, 8>(g, ncols, seg_rows, st); break;
+        case 13: launch_gemv_shared<13, true, 8>(g, ncols, seg_rows, st); break;
+        case 14: launch_gemv_shared<14, true, 8>(g, ncols, seg_rows, st); break;
+        case 15: launch_gemv_shared<15, true, 8>(g, ncols, seg_rows, st); break;
+        default: launch_gemv_shared<16, true, 8>(g, ncols, seg_rows, st); break;
     }
     if constexpr (EPI != EPI_RESID) {
         const int cols = EPI == EPI_SWIGLU ? ncols / 2 : ncols;
@@ -1294,12 +1299,11 @@ int run_gemv_shared(GemmArgs g, hipStream_t st) {
 // Column blocks a workgroup of k_gemv_bf16 takes, with mt > 1 token groups: every workgroup fetches the whole token operand, a KB per
 // group and k-step, next to a KB per column block, and a CU takes in about 50 GB/s of the two, so the fewest KB per CU are taken
 // (several blocks where that still leaves one round of workgroups).  Per launch, one block -> the rule's choice, 52 tokens of width
-// 4096 from the weight copy, us: q|k|v 43.4 -> 29.4 (3 blocks), gate|up 48.1 -> 34.9 (3), lm-head 48.7 -> 34 (4); out and down have
-// 256 blocks and keep one.
-inline int gemv_blocks(int blocks, int mt, int na, int ksplit) {
+// 4096 from the weight copy, us: q|k|v 43.4 -> 29.4 (3 blocks), gate|up 48.1 -> 34.9 (3), lm-head 48.7 -> 34 (4).
+inline int gemv_blocks(int blocks, int mt, int na) {
     int best = 1, best_cost = 0x7fffffff;
     for (int nb = 1; nb <= (na == 2 ? 3 : 4); ++nb) {
-        const int wgs = (blocks + nb - 1) / nb * ksplit, rounds = (wgs + cu_count() - 1) / cu_count(), cost = rounds * (nb * na + mt);
+        const int wgs = (blocks + nb - 1) / nb, rounds = (wgs + cu_count() - 1) / cu_count(), cost = rounds * (nb * na + mt);
         if (cost < best_cost) { best = nb; best_cost = cost; }
     }
     return best;
@@ -1327,12 +1331,30 @@ int run_gemv(GemmArgs g, hipStream_t st) {
             return 0;
         }
     }
-    g.ksplit = EPI == EPI_RESID && g.ksums && mt > 1 ? stream_resid_split(g.K) : 1;
+    if constexpr (EPI == EPI_RESID) {
+        if (mt > 1 && g.K >= STREAM_RESID_K) {
+            g.ksplit = STREAM_RESID_SLICES;
+            // 64 columns a workgroup where 128 leave CUs idle, and for weights as they come, whose lane exchanges want the wavefronts
+            // in more workgroups (52 tokens, 8 layers of width 2048 614 -> 580 us, from the copy 544 -> 527; width 4096 1133 -> 1120);
+            // 128 of the copy's where those fill the chip (977 -> 968)
+            const bool wide = g.w_frag && (g.N + 127) / 128 * g.ksplit >= cu_count();
+            auto launch = [&](auto mtc) {
+                constexpr int MT = decltype(mtc)::value;
+                if (wide) launch_gemv_shared<MT, true, 8>(g, g.N, g.N, st);
+                else if (g.w_frag) launch_gemv_shared<MT, true, 4>(g, g.N, g.N, st);
+                else launch_gemv_shared<MT, false, 4>(g, g.N, g.N, st);
+            };
+            if (mt == 2) launch(std::integral_constant<int, 2>{});
+            else if (mt == 3) launch(std::integral_constant<int, 3>{});
+            else launch(std::integral_constant<int, 4>{});
+            return g.ksplit;
+        }
+    }
     const int blocks = (cols + 15) / 16;
-    const int nb = mt == 1 ? 1 : gemv_blocks(blocks, mt, EPI == EPI_SWIGLU ? 2 : 1, g.ksplit);
+    const int nb = mt == 1 ? 1 : gemv_blocks(blocks, mt, EPI == EPI_SWIGLU ? 2 : 1);
     auto launch = [&](auto mtc, auto nbc) {
         constexpr int MT = decltype(mtc)::value, NB = decltype(nbc)::value;
-        const dim3 grid((blocks + NB - 1) / NB * g.ksplit);
+        const dim3 grid((blocks + NB - 1) / NB);
         if (g.w_frag) hipLaunchKernelGGL((k_gemv_bf16<EPI, MT, NB, true>), grid, dim3(512), 0, st, g);
         else hipLaunchKernelGGL((k_gemv_bf16<EPI, MT, NB, false>), grid, dim3(512), 0, st, g);
     };
@@ -1349,7 +1371,7 @@ int run_gemv(GemmArgs g, hipStream_t st) {
     else if (nb == 2) with_groups(std::integral_constant<int, 2>{});
     else if (nb == 3) with_groups(std::integral_constant<int, 3>{});
     else if constexpr (EPI != EPI_SWIGLU) with_groups(std::integral_constant<int, 4>{});
-    return g.ksplit > 1 ? g.ksplit : 0;
+    return 0;
 }
 
 // one thread per 16-byte piece of the copy: piece p of block (nb, s) is lane p % 64

@@ -196,9 +196,9 @@ bool enqueue_forward(mulo_ctx* c, mulo_kv* kv, int B, int L, int P, const int32_
     const bool has_copy = c->pk_wq != nullptr;
     const bool frag = dt == MULO_BF16 && M <= (has_copy ? STREAM_MAX_TOKENS_COPY : STREAM_MAX_TOKENS);
     const bool wfrag = frag && has_copy;
-    // The slices of at most 64 tokens (4 x 64 rows at most) go to the attention's partial results (512 rows of d and more), which
+    // The slices of at most 64 tokens (8 x 64 rows at most) go to the attention's partial results (512 rows of d and more), which
     // are done with before the out projection and not begun before the next layer's attention: the norm in between takes them.
-    static_assert(4 * STREAM_MAX_TOKENS <= 512, "rows of slices");
+    static_assert(STREAM_RESID_SLICES * STREAM_MAX_TOKENS <= 512, "rows of slices");
     auto sm = [&](int projection) { return StreamMode{frag, wfrag, M <= STREAM_MAX_TOKENS ? c->attn_part : c->ksums, c->tile, &c->tiles_ran[projection]}; };
     Slices add{nullptr, 0};   // what the last residual projection left for the norm behind it to add
     { PROF(MULO_PROF_NORM_EMBED); launch_embed(c->w.embed, dt, tok, emb, up ? *up : StepTokens{}, c->x, M, d, V, st); }

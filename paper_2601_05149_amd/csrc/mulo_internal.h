@@ -34,7 +34,7 @@ constexpr int STREAM_MAX_TOKENS_COPY = 256;
 // How a launch of few tokens runs its projections (decided once per forward, the same for every kernel of it):
 //   stream  the token operands are in fragment order and the projections run in the weight-streaming kernels
 //   w_frag  the weight pointers are the context's copies in fragment order
-//   ksums   scratch for the sums of the K slices when the launch streams (stream_ksum_floats; stream_resid_split(K) [M, d] up to 64 tokens)
+//   ksums   scratch for the sums of the K slices when the launch streams (stream_ksum_floats; STREAM_RESID_SLICES [M, d] up to 64 tokens)
 // and, for the tests of the tiled kernels, which tile a launch that does not stream runs on:
 //   tile    index into the tile table (gemm.hip), taken where the projection has it; -1: the rule's choice
 //   ran     host variable that receives the tile (-1: streamed)
@@ -49,14 +49,13 @@ inline int stream_ksplit(int ncols, int K) {
     const int most = steps / 8 > 1 ? steps / 8 : 1;
     return ks > most ? most : ks;
 }
-// K slices of the out and down projections of 17 to STREAM_MAX_TOKENS tokens, 64 k-steps or more each: with them a workgroup takes
-// several column blocks and fetches the token operand of its slice alone, and the norm behind the projection adds the slices.
-// 52 tokens, from the copy, us: 4096 x 4096 13.2 -> 11.7, 4096 x 11008 32.8 -> 25.4, the norms 5.1 -> 6.2.  One group of tokens loses
-// by it (4096 x 11008: 22 -> 26, from the copy 19.6 -> 20.7: four times the workgroups, a quarter of the steps each).
-inline int stream_resid_split(int K) {
-    const int ks = K / 32 / 64;
-    return ks < 1 ? 1 : ks > 4 ? 4 : ks;
-}
+// Out and down projections of 17 to STREAM_MAX_TOKENS tokens whose sums are STREAM_RESID_K long or longer: the eight shares of K that
+// k_gemv_bf16 deals to the wavefronts of a workgroup go to a workgroup each (k_gemv_shared), which shares the token operand of its
+// slice among 64 or 128 columns, and the norm behind adds the eight in the order that kernel adds them in: the same bits as up to 16
+// tokens.  52 tokens, us: 4096 x 4096 17.7 -> 13.8, from the copy 16.2 -> 12.9, 4096 x 11008 38.6 -> 26.6 and 36.4 -> 23.9, the norms
+// 6.4 -> 8.5; 4096 x 1024 15.7 -> 8.9.  Shorter sums were not timed at enough widths to draw the line there.  One group of tokens loses by
+// slices (4096 x 11008: 22 -> 26, from the copy 19.6 -> 20.7, with four of them).
+constexpr int STREAM_RESID_SLICES = 8, STREAM_RESID_K = 4096;
 // floats of partial sums such a launch of M tokens over `ncols` output columns (gate|up: 2 f, q|k|v: 3 d) needs
 inline size_t stream_ksum_floats(int M, int ncols, int K) { return (size_t)stream_ksplit(ncols, K) * M * ncols; }
 __host__ __device__ inline int64_t frag_index(int m, int k, int K) {   // in elements; runs of 8 k stay contiguous

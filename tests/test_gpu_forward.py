@@ -601,12 +601,12 @@ def test_forward_few_tokens_keeps_its_operands_in_fragment_order(B, L, copy):
 
 @pytest.mark.parametrize("d,nh,f,V", [
     (1408, 11, 4160, 12308),   # q|k|v 264 blocks of 16 columns: two a workgroup; gate|up 260 (halves for one token group); lm-head 770, a ragged last one
-    (768, 6, 8256, 16388),     # gate|up 516 blocks: two and three; lm-head 1025: a workgroup's last blocks lie past the end; down: 258 steps in 4 slices
+    (768, 6, 8256, 16388),     # gate|up 516 blocks: two and three; lm-head 1025: a workgroup's last blocks lie past the end; down: 258 steps in 8 slices
 ])
 def test_streamed_sums_do_not_depend_on_the_columns_a_workgroup_takes(d, nh, f, V):
-    """Blocks of 17, 40 and 64 tokens (two to four token groups: other column blocks per workgroup; K of 4096 and more in slices
-    that the norm adds), with the weight copy and without: the rows they share are the same bits, those of 64 tokens are the
-    oracle's.  One group, which deals K in one slice: the same cache rows, and logits within the oracle's bound."""
+    """Blocks of 5 to 64 tokens (one to four token groups: other column blocks per workgroup; from two groups on, K of 4096 and more in
+    slices that the norm adds), with the weight copy and without: the rows they share are the same bits, those of 64 tokens are the
+    oracle's."""
     m = dict(n_layers=1, d_model=d, n_heads=nh, head_dim=d // nh, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
     w, P, S = G.make_weights(m, seed=31), 9, 80
     pre, blk = G.uniform_tokens((1, P), V, 31, tag=0), G.uniform_tokens((1, 64), V, 31, tag=1)
@@ -615,7 +615,7 @@ def test_streamed_sums_do_not_depend_on_the_columns_a_workgroup_takes(d, nh, f, 
         ctx, cos, sin = make_ctx(m, w, 1, S, 64, stream_copy=copy)
         kv = mulo.alloc_kv(ctx, DEV)
         gpu_forward(ctx, kv, pre, 0)
-        for L in (64, 40, 17, 16):
+        for L in (64, 48, 40, 32, 17, 16, 5):
             z = gpu_forward(ctx, kv, blk[:, :L], P)
             if ref is None:
                 dr, du = pair(m, w, cos, sin, 1, S)
@@ -625,10 +625,7 @@ def test_streamed_sums_do_not_depend_on_the_columns_a_workgroup_takes(d, nh, f, 
                 check_bf16_logits("64 streamed tokens, width %d" % d, z, zr, zu)
                 ref = z
                 k1, v1 = kv[0][0, 0, :, P:P + 64].clone(), kv[1][0, 0, :, :, P:P + 64].clone()
-            if L > 16:
-                assert np.array_equal(z, ref[:, :L]), (copy, L)
-            else:
-                check_bf16_logits("%d streamed tokens, width %d" % (L, d), z, zr[:, :L], zu[:, :L])
+            assert np.array_equal(z, ref[:, :L]), (copy, L)
             assert torch.equal(kv[0][0, 0, :, P:P + L], k1[:, :L]) and torch.equal(kv[1][0, 0, :, :, P:P + L], v1[:, :, :L]), (copy, L)
 
 
@@ -762,3 +759,24 @@ def test_a_norm_gives_the_same_bits_with_slices_to_add_and_without(d, nh, f, cop
         z = gpu_forward(ctx, kv, np.zeros((4, 16), np.int32), 0, emb)
         for b in range(4):
             assert np.array_equal(gpu_forward(ctx, kv, np.zeros((1, 16), np.int32), 0, emb[b:b + 1].contiguous())[0], z[b]), (seed, b)
+
+
+@pytest.mark.parametrize("d,nh,f", [(4096, 32, 4096), (2048, 16, 8192), (4224, 33, 4160), (8320, 65, 4096)])
+@pytest.mark.parametrize("copy", [False, True])
+def test_a_row_has_the_same_bits_in_every_streamed_block(d, nh, f, copy):
+    """Out and down in slices in workgroups of 128 columns (the copy of widths that fill the chip) and of 64, one slice shorter than the
+    others or as long, the norm over up to eight 16-byte pieces a thread and over longer rows: four sequences of 16 tokens
+    together, three, two and each alone (no slices).  The logits and the cache rows of two layers, bit for bit."""
+    V = 1024
+    m = dict(n_layers=2, d_model=d, n_heads=nh, head_dim=d // nh, d_ffn=f, vocab=V, dtype="bf16", rms_eps=1e-5)
+    ctx, _, _ = make_ctx_from_device(m, _random_device_weights(m), 4, 32, 16, stream_copy=copy)
+    kv = mulo.alloc_kv(ctx, DEV)
+    toks = G.uniform_tokens((4, 16), V, 43, tag=d)
+    z = gpu_forward(ctx, kv, toks, 0)
+    k4, v4 = kv[0].clone(), kv[1].clone()
+    for B in (3, 2):
+        assert np.array_equal(gpu_forward(ctx, kv, toks[:B], 0), z[:B]), B
+        assert torch.equal(kv[0][:, :B, :, :16], k4[:, :B, :, :16]) and torch.equal(kv[1][:, :B, :, :, :16], v4[:, :B, :, :, :16]), B
+    for b in range(4):
+        assert np.array_equal(gpu_forward(ctx, kv, toks[b:b + 1], 0)[0], z[b]), b
+        assert torch.equal(kv[0][:, 0, :, :16], k4[:, b, :, :16]) and torch.equal(kv[1][:, 0, :, :, :16], v4[:, b, :, :, :16]), b
