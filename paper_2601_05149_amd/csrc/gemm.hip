@@ -67,6 +67,11 @@ __device__ __forceinline__ void static_for(F&& f) {
 // g * sigmoid(g) with the hardware reciprocal (1 ulp; the product is rounded to bf16 right after)
 __device__ __forceinline__ float silu(float g) { return g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)); }
 
+// Rotary on an adjacent pair, in one order of fused operations: left to the compiler, which product of the second it rounds first
+// differed between instantiations (and with it the last bit of some keys, between 32 and 64 streamed tokens)
+__device__ __forceinline__ float rotate0(float x0, float x1, float cs, float sn) { return fmaf(x0, cs, -__fmul_rn(x1, sn)); }
+__device__ __forceinline__ float rotate1(float x0, float x1, float cs, float sn) { return fmaf(x1, cs, __fmul_rn(x0, sn)); }
+
 // Source of weight-tile row nl (fixed over the K loop) for each fused problem: row index, and which of the
 // two weight matrices (0: W0, 1: W1) it belongs to.
 template <int EPI, int BN, int TN>
@@ -272,8 +277,8 @@ __device__ __forceinline__ void epilogue(const GemmArgs& g, f32x16 (&acc)[MB][NB
                             bf16x8s o;
 #pragma unroll
                             for (int pr = 0; pr < 4; ++pr) {
-                                o[2 * pr] = (__bf16)(v[2 * pr] * cs[pr] - v[2 * pr + 1] * sn[pr]);
-                                o[2 * pr + 1] = (__bf16)(v[2 * pr] * sn[pr] + v[2 * pr + 1] * cs[pr]);
+                                o[2 * pr] = (__bf16)rotate0(v[2 * pr], v[2 * pr + 1], cs[pr], sn[pr]);
+                                o[2 * pr + 1] = (__bf16)rotate1(v[2 * pr], v[2 * pr + 1], cs[pr], sn[pr]);
                             }
                             bf16* dst;
                             if (seg == 0) {
@@ -464,8 +469,8 @@ __device__ __forceinline__ void epilogue_qkv(const GemmArgs& g, const f32x16 (&a
                 bf16x8s o;
 #pragma unroll
                 for (int pr = 0; pr < 4; ++pr) {
-                    o[2 * pr] = (__bf16)(v[2 * pr] * cs_[pr] - v[2 * pr + 1] * sn_[pr]);
-                    o[2 * pr + 1] = (__bf16)(v[2 * pr] * sn_[pr] + v[2 * pr + 1] * cs_[pr]);
+                    o[2 * pr] = (__bf16)rotate0(v[2 * pr], v[2 * pr + 1], cs_[pr], sn_[pr]);
+                    o[2 * pr + 1] = (__bf16)rotate1(v[2 * pr], v[2 * pr + 1], cs_[pr], sn_[pr]);
                 }
                 if (rw[h & 1][t].pos >= 0) *reinterpret_cast<bf16x8s*>(dst + (int64_t)rw[h & 1][t].row * dh) = o;
             }
@@ -915,8 +920,8 @@ __device__ __forceinline__ void stream_epilogue(const GemmArgs& g, int m, int n,
                 const int64_t hb = ((int64_t)g.ra.layer * g.ra.max_batch + pl.bc) * g.ra.n_heads + hd;
                 dst = g.kc + (hb * g.ra.max_seq + pos) * dh + cc;
             }
-            dst[0] = __float2bfloat16(v0[0] * cs - v0[1] * sn);
-            dst[1] = __float2bfloat16(v0[0] * sn + v0[1] * cs);
+            dst[0] = __float2bfloat16(rotate0(v0[0], v0[1], cs, sn));
+            dst[1] = __float2bfloat16(rotate1(v0[0], v0[1], cs, sn));
         } else {   // V: transposed cache
             const int nv = n - 2 * g.d;
 #pragma unroll
