@@ -47,7 +47,8 @@ struct GemmArgs {
     int n_parts;
     bool stream;          // A is in fragment order: the launch runs in the weight-streaming kernels
     bool w_frag;          // weight-streaming launches: W0 .. W2 point at copies in fragment order
-    float* ksums;         // more than STREAM_SHARED_MIN_TOKENS tokens: sums of the K slices [ksplit, M, columns]
+    float* ksums;         // k_gemv_shared: sums of the K slices [ksplit, M, columns]
+    int64_t ksum_floats;  // what ksums holds
     int ksplit;           // set by the launcher
     RopeArgs ra;
 };
@@ -1263,35 +1264,43 @@ __global__ __launch_bounds__(256) void k_stream_finish(const GemmArgs g, int nco
     stream_epilogue<EPI>(g, m, n, v0, v1);
 }
 
-// the sums of g.ksplit slices of K over `ncols` columns into g.ksums; WFRAG: the weights are in fragment order, NW: wavefronts a workgroup
+// the sums of g.ksplit slices of K over `ncols` columns into g.ksums; WFRAG: the weights are in fragment order, NW: wavefronts a
+// workgroup.  False, with the error noted, where it could not be launched: the sums are not to be read.
 template <int MTB, bool WFRAG, int NW>
-void launch_gemv_shared(const GemmArgs& g, int ncols, int seg_rows, hipStream_t st) {
+bool launch_gemv_shared(const GemmArgs& g, int ncols, int seg_rows, hipStream_t st) {
     auto kern = k_gemv_shared<MTB, WFRAG, NW>;
     static int attr_state = 0;
-    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), MTB * 8 * 1024, &attr_state)) return;
+    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), MTB * 8 * 1024, &attr_state)) return false;
+    if ((int64_t)g.ksplit * g.M * ncols > g.ksum_floats) {   // no room for the slices
+        note_hip_error(hipErrorInvalidValue);
+        return false;
+    }
     const int ncg = (ncols + NW * 16 - 1) / (NW * 16);
     hipLaunchKernelGGL(kern, dim3(ncg * g.ksplit), dim3(NW * 64), (size_t)MTB * 8 * 1024, st, g, ncols, seg_rows, ncg);
+    return true;
 }
 
 template <int EPI>
 int run_gemv_shared(GemmArgs g, hipStream_t st) {
     const int ncols = g.N, seg_rows = EPI == EPI_QKV ? g.d : EPI == EPI_SWIGLU ? g.N / 2 : g.N;
-    g.ksplit = stream_ksplit(ncols, g.K);
+    g.ksplit = stream_slices(g.M, ncols, g.K, true, EPI == EPI_RESID);
+    bool ok;
     switch ((g.M + 15) / 16) {   // one instantiation per number of token groups: LDS reads and MFMAs follow it
-        case 1: case 2: case 3: case 4: launch_gemv_shared<4, true, 8>(g, ncols, seg_rows, st); break;
-        case 5: launch_gemv_shared<5, true, 8>(g, ncols, seg_rows, st); break;
-        case 6: launch_gemv_shared<6, true, 8>(g, ncols, seg_rows, st); break;
-        case 7: launch_gemv_shared<7, true, 8>(g, ncols, seg_rows, st); break;
-        case 8: launch_gemv_shared<8, true, 8>(g, ncols, seg_rows, st); break;
-        case 9: launch_gemv_shared<9, true, 8>(g, ncols, seg_rows, st); break;
-        case 10: launch_gemv_shared<10, true, 8>(g, ncols, seg_rows, st); break;
-        case 11: launch_gemv_shared<11, true, 8>(g, ncols, seg_rows, st); break;
-        case 12: launch_gemv_shared<12, true, 8>(g, ncols, seg_rows, st); break;
-        case 13: launch_gemv_shared<13, true, 8>(g, ncols, seg_rows, st); break;
-        case 14: launch_gemv_shared<14, true, 8>(g, ncols, seg_rows, st); break;
-        case 15: launch_gemv_shared<15, true, 8>(g, ncols, seg_rows, st); break;
-        default: launch_gemv_shared<16, true, 8>(g, ncols, seg_rows, st); break;
+        case 1: case 2: case 3: case 4: ok = launch_gemv_shared<4, true, 8>(g, ncols, seg_rows, st); break;
+        case 5: ok = launch_gemv_shared<5, true, 8>(g, ncols, seg_rows, st); break;
+        case 6: ok = launch_gemv_shared<6, true, 8>(g, ncols, seg_rows, st); break;
+        case 7: ok = launch_gemv_shared<7, true, 8>(g, ncols, seg_rows, st); break;
+        case 8: ok = launch_gemv_shared<8, true, 8>(g, ncols, seg_rows, st); break;
+        case 9: ok = launch_gemv_shared<9, true, 8>(g, ncols, seg_rows, st); break;
+        case 10: ok = launch_gemv_shared<10, true, 8>(g, ncols, seg_rows, st); break;
+        case 11: ok = launch_gemv_shared<11, true, 8>(g, ncols, seg_rows, st); break;
+        case 12: ok = launch_gemv_shared<12, true, 8>(g, ncols, seg_rows, st); break;
+        case 13: ok = launch_gemv_shared<13, true, 8>(g, ncols, seg_rows, st); break;
+        case 14: ok = launch_gemv_shared<14, true, 8>(g, ncols, seg_rows, st); break;
+        case 15: ok = launch_gemv_shared<15, true, 8>(g, ncols, seg_rows, st); break;
+        default: ok = launch_gemv_shared<16, true, 8>(g, ncols, seg_rows, st); break;
     }
+    if (!ok) return 0;
     if constexpr (EPI != EPI_RESID) {
         const int cols = EPI == EPI_SWIGLU ? ncols / 2 : ncols;
         const int64_t threads = (int64_t)g.M * (cols / 2);
@@ -1317,7 +1326,7 @@ inline int gemv_blocks(int blocks, int mt, int na) {
 // returns how many slices of K the projection left in g.ksums (RESID: for the norm behind it; 0: the sums are where they belong)
 template <int EPI>
 int run_gemv(GemmArgs g, hipStream_t st) {
-    if (g.M > STREAM_SHARED_MIN_TOKENS && g.w_frag && g.ksums)     // several token groups: the token operand goes through LDS
+    if (shares_tokens(g.M, g.w_frag))   // several token groups: the token operand goes through LDS
         return run_gemv_shared<EPI>(g, st);
     if (g.M > STREAM_MAX_TOKENS) {   // the kernel below holds four token groups
         note_hip_error(hipErrorInvalidValue);
@@ -1337,22 +1346,21 @@ int run_gemv(GemmArgs g, hipStream_t st) {
         }
     }
     if constexpr (EPI == EPI_RESID) {
-        if (mt > 1 && g.K >= STREAM_RESID_K) {
-            g.ksplit = STREAM_RESID_SLICES;
+        g.ksplit = stream_slices(g.M, g.N, g.K, g.w_frag, true);
+        if (g.ksplit) {
             // 64 columns a workgroup where 128 leave CUs idle, and for weights as they come, whose lane exchanges want the wavefronts
             // in more workgroups (52 tokens, 8 layers of width 2048 614 -> 580 us, from the copy 544 -> 527; width 4096 1133 -> 1120);
             // 128 of the copy's where those fill the chip (977 -> 968)
             const bool wide = g.w_frag && (g.N + 127) / 128 * g.ksplit >= cu_count();
             auto launch = [&](auto mtc) {
                 constexpr int MT = decltype(mtc)::value;
-                if (wide) launch_gemv_shared<MT, true, 8>(g, g.N, g.N, st);
-                else if (g.w_frag) launch_gemv_shared<MT, true, 4>(g, g.N, g.N, st);
-                else launch_gemv_shared<MT, false, 4>(g, g.N, g.N, st);
+                if (wide) return launch_gemv_shared<MT, true, 8>(g, g.N, g.N, st);
+                else if (g.w_frag) return launch_gemv_shared<MT, true, 4>(g, g.N, g.N, st);
+                else return launch_gemv_shared<MT, false, 4>(g, g.N, g.N, st);
             };
-            if (mt == 2) launch(std::integral_constant<int, 2>{});
-            else if (mt == 3) launch(std::integral_constant<int, 3>{});
-            else launch(std::integral_constant<int, 4>{});
-            return g.ksplit;
+            const bool ok = mt == 2 ? launch(std::integral_constant<int, 2>{}) : mt == 3 ? launch(std::integral_constant<int, 3>{})
+                                                                                        : launch(std::integral_constant<int, 4>{});
+            return ok ? g.ksplit : 0;
         }
     }
     const int blocks = (cols + 15) / 16;
@@ -1488,7 +1496,7 @@ void run_ring(GemmArgs g, hipStream_t st, int tile_n0 = 0, int tiles_n = 0) {
 // launch left for the norm behind it to add (RESID)
 template <int EPI>
 int dispatch(GemmArgs g, const StreamMode& sm, hipStream_t st) {
-    g.stream = sm.stream; g.w_frag = sm.w_frag; g.ksums = sm.ksums;
+    g.stream = sm.stream; g.w_frag = sm.w_frag; g.ksums = sm.ksums; g.ksum_floats = sm.ksum_floats;
     *sm.ran = -1;
     if (g.stream) {   // a handful of tokens: stream the weights (A is in fragment order)
         return run_gemv<EPI>(g, st);

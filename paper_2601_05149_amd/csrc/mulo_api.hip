@@ -63,6 +63,7 @@ struct mulo_ctx {
     // (same layer strides as the caller's, the lm-head padded to whole groups of 16 rows); nullptr without the copy
     const char *pk_wq, *pk_wk, *pk_wv, *pk_wo, *pk_gate, *pk_up, *pk_down, *pk_lm;
     float* ksums;        // with the copy: sums of the K slices of a 65..256-token launch's projections
+    int64_t ksum_floats;
     int32_t tile = -1;   // mulo_internal_tiles
     int32_t tiles_ran[5] = {-1, -1, -1, -1, -1};
     void* base;      // single allocation
@@ -196,10 +197,13 @@ bool enqueue_forward(mulo_ctx* c, mulo_kv* kv, int B, int L, int P, const int32_
     const bool has_copy = c->pk_wq != nullptr;
     const bool frag = dt == MULO_BF16 && M <= (has_copy ? STREAM_MAX_TOKENS_COPY : STREAM_MAX_TOKENS);
     const bool wfrag = frag && has_copy;
-    // The slices of at most 64 tokens (8 x 64 rows at most) go to the attention's partial results (512 rows of d and more), which
-    // are done with before the out projection and not begun before the next layer's attention: the norm in between takes them.
+    // The slices of out and down of at most 64 tokens (8 x 64 rows) go to the attention's partial results (512 rows of d and more),
+    // which are done with before the out projection and not begun before the next layer's attention: the norm in between takes them.
     static_assert(STREAM_RESID_SLICES * STREAM_MAX_TOKENS <= 512, "rows of slices");
-    auto sm = [&](int projection) { return StreamMode{frag, wfrag, M <= STREAM_MAX_TOKENS ? c->attn_part : c->ksums, c->tile, &c->tiles_ran[projection]}; };
+    const bool shared = shares_tokens(M, wfrag);
+    float* const sums = shared ? c->ksums : c->attn_part;
+    const int64_t sum_floats = shared ? c->ksum_floats : (int64_t)(attention_scratch_bytes(m.max_batch, m.n_heads, m.head_dim) / sizeof(float));
+    auto sm = [&](int projection) { return StreamMode{frag, wfrag, sums, sum_floats, c->tile, &c->tiles_ran[projection]}; };
     Slices add{nullptr, 0};   // what the last residual projection left for the norm behind it to add
     { PROF(MULO_PROF_NORM_EMBED); launch_embed(c->w.embed, dt, tok, emb, up ? *up : StepTokens{}, c->x, M, d, V, st); }
     for (int l = 0; l < m.n_layers; ++l) {
@@ -403,6 +407,7 @@ mulo_status mulo_create(const mulo_model_cfg* cfg, const mulo_weights* w, void* 
     c->row_parts = c->esz == 2 ? (float*)(b + l.off[15]) : nullptr;
     c->pk_wq = c->pk_wk = c->pk_wv = c->pk_wo = c->pk_gate = c->pk_up = c->pk_down = c->pk_lm = nullptr;
     c->ksums = cfg->stream_copy ? (float*)(b + l.off[17]) : nullptr;
+    c->ksum_floats = cfg->stream_copy ? (int64_t)(ksum_bytes(*cfg) / sizeof(float)) : 0;
     if (cfg->stream_copy) {   // bf16 (checked): the second copy of the weights, made once on the context's stream
         const int nl = cfg->n_layers, d = cfg->d_model, f = cfg->d_ffn;
         char* p = b + l.off[16];

@@ -31,14 +31,17 @@ constexpr int STREAM_MAX_TOKENS_COPY = 256;
 #ifndef STREAM_SHARED_MIN_TOKENS
 #define STREAM_SHARED_MIN_TOKENS 64
 #endif
+inline bool shares_tokens(int M, bool w_frag) { return w_frag && M > STREAM_SHARED_MIN_TOKENS; }
 // How a launch of few tokens runs its projections (decided once per forward, the same for every kernel of it):
 //   stream  the token operands are in fragment order and the projections run in the weight-streaming kernels
 //   w_frag  the weight pointers are the context's copies in fragment order
-//   ksums   scratch for the sums of the K slices when the launch streams (stream_ksum_floats; STREAM_RESID_SLICES [M, d] up to 64 tokens)
+//   ksums   scratch for the sums of the K slices when the launch streams: the context's own for launches that share tokens
+//           (stream_ksum_floats), the attention's partial results for out and down of the others (STREAM_RESID_SLICES [M, d])
+//   ksum_floats   what that scratch holds; more is an error
 // and, for the tests of the tiled kernels, which tile a launch that does not stream runs on:
 //   tile    index into the tile table (gemm.hip), taken where the projection has it; -1: the rule's choice
 //   ran     host variable that receives the tile (-1: streamed)
-struct StreamMode { bool stream, w_frag; float* ksums; int tile; int32_t* ran; };
+struct StreamMode { bool stream, w_frag; float* ksums; int64_t ksum_floats; int tile; int32_t* ran; };
 // K slices per 128-column group in the LDS-sharing kernel: as many as keep the launch within one round of 256
 // workgroups, at most 8, at least 8 k-steps each.  A function of the projection's shape only, so the order of every
 // sum is fixed by the model.
@@ -56,7 +59,12 @@ inline int stream_ksplit(int ncols, int K) {
 // 6.4 -> 8.5; 4096 x 1024 15.7 -> 8.9.  Shorter sums were not timed at enough widths to draw the line there.  One group of tokens loses by
 // slices (4096 x 11008: 22 -> 26, from the copy 19.6 -> 20.7, with four of them).
 constexpr int STREAM_RESID_SLICES = 8, STREAM_RESID_K = 4096;
-// floats of partial sums such a launch of M tokens over `ncols` output columns (gate|up: 2 f, q|k|v: 3 d) needs
+// K slices that a projection of a streamed launch leaves in its scratch (0: none); resid: out or down
+inline int stream_slices(int M, int ncols, int K, bool w_frag, bool resid) {
+    if (shares_tokens(M, w_frag)) return stream_ksplit(ncols, K);
+    return resid && M > 16 && K >= STREAM_RESID_K ? STREAM_RESID_SLICES : 0;
+}
+// floats of partial sums a launch of M shared tokens over `ncols` output columns (gate|up: 2 f, q|k|v: 3 d) needs
 inline size_t stream_ksum_floats(int M, int ncols, int K) { return (size_t)stream_ksplit(ncols, K) * M * ncols; }
 __host__ __device__ inline int64_t frag_index(int m, int k, int K) {   // in elements; runs of 8 k stay contiguous
     return ((int64_t)(m >> 4) * (K >> 5) + (k >> 5)) * 512 + (((k & 31) >> 3) * 16 + (m & 15)) * 8 + (k & 7);

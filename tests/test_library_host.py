@@ -4,6 +4,7 @@ import ctypes as C
 import os
 import re
 import struct
+import subprocess
 
 import msgpack
 import pytest
@@ -204,3 +205,42 @@ def test_static_entry_point_rejects_bad_arguments_before_any_gpu_call(lib):
     assert call(V, B, C.byref(bad)) == 2
     header = open(os.path.join(ROOT, "include", "mulo.h")).read()
     assert "#define MULO_STATIC_MAX_ROWS %d" % BD.MULO_STATIC_MAX_ROWS in header
+
+
+SCRATCH_CHECK = r"""
+#include "mulo_internal.h"
+#include <cstdio>
+using namespace mulo;
+// the scratch of a streamed launch holds the slices of each of its projections
+int main() {
+    const int shapes[][3] = {{128, 128, 260}, {768, 8256, 16388}, {1024, 2816, 8192}, {1408, 4160, 12308}, {4096, 11008, 16384}, {8192, 4096, 1024}};
+    for (auto& s : shapes)
+        for (int copy = 0; copy < 2; ++copy)
+            for (int M = 1; M <= (copy ? STREAM_MAX_TOKENS_COPY : STREAM_MAX_TOKENS); ++M) {
+                const int d = s[0], f = s[1], V = s[2], n[5] = {3 * d, d, 2 * f, d, V}, K[5] = {d, d, d, f, d};
+                long long own = 0;   // the context's scratch: one that holds no more than these tokens
+                for (int p = 0; p < 5; ++p) {
+                    const long long x = (long long)stream_ksum_floats(M, n[p], K[p]);
+                    own = x > own ? x : own;
+                }
+                for (int p = 0; p < 5; ++p) {
+                    const long long need = (long long)stream_slices(M, n[p], K[p], copy, p == 1 || p == 3) * M * n[p];
+                    const long long has = shares_tokens(M, copy) ? own : 512LL * d;   // 512 rows of d: the attention's, and more
+                    if (need > has) { std::printf("width %d copy %d, %d tokens, projection %d: %lld of %lld\n", d, copy, M, p, need, has); return 1; }
+                }
+            }
+    return 0;
+}
+"""
+
+
+@pytest.mark.parametrize("least", [16, 48, 64])
+def test_the_scratch_of_a_streamed_launch_holds_its_slices(least, tmp_path):
+    """From wherever on (STREAM_SHARED_MIN_TOKENS may be set) launches share tokens through LDS: they and the ones below it each leave
+    their slices in the buffer that is made for them."""
+    src, exe = tmp_path / "check.hip", str(tmp_path / "check")
+    src.write_text(SCRATCH_CHECK)
+    subprocess.run(["hipcc", "--offload-arch=gfx950", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                    "-DSTREAM_SHARED_MIN_TOKENS=%d" % least, "-I", os.path.join(ROOT, "paper_2601_05149_amd", "csrc"), str(src), "-o", exe], check=True, capture_output=True)
+    done = subprocess.run([exe], capture_output=True, text=True)
+    assert done.returncode == 0, done.stdout
