@@ -524,9 +524,11 @@ __global__ __launch_bounds__(TPB) void k_accept_parts(const DecideArgs a, const 
 // rejected positions and near ties, then R_X: position t is marked when it is at or after t0 and within Chebyshev
 // distance rho of some rejected position of the block (rho < 0: the raster rule, everything from t0 on).  Writes
 // mask, t0 and stats = (accepted, rejected, marked, near ties); no atomics on global memory anywhere.
-// A chain of latencies, so a position per thread up to blocks of 1024 where there is a window to search (4 x 1024, radius 2:
-// 256 threads 7.5 us, 1024 6.8); without one (2 x 1024, radius 0: 4.7 / 5.3) the larger workgroup only costs.
-__device__ __forceinline__ void finish_sequence(const DecideArgs& a, int b, uint8_t* acc_s, int (*red)[4]) {   // acc_s: [L] of LDS
+// A chain of latencies, so in a launch of its own a position per thread up to blocks of 1024 where there is a window to search (4 x 1024,
+// radius 2: 256 threads 7.5 us, 1024 6.8); without one (2 x 1024, radius 0: 4.7 / 5.3) the larger workgroup only costs.
+// near_s: [L] of LDS too, or nullptr.  With it a window is searched along its row first, for all positions, and then down the rows:
+// 2 (2 rho + 1) flags a position instead of (2 rho + 1)^2.
+__device__ __forceinline__ void finish_sequence(const DecideArgs& a, int b, uint8_t* acc_s, uint8_t* near_s, int (*red)[4]) {   // acc_s: [L] of LDS
     const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, wv = tid >> 6;
     const uint8_t* acc_g = a.accept + (int64_t)b * a.L;
     const float* inv_g = a.rowinv + (int64_t)b * a.L;
@@ -560,6 +562,21 @@ __device__ __forceinline__ void finish_sequence(const DecideArgs& a, int b, uint
     int zero = 0;
     reduce_counts(n_acc, n_near, tmin, zero);   // the barriers inside also publish acc_s
     const int t0 = tmin;
+    if (near_s && a.rho > 0 && t0 < a.L) {             // uniform over the workgroup
+        // A block is whole rows of the grid; those before t0's hold no rejection.  Eight flags at a time: a chain of single reads costs
+        // the latency of each.  A wavefront leaves a search as one: of lanes that leave on their own the compiler lost the flag
+        // that made them (it kept it as the lane mask of the loop's last round).
+        const int first = t0 - t0 % a.W, across = 2 * a.rho < a.W - 1 ? 2 * a.rho : a.W - 1;
+        for (int t = tid; t < a.L; t += nt) {
+            const int gj = t % a.W, u0 = gj < a.rho ? t - gj : t - a.rho, u1 = a.W - 1 - gj < a.rho ? t + a.W - 1 - gj : t + a.rho;
+            uint32_t ok = 1;
+            for (int o = 0; o <= across && __any(ok && t >= first); o += 8)
+#pragma unroll
+                for (int k = 0; k < 8; ++k) ok &= acc_s[u0 + o + k < u1 ? u0 + o + k : u1];
+            near_s[t] = ok == 0;
+        }
+        __syncthreads();
+    }
     int n_marked = 0;
     for (int t = tid; t < a.L; t += nt) {
         int marked = 0;
@@ -571,7 +588,12 @@ __device__ __forceinline__ void finish_sequence(const DecideArgs& a, int b, uint
                 const int g = a.n0 + t, gi = g / a.W, gj = g % a.W, r0 = a.n0 / a.W, r1 = (a.n0 + a.L - 1) / a.W;
                 const int i_lo = gi - a.rho > r0 ? gi - a.rho : r0, i_hi = gi + a.rho < r1 ? gi + a.rho : r1;
                 const int j_lo = gj - a.rho > 0 ? gj - a.rho : 0, j_hi = gj + a.rho < a.W - 1 ? gj + a.rho : a.W - 1;
-                for (int ii = i_lo; ii <= i_hi && !marked; ++ii)
+                if (near_s && a.rho > 0) {
+                    const int down = 2 * a.rho < r1 - r0 ? 2 * a.rho : r1 - r0;
+                    for (int o = 0; o <= down && __any(!marked); o += 8)
+#pragma unroll
+                        for (int k = 0; k < 8; ++k) marked |= near_s[(i_lo + o + k < i_hi ? i_lo + o + k : i_hi) * a.W + gj - a.n0];
+                } else for (int ii = i_lo; ii <= i_hi && !marked; ++ii)
                     for (int jj = j_lo; jj <= j_hi; ++jj)
                         if (acc_s[ii * a.W + jj - a.n0] == 0) { marked = 1; break; }
             }
@@ -593,27 +615,51 @@ __device__ __forceinline__ void finish_sequence(const DecideArgs& a, int b, uint
 __global__ __launch_bounds__(1024) void k_decide_finish(const DecideArgs a) {
     extern __shared__ uint8_t acc_s[];   // [L]
     __shared__ int red[16][4];
-    finish_sequence(a, blockIdx.x, acc_s, red);
+    finish_sequence(a, blockIdx.x, acc_s, nullptr, red);
 }
 
-// Blocks of up to FUSED_L positions have no launch for it: the first workgroups of the re-draw run finish_sequence, a sequence each
-// (n_fin of them, whole rounds of XCDs), while those of the positions find out for themselves whether theirs is marked,
-// a wavefront over the flags in front of it and in its window.  A chain of latencies of 6.6 us less in a decision stage.
+// Small decisions have no launch for it (decide_finish's rule; blocks of up to FUSED_L positions, whose flags the kernels hold): the first workgroups of the re-draw run
+// finish_sequence, a sequence each (n_fin of them, whole rounds of XCDs), while those of the positions find out for themselves whether
+// theirs is marked, a wavefront each: over the window (a rejection there at or before t says it all, none says no) and, where that leaves
+// it open, over the flags in front of t up to the first rejection; windows of more than one batch of flags after those.
 constexpr int FUSED_L = 4096;
 __device__ __forceinline__ bool position_marked(const DecideArgs& a, int b, int t, int lane) {
+    b = __builtin_amdgcn_readfirstlane(b);
+    t = __builtin_amdgcn_readfirstlane(t);
     const uint8_t* const acc = a.accept + (int64_t)b * a.L;
-    bool before = false, near = false;   // a rejected position at or before t (t >= t0), one inside its window
-#pragma unroll 4
-    for (int u = lane; u <= t; u += 64) before |= acc[u] == 0;
-    if (a.rho >= 0) {
-        const int g = a.n0 + t, gi = g / a.W, gj = g % a.W, r0 = a.n0 / a.W, r1 = (a.n0 + a.L - 1) / a.W;
-        const int i_lo = gi - a.rho > r0 ? gi - a.rho : r0, i_hi = gi + a.rho < r1 ? gi + a.rho : r1;
-        const int j_lo = gj - a.rho > 0 ? gj - a.rho : 0, j_hi = gj + a.rho < a.W - 1 ? gj + a.rho : a.W - 1, nj = j_hi - j_lo + 1;
-        for (int c = lane; c < (i_hi - i_lo + 1) * nj; c += 64) near |= acc[(i_lo + c / nj) * a.W + j_lo + c % nj - a.n0] == 0;
-    } else {
-        near = before;
+    auto rejected_up_to_t = [&]() {
+        for (int u0 = 0; u0 <= t; u0 += 256) {
+            bool hit = false;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int u = u0 + k * 64 + lane;
+                hit |= acc[u < t ? u : t] == 0;
+            }
+            if (__any(hit)) return true;
+        }
+        return false;
+    };
+    if (a.rho < 0) return rejected_up_to_t();
+    const int g = a.n0 + t, gi = g / a.W, gj = g % a.W, r0 = a.n0 / a.W, r1 = (a.n0 + a.L - 1) / a.W;
+    const int i_lo = gi - a.rho > r0 ? gi - a.rho : r0, i_hi = gi + a.rho < r1 ? gi + a.rho : r1;
+    const int j_lo = gj - a.rho > 0 ? gj - a.rho : 0, j_hi = gj + a.rho < a.W - 1 ? gj + a.rho : a.W - 1, nj = j_hi - j_lo + 1;
+    const int n = (i_hi - i_lo + 1) * nj;
+    const bool wide = n > 256;
+    if (wide && !rejected_up_to_t()) return false;
+    bool near = false;
+    for (int c0 = 0; c0 < n; c0 += 256) {
+        bool enough = false;   // a rejection in the window, at or before t unless one is known to be
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (c0 + k * 64 >= n) break;   // uniform
+            const int c = c0 + k * 64 + lane < n ? c0 + k * 64 + lane : n - 1, u = (i_lo + c / nj) * a.W + j_lo + c % nj - a.n0;
+            const bool hit = acc[u] == 0;
+            near |= hit;
+            enough |= hit && (wide || u <= t);
+        }
+        if (__any(enough)) return true;
     }
-    return __any(before) && __any(near);
+    return !wide && __any(near) && rejected_up_to_t();
 }
 
 // ---- Step 5 + Eq. 2: neighbourhood mask, then the residual draw -------------
@@ -730,16 +776,20 @@ __device__ __forceinline__ void cdf_draw(const Guided z, const float4* __restric
     }
 }
 
+template <bool FUSED>
 __global__ __launch_bounds__(TPB) void k_mask_sample(const DecideArgs a, int n_fin) {
     __shared__ unsigned long long chunk[MAX_CHUNKS];
     __shared__ int s_retry;
-    if ((int)blockIdx.x < n_fin) {                     // uniform over the workgroup
-        __shared__ int red[16][4];
-        static_assert(FUSED_L <= MAX_CHUNKS * 8, "the flags of a block");
-        if ((int)blockIdx.x < a.B) finish_sequence(a, blockIdx.x, reinterpret_cast<uint8_t*>(chunk), red);
-        return;
+    if constexpr (FUSED) {
+        if ((int)blockIdx.x < n_fin) {                 // uniform over the workgroup
+            __shared__ int red[16][4];
+            static_assert(2 * FUSED_L <= MAX_CHUNKS * 8, "two flags a position");
+            uint8_t* const acc_s = reinterpret_cast<uint8_t*>(chunk);
+            if ((int)blockIdx.x < a.B) finish_sequence(a, blockIdx.x, acc_s, acc_s + FUSED_L, red);
+            return;
+        }
     }
-    const int wg = blockIdx.x - n_fin;
+    const int wg = FUSED ? blockIdx.x - n_fin : blockIdx.x;
     // Which position this workgroup handles.  Workgroup ids go round-robin over the 8 XCDs (each with its own L2).
     // When the draft rows are shared by r x r children (replication up-sampling), the children of a draft row are
     // given to consecutive workgroups of ONE XCD, so that the row comes from memory once instead of once per child.
@@ -756,7 +806,7 @@ __global__ __launch_bounds__(TPB) void k_mask_sample(const DecideArgs a, int n_f
     const int b = row / a.L, t = row % a.L, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
 
     // R_X membership of this position (Eq. 6-7)
-    const bool marked = n_fin ? position_marked(a, b, t, lane) : a.mask[row] != 0;
+    const bool marked = FUSED ? position_marked(a, b, t, lane) : a.mask[row] != 0;
     const int draft = clamp_tok(a.draft_tokens[row], a.V);
     if (!marked) {   // uniform over the workgroup
         if (tid == 0) a.tokens_out[row] = draft;
@@ -776,19 +826,22 @@ __global__ __launch_bounds__(TPB) void k_mask_sample(const DecideArgs a, int n_f
 
 // The re-draw from the chunk sums that k_accept_sums left (at most 64 chunks, a lane each): one wavefront per position finds
 // the chunk and reads its 256 entries.  The same draw as cdf_draw's, empty residual included.
+template <bool FUSED>
 __global__ __launch_bounds__(TPB) void k_sample_sums(const DecideArgs a, const unsigned long long* __restrict__ sums, int n_fin) {
-    if ((int)blockIdx.x < n_fin) {                             // uniform over the workgroup
-        __shared__ uint8_t acc_s[FUSED_L];
-        __shared__ int red[16][4];
-        if ((int)blockIdx.x < a.B) finish_sequence(a, blockIdx.x, acc_s, red);
-        return;
+    if constexpr (FUSED) {
+        if ((int)blockIdx.x < n_fin) {                         // uniform over the workgroup
+            __shared__ uint8_t acc_s[2 * FUSED_L];
+            __shared__ int red[16][4];
+            if ((int)blockIdx.x < a.B) finish_sequence(a, blockIdx.x, acc_s, acc_s + FUSED_L, red);
+            return;
+        }
     }
     const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)(blockIdx.x - n_fin) * WAVES + (threadIdx.x >> 6);
+    const int64_t row = (int64_t)(FUSED ? blockIdx.x - n_fin : blockIdx.x) * WAVES + (threadIdx.x >> 6);
     if (row >= (int64_t)a.B * a.L) return;                     // uniform over the wavefront; no barrier follows
     const int b = row / a.L, t = row % a.L, V = a.V, nv4 = V >> 2, nchunks = (nv4 + 63) >> 6;
     const int draft = clamp_tok(a.draft_tokens[row], V);
-    if (!(n_fin ? position_marked(a, b, t, lane) : a.mask[row] != 0)) {
+    if (!(FUSED ? position_marked(a, b, t, lane) : a.mask[row] != 0)) {
         if (lane == 0) a.tokens_out[row] = draft;
         return;
     }
@@ -1141,8 +1194,16 @@ void launch_island_draw(const float* logits, const int32_t* pos_tab, int32_t* to
 }
 
 // the counters and the mask, in front of a re-draw that does not make them itself; returns how many workgroups of it do (0: none)
-static int decide_finish(const DecideArgs& a, hipStream_t st) {   // a.L <= 131072 (the caller checks): flags in LDS
-    if (a.L <= FUSED_L) return (a.B + 7) / 8 * 8;
+// The re-draw makes them where the launch it saves, 3 to 6 us of a decision, is more than the look that every position takes at
+// its window.  us of a decision, launch / none, 1024 entries a row, 60 % accepted and radius 1 where nothing else is said:
+//   k_mask_sample: 1 x 256 13.0 / 10.8, 4 x 1024 of radius 2 30.1 / 25.8, 1 x 4096 35.8 / 25.9, of 16384 entries 4 x 1024 143 / 138; but
+//     8 x 1024 48.2 / 45.8 and with next to all accepted and radius 0 26.5 / 28.8, 64 x 256 there 38.4 / 49.1, 16 x 1024 81.6 / 83.8
+//     and 39.8 / 49.3: up to 4096 positions of all sequences
+//   k_sample_sums, four positions a workgroup: 4 x 1024 of radius 2 23.8 / 18.2, 2 x 2048 with 3 % rejected and radius 3 35.8 / 20.3, 16 x 1024
+//     52.7 / 48.6, 4 x 4096 56 / 51, 64 x 256 50.1 / 48.7 (30 % accepted): up to 16384
+// 1 x 4096 positions can lose by it (radius 8, 20 % accepted, 25.8 / 27.0) and win by it (1 rejected of a thousand, 159 / 33).
+static int decide_finish(const DecideArgs& a, int most, hipStream_t st) {   // a.L <= 131072 (the caller checks): flags in LDS
+    if (a.L <= FUSED_L && (int64_t)a.B * a.L <= most) return (a.B + 7) / 8 * 8;
     static int attr_state = 0;
     if (!ensure_dynamic_lds(reinterpret_cast<const void*>(k_decide_finish), 131072, &attr_state)) return 0;
     hipLaunchKernelGGL(k_decide_finish, dim3(a.B), dim3(a.rho > 0 ? block_threads(a.L, 256) : 256), (size_t)a.L, st, a);
@@ -1181,8 +1242,10 @@ bool launch_accept(const DecideArgs& a, unsigned long long* sums, hipStream_t st
 
 void launch_sample_sums(const DecideArgs& a, const unsigned long long* sums, hipStream_t st) {
     const int64_t rows = (int64_t)a.B * a.L;
-    const int n_fin = decide_finish(a, st);
-    hipLaunchKernelGGL(k_sample_sums, dim3((unsigned)((rows + WAVES - 1) / WAVES + n_fin)), dim3(TPB), 0, st, a, sums, n_fin);
+    const int n_fin = decide_finish(a, 16384, st);
+    const dim3 grid((unsigned)((rows + WAVES - 1) / WAVES + n_fin));
+    if (n_fin) hipLaunchKernelGGL(k_sample_sums<true>, grid, dim3(TPB), 0, st, a, sums, n_fin);
+    else hipLaunchKernelGGL(k_sample_sums<false>, grid, dim3(TPB), 0, st, a, sums, 0);
 }
 
 void launch_accept_from_parts(const DecideArgs& a, const float* parts, int n_parts, hipStream_t st) {
@@ -1198,8 +1261,9 @@ void launch_mask_sample(const DecideArgs& a, hipStream_t st) {
         const int64_t parents = (int64_t)a.B * (a.L / r2);
         blocks = (unsigned)(((parents + 7) / 8) * 8 * r2);
     }
-    const int n_fin = decide_finish(a, st);
-    hipLaunchKernelGGL(k_mask_sample, dim3(blocks + n_fin), dim3(TPB), 0, st, a, n_fin);
+    const int n_fin = decide_finish(a, 4096, st);
+    if (n_fin) hipLaunchKernelGGL(k_mask_sample<true>, dim3(blocks + n_fin), dim3(TPB), 0, st, a, n_fin);
+    else hipLaunchKernelGGL(k_mask_sample<false>, dim3(blocks), dim3(TPB), 0, st, a, 0);
 }
 
 }  // namespace mulo

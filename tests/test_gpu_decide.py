@@ -386,30 +386,28 @@ def test_draw_from_chunk_sums_equals_the_draw_from_the_rows(V, kw):
 
 
 # --------------------------------------------------------------- rejection islands (Eq. 8)
-@pytest.mark.parametrize("W,rows", [(64, 64), (64, 65), (4097, 1), (1, 4096), (61, 67)])
-@pytest.mark.parametrize("rho", [-1, 0, 2, 70])
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])   # a bf16 context draws from chunk sums where there is a window (k_sample_sums)
-def test_mask_and_counters_on_both_sides_of_the_longest_fused_block(W, rows, rho, dtype):
-    """Blocks of 4096 positions (the re-draw makes mask and counters itself) and a few more (a launch in front of it does): few and late
-    rejections, so that windows hold rejections in front of, behind and at the position, and sequences that accept everything.
-    t0, mask and counters from the flags by numpy, and every unmarked token kept."""
-    B, L, V = 3, W * rows, 8
-    key = (dtype, V, 3, 4160)
+def _check_mask_and_counters(dtype, B, W, rows, rho, row0=0):
+    """Few and late rejections, so that windows hold rejections in front of, behind and at the position, and sequences that accept
+    everything.  t0, mask and counters from the flags by numpy, and every unmarked token kept."""
+    L, V = W * rows, 8
+    key = (dtype, V, B, L)
     if key not in _CTX:
         m = dict(n_layers=1, d_model=128, n_heads=2, head_dim=64, d_ffn=128, vocab=V, dtype=dtype, rms_eps=1e-5)
-        _CTX[key] = make_ctx(m, G.make_weights(m, seed=0, threads=4), 3, 4168, 4160)[0]
+        block = (L + 3) // 4 * 4
+        _CTX[key] = make_ctx(m, G.make_weights(m, seed=0, threads=4), B, (block + 7) // 8 * 8 + 8, block)[0]
     ctx = _CTX[key]
     rng = np.random.default_rng(7)
     zp = np.zeros((B, L, V), np.float32)
     q = np.full((B, L, V), 1.0 / V, np.float32)
     toks = rng.integers(0, V, (B, L)).astype(np.int32)
-    for b, at in ((0, [L // 3, L // 3 + 7, L - 1]), (1, [L - 2])):
-        zp[b, at, toks[b, at]] = -40.0                                  # p of the draft token is 0: rejected whatever the uniform
-    res = run_decide(ctx, zp, q, toks, H=rows, W=W, n0=0, L=L, radius=rho, seed=3, rng_counter=1)
+    at = [sorted({L // 3, min(L // 3 + 7, L - 1), L - 1}), [L - 2], []]
+    for b in range(B):
+        zp[b, at[b % 3], toks[b, at[b % 3]]] = -40.0                    # p of the draft token is 0: rejected whatever the uniform
+    res = run_decide(ctx, zp, q, toks, H=rows + row0, W=W, n0=row0 * W, L=L, radius=rho, seed=3, rng_counter=1)
     for b in range(B):
         rej = np.flatnonzero(res["accept"][b] == 0)
         t0 = int(rej[0]) if rej.size else L
-        assert rej.size == (3, 1, 0)[b] and res["t0"][b] == t0
+        assert list(rej) == at[b % 3] and res["t0"][b] == t0
         ii, jj = np.arange(L) // W, np.arange(L) % W
         hit = np.zeros(L, bool) if rho >= 0 else np.full(L, rej.size > 0)
         for t in rej if rho >= 0 else ():
@@ -418,6 +416,31 @@ def test_mask_and_counters_on_both_sides_of_the_longest_fused_block(W, rows, rho
         assert np.array_equal(res["mask"][b] != 0, want)
         assert list(res["stats"][b][:3]) == [L - rej.size, rej.size, int(want.sum())]
         assert np.array_equal(res["tokens_out"][b][~want], toks[b][~want])
+
+
+@pytest.mark.parametrize("W,rows", [(64, 64), (64, 65), (4097, 1), (1, 4096), (61, 67)])
+@pytest.mark.parametrize("rho", [-1, 0, 2, 70])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])   # a bf16 context draws from chunk sums where there is a window (k_sample_sums)
+def test_mask_and_counters_of_long_blocks(W, rows, rho, dtype):
+    """Three blocks of 4096 positions and a few more, which a launch in front of the re-draw finishes."""
+    _check_mask_and_counters(dtype, 3, W, rows, rho)
+
+
+@pytest.mark.parametrize("B,W,rows,rhos", [
+    (1, 64, 64, (-1, 0, 1, 5, 70)), (1, 241, 17, (-1, 0, 5)),   # 4096 positions: the re-draw finishes them; 4097: a launch does
+    (4, 64, 16, (-1, 0, 2, 3)), (5, 64, 16, (-1, 0, 2)),        # of several sequences: a launch from 4097 on where it draws from the rows,
+    (16, 64, 16, (1, 8)), (17, 61, 16, (1, 8)),                 # from 16385 on where it draws from chunk sums
+    (2, 16, 32, (3, 4, 6)), (1, 64, 32, (1, 2, 9)),             # windows within eight flags a row, more, and of more than 256 flags
+    (3, 257, 1, (2, 70)), (3, 1, 300, (2, 70)),                 # one row, one column
+    (17, 7, 9, (-1, 0, 2, 70)), (1, 1, 5, (0, 3)),              # more sequences than two rounds of eight workgroups; a handful of positions
+])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_mask_and_counters_on_both_sides_of_the_rule(B, W, rows, rhos, dtype):
+    """Decisions whose re-draw makes mask and counters itself, and the next larger ones, which a launch in front of it finishes; also of a
+    block that does not begin the grid."""
+    for rho in rhos:
+        for row0 in (0, 3):
+            _check_mask_and_counters(dtype, B, W, rows, rho, row0)
 
 
 def _islands_gpu(ctx, mask, W, n0):
