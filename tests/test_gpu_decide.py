@@ -336,7 +336,7 @@ def test_guided_decide_parity(B, V, scale, amode):
 
 
 # ------------------------------------------- the draw from the chunk sums that the accept test leaves
-@pytest.mark.parametrize("V", [4, 260, 512, 516, 1028, 2048, 2052, 4096, 8196, 10004, 12288, 12292, 16384, 16388])
+@pytest.mark.parametrize("V", [4, 260, 508, 516, 1028, 2048, 2052, 4096, 8196, 10004, 12288, 12292, 16384, 16388])
 @pytest.mark.parametrize("kw", [dict(radius=1), dict(radius=-1, resample_mode=1), dict(radius=0, resample_mode=2),
                                 dict(radius=2, resample_mode=1, pool=5), dict(radius=1, cfg_scale=3.0), dict(radius=0),
                                 dict(radius=1, accept_mode=1, tau=1e-3, resample_mode=2, cfg_scale=2.0),
