@@ -267,7 +267,7 @@ __global__ __launch_bounds__(NW * 64) void k_attn_mfma_f32(const float* __restri
         f32x4 kf[NB], vf[NB];
 #pragma unroll
         for (int s = 0; s < NB; ++s) { kf[s] = nk[s]; vf[s] = nv[s]; }
-        if (FULL && k0 + 15 > kmax) {                     // uniform over the workgroup
+        if (FULL && k0 + 15 > kmax) {                     // uniform over the wavefront
 #pragma unroll
             for (int s = 0; s < NB; ++s)
 #pragma unroll

@@ -1410,10 +1410,12 @@ __global__ __launch_bounds__(256) void k_pack_weights(const bf16* __restrict__ s
 // t0, where few CUs fetch, and tf: t0 + (tf - t0) r / S).  per_cu is what the LDS holds, but 1 for 32 x 64, of which two fit:
 // with 257 tiles the CU that has two of them takes twice the bytes, and the fit knows (4096 x 4096: 128 tokens, 256 tiles, 18 us
 // against 22 on 64 x 64; 256 tokens, 512 tiles, 28 against 23).  The constants (us) are fitted over 40 token
-// counts from 72 to 4096 and the ten projection shapes of the two bf16 configurations (widths 1024 and 4096; no other width
-// was timed), cold weights, for the picks first and the times second, with no pick slower than the one of the rule before: the picks
+// counts from 72 to 4096 and the ten projection shapes of the two bf16 configurations (widths 1024 and 4096), cold weights, for the picks
+// first and the times second (so a cost of a round may be below 0), with no pick slower than the one of the rule before: the picks
 // take 0.6 % longer than the best tile on average, 20 of 400 more than 5 %; with the least squares fit to the times alone that was
-// here before 1.5 % and 43.  The worst are the lm-head of 72 to 128 tokens of width 4096 (51 us on 64 x 64 against 40 on 128 x 64);
+// here before 1.5 % and 43.  Widths that were not fitted, 1536, 2048, 3072 and 5120: 1.0 % and 26 of 320, with the fit before
+// 1.3 % and 33; slower than its picks by up to 8 % at width 2048 (q|k|v and lm-head of 288 to 384 tokens), faster by up to 12 % at
+// 1536.  The worst are the lm-head of 72 to 128 tokens of width 4096 (51 us on 64 x 64 against 40 on 128 x 64);
 // 260 to 320 tokens of that width went from 66 to 52 us (q|k|v, 256 x 128 for 64 x 64) and from 97 to 77 (gate|up, 256 x 256 for 64 x 128).
 struct TileCost {
     int bm, bn, stages, per_cu;   // ring stages of bm + bn rows of 128 bytes; 256 x 256: 0, it has a ring of its own

@@ -56,7 +56,8 @@ inline int stream_ksplit(int ncols, int K) {
 // k_gemv_bf16 deals to the wavefronts of a workgroup go to a workgroup each (k_gemv_shared), which shares the token operand of its
 // slice among 64 or 128 columns, and the norm behind adds the eight in the order that kernel adds them in: the same bits as up to 16
 // tokens.  52 tokens, us: 4096 x 4096 17.7 -> 13.8, from the copy 16.2 -> 12.9, 4096 x 11008 38.6 -> 26.6 and 36.4 -> 23.9, the norms
-// 6.4 -> 8.5; 4096 x 1024 15.7 -> 8.9.  Shorter sums were not timed at enough widths to draw the line there.  One group of tokens loses by
+// 6.4 -> 8.5; 4096 x 1024 15.7 -> 8.9.  Shorter sums gain less: 8 layers of width 1024 with 2816 feed-forward columns, neither / both in slices,
+// 17 tokens 282 / 256, 40 278 / 279, 64 315 / 311, from the copy 251 / 236, 260 / 261, 295 / 292.  One group of tokens loses by
 // slices (4096 x 11008: 22 -> 26, from the copy 19.6 -> 20.7, with four of them).
 constexpr int STREAM_RESID_SLICES = 8, STREAM_RESID_K = 4096;
 // K slices that a projection of a streamed launch leaves in its scratch (0: none); resid: out or down
